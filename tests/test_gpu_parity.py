@@ -235,6 +235,56 @@ def test_amg_setup_aggressive_bit_exact(ctx, which, coarsening, levels):
                        what="aggressive V-cycle")
 
 
+def _hub_matrix(n, weak, strong, seed):
+    """M-matrix on an n x n grid with extra rows' worth of couplings: row 17 + 101 k gets
+    weak[k] small one-way couplings, and row 60 + 101 k strong[k] couplings that are strong
+    for that row only (so it becomes an F point with that many neighbours to choose from)."""
+    rng = np.random.default_rng(seed)
+    N = n * n
+    e = np.ones(N)
+    T = sp.diags([-e[:-1], -e[:-1]], [-1, 1], shape=(n, n)) if n > 1 else sp.csr_matrix((1, 1))
+    A = (sp.kron(sp.identity(n), T) + sp.kron(T, sp.identity(n))).tolil()
+    A = A.tocsr()
+    A.data *= rng.uniform(0.8, 1.2, A.nnz)
+    rows, cols, vals = [], [], []
+    for k, d in enumerate(weak):
+        j = rng.choice(N, size=d, replace=False)
+        rows += [17 + 101 * k] * d
+        cols += list(j)
+        vals += list(-rng.uniform(1e-5, 1e-4, d))
+    for k, d in enumerate(strong):
+        j = rng.choice(N, size=d, replace=False)
+        rows += [60 + 101 * k] * d
+        cols += list(j)
+        vals += list(-rng.uniform(3.0, 4.0, d))
+    X = sp.csr_matrix((vals, (rows, cols)), shape=(N, N))
+    A = sp.csr_matrix(A + X)
+    A.setdiag(0.0)
+    A.eliminate_zeros()
+    d = -np.asarray(A.sum(1)).reshape(-1) + 0.01
+    A = sp.csr_matrix(A + sp.diags(d))
+    A.sort_indices()
+    return A
+
+
+@pytest.mark.parametrize("n,weak,strong", [
+    (40, (10, 25, 48, 100), (9, 33, 40)),            # the smallest tables, one lane group and more
+    (70, (200, 700, 1500), (33, 130, 260)),          # middle tables, rows past the lane groups' lists
+    (130, (2500, 4200, 9000), (5,)),                 # the largest table and rows past it
+])
+def test_amg_setup_long_rows_bit_exact(ctx, n, weak, strong):
+    """Rows far longer than the stencils': every table size of the sparse
+    products and the range form beyond them, and interpolation rows with more
+    strong C neighbours than a lane group lists; bit for bit the oracle's."""
+    api = gpu_modules()
+    A = _hub_matrix(n, weak, strong, 11)
+    H = oamg.setup(A, oamg.AMGParams(seed=4, max_levels=3, dense_max=100))
+    g = api.AMG(ctx, A.indptr, A.indices, A.data, seed=4, max_levels=3, dense_max=100)
+    lens = np.diff(H.levels[0].P.indptr)
+    assert lens.max() >= min(max(strong), 200) // 4
+    _compare_hierarchies(g, H, exact_values=True)
+
+
 def test_amg_levelwise_on_gpu_levels(ctx):
     """Binding test: the oracle's strength, PMIS and interpolation applied to
     each GPU level matrix give the GPU's C/F splitting and P bit for bit."""
