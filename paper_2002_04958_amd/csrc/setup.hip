@@ -687,76 +687,304 @@ void transpose(Ctx* c, const Csr<double>& A, Csr<double>& T) {
 }
 
 // ---------------------------------------------------------------------------
-// SpGEMM: row-wise multiway merge.  Every output column of row i is produced
-// in ascending order; its value is 0 + a_ik1 b_k1j + a_ik2 b_k2j + ... over
+// SpGEMM.  Row i of C = A B holds every column some b_k of the row's entries
+// reaches, ascending, with the value 0 + a_ik1 b_k1j + a_ik2 b_k2j + ... over
 // the row's entries in ascending k.
+//
+// A row is collected in a hash table in LDS by a group of GL lanes: the row's
+// entries k in turn, the lanes side by side over row k of B.  The columns of one
+// row of B are distinct, so no two lanes meet in a slot, and a slot gets its
+// terms in ascending k: the sum above, term by term.  Rows are sorted into
+// classes by the table they need (load at most 3/4): from the sum of their B
+// rows' lengths before the columns are counted, from the count itself before
+// the values are formed, and from the number of columns that exist at all in
+// both.  The kernels of a class walk its list with a grid of at most kSpGrid
+// workgroups and read the list's length on the device, so classes without rows
+// cost an empty launch and no readback.  Rows too long for the largest table are
+// formed one range of columns after another.  One lane per row merging the
+// B rows' heads through memory took 200 ms of a step with new coefficients at
+// 3D 64^3, G = 20 (22 hierarchies); the tables take 38 ms.
 // ---------------------------------------------------------------------------
+constexpr int kSpClasses = 5;             // four table sizes, then ranges of columns
+constexpr int kSpTable[4] = {64, 256, 1024, 4096};
+constexpr int kSpGrid = 4096;
+constexpr int kSpBinRows = 8;             // rows per thread of the sorting kernel
+
+__host__ __device__ constexpr int sp_class(int cols) {
+  return cols <= 48 ? 0 : cols <= 192 ? 1 : cols <= 768 ? 2 : cols <= 3072 ? 3 : 4;
+}
+
+// lists[c * n ...] = the rows of class c, count[c] their number.  COUNTED: the
+// class from crp's row lengths, else from the B rows' total length; rows
+// without entries are in no list (cnt[i] = 0 for them before the count).
+template <bool COUNTED>
+__global__ void __launch_bounds__(256) k_spgemm_bin(int n, int max_cols,
+                                                    const int* __restrict__ arp,
+                                                    const int* __restrict__ aci,
+                                                    const int* __restrict__ brp,
+                                                    const int* __restrict__ crp,
+                                                    int* __restrict__ cnt,
+                                                    int* __restrict__ lists,
+                                                    int* __restrict__ count) {
+  __shared__ int s_n[kSpClasses], s_base[kSpClasses];
+  if (threadIdx.x < kSpClasses) s_n[threadIdx.x] = 0;
+  __syncthreads();
+  const int r0 = blockIdx.x * 256 * kSpBinRows;
+  int cls[kSpBinRows], pos[kSpBinRows];
+#pragma unroll
+  for (int t = 0; t < kSpBinRows; ++t) {
+    const int i = r0 + t * 256 + threadIdx.x;
+    cls[t] = -1;
+    pos[t] = 0;
+    if (i < n) {
+      long long len = 0;
+      if (COUNTED) {
+        len = crp[i + 1] - crp[i];
+      } else {
+        for (int e = arp[i]; e < arp[i + 1]; ++e) {
+          const int k = aci[e];
+          len += brp[k + 1] - brp[k];
+        }
+        if (len == 0) cnt[i] = 0;
+      }
+      if (len > 0) cls[t] = sp_class((int)min(len, (long long)max_cols));
+    }
+#pragma unroll
+    for (int c = 0; c < kSpClasses; ++c) {
+      const uint64_t w = __ballot(cls[t] == c);
+      if (w == 0) continue;
+      int base = 0;
+      if ((threadIdx.x & 63) == 0) base = atomicAdd(&s_n[c], (int)__popcll(w));
+      base = __shfl(base, 0, 64);
+      if (cls[t] == c) pos[t] = base + (int)__popcll(w & ((1ull << (threadIdx.x & 63)) - 1));
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < kSpClasses)
+    s_base[threadIdx.x] = s_n[threadIdx.x] ? atomicAdd(&count[threadIdx.x], s_n[threadIdx.x]) : 0;
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < kSpBinRows; ++t)
+    if (cls[t] >= 0)
+      lists[(size_t)cls[t] * n + s_base[cls[t]] + pos[t]] = r0 + t * 256 + threadIdx.x;
+}
+
+template <int H, int GL, int WG, bool FILL>
+__global__ void __launch_bounds__(WG) k_spgemm_hash(
+    const int* __restrict__ list, const int* __restrict__ count, const int* __restrict__ arp,
+    const int* __restrict__ aci, const double* __restrict__ av, const int* __restrict__ brp,
+    const int* __restrict__ bci, const double* __restrict__ bv, const int* __restrict__ crp,
+    int* __restrict__ cnt_or_cci, double* __restrict__ cv, int* __restrict__ err) {
+  constexpr int kGroups = WG / GL, kMost = 3 * H / 4;
+  constexpr int kShift = 32 - (H == 64 ? 6 : H == 256 ? 8 : H == 1024 ? 10 : 12);
+  __shared__ int s_key[kGroups][H];
+  __shared__ double s_val[FILL ? kGroups : 1][FILL ? H : 1];
+  __shared__ int s_col[FILL ? kGroups : 1][FILL ? kMost : 1];
+  __shared__ uint16_t s_slot[FILL ? kGroups : 1][FILL ? kMost : 1];
+  const int grp = threadIdx.x / GL, lane = threadIdx.x % GL;
+  const int sh = (threadIdx.x & 63) / GL * GL;
+  const uint64_t gm = (GL == 64 ? ~0ull : ((1ull << (GL & 63)) - 1)) << sh;
+  // volatile: a group's lanes are in one wave, whose LDS operations are done in
+  // program order; no barrier is needed between them
+  volatile int* key = s_key[grp];
+  volatile double* val = s_val[FILL ? grp : 0];
+  volatile int* col = s_col[FILL ? grp : 0];
+  volatile uint16_t* slot = s_slot[FILL ? grp : 0];
+  const int nr = *count;
+  for (int r = blockIdx.x * kGroups + grp; r < nr; r += gridDim.x * kGroups) {
+    const int i = list[r];
+    const int e0 = arp[i], e1 = arp[i + 1];
+    for (int s = lane; s < H; s += GL) {
+      key[s] = -1;
+      if (FILL) val[s] = 0.0;
+    }
+    int fresh = 0;
+    bool lost = false;
+    for (int b = e0; b < e1; b += GL) {
+      const int e = b + lane;
+      int f0 = 0, f1 = 0;
+      double a = 0.0;
+      if (e < e1) {
+        const int k = aci[e];
+        f0 = brp[k];
+        f1 = brp[k + 1];
+        if (FILL) a = av[e];
+      }
+      const int cnt = min(GL, e1 - b);
+      for (int q = 0; q < cnt; ++q) {
+        const int k0 = __shfl(f0, q, GL), k1 = __shfl(f1, q, GL);
+        const double aq = FILL ? __shfl(a, q, GL) : 0.0;
+        for (int f = k0 + lane; f < k1; f += GL) {
+          const int j = bci[f];
+          double x = 0.0;
+          if (FILL) x = bv[f];
+          int h = (int)(((unsigned)j * 2654435769u) >> kShift);
+          int tries = 0;
+          for (; tries < H; ++tries) {  // a table is at most 3/4 full
+            int at = key[h];
+            if (at == -1) {
+              at = atomicCAS(&s_key[grp][h], -1, j);
+              if (at == -1) {
+                ++fresh;
+                break;
+              }
+            }
+            if (at == j) break;
+            h = (h + 1) & (H - 1);
+          }
+          if (tries == H) {
+            lost = true;
+            continue;
+          }
+          if (FILL) val[h] = val[h] + aq * x;
+        }
+      }
+    }
+    if (lost) atomicOr(err, 1);
+    if (!FILL) {
+#pragma unroll
+      for (int o = GL / 2; o > 0; o >>= 1) fresh += __shfl_xor(fresh, o, GL);
+      if (lane == 0) cnt_or_cci[i] = fresh;
+      continue;
+    }
+    // the columns present, in slot order, then each at its rank
+    int m = 0;
+    for (int s0 = 0; s0 < H; s0 += GL) {
+      const int k = key[s0 + lane];
+      const uint64_t w = (__ballot(k >= 0) & gm) >> sh;
+      const int at = m + (int)__popcll(w & ((1ull << lane) - 1));
+      if (k >= 0 && at < kMost) {
+        col[at] = k;
+        slot[at] = (uint16_t)(s0 + lane);
+      }
+      m += (int)__popcll(w);
+    }
+    const int o = crp[i];
+    if (m != crp[i + 1] - o || m > kMost) {  // another number of columns than were counted
+      if (lane == 0) atomicOr(err, 2);
+      continue;
+    }
+    for (int t = lane; t < m; t += GL) {
+      const int k = col[t];
+      int rank = 0;
+      for (int u = 0; u < m; ++u) rank += col[u] < k ? 1 : 0;
+      cnt_or_cci[o + rank] = k;
+      cv[o + rank] = val[slot[t]];
+    }
+  }
+}
+
+// Rows of the last class, one wave per row: the columns kSpRange at a time, each
+// range in an array indexed by column (the row's products are read again for
+// every range), so the columns come out in order without a search or a sort.
+constexpr int kSpRange = 4096;
 template <bool FILL>
-__global__ void k_spgemm(int n, const int* __restrict__ arp, const int* __restrict__ aci,
-                         const double* __restrict__ av, const int* __restrict__ brp,
-                         const int* __restrict__ bci, const double* __restrict__ bv,
-                         int* __restrict__ head, int* __restrict__ hend,
-                         const int* __restrict__ crp, int* __restrict__ cnt_or_cci,
-                         double* __restrict__ cv, int* __restrict__ err) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int e0 = arp[i], e1 = arp[i + 1];
-  for (int e = e0; e < e1; ++e) {
-    const int k = aci[e];
-    head[e] = brp[k];
-    hend[e] = brp[k + 1];
-  }
-  int out = FILL ? crp[i] : 0;
-  const int oend = FILL ? crp[i + 1] : INT_MAX;
-  for (;;) {
-    int jmin = INT_MAX;
-    for (int e = e0; e < e1; ++e)
-      if (head[e] < hend[e]) jmin = min(jmin, bci[head[e]]);
-    if (jmin == INT_MAX) break;
-    double acc = 0.0;
-    for (int e = e0; e < e1; ++e) {
-      const int h = head[e];
-      if (h < hend[e] && bci[h] == jmin) {
-        if (FILL) acc = acc + av[e] * bv[h];
-        head[e] = h + 1;
+__global__ void __launch_bounds__(64) k_spgemm_range(
+    const int* __restrict__ list, const int* __restrict__ count, int n_cols,
+    const int* __restrict__ arp, const int* __restrict__ aci, const double* __restrict__ av,
+    const int* __restrict__ brp, const int* __restrict__ bci, const double* __restrict__ bv,
+    const int* __restrict__ crp, int* __restrict__ cnt_or_cci, double* __restrict__ cv,
+    int* __restrict__ err) {
+  __shared__ double s_val[FILL ? kSpRange : 1];
+  __shared__ unsigned s_bits[kSpRange / 32];
+  volatile double* val = s_val;
+  volatile unsigned* bits = s_bits;
+  const int lane = threadIdx.x;
+  const int nr = *count;
+  for (int r = blockIdx.x; r < nr; r += gridDim.x) {
+    const int i = list[r];
+    const int e0 = arp[i], e1 = arp[i + 1];
+    int out = FILL ? crp[i] : 0;
+    const int oend = FILL ? crp[i + 1] : INT_MAX;
+    for (long long lo = 0; lo < n_cols; lo += kSpRange) {
+      for (int s = lane; s < kSpRange / 32; s += 64) bits[s] = 0;
+      if (FILL)
+        for (int s = lane; s < kSpRange; s += 64) val[s] = 0.0;
+      for (int b = e0; b < e1; b += 64) {
+        const int e = b + lane;
+        int f0 = 0, f1 = 0;
+        double a = 0.0;
+        if (e < e1) {
+          const int k = aci[e];
+          f0 = brp[k];
+          f1 = brp[k + 1];
+          if (FILL) a = av[e];
+        }
+        const int cnt = min(64, e1 - b);
+        for (int q = 0; q < cnt; ++q) {
+          const int k0 = __shfl(f0, q, 64), k1 = __shfl(f1, q, 64);
+          const double aq = FILL ? __shfl(a, q, 64) : 0.0;
+          for (int f = k0 + lane; f < k1; f += 64) {
+            const long long s = (long long)bci[f] - lo;
+            if (s < 0 || s >= kSpRange) continue;
+            atomicOr(&s_bits[s >> 5], 1u << (s & 31));
+            if (FILL) val[s] = val[s] + aq * bv[f];
+          }
+        }
+      }
+      for (int s0 = 0; s0 < kSpRange; s0 += 64) {
+        const uint64_t w = (uint64_t)bits[s0 >> 5] | ((uint64_t)bits[(s0 >> 5) + 1] << 32);
+        const int at = out + (int)__popcll(w & ((1ull << lane) - 1));
+        if (FILL && ((w >> lane) & 1) && at < oend) {
+          cnt_or_cci[at] = (int)lo + s0 + lane;
+          cv[at] = val[s0 + lane];
+        }
+        out += (int)__popcll(w);
       }
     }
-    if (FILL) {
-      if (out >= oend) {  // more columns than the symbolic pass counted
-        atomicOr(err, 1);
-        return;
-      }
-      cnt_or_cci[out] = jmin;
-      cv[out] = acc;
-    }
-    ++out;
+    if (!FILL && lane == 0) cnt_or_cci[i] = out;
+    if (FILL && out != oend && lane == 0) atomicOr(err, 2);  // not the columns counted
   }
-  if (!FILL) cnt_or_cci[i] = out;
-  if (FILL && out != oend) atomicOr(err, 2);
+}
+
+template <bool FILL>
+static void spgemm_pass(Ctx* c, const Csr<double>& A, const Csr<double>& B, int max_cols,
+                        DBuf<int>& lists, DBuf<int>& count, const int* crp, int* cnt_or_cci, double* cv) {
+  const int n = A.n_rows;
+  fill<int>(c, count.get(), 0, kSpClasses);
+  hipLaunchKernelGGL(k_spgemm_bin<FILL>, dim3(cdiv(n, 256 * kSpBinRows)), dim3(256), 0, c->stream,
+                     n, max_cols, A.rp.get(), A.ci.get(), B.rp.get(), crp,
+                     FILL ? (int*)nullptr : cnt_or_cci, lists.get(), count.get());
+  MGD_CHECK_LAUNCH();
+  const int top = sp_class(max_cols);  // no row needs more than all columns
+#define MGD_SPGEMM(CLS, H, GL, WG)                                                                \
+  if (CLS <= top) {                                                                               \
+    hipLaunchKernelGGL((k_spgemm_hash<H, GL, WG, FILL>), dim3(std::min(cdiv(n, WG / GL), kSpGrid)), \
+                       dim3(WG), 0, c->stream, (const int*)lists.get() + (size_t)CLS * n,         \
+                       (const int*)count.get() + CLS, A.rp.get(), A.ci.get(), A.v.get(),          \
+                       B.rp.get(), B.ci.get(), B.v.get(), crp, cnt_or_cci, cv, c->err_flag());    \
+    MGD_CHECK_LAUNCH();                                                                           \
+  }
+  MGD_SPGEMM(0, 64, 8, 256)
+  MGD_SPGEMM(1, 256, 32, 256)
+  MGD_SPGEMM(2, 1024, 64, 256)
+  MGD_SPGEMM(3, 4096, 64, 64)
+#undef MGD_SPGEMM
+  if (top == 4) {
+    hipLaunchKernelGGL(k_spgemm_range<FILL>, dim3(std::min(n, kSpGrid)), dim3(64), 0, c->stream,
+                       (const int*)lists.get() + (size_t)4 * n, (const int*)count.get() + 4,
+                       B.n_cols, A.rp.get(), A.ci.get(), A.v.get(), B.rp.get(), B.ci.get(),
+                       B.v.get(), crp, cnt_or_cci, cv, c->err_flag());
+    MGD_CHECK_LAUNCH();
+  }
 }
 
 void spgemm(Ctx* c, const Csr<double>& A, const Csr<double>& B, Csr<double>& C) {
   MGD_REQUIRE(A.n_cols == B.n_rows, "spgemm: inner dimensions differ");
   const int n = A.n_rows;
-  DBuf<int> head(c, (size_t)std::max(A.nnz, 1)), hend(c, (size_t)std::max(A.nnz, 1));
-  DBuf<int> cnt(c, (size_t)std::max(n, 1));
+  DBuf<int> cnt(c, (size_t)std::max(n, 1)), lists(c, (size_t)kSpClasses * std::max(n, 1));
+  DBuf<int> count(c, kSpClasses);
   C.n_rows = n;
   C.n_cols = B.n_cols;
   C.rp.alloc(c, (size_t)n + 1);
-  const int g = cdiv(n, 128);
   if (n)
-    hipLaunchKernelGGL(k_spgemm<false>, dim3(g), dim3(128), 0, c->stream, n, A.rp.get(),
-                       A.ci.get(), A.v.get(), B.rp.get(), B.ci.get(), B.v.get(), head.get(),
-                       hend.get(), (const int*)nullptr, cnt.get(), (double*)nullptr, c->err_flag());
-  MGD_CHECK_LAUNCH();
+    spgemm_pass<false>(c, A, B, B.n_cols, lists, count, nullptr, cnt.get(), nullptr);
   C.nnz = exclusive_scan_total(c, cnt.get(), C.rp.get(), n);
   C.ci.alloc(c, (size_t)C.nnz);
   C.v.alloc(c, (size_t)C.nnz);
   if (n)
-    hipLaunchKernelGGL(k_spgemm<true>, dim3(g), dim3(128), 0, c->stream, n, A.rp.get(), A.ci.get(),
-                       A.v.get(), B.rp.get(), B.ci.get(), B.v.get(), head.get(), hend.get(),
-                       (const int*)C.rp.get(), C.ci.get(), C.v.get(), c->err_flag());
-  MGD_CHECK_LAUNCH();
+    spgemm_pass<true>(c, A, B, B.n_cols, lists, count, C.rp.get(), C.ci.get(),
+                      C.v.get());
   c->check_device_errors("SpGEMM fill");
 }
 
