@@ -79,8 +79,22 @@ void* Ctx::dmalloc(size_t bytes) {
   }
   return p;
 }
+void Ctx::free_dead() {
+  std::vector<void*> d;
+  d.swap(dead);
+  for (void* p : d) {
+    if (has_alloc)
+      alloc.free(p, (void*)stream, alloc.user);
+    else
+      (void)hipFree(p);
+  }
+}
 void Ctx::dfree(void* p) {
   if (!p) return;
+  if (defer) {
+    dead.push_back(p);
+    return;
+  }
   if (has_alloc)
     alloc.free(p, (void*)stream, alloc.user);
   else
@@ -152,6 +166,7 @@ void Ctx::prof_collect() {
 }
 Ctx::~Ctx() {
   gmres_ws.reset();  // its buffers go back through this context
+  free_dead();
   if (dev_err) dfree(dev_err);
   for (auto& p : pending) {
     hipEventDestroy(p.a);
@@ -173,23 +188,26 @@ void check_csr_meta(const mgd_csr* A, bool square) {
 __global__ void k_validate(int n, int ncols, long long nnz, const int* __restrict__ rp,
                            const int* __restrict__ ci, int flags, int* __restrict__ bad) {
   const int require_diag = flags & 1, unsorted = flags & 2;
+  const int mark = flags & 4 ? kErrStructure : 0;  // added to every bit set
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const int e0 = rp[i], e1 = rp[i + 1];
-  if (i == 0 && e0 != 0) atomicOr(bad, 1);
-  if (i == n - 1 && e1 != nnz) atomicOr(bad, 1);
+  if (i == 0 && e0 != 0) atomicOr(bad, 1 | mark);
+  if (i == n - 1 && e1 != nnz) atomicOr(bad, 1 | mark);
   if (e1 < e0 || e0 < 0 || e1 > nnz) {
-    atomicOr(bad, 1);
+    atomicOr(bad, 1 | mark);
     return;
   }
   bool diag = false;
+  int last = -1;
   for (int e = e0; e < e1; ++e) {
     const int j = ci[e];
-    if (j < 0 || j >= ncols) atomicOr(bad, 2);
-    if (!unsorted && e > e0 && ci[e - 1] >= j) atomicOr(bad, 4);
+    if (j < 0 || j >= ncols) atomicOr(bad, 2 | mark);
+    if (!unsorted && e > e0 && last >= j) atomicOr(bad, 4 | mark);
     if (j == i) diag = true;
+    last = j;
   }
-  if (require_diag && !diag) atomicOr(bad, 8);
+  if (require_diag && !diag) atomicOr(bad, 8 | mark);
 }
 
 static int csr_check_bits(Ctx* c, int n_rows, int n_cols, long long nnz, const int* rp,
@@ -236,6 +254,15 @@ void check_index_structure(Ctx* c, int n_rows, int n_cols, long long nnz, const 
 }
 template void check_structure<float>(Ctx*, const Csr<float>&, const char*, bool);
 
+void check_structure_async(Ctx* c, int n_rows, int n_cols, long long nnz, const int* rp,
+                           const int* ci, bool require_diag, bool unsorted) {
+  if (n_rows == 0) return;
+  hipLaunchKernelGGL(k_validate, dim3(cdiv(n_rows, 256)), dim3(256), 0, c->stream, n_rows, n_cols,
+                     nnz, rp, ci,
+                     (require_diag ? 1 : 0) | (unsorted ? 2 : 0) | 4, c->err_flag());
+  MGD_CHECK_LAUNCH();
+}
+
 int* Ctx::err_flag() {
   if (!dev_err) {
     dev_err = static_cast<int*>(dmalloc(sizeof(int)));
@@ -246,7 +273,9 @@ int* Ctx::err_flag() {
 
 void Ctx::check_device_errors(const char* where) {
   if (!dev_err) return;
-  const int e = read1(this, dev_err);
+  throw_device_errors(read1(this, dev_err), where);
+}
+void Ctx::throw_device_errors(int e, const char* where) {
   if (e) {
     fill<int>(this, dev_err, 0, 1);
     sync();

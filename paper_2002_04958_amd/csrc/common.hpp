@@ -109,6 +109,9 @@ struct Ctx {
   std::vector<Pending> pending;
   std::vector<hipEvent_t> event_pool;
   int* dev_err = nullptr;  // set by in-kernel bounds checks
+  // frees held back until the stream has been waited for (DeferFrees)
+  int defer = 0;
+  std::vector<void*> dead;
   int64_t launches[KC_COUNT] = {};
   double ms[KC_COUNT] = {};
   double bytes[KC_COUNT] = {};
@@ -117,10 +120,16 @@ struct Ctx {
   void* dmalloc(size_t bytes);
   void dfree(void* p);
   void* host_stage(size_t bytes);  // pinned buffer of at least `bytes`
-  void sync() { MGD_HIP(hipStreamSynchronize(stream)); }
+  void sync() {
+    MGD_HIP(hipStreamSynchronize(stream));
+    if (!dead.empty()) free_dead();
+  }
+  void free_dead();
   void make_current() { MGD_HIP(hipSetDevice(device)); }
   int* err_flag();                           // device int, zero until a check fails
   void check_device_errors(const char* where);  // synchronises; throws when set
+  // the flag's value e, read back with other results: clears the flag and throws when set
+  void throw_device_errors(int e, const char* where);
   // profiling hooks
   hipEvent_t take_event();
   void prof_begin(int cls, hipEvent_t* a, hipStream_t s);
@@ -128,6 +137,23 @@ struct Ctx {
                 hipStream_t s);
   void prof_collect();  // synchronises
   ~Ctx();
+};
+
+// While a scope is open, buffers released on the context stay allocated until
+// the next synchronisation (or the end of the scope, which waits if any are
+// left): a chain of launches may let its temporaries go without waiting for
+// them, whatever the allocator does with returned memory.
+struct DeferFrees {
+  Ctx* c;
+  explicit DeferFrees(Ctx* c_) : c(c_) { ++c->defer; }
+  DeferFrees(const DeferFrees&) = delete;
+  DeferFrees& operator=(const DeferFrees&) = delete;
+  ~DeferFrees() {
+    if (--c->defer == 0 && !c->dead.empty()) {
+      (void)hipStreamSynchronize(c->stream);
+      c->free_dead();
+    }
+  }
 };
 
 // RAII scope: events around one launch (or a short fixed sequence) when
@@ -233,6 +259,14 @@ inline void copy_d2d(Ctx* c, T* d, const T* s, size_t n) {
   if (!n) return;
   device_copy(c, d, s, n * sizeof(T));
 }
+// n values through the pinned staging buffer (synchronises).
+template <typename T>
+inline std::vector<T> read_vec(Ctx* c, const T* d, size_t n) {
+  T* h = static_cast<T*>(c->host_stage(n * sizeof(T)));
+  MGD_HIP(hipMemcpyAsync(h, d, n * sizeof(T), hipMemcpyDeviceToHost, c->stream));
+  c->sync();
+  return std::vector<T>(h, h + n);
+}
 // Read a single device value (synchronises).
 template <typename T>
 inline T read1(Ctx* c, const T* d) {
@@ -280,6 +314,14 @@ inline int cdiv(long long a, long long b) { return (int)((a + b - 1) / b); }
 // throws MGD_EHIP naming `what` when a library-built structure is malformed.
 template <typename V>
 void check_structure(Ctx* c, const Csr<V>& A, const char* what, bool require_diag);
+
+// The same checks enqueued only: a malformed structure sets the context's error
+// flag (with bit kErrStructure), which the next check_device_errors or
+// throw_device_errors reports; kernels that follow read the flag and do nothing
+// once it is set.
+constexpr int kErrStructure = 1 << 20;
+void check_structure_async(Ctx* c, int n_rows, int n_cols, long long nnz, const int* rp,
+                           const int* ci, bool require_diag, bool unsorted);
 
 // Same for an index structure whose rows need not be sorted.
 void check_index_structure(Ctx* c, int n_rows, int n_cols, long long nnz, const int* rp,

@@ -617,16 +617,17 @@ void interpolation(Ctx* c, const Csr<double>& A, const DBuf<uint8_t>& S,
 // ---------------------------------------------------------------------------
 // sorted transpose
 // ---------------------------------------------------------------------------
-__global__ void k_count_cols(int nnz, const int* __restrict__ ci, int* __restrict__ cnt) {
+__global__ void k_count_cols(int nnz, const int* __restrict__ ci, int* __restrict__ cnt,
+                             const int* __restrict__ err) {
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < nnz) atomicAdd(&cnt[ci[e]], 1);
+  if (e < nnz && !*err) atomicAdd(&cnt[ci[e]], 1);
 }
 __global__ void k_transpose_fill(int n, const int* __restrict__ rp, const int* __restrict__ ci,
                                  const double* __restrict__ v, int* __restrict__ fillpos,
                                  int* __restrict__ tci, double* __restrict__ tv, int cap,
                                  int* __restrict__ err) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
+  if (i >= n || *err) return;
   for (int e = rp[i]; e < rp[i + 1]; ++e) {
     const int p = atomicAdd(&fillpos[ci[e]], 1);
     if (p < 0 || p >= cap) {
@@ -637,52 +638,66 @@ __global__ void k_transpose_fill(int n, const int* __restrict__ rp, const int* _
     tv[p] = v[e];
   }
 }
-// insertion sort of each row by column (rows of a transpose are short)
-__global__ void k_sort_rows(int n, const int* __restrict__ rp, int* __restrict__ ci,
-                            double* __restrict__ v) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int e0 = rp[i], e1 = rp[i + 1];
-  for (int e = e0 + 1; e < e1; ++e) {
-    const int kc = ci[e];
-    const double kv = v[e];
-    int q = e - 1;
-    while (q >= e0 && ci[q] > kc) {
-      ci[q + 1] = ci[q];
-      v[q + 1] = v[q];
-      --q;
-    }
-    ci[q + 1] = kc;
-    v[q + 1] = kv;
+// rows sorted by column out of place, GL lanes per row: an entry's place is the
+// number of smaller columns in its row (columns of a transpose are distinct)
+template <int GL>
+__global__ void __launch_bounds__(256) k_sort_rows(int n, const int* __restrict__ rp,
+                                                   const int* __restrict__ ci,
+                                                   const double* __restrict__ v,
+                                                   int* __restrict__ oci, double* __restrict__ ov,
+                                                   const int* __restrict__ err) {
+  const int i = blockIdx.x * (256 / GL) + threadIdx.x / GL, lane = threadIdx.x % GL;
+  if (i >= n || *err) return;
+  const int e0 = rp[i], m = rp[i + 1] - e0;
+  for (int t = lane; t < m; t += GL) {
+    const int k = ci[e0 + t];
+    int rank = 0;
+    for (int u = 0; u < m; ++u) rank += ci[e0 + u] < k ? 1 : 0;
+    oci[e0 + rank] = k;
+    ov[e0 + rank] = v[e0 + t];
   }
 }
 
+// Enqueued without waiting inside a DeferFrees scope (a malformed result then
+// shows in the error flag), otherwise complete and checked on return.
 void transpose(Ctx* c, const Csr<double>& A, Csr<double>& T) {
   T.n_rows = A.n_cols;
   T.n_cols = A.n_rows;
   T.nnz = A.nnz;
   DBuf<int> cnt(c, (size_t)std::max(A.n_cols, 1)), fillpos(c, (size_t)std::max(A.n_cols, 1));
+  DBuf<int> uci(c, (size_t)std::max(A.nnz, 1));  // rows in arrival order
+  DBuf<double> uv(c, (size_t)std::max(A.nnz, 1));
   fill<int>(c, cnt.get(), 0, (size_t)A.n_cols);
   if (A.nnz)
     hipLaunchKernelGGL(k_count_cols, dim3(cdiv(A.nnz, 256)), dim3(256), 0, c->stream, A.nnz,
-                       A.ci.get(), cnt.get());
+                       A.ci.get(), cnt.get(), (const int*)c->err_flag());
   MGD_CHECK_LAUNCH();
   T.rp.alloc(c, (size_t)A.n_cols + 1);
   exclusive_scan(c, cnt.get(), T.rp.get(), A.n_cols);
-  T.ci.alloc(c, (size_t)A.nnz);
-  T.v.alloc(c, (size_t)A.nnz);
+  T.ci.alloc(c, (size_t)std::max(A.nnz, 1));
+  T.v.alloc(c, (size_t)std::max(A.nnz, 1));
   copy_d2d(c, fillpos.get(), T.rp.get(), (size_t)A.n_cols);
   if (A.n_rows)
     hipLaunchKernelGGL(k_transpose_fill, dim3(cdiv(A.n_rows, 256)), dim3(256), 0, c->stream,
-                       A.n_rows, A.rp.get(), A.ci.get(), A.v.get(), fillpos.get(), T.ci.get(),
-                       T.v.get(), A.nnz, c->err_flag());
+                       A.n_rows, A.rp.get(), A.ci.get(), A.v.get(), fillpos.get(), uci.get(),
+                       uv.get(), A.nnz, c->err_flag());
   MGD_CHECK_LAUNCH();
+  if (T.n_rows && T.nnz) {
+    if ((double)T.nnz <= 16.0 * T.n_rows)
+      hipLaunchKernelGGL(k_sort_rows<8>, dim3(cdiv(T.n_rows, 32)), dim3(256), 0, c->stream,
+                         T.n_rows, T.rp.get(), (const int*)uci.get(), (const double*)uv.get(),
+                         T.ci.get(), T.v.get(), (const int*)c->err_flag());
+    else
+      hipLaunchKernelGGL(k_sort_rows<64>, dim3(cdiv(T.n_rows, 4)), dim3(256), 0, c->stream,
+                         T.n_rows, T.rp.get(), (const int*)uci.get(), (const double*)uv.get(),
+                         T.ci.get(), T.v.get(), (const int*)c->err_flag());
+    MGD_CHECK_LAUNCH();
+  }
+  if (c->defer) {
+    check_structure_async(c, T.n_rows, T.n_cols, T.nnz, T.rp.get(), T.ci.get(), false, false);
+    return;
+  }
   c->check_device_errors("transpose");
-  if (T.n_rows)
-      hipLaunchKernelGGL(k_sort_rows, dim3(cdiv(T.n_rows, 256)), dim3(256), 0, c->stream, T.n_rows,
-                       T.rp.get(), T.ci.get(), T.v.get());
-  MGD_CHECK_LAUNCH();
-  c->sync();
   check_structure(c, T, "transpose", false);
 }
 
@@ -1152,7 +1167,7 @@ int aggressive_split(Ctx* c, const Csr<double>& A, const DBuf<uint8_t>& S,
   fill<int>(c, stc2.get(), 0, (size_t)n1);
   if (G2.nnz)
     hipLaunchKernelGGL(k_count_cols, dim3(cdiv(G2.nnz, 256)), dim3(256), 0, c->stream, G2.nnz,
-                       G2.ci.get(), stc2.get());
+                       G2.ci.get(), stc2.get(), (const int*)c->err_flag());
   MGD_CHECK_LAUNCH();
   DBuf<int8_t> st2;
   const int rounds = pmis(c, G2, S2, stc2, seed, level + kAggressiveSalt, st2, hmis_tile);
@@ -1344,28 +1359,6 @@ void multipass_interpolation(Ctx* c, const Csr<double>& A, const DBuf<uint8_t>& 
 }
 
 // ---------------------------------------------------------------------------
-// l1 diagonal
-// ---------------------------------------------------------------------------
-__global__ void k_l1diag(int n, const int* __restrict__ rp, const int* __restrict__ ci,
-                         const double* __restrict__ v, double* __restrict__ d) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int e0 = rp[i], e1 = rp[i + 1];
-  double acc = 0.0;
-  for (int e = e0; e < e1; ++e)
-    if (ci[e] == i) acc = v[e];
-  for (int e = e0; e < e1; ++e)
-    if (ci[e] != i) acc = acc + fabs(v[e]);
-  d[i] = acc;
-}
-void plain_diagonal(Ctx* c, const Csr<double>& A, double* d) {
-  if (!A.n_rows) return;
-  hipLaunchKernelGGL(k_diag, dim3(cdiv(A.n_rows, 256)), dim3(256), 0, c->stream, A.n_rows,
-                     A.rp.get(), A.ci.get(), A.v.get(), d);
-  MGD_CHECK_LAUNCH();
-}
-
-// ---------------------------------------------------------------------------
 // Jones-Plassmann colouring (multicolour Gauss-Seidel): every stored
 // off-diagonal entry of A is an edge in both directions; in round c every
 // uncoloured row whose (hash32(seed, level, i), i) beats all uncoloured
@@ -1436,13 +1429,6 @@ int jp_colouring(Ctx* c, const Csr<double>& A, uint64_t seed, int level, DBuf<in
     if (round > n) fail(MGD_EHIP, "colouring did not terminate");
   }
   return round;
-}
-
-void l1_diagonal(Ctx* c, const Csr<double>& A, double* d) {
-  if (!A.n_rows) return;
-  hipLaunchKernelGGL(k_l1diag, dim3(cdiv(A.n_rows, 256)), dim3(256), 0, c->stream, A.n_rows,
-                     A.rp.get(), A.ci.get(), A.v.get(), d);
-  MGD_CHECK_LAUNCH();
 }
 
 // ---------------------------------------------------------------------------

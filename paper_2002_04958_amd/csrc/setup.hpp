@@ -6,6 +6,27 @@ namespace mgd {
 
 constexpr int8_t kC = 1, kF = -1, kU = 0;
 
+// Rows of a level member after member: member q has [off[q], off[q + 1]), none
+// where the two are equal.  Passed by value as a kernel argument.
+constexpr int kMaxMembers = 66;
+struct RowRanges {
+  int nm = 0;
+  int off[kMaxMembers + 1] = {};
+};
+__device__ __forceinline__ int member_of(const RowRanges& R, int i) {
+  int lo = 0, hi = R.nm;  // off[lo] <= i < off[hi]
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (R.off[mid] <= i)
+      lo = mid;
+    else
+      hi = mid;
+  }
+  return lo;
+}
+
+struct UMember;  // a member's arrays at one level, for the union builder
+
 struct SetupLevel {
   Csr<double> A;
   DBuf<int8_t> cf;  // empty on the coarsest level
@@ -20,6 +41,11 @@ struct SetupHierarchy {
   std::vector<SetupLevel> levels;
   int coarse_kind = 0;           // 0 dense LU (explicit inverse), 1 l1-Jacobi sweeps
   DBuf<double> coarse_inv;       // n_L x n_L, column-major, when coarse_kind == 0
+  size_t n_levels() const { return levels.size(); }
+  long long nnz(size_t l) const { return l < levels.size() ? levels[l].A.nnz : 0; }
+  long long nnz_P(size_t l) const { return l < levels.size() ? levels[l].P.nnz : 0; }
+  const double* inverse() const { return coarse_inv.get(); }
+  UMember member(size_t l) const;
 };
 
 // Copy a caller matrix into an owned one.
@@ -40,10 +66,6 @@ void interpolation(Ctx* c, const Csr<double>& A, const DBuf<uint8_t>& S,
 void transpose(Ctx* c, const Csr<double>& A, Csr<double>& T);
 // C = A B, structural pattern, entries summed over ascending k from 0.
 void spgemm(Ctx* c, const Csr<double>& A, const Csr<double>& B, Csr<double>& C);
-// d_i = a_ii + sum_{j != i} |a_ij| (ascending column order)
-void l1_diagonal(Ctx* c, const Csr<double>& A, double* d);
-// d_i = a_ii
-void plain_diagonal(Ctx* c, const Csr<double>& A, double* d);
 // Jones-Plassmann colouring of the structural graph of A; returns the number of colours
 int jp_colouring(Ctx* c, const Csr<double>& A, uint64_t seed, int level, DBuf<int>& colour);
 // Explicit inverse via LU with partial pivoting; returns false on a zero pivot.

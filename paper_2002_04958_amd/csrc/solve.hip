@@ -19,112 +19,282 @@ namespace mgd {
 // ===========================================================================
 // union construction
 // ===========================================================================
-// The kernels below take a C/F marker only where one exists (members with a
-// coarser level); members without one are all-F and use the _allf variants.
-// Per-row choices are written as arithmetic on both candidates rather than as
-// a select between kernel arguments under a divergent branch.
-__global__ void k_flags(int n, const int8_t* __restrict__ cf, int* __restrict__ isc,
-                        int* __restrict__ isf) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int c = cf[i] == kC ? 1 : 0;
-  isc[i] = c;
-  isf[i] = 1 - c;
+// The rows of a union level are numbered member after member ("natural", see
+// RowRanges); ext maps a natural row to its place in extended stored order and
+// perm back.  All levels are mapped and measured first, with one readback of
+// their sizes, then every level's matrices are gathered row by row straight
+// into stored order with their columns mapped on the way.  One set of launches
+// serves all members, and the windows of the length order are sorted here: a
+// wait per member and step and a sort on the host cost 60 of the 280 ms of a
+// step with new coefficients at 3D 64^3, G = 20, and 11.5 of the 21.8 ms of a
+// scalar hierarchy of 2D 1024^2.
+
+// one member at one level, as the kernels see it
+struct UMember {
+  const int* rp;      // its rows of the level matrix, columns ci - cbase local
+  const int* ci;
+  const double* v;
+  const int8_t* cf;   // C/F marker; null where the member has no coarser level
+  const int* prp;     // its rows of the interpolation, columns pci - pbase local
+  const int* pci;
+  const double* pv;
+  const int* colour;  // multicolour Gauss-Seidel only
+  int cbase, pbase;
+  int off, n;         // natural rows [off, off + n)
+  int coff;           // its first row at the next level (natural)
+  int nc;
+  int kind;           // 0 coarsening, 1 relaxed last level, 2 dense last level
+  int dense_before;   // rows of kind 2 in the members before it
+};
+
+UMember SetupHierarchy::member(size_t l) const {
+  UMember m{};
+  if (l >= levels.size()) return m;
+  const SetupLevel& L = levels[l];
+  m.rp = L.A.rp.get();
+  m.ci = L.A.ci.get();
+  m.v = L.A.v.get();
+  m.n = L.A.n_rows;
+  m.colour = L.colour.get();
+  if (l + 1 < levels.size()) {
+    m.cf = L.cf.get();
+    m.prp = L.P.rp.get();
+    m.pci = L.P.ci.get();
+    m.pv = L.P.v.get();
+    m.nc = L.nc;
+  } else {
+    m.kind = coarse_kind == 1 ? 1 : 2;
+  }
+  return m;
 }
 
-// stored index of every member row (C rows from cbase, F rows from fbase);
-// perm[stored] = off + natural
-__global__ void k_map_rows(int n, const int8_t* __restrict__ cf, const int* __restrict__ cidx,
-                           const int* __restrict__ fidx, int cbase, int fbase, int off,
-                           int* __restrict__ srow, int* __restrict__ perm) {
+// isc[i] = 1 for C rows.  Members without a coarser level are all F.
+__global__ void k_u_flags(int n, RowRanges R, const UMember* __restrict__ tab,
+                          int* __restrict__ isc) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  const int c = cf[i] == kC ? 1 : 0;
-  const int sc = cbase + cidx[i], sf = fbase + fidx[i];
-  const int s = sf + c * (sc - sf);
-  srow[i] = s;
-  perm[s] = off + i;
-}
-__global__ void k_map_rows_allf(int n, int fbase, int off, int* __restrict__ srow,
-                                int* __restrict__ perm) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  srow[i] = fbase + i;
-  perm[fbase + i] = off + i;
+  const UMember m = tab[member_of(R, i)];
+  isc[i] = m.cf ? (m.cf[i - m.off] == kC ? 1 : 0) : 0;
 }
 
-// every stored row must be hit exactly once before the map drives any write
-__global__ void k_count_hits(int n, const int* __restrict__ srow, int nS, int* __restrict__ hits,
-                             int* __restrict__ bad) {
+// extended stored position of every row: C rows in order, then F rows (and rows
+// of relaxed last levels), then dense rows.  The candidates are combined by
+// arithmetic rather than by a select between kernel arguments under a divergent
+// branch.
+__global__ void k_u_map(int n, int nC, int nS, RowRanges R, const UMember* __restrict__ tab,
+                        const int* __restrict__ isc, const int* __restrict__ cidx,
+                        int* __restrict__ ext, int* __restrict__ perm, int* __restrict__ err) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  const int s = srow[i];
-  if (s < 0 || s >= nS) {
-    atomicOr(bad, 1);
+  const UMember m = tab[member_of(R, i)];
+  const int c = isc[i], d = m.kind == 2 ? 1 : 0;
+  const int sc = cidx[i], sf = nC + i - cidx[i] - m.dense_before;
+  const int sd = nS + m.dense_before + (i - m.off);
+  int s = sf + c * (sc - sf);
+  s = s + d * (sd - s);
+  ext[i] = s;
+  if (s < 0 || s >= n) {
+    atomicOr(err, 1);
     return;
   }
-  atomicAdd(&hits[s], 1);
+  perm[s] = i;
 }
-__global__ void k_check_hits(int nS, const int* __restrict__ hits, int* __restrict__ bad) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s < nS && hits[s] != 1) atomicOr(bad, 2);
-}
-
-// row lengths into the stored order: all rows, or F rows only (W)
-__global__ void k_row_len(int n, const int* __restrict__ rp, const int* __restrict__ srow,
-                          int* __restrict__ len) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  len[srow[i]] = rp[i + 1] - rp[i];
-}
-__global__ void k_row_len_f(int n, const int* __restrict__ rp, const int* __restrict__ srow,
-                            int sbase, const int8_t* __restrict__ cf, int* __restrict__ len) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  if (cf[i] == kC) return;
-  len[srow[i] - sbase] = rp[i + 1] - rp[i];
+// n rows on n places, each place taken (perm starts as -1): a permutation
+__global__ void k_u_check(int n, const int* __restrict__ ext, const int* __restrict__ perm,
+                          int* __restrict__ err) {
+  const int k = blockIdx.x * blockDim.x + threadIdx.x;
+  if (k >= n) return;
+  const int i = perm[k];
+  if (i < 0 || i >= n || ext[i] != k) atomicOr(err, 2);
 }
 
-// copy rows into the stored order (columns shifted by coloff): all rows, or F rows only
-__device__ __forceinline__ void copy_row(const int* __restrict__ rp, const int* __restrict__ ci,
-                                         const double* __restrict__ v, int i, int coloff, int p,
-                                         int pend, int* __restrict__ dci, double* __restrict__ dv,
-                                         int* __restrict__ err) {
-  if (rp[i + 1] - rp[i] != pend - p) {  // target row length differs from the source row
-    atomicOr(err, 4);
+constexpr int kSortWindow = 128;  // two 64-row slices: less padding, gathers stay local
+
+// Rows of the C-block and of the F-block in order of decreasing length (stable)
+// within windows of kSortWindow rows, one workgroup per window: a row's rank is
+// the number of longer rows, and of equally long ones before it.
+__global__ void __launch_bounds__(kSortWindow) k_u_window_sort(int nC, int nS, int nwC, RowRanges R,
+                                                               const UMember* __restrict__ tab,
+                                                               int* __restrict__ ext,
+                                                               int* __restrict__ perm,
+                                                               const int* __restrict__ err) {
+  __shared__ int lens[kSortWindow];
+  if (*err) return;
+  const int b = blockIdx.x, t = threadIdx.x;
+  const int w0 = b < nwC ? b * kSortWindow : nC + (b - nwC) * kSortWindow;
+  const int w1 = min(b < nwC ? nC : nS, w0 + kSortWindow);
+  int i = 0, len = -1;
+  if (w0 + t < w1) {
+    i = perm[w0 + t];
+    const UMember m = tab[member_of(R, i)];
+    len = m.rp[i - m.off + 1] - m.rp[i - m.off];
+  }
+  lens[t] = len;
+  __syncthreads();
+  if (w0 + t >= w1) return;
+  int rank = 0;
+  for (int u = 0; u < kSortWindow; ++u) rank += (lens[u] > len || (lens[u] == len && u < t)) ? 1 : 0;
+  perm[w0 + rank] = i;
+  ext[i] = w0 + rank;
+}
+
+// the colour of every stored row (multicolour Gauss-Seidel)
+__global__ void k_u_colours(int nS, RowRanges R, const UMember* __restrict__ tab,
+                            const int* __restrict__ perm, int* __restrict__ col) {
+  const int k = blockIdx.x * blockDim.x + threadIdx.x;
+  if (k >= nS) return;
+  const int i = perm[k];
+  const UMember m = tab[member_of(R, i)];
+  col[k] = m.colour[i - m.off];
+}
+
+// row lengths in stored order: the level matrix, and W (F rows)
+__global__ void k_u_len(int nC, int nS, RowRanges R, const UMember* __restrict__ tab,
+                        const int* __restrict__ perm, int* __restrict__ alen,
+                        int* __restrict__ wlen, const int* __restrict__ err) {
+  const int k = blockIdx.x * blockDim.x + threadIdx.x;
+  if (k >= nS) return;
+  if (*err) {  // a malformed map: empty rows, reported with the sizes
+    alen[k] = 0;
+    if (k >= nC) wlen[k - nC] = 0;
     return;
   }
-  for (int e = rp[i]; e < rp[i + 1]; ++e, ++p) {
-    dci[p] = ci[e] + coloff;
-    dv[p] = v[e];
-  }
-}
-__global__ void k_row_copy(int n, const int* __restrict__ rp, const int* __restrict__ ci,
-                           const double* __restrict__ v, const int* __restrict__ srow, int coloff,
-                           const int* __restrict__ drp, int* __restrict__ dci,
-                           double* __restrict__ dv, int* __restrict__ err) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int s = srow[i];
-  copy_row(rp, ci, v, i, coloff, drp[s], drp[s + 1], dci, dv, err);
-}
-__global__ void k_row_copy_f(int n, const int* __restrict__ rp, const int* __restrict__ ci,
-                             const double* __restrict__ v, const int* __restrict__ srow, int sbase,
-                             const int8_t* __restrict__ cf, int coloff,
-                             const int* __restrict__ drp, int* __restrict__ dci,
-                             double* __restrict__ dv, int* __restrict__ err) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  if (cf[i] == kC) return;
-  const int s = srow[i] - sbase;
-  copy_row(rp, ci, v, i, coloff, drp[s], drp[s + 1], dci, dv, err);
+  const int i = perm[k];
+  const UMember m = tab[member_of(R, i)];
+  const int r = i - m.off;
+  alen[k] = m.rp[r + 1] - m.rp[r];
+  if (k >= nC) wlen[k - nC] = m.kind == 0 ? m.prp[r + 1] - m.prp[r] : 0;
 }
 
-__global__ void k_iota(int n, int first, int* __restrict__ out) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] = first + i;
+// 64 x the longest row of every 64-row slice, and the longest row of all: one
+// wave per slice, at most kStatBlocks workgroups so that few of them meet in the
+// one maximum
+constexpr int kStatBlocks = 1024;
+__global__ void __launch_bounds__(256) k_row_stats(int rows, const int* __restrict__ rp,
+                                                   int* __restrict__ w64,
+                                                   int* __restrict__ longest) {
+  int most = 0;
+  const int ns = (rows + 63) / 64;
+  for (int s = blockIdx.x * 4 + (threadIdx.x >> 6); s < ns; s += gridDim.x * 4) {
+    const int k = 64 * s + (threadIdx.x & 63);
+    int m = k < rows ? rp[k + 1] - rp[k] : 0;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) m = max(m, __shfl_xor(m, off, 64));
+    if ((threadIdx.x & 63) == 0) w64[s] = 64 * m;
+    most = max(most, m);
+  }
+  if ((threadIdx.x & 63) == 0 && most > 0) atomicMax(longest, most);
 }
-// inverse of a permutation given as perm[k] (k < n), with a range check
+
+// sizes of one level for the readback (slots may be absent)
+__global__ void k_u_sizes(const int* __restrict__ arp, int nS, int nC, const int* __restrict__ wrp,
+                          int nF, const int* __restrict__ err, int* __restrict__ out) {
+  out[0] = nS > 0 ? arp[nS] : 0;
+  out[1] = nS > 0 ? arp[nC] : 0;
+  out[2] = nF > 0 ? wrp[nF] : 0;
+  out[3] = *err;
+}
+
+// GL lanes copy one stored row: entries in source order, columns through the map
+template <int GL>
+__global__ void __launch_bounds__(256) k_u_rows(int nS, int n, RowRanges R,
+                                                const UMember* __restrict__ tab,
+                                                const int* __restrict__ perm,
+                                                const int* __restrict__ ext,
+                                                const int* __restrict__ arp, int* __restrict__ ci,
+                                                double* __restrict__ v, int* __restrict__ err) {
+  const int k = blockIdx.x * (256 / GL) + threadIdx.x / GL, lane = threadIdx.x % GL;
+  if (k >= nS) return;
+  const int i = perm[k];
+  const UMember m = tab[member_of(R, i)];
+  const int e0 = m.rp[i - m.off], len = m.rp[i - m.off + 1] - e0, p = arp[k];
+  if (len != arp[k + 1] - p) {  // another length than the row was given
+    if (lane == 0) atomicOr(err, 4);
+    return;
+  }
+  for (int e = lane; e < len; e += GL) {
+    const int j = m.ci[e0 + e] - m.cbase;
+    if (j < 0 || j >= m.n) {
+      atomicOr(err, 16);
+      ci[p + e] = 0;
+      continue;
+    }
+    ci[p + e] = ext[m.off + j];
+    v[p + e] = m.v[e0 + e];
+  }
+}
+// W: the interpolation's F rows, columns in the next level's extended order
+template <int GL>
+__global__ void __launch_bounds__(256) k_u_wrows(int nC, int nF, RowRanges R,
+                                                 const UMember* __restrict__ tab,
+                                                 const int* __restrict__ perm,
+                                                 const int* __restrict__ ext_next,
+                                                 const int* __restrict__ wrp,
+                                                 int* __restrict__ ci, double* __restrict__ v,
+                                                 int* __restrict__ err) {
+  const int f = blockIdx.x * (256 / GL) + threadIdx.x / GL, lane = threadIdx.x % GL;
+  if (f >= nF) return;
+  const int i = perm[nC + f];
+  const UMember m = tab[member_of(R, i)];
+  if (m.kind != 0) return;
+  const int e0 = m.prp[i - m.off], len = m.prp[i - m.off + 1] - e0, p = wrp[f];
+  if (len != wrp[f + 1] - p) {
+    if (lane == 0) atomicOr(err, 4);
+    return;
+  }
+  for (int e = lane; e < len; e += GL) {
+    const int j = m.pci[e0 + e] - m.pbase;
+    if (j < 0 || j >= m.nc) {
+      atomicOr(err, 16);
+      ci[p + e] = 0;
+      continue;
+    }
+    ci[p + e] = ext_next[m.coff + j];
+    v[p + e] = m.pv[e0 + e];
+  }
+}
+// C position <-> the next level's extended index (a C row's interpolation is
+// its one coarse point)
+__global__ void k_u_cmap(int nC, int n_next, RowRanges R, const UMember* __restrict__ tab,
+                         const int* __restrict__ perm, const int* __restrict__ ext_next,
+                         int* __restrict__ cmap, int* __restrict__ cpos, int* __restrict__ err) {
+  const int k = blockIdx.x * blockDim.x + threadIdx.x;
+  if (k >= nC) return;
+  const int i = perm[k];
+  const UMember m = tab[member_of(R, i)];
+  const int j = m.pci[m.prp[i - m.off]] - m.pbase;
+  if (j < 0 || j >= m.nc || m.coff + j >= n_next) {
+    atomicOr(err, 64);
+    cmap[k] = 0;
+    return;
+  }
+  const int x = ext_next[m.coff + j];
+  cmap[k] = x;
+  cpos[x] = k;
+}
+// every C position is the one its coarse point names
+__global__ void k_u_cmap_check(int nC, const int* __restrict__ cmap, const int* __restrict__ cpos,
+                               int* __restrict__ err) {
+  const int k = blockIdx.x * blockDim.x + threadIdx.x;
+  if (k < nC && cpos[cmap[k]] != k) atomicOr(err, 8);
+}
+// 1 / l1 diagonal of the stored rows (a_kk, then |a_kj| in entry order), and
+// 1 / a_kk where wanted
+template <typename T>
+__global__ void k_u_dinv(int nS, const int* __restrict__ rp, const int* __restrict__ ci,
+                         const double* __restrict__ v, T* __restrict__ dinv, T* __restrict__ dgs) {
+  const int k = blockIdx.x * blockDim.x + threadIdx.x;
+  if (k >= nS) return;
+  const int e0 = rp[k], e1 = rp[k + 1];
+  double dg = 0.0;
+  for (int e = e0; e < e1; ++e)
+    if (ci[e] == k) dg = v[e];
+  double acc = dg;
+  for (int e = e0; e < e1; ++e)
+    if (ci[e] != k) acc = acc + fabs(v[e]);
+  dinv[k] = (T)(1.0 / acc);
+  if (dgs) dgs[k] = (T)(1.0 / dg);
+}
 template <typename T>
 __global__ void k_dinv_nat(int n, int nC, const int* __restrict__ iperm,
                            const T* __restrict__ dinv, T* __restrict__ dn) {
@@ -133,113 +303,29 @@ __global__ void k_dinv_nat(int n, int nC, const int* __restrict__ iperm,
   const int k = iperm[p];
   dn[p] = k < nC ? dinv[k] : (T)0;
 }
-__global__ void k_invert(int n, const int* __restrict__ perm, int* __restrict__ inv,
-                         int* __restrict__ err) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n) return;
-  const int i = perm[k];
-  if (i < 0 || i >= n) {
-    atomicOr(err, 8);
-    return;
-  }
-  inv[i] = k;
-}
-// columns through a map (entry order kept)
-__global__ void k_remap(long long nnz, const int* __restrict__ map, int ncols_map,
-                        int* __restrict__ ci, int* __restrict__ err) {
-  const long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-  if (e >= nnz) return;
-  const int j = ci[e];
-  if (j < 0 || j >= ncols_map) {
-    atomicOr(err, 16);
-    return;
-  }
-  ci[e] = map[j];
-}
-// row gather: out row k = in row src[k]
-__global__ void k_gather_len(int n, const int* __restrict__ rp, const int* __restrict__ src,
-                             int* __restrict__ len) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < n) len[k] = rp[src[k] + 1] - rp[src[k]];
-}
-__global__ void k_gather_rows(int n, const int* __restrict__ rp, const int* __restrict__ ci,
-                              const double* __restrict__ v, const int* __restrict__ src,
-                              const int* __restrict__ orp, int* __restrict__ oci,
-                              double* __restrict__ ov, int* __restrict__ err) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n) return;
-  const int i = src[k];
-  int p = orp[k];
-  if (orp[k + 1] - p != rp[i + 1] - rp[i]) {
-    atomicOr(err, 32);
-    return;
-  }
-  for (int e = rp[i]; e < rp[i + 1]; ++e, ++p) {
-    oci[p] = ci[e];
-    ov[p] = v[e];
-  }
-}
-// out[idx[i]] = v[i]
-__global__ void k_scatter_int(int n, const int* __restrict__ idx, const int* __restrict__ v,
-                              int* __restrict__ out) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[idx[i]] = v[i];
-}
 
-// out[i] = a[b[i]] with b[i] in [0, na)
-__global__ void k_compose(int n, const int* __restrict__ a, int na, const int* __restrict__ bidx,
-                          int* __restrict__ out, int* __restrict__ err) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int j = bidx[i];
-  if (j < 0 || j >= na) {
-    atomicOr(err, 64);
-    return;
-  }
-  out[i] = a[j];
-}
+static void row_stats(Ctx* c, int rows, const int* rp, DBuf<int>& w64, DBuf<int>& soff,
+                      int* longest);
 
-template <typename T>
-__global__ void k_dinv(int n, const double* __restrict__ d, const int* __restrict__ srow,
-                       T* __restrict__ dinv) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  dinv[srow[i]] = (T)(1.0 / d[i]);
-}
-
-struct MemberAtLevel {
-  const SetupHierarchy* H;
-  const SetupLevel* lev;
-  int kind;  // 0 coarsening, 1 relaxed last level, 2 dense last level
-  int off, n, nc;
-};
-
-// Level products of the construction pass, before the stored-order finalisation.
+// Level products between the mapping pass and the layouts.
 template <typename T>
 struct BuildLevel {
-  int n = 0, nS = 0, nC = 0, n_coarse = 0;
-  Csr<double> A;   // nS rows (stored order), natural columns
-  Csr<double> W;   // nS - nC rows, coarse natural columns
-  Csr<double> Wt;  // n_coarse rows (coarse natural), F-index columns
-  DBuf<int> perm;  // stored -> natural (nS)
-  DBuf<int> cnat;  // C-block position -> coarse natural index (nC); empty: identity
-  DBuf<T> dinv;    // nS
-  DBuf<T> dgs;     // 1 / a_ii (multicolour Gauss-Seidel)
-  std::vector<std::array<int, 4>> cranges;  // per colour: C-block [lo, hi), F-block [lo, hi)
-  long long nnz_C = 0;
-  struct Dense {
-    int off, n;
-    const double* inv;
-  };
-  std::vector<Dense> dense;  // natural offsets
+  int n = 0, nS = 0, nC = 0, nF = 0, n_coarse = 0;
+  RowRanges R;
+  size_t tab = 0;            // its members in the device table
+  long long want_a = 0, want_w = 0;  // entries the stored matrix and W must end with
+  DBuf<int> ext, perm;       // natural -> extended stored order, and back
+  DBuf<int> arp, wrp;
+  DBuf<int> aw64, asoff, ww64, wsoff, tw64, tsoff;  // SELL widths and offsets (A, W, W^T)
+  Csr<double> A, W, Wt;      // stored order
 };
 template <typename T>
-static void finalize_levels(Ctx* c, std::vector<BuildLevel<T>>& bl, Union<T>& U, int autotune);
+static void layout_levels(Ctx* c, std::vector<BuildLevel<T>>& bl, const int* stats, Union<T>& U,
+                          int autotune);
 
-// Host-side verification of a union level (MGD_DEBUG_UNION=1): the stored-row
-// map is a permutation, row lengths and row pointers agree with the members'
-// matrices, and every copied row equals its source row.  Throws with the first
-// mismatch; used to diagnose, never needed for correct operation.
+// Host-side verification of a union level (MGD_DEBUG_UNION=1): the map is a
+// permutation and every stored row equals its source row.  Throws with the
+// first mismatch; used to diagnose, never needed for correct operation.
 static bool debug_union() {
   static const bool on = [] {
     const char* e = std::getenv("MGD_DEBUG_UNION");
@@ -247,361 +333,298 @@ static bool debug_union() {
   }();
   return on;
 }
-static void verify_flags_and_scans(Ctx* c, int n, const int8_t* cf_d, const int* isc_d,
-                                   const int* isf_d, const int* cidx_d, const int* fidx_d) {
-  std::vector<int8_t> cf(n, 0);
-  std::vector<int> isc(n), isf(n), cidx((size_t)n + 1), fidx((size_t)n + 1);
-  if (cf_d) copy_d2h(c, cf.data(), cf_d, (size_t)n);
-  copy_d2h(c, isc.data(), isc_d, (size_t)n);
-  copy_d2h(c, isf.data(), isf_d, (size_t)n);
-  copy_d2h(c, cidx.data(), cidx_d, (size_t)n + 1);
-  copy_d2h(c, fidx.data(), fidx_d, (size_t)n + 1);
-  int sc = 0, sf = 0;
-  for (int i = 0; i <= n; ++i) {
-    if (cidx[i] != sc || fidx[i] != sf) {
-      std::string ctx = "";
-      for (int k = std::max(0, i - 3); k < std::min(n, i + 4); ++k)
-        ctx += " [" + std::to_string(k) + ": cf " + std::to_string((int)cf[k]) + " isc " +
-               std::to_string(isc[k]) + " isf " + std::to_string(isf[k]) + " cidx " +
-               std::to_string(cidx[k]) + " fidx " + std::to_string(fidx[k]) + "]";
-      fail(MGD_EHIP, "union debug: scan mismatch at " + std::to_string(i) + " of " +
-                         std::to_string(n) + ": cidx " + std::to_string(cidx[i]) + " expected " +
-                         std::to_string(sc) + ", fidx " + std::to_string(fidx[i]) + " expected " +
-                         std::to_string(sf) + ";" + ctx);
-    }
-    if (i == n) break;
-    const int want = cf_d && cf[i] == kC ? 1 : 0;
-    if (isc[i] != want || isf[i] != 1 - want)
-      fail(MGD_EHIP, "union debug: flags at " + std::to_string(i) + ": cf " +
-                         std::to_string((int)cf[i]) + " isc " + std::to_string(isc[i]) + " isf " +
-                         std::to_string(isf[i]));
-    sc += isc[i];
-    sf += isf[i];
-  }
-}
-static void verify_union_level(Ctx* c, const std::vector<MemberAtLevel>& ms,
-                               const std::vector<DBuf<int>>& srows, int nS, const int* alen_d,
-                               const Csr<double>* Ad) {
-  std::vector<int> alen(nS), seen(nS, -1);
-  copy_d2h(c, alen.data(), alen_d, (size_t)nS);
-  std::vector<int> arp, aci;
-  if (Ad) {
-    arp.resize((size_t)nS + 1);
-    aci.resize((size_t)std::max(Ad->nnz, 1));
-    copy_d2h(c, arp.data(), Ad->rp.get(), (size_t)nS + 1);
-    copy_d2h(c, aci.data(), Ad->ci.get(), (size_t)Ad->nnz);
-    long long acc = 0;
-    for (int s = 0; s < nS; ++s) {
-      if (arp[s] != acc)
-        fail(MGD_EHIP, "union debug: row_ptr[" + std::to_string(s) + "] = " +
-                           std::to_string(arp[s]) + ", scan of lengths gives " + std::to_string(acc));
-      acc += alen[s];
-    }
-    if (arp[nS] != acc || acc != Ad->nnz)
-      fail(MGD_EHIP, "union debug: row_ptr[nS] = " + std::to_string(arp[nS]) + ", total " +
-                         std::to_string(acc) + ", nnz " + std::to_string(Ad->nnz));
-  }
-  for (size_t q = 0; q < ms.size(); ++q) {
-    const auto& m = ms[q];
-    if (m.kind == 2) continue;
-    const int n = m.n;
-    std::vector<int> srow(n), rp((size_t)n + 1), ci((size_t)std::max(m.lev->A.nnz, 1));
-    copy_d2h(c, srow.data(), srows[q].get(), (size_t)n);
-    copy_d2h(c, rp.data(), m.lev->A.rp.get(), (size_t)n + 1);
-    copy_d2h(c, ci.data(), m.lev->A.ci.get(), (size_t)m.lev->A.nnz);
-    for (int i = 0; i < n; ++i) {
-      const int s = srow[i];
+template <typename T>
+static void verify_union_level(Ctx* c, const std::vector<UMember>& tab, const BuildLevel<T>& b) {
+  std::vector<int> ext(b.n), arp((size_t)b.nS + 1), aci((size_t)std::max(b.A.nnz, 1)), seen(b.n, 0);
+  std::vector<double> av((size_t)std::max(b.A.nnz, 1));
+  copy_d2h(c, ext.data(), b.ext.get(), (size_t)b.n);
+  if (b.nS > 0) copy_d2h(c, arp.data(), b.A.rp.get(), (size_t)b.nS + 1);
+  copy_d2h(c, aci.data(), b.A.ci.get(), (size_t)b.A.nnz);
+  copy_d2h(c, av.data(), b.A.v.get(), (size_t)b.A.nnz);
+  for (int q = 0; q < b.R.nm; ++q) {
+    const UMember& m = tab[b.tab + q];
+    if (m.n == 0) continue;
+    std::vector<int> rp((size_t)m.n + 1);
+    copy_d2h(c, rp.data(), m.rp, (size_t)m.n + 1);
+    const int e0 = rp[0], ne = rp[m.n] - e0;
+    std::vector<int> ci((size_t)std::max(ne, 1));
+    std::vector<double> v((size_t)std::max(ne, 1));
+    copy_d2h(c, ci.data(), m.ci + e0, (size_t)ne);
+    copy_d2h(c, v.data(), m.v + e0, (size_t)ne);
+    for (int i = 0; i < m.n; ++i) {
+      const int s = ext[m.off + i];
       const std::string at = "member " + std::to_string(q) + " row " + std::to_string(i) +
                              " -> stored " + std::to_string(s);
-      if (s < 0 || s >= nS) fail(MGD_EHIP, "union debug: " + at + " out of range");
-      if (seen[s] >= 0)
-        fail(MGD_EHIP, "union debug: " + at + " also taken by row " + std::to_string(seen[s]));
-      seen[s] = i;
+      if (s < 0 || s >= b.n) fail(MGD_EHIP, "union debug: " + at + " out of range");
+      if (seen[s]++) fail(MGD_EHIP, "union debug: " + at + " taken twice");
+      if ((m.kind == 2) != (s >= b.nS)) fail(MGD_EHIP, "union debug: " + at + " in the wrong region");
+      if (m.kind == 2) continue;
       const int len = rp[i + 1] - rp[i];
-      if (alen[s] != len)
-        fail(MGD_EHIP, "union debug: " + at + " length " + std::to_string(alen[s]) + ", source " +
-                           std::to_string(len));
-      if (Ad)
-        for (int k = 0; k < len; ++k)
-          if (aci[(size_t)arp[s] + k] != ci[(size_t)rp[i] + k] + m.off)
-            fail(MGD_EHIP, "union debug: " + at + " entry " + std::to_string(k) + " column " +
-                               std::to_string(aci[(size_t)arp[s] + k]) + ", source " +
-                               std::to_string(ci[(size_t)rp[i] + k]) + " + " + std::to_string(m.off));
+      if (arp[s + 1] - arp[s] != len)
+        fail(MGD_EHIP, "union debug: " + at + " length " + std::to_string(arp[s + 1] - arp[s]) +
+                           ", source " + std::to_string(len));
+      for (int k = 0; k < len; ++k)
+        if (aci[(size_t)arp[s] + k] != ext[m.off + ci[(size_t)rp[i] - e0 + k] - m.cbase] ||
+            av[(size_t)arp[s] + k] != v[(size_t)rp[i] - e0 + k])
+          fail(MGD_EHIP, "union debug: " + at + " entry " + std::to_string(k) + " differs");
     }
   }
 }
 
-constexpr int kSortWindow = 128;  // two 64-row slices: less padding, gathers stay local
+// multicolour Gauss-Seidel: stored rows of each block in order of their colour
+template <typename T>
+static void colour_order(Ctx* c, BuildLevel<T>& b, const UMember* tab,
+                         std::vector<std::array<int, 4>>& cranges) {
+  const int nS = b.nS, nC = b.nC;
+  DBuf<int> cold(c, (size_t)nS);
+  hipLaunchKernelGGL(k_u_colours, dim3(cdiv(nS, 256)), dim3(256), 0, c->stream, nS, b.R, tab,
+                     (const int*)b.perm.get(), cold.get());
+  MGD_CHECK_LAUNCH();
+  std::vector<int> col(nS), pm(nS), order(nS), ext(b.n);
+  copy_d2h(c, col.data(), cold.get(), (size_t)nS);
+  copy_d2h(c, pm.data(), b.perm.get(), (size_t)nS);
+  copy_d2h(c, ext.data(), b.ext.get(), (size_t)b.n);
+  for (int k = 0; k < nS; ++k) order[k] = k;
+  auto by_col = [&](int x, int y) { return col[x] < col[y]; };
+  std::stable_sort(order.begin(), order.begin() + nC, by_col);
+  std::stable_sort(order.begin() + nC, order.end(), by_col);
+  int ncol = 0;
+  for (int k = 0; k < nS; ++k) ncol = std::max(ncol, col[k] + 1);
+  cranges.assign(ncol, {nC, nC, nS, nS});
+  for (int k = nS - 1; k >= 0; --k) cranges[col[order[k]]][k < nC ? 0 : 2] = k;
+  for (int k = 0; k < nS; ++k) cranges[col[order[k]]][k < nC ? 1 : 3] = k + 1;
+  for (auto& r : cranges) {  // colours absent from a block: empty range
+    if (r[1] <= r[0]) r[0] = r[1] = 0;
+    if (r[3] <= r[2]) r[2] = r[3] = 0;
+  }
+  std::vector<int> pm2(nS);
+  for (int k = 0; k < nS; ++k) {
+    pm2[k] = pm[order[k]];
+    MGD_REQUIRE(pm2[k] >= 0 && pm2[k] < b.n, "internal: malformed stored-row map");
+    ext[pm2[k]] = k;
+  }
+  copy_h2d(c, b.perm.get(), pm2.data(), (size_t)nS);
+  copy_h2d(c, b.ext.get(), ext.data(), (size_t)b.n);
+}
 
 template <typename T>
 std::unique_ptr<Union<T>> build_union(Ctx* c, const std::vector<const SetupHierarchy*>& members,
                                       int n_pre, int n_post, int autotune, int smoother) {
+  DeferFrees frees(c);
   auto U = std::make_unique<Union<T>>();
   U->n_pre = n_pre;
   U->n_post = n_post;
   U->gs = smoother == 1;
   U->members = (int)members.size();
-  std::vector<BuildLevel<T>> built;
+  MGD_REQUIRE(members.size() <= (size_t)kMaxMembers, "internal: too many members in a union");
   size_t maxL = 0;
-  for (auto* H : members) maxL = std::max(maxL, H->levels.size());
+  for (auto* H : members) maxL = std::max(maxL, H->n_levels());
+  // host side: the levels' sizes and the members' places in them
+  std::vector<BuildLevel<T>> bl;
+  std::vector<UMember> tab;
   for (size_t l = 0; l < maxL; ++l) {
-    StepScope st("solve-phase build: level " + std::to_string(l) + " of " +
+    BuildLevel<T> b;
+    b.tab = tab.size();
+    b.R.nm = (int)members.size();
+    int dense = 0;
+    for (size_t q = 0; q < members.size(); ++q) {
+      const SetupHierarchy* H = members[q];
+      UMember m = H->member(l);
+      m.off = b.n;
+      m.coff = b.n_coarse;
+      m.dense_before = dense;
+      b.R.off[q] = b.n;
+      if (m.n > 0) {
+        if (m.kind == 2)
+          dense += m.n;
+        else
+          b.want_a += H->nnz(l);
+        if (m.kind == 0) b.want_w += H->nnz_P(l) - m.nc;
+      }
+      b.n += m.n;
+      b.nC += m.nc;
+      b.n_coarse += m.nc;
+      tab.push_back(m);
+    }
+    b.R.off[b.R.nm] = b.n;
+    b.nS = b.n - dense;
+    b.nF = b.nS - b.nC;
+    MGD_REQUIRE(b.want_a < INT32_MAX && b.want_w < INT32_MAX, "union too large for int32 indices");
+    bl.push_back(std::move(b));
+    if (bl.back().n_coarse == 0) break;
+  }
+  const int nl = (int)bl.size();
+  DBuf<UMember> dtab(c, std::max<size_t>(tab.size(), 1));
+  copy_h2d(c, dtab.get(), tab.data(), tab.size());
+  U->L.resize(nl);
+  int* err = c->err_flag();
+  // maps and row lengths of every level
+  DBuf<int> sizes(c, (size_t)nl * 4), stats(c, (size_t)nl * 6);
+  fill<int>(c, stats.get(), 0, (size_t)nl * 6);
+  for (int l = 0; l < nl; ++l) {
+    StepScope st("solve-phase build: order of level " + std::to_string(l) + " of " +
                  std::to_string(members.size()) + " hierarchies");
-    std::vector<MemberAtLevel> ms;
-    int off = 0, nCtot = 0, nFtot = 0, ncoarse = 0;
-    for (auto* H : members) {
-      if (l >= H->levels.size()) continue;
-      MemberAtLevel m;
-      m.H = H;
-      m.lev = &H->levels[l];
-      const bool last = (l + 1 == H->levels.size());
-      m.kind = !last ? 0 : (H->coarse_kind == 1 ? 1 : 2);
-      m.off = off;
-      m.n = m.lev->A.n_rows;
-      m.nc = m.kind == 0 ? m.lev->nc : 0;
-      off += m.n;
-      if (m.kind == 0) {
-        nCtot += m.nc;
-        nFtot += m.n - m.nc;
-        ncoarse += m.nc;
-      } else if (m.kind == 1) {
-        nFtot += m.n;
-      }
-      ms.push_back(m);
-    }
-    BuildLevel<T> lv;
-    lv.n = off;
-    lv.nC = nCtot;
-    lv.nS = nCtot + nFtot;
-    lv.n_coarse = ncoarse;
-    const int nS = lv.nS, nF = nFtot;
-    lv.perm.alloc(c, (size_t)std::max(nS, 1));
-    lv.dinv.alloc(c, (size_t)std::max(nS, 1));
-    if (smoother == 1) lv.dgs.alloc(c, (size_t)std::max(nS, 1));
-    DBuf<int> alen(c, (size_t)nS + 1), wlen(c, (size_t)nF + 1), hits(c, (size_t)nS + 1);
-    fill<int>(c, alen.get(), 0, (size_t)nS + 1);
-    fill<int>(c, wlen.get(), 0, (size_t)nF + 1);
-    fill<int>(c, hits.get(), 0, (size_t)nS + 1);
-    int* bad = c->err_flag();
-    std::vector<DBuf<int>> srows;
-    int cbase = 0, fbase = nCtot;
-    long long want_a = 0, want_w = 0;  // nnz the stored matrix and W must end with
-    for (auto& m : ms) {
-      DBuf<int> srow;
-      if (m.kind == 2) {
-        srows.push_back(std::move(srow));
-        continue;
-      }
-      const int n = m.n, g = cdiv(n, 256);
-      srow.alloc(c, (size_t)n);
-      const int8_t* cf = m.kind == 0 ? m.lev->cf.get() : nullptr;
-      if (m.kind == 0) {
-        DBuf<int> isc(c, n), isf(c, n), cidx(c, (size_t)n + 1), fidx(c, (size_t)n + 1);
-        hipLaunchKernelGGL(k_flags, dim3(g), dim3(256), 0, c->stream, n, cf, isc.get(), isf.get());
-        MGD_CHECK_LAUNCH();
-        exclusive_scan(c, isc.get(), cidx.get(), n);
-        exclusive_scan(c, isf.get(), fidx.get(), n);
-        if (debug_union()) verify_flags_and_scans(c, n, cf, isc.get(), isf.get(), cidx.get(), fidx.get());
-        hipLaunchKernelGGL(k_map_rows, dim3(g), dim3(256), 0, c->stream, n, cf,
-                           (const int*)cidx.get(), (const int*)fidx.get(), cbase, fbase, m.off,
-                           srow.get(), lv.perm.get());
-        MGD_CHECK_LAUNCH();
-        c->sync();
-      } else {
-        hipLaunchKernelGGL(k_map_rows_allf, dim3(g), dim3(256), 0, c->stream, n, fbase, m.off,
-                           srow.get(), lv.perm.get());
-        MGD_CHECK_LAUNCH();
-      }
-      hipLaunchKernelGGL(k_count_hits, dim3(g), dim3(256), 0, c->stream, n,
-                         (const int*)srow.get(), nS, hits.get(), bad);
+    BuildLevel<T>& b = bl[l];
+    const UMember* dt = dtab.get() + b.tab;
+    const int n = b.n, g = cdiv(std::max(n, 1), 256);
+    b.ext.alloc(c, (size_t)std::max(n, 1));
+    b.perm.alloc(c, (size_t)std::max(n, 1));
+    fill<int>(c, b.perm.get(), -1, (size_t)n);
+    if (n > 0) {
+      DBuf<int> isc(c, (size_t)n), cidx(c, (size_t)n + 1);
+      hipLaunchKernelGGL(k_u_flags, dim3(g), dim3(256), 0, c->stream, n, b.R, dt, isc.get());
       MGD_CHECK_LAUNCH();
-      want_a += m.lev->A.nnz;
-      if (m.kind == 0) want_w += (long long)m.lev->P.nnz - m.nc;
-      cbase += m.nc;
-      fbase += (m.kind == 0) ? m.n - m.nc : m.n;
-      srows.push_back(std::move(srow));
-    }
-    if (nS > 0) {
-      hipLaunchKernelGGL(k_check_hits, dim3(cdiv(nS, 256)), dim3(256), 0, c->stream, nS,
-                         (const int*)hits.get(), bad);
+      exclusive_scan(c, isc.get(), cidx.get(), n);
+      hipLaunchKernelGGL(k_u_map, dim3(g), dim3(256), 0, c->stream, n, b.nC, b.nS, b.R, dt,
+                         (const int*)isc.get(), (const int*)cidx.get(), b.ext.get(), b.perm.get(),
+                         err);
+      hipLaunchKernelGGL(k_u_check, dim3(g), dim3(256), 0, c->stream, n, (const int*)b.ext.get(),
+                         (const int*)b.perm.get(), err);
       MGD_CHECK_LAUNCH();
     }
-    c->check_device_errors("stored-row map of a solve-phase level");
     // Below the finest level, rows of the C-block and of the F-block are ordered
     // by decreasing length (stable) within windows of kSortWindow rows, so that
     // 64-row slices hold rows of similar length while neighbouring rows stay
-    // close; the coarse numbering stays member order and is kept in cnat.
-    // With multicolour Gauss-Seidel the blocks are ordered by colour instead, so
-    // each colour is one range of the C-block and one of the F-block.
-    if (nS > 0 && (smoother == 1 || l > 0)) {
-      for (size_t q = 0; q < ms.size(); ++q) {
-        const auto& m = ms[q];
-        if (m.kind == 2) continue;
-        if (smoother == 1) {
-          MGD_REQUIRE(m.lev->colour.p, "internal: level without colours");
-          hipLaunchKernelGGL(k_scatter_int, dim3(cdiv(m.n, 256)), dim3(256), 0, c->stream, m.n,
-                             (const int*)srows[q].get(), (const int*)m.lev->colour.get(),
-                             alen.get());
-        } else {
-          hipLaunchKernelGGL(k_row_len, dim3(cdiv(m.n, 256)), dim3(256), 0, c->stream, m.n,
-                             m.lev->A.rp.get(), (const int*)srows[q].get(), alen.get());
-        }
-        MGD_CHECK_LAUNCH();
-      }
-      std::vector<int> len(nS), pm(nS), qpos(nS), cn(std::max(nCtot, 1));
-      copy_d2h(c, len.data(), alen.get(), (size_t)nS);
-      copy_d2h(c, pm.data(), lv.perm.get(), (size_t)nS);
-      std::vector<int> order(nS);
-      for (int k = 0; k < nS; ++k) order[k] = k;
-      if (smoother == 1) {  // ascending colour (len holds colours here)
-        auto by_col = [&](int a, int b2) { return len[a] < len[b2]; };
-        std::stable_sort(order.begin(), order.begin() + nCtot, by_col);
-        std::stable_sort(order.begin() + nCtot, order.end(), by_col);
-        int ncol = 0;
-        for (int k = 0; k < nS; ++k) ncol = std::max(ncol, len[k] + 1);
-        lv.cranges.assign(ncol, {0, 0, 0, 0});
-        for (int cc = 0; cc < ncol; ++cc) lv.cranges[cc] = {nCtot, nCtot, nS, nS};
-        for (int k = nS - 1; k >= 0; --k) {  // first and last position of each colour
-          const int cc = len[order[k]], blk = k < nCtot ? 0 : 2;
-          lv.cranges[cc][blk] = k;
-        }
-        for (int k = 0; k < nS; ++k) {
-          const int cc = len[order[k]], blk = k < nCtot ? 1 : 3;
-          lv.cranges[cc][blk] = k + 1;
-        }
-        for (auto& r : lv.cranges) {  // colours absent from a block: empty range
-          if (r[1] <= r[0]) r[0] = r[1] = 0;
-          if (r[3] <= r[2]) r[2] = r[3] = 0;
-        }
-      } else {
-        // windows of kSortWindow rows keep neighbouring rows close together
-        auto by_len = [&](int a, int b2) { return len[a] > len[b2]; };
-        for (int w0 = 0; w0 < nCtot; w0 += kSortWindow)
-          std::stable_sort(order.begin() + w0, order.begin() + std::min(nCtot, w0 + kSortWindow),
-                           by_len);
-        for (int w0 = nCtot; w0 < nS; w0 += kSortWindow)
-          std::stable_sort(order.begin() + w0, order.begin() + std::min(nS, w0 + kSortWindow),
-                           by_len);
-      }
-      std::vector<int> pm2(nS);
-      for (int k = 0; k < nS; ++k) {
-        qpos[order[k]] = k;  // old position -> new position
-        pm2[k] = pm[order[k]];
-      }
-      for (int k = 0; k < nCtot; ++k) cn[k] = order[k];  // coarse index of C position k
-      DBuf<int> qd(c, (size_t)nS);
-      copy_h2d(c, qd.get(), qpos.data(), (size_t)nS);
-      copy_h2d(c, lv.perm.get(), pm2.data(), (size_t)nS);
-      lv.cnat.alloc(c, (size_t)std::max(nCtot, 1));
-      copy_h2d(c, lv.cnat.get(), cn.data(), (size_t)std::max(nCtot, 1));
-      for (size_t q = 0; q < ms.size(); ++q) {
-        if (ms[q].kind == 2) continue;
-        hipLaunchKernelGGL(k_remap, dim3(cdiv(ms[q].n, 256)), dim3(256), 0, c->stream,
-                           (long long)ms[q].n, (const int*)qd.get(), nS, srows[q].get(), bad);
-        MGD_CHECK_LAUNCH();
-      }
-      fill<int>(c, alen.get(), 0, (size_t)nS + 1);
-      c->check_device_errors("length order of a solve-phase level");
+    // close.  With multicolour Gauss-Seidel the blocks are ordered by colour
+    // instead, so each colour is one range of the C-block and one of the F-block.
+    if (b.nS > 0 && smoother == 1) {
+      c->check_device_errors("stored-row map of a solve-phase level");
+      colour_order(c, b, dt, U->L[l].cranges);
+    } else if (b.nS > 0 && l > 0) {
+      const int nwC = cdiv(b.nC, kSortWindow), nwF = cdiv(b.nF, kSortWindow);
+      hipLaunchKernelGGL(k_u_window_sort, dim3(nwC + nwF), dim3(kSortWindow), 0, c->stream, b.nC,
+                         b.nS, nwC, b.R, dt, b.ext.get(), b.perm.get(), (const int*)err);
+      MGD_CHECK_LAUNCH();
     }
-    // the map is a permutation: lengths, diagonals
-    for (size_t q = 0; q < ms.size(); ++q) {
-      auto& m = ms[q];
-      if (m.kind == 2) continue;
-      const int n = m.n, g = cdiv(n, 256);
-      hipLaunchKernelGGL(k_row_len, dim3(g), dim3(256), 0, c->stream, n, m.lev->A.rp.get(),
-                         (const int*)srows[q].get(), alen.get());
+    DBuf<int> alen(c, (size_t)std::max(b.nS, 1)), wlen(c, (size_t)std::max(b.nF, 1));
+    b.arp.alloc(c, (size_t)b.nS + 1);
+    b.wrp.alloc(c, (size_t)b.nF + 1);
+    if (b.nS > 0) {
+      hipLaunchKernelGGL(k_u_len, dim3(cdiv(b.nS, 256)), dim3(256), 0, c->stream, b.nC, b.nS, b.R,
+                         dt, (const int*)b.perm.get(), alen.get(), wlen.get(), (const int*)err);
       MGD_CHECK_LAUNCH();
-      if (m.kind == 0)
-        hipLaunchKernelGGL(k_row_len_f, dim3(g), dim3(256), 0, c->stream, n, m.lev->P.rp.get(),
-                           (const int*)srows[q].get(), nCtot, (const int8_t*)m.lev->cf.get(),
-                           wlen.get());
-      MGD_CHECK_LAUNCH();
-      DBuf<double> d(c, (size_t)n);
-      l1_diagonal(c, m.lev->A, d.get());
-      hipLaunchKernelGGL(k_dinv<T>, dim3(g), dim3(256), 0, c->stream, n, (const double*)d.get(),
-                         (const int*)srows[q].get(), lv.dinv.get());
-      MGD_CHECK_LAUNCH();
-      if (smoother == 1) {
-        plain_diagonal(c, m.lev->A, d.get());
-        hipLaunchKernelGGL(k_dinv<T>, dim3(g), dim3(256), 0, c->stream, n, (const double*)d.get(),
-                           (const int*)srows[q].get(), lv.dgs.get());
-        MGD_CHECK_LAUNCH();
-      }
-      c->sync();
     }
-    if (debug_union()) verify_union_level(c, ms, srows, nS, alen.get(), nullptr);
-    // stored matrix (natural columns)
-    Csr<double> Ad, Wd, Wtd;
-    Ad.n_rows = nS;
-    Ad.n_cols = lv.n;
-    Ad.rp.alloc(c, (size_t)nS + 1);
-    Ad.nnz = exclusive_scan_total(c, alen.get(), Ad.rp.get(), nS);
-    if (Ad.nnz != want_a)
-      fail(MGD_EHIP, "internal check failed: stored level matrix has " + std::to_string(Ad.nnz) +
-                         " entries, its members " + std::to_string(want_a) + step_suffix());
-    Ad.ci.alloc(c, (size_t)std::max(Ad.nnz, 1));
-    Ad.v.alloc(c, (size_t)std::max(Ad.nnz, 1));
-    Wd.n_rows = nF;
-    Wd.n_cols = ncoarse;
-    Wd.rp.alloc(c, (size_t)nF + 1);
-    Wd.nnz = exclusive_scan_total(c, wlen.get(), Wd.rp.get(), nF);
-    if (Wd.nnz != want_w)
-      fail(MGD_EHIP, "internal check failed: W has " + std::to_string(Wd.nnz) + " entries, " +
-                         std::to_string(want_w) + " expected" + step_suffix());
-    Wd.ci.alloc(c, (size_t)std::max(Wd.nnz, 1));
-    Wd.v.alloc(c, (size_t)std::max(Wd.nnz, 1));
-    int coarse_off = 0;
-    for (size_t q = 0; q < ms.size(); ++q) {
-      auto& m = ms[q];
-      if (m.kind == 2) {
-        lv.dense.push_back({m.off, m.n, m.H->coarse_inv.get()});
-        continue;
-      }
-      const int n = m.n, g = cdiv(n, 256);
-      hipLaunchKernelGGL(k_row_copy, dim3(g), dim3(256), 0, c->stream, n, m.lev->A.rp.get(),
-                         m.lev->A.ci.get(), m.lev->A.v.get(), (const int*)srows[q].get(), m.off,
-                         (const int*)Ad.rp.get(), Ad.ci.get(), Ad.v.get(), bad);
-      MGD_CHECK_LAUNCH();
-      if (m.kind == 0) {
-        hipLaunchKernelGGL(k_row_copy_f, dim3(g), dim3(256), 0, c->stream, n, m.lev->P.rp.get(),
-                           m.lev->P.ci.get(), m.lev->P.v.get(), (const int*)srows[q].get(), nCtot,
-                           (const int8_t*)m.lev->cf.get(), coarse_off, (const int*)Wd.rp.get(),
-                           Wd.ci.get(), Wd.v.get(), bad);
-        MGD_CHECK_LAUNCH();
-        coarse_off += m.nc;
-      }
-    }
-    c->check_device_errors("row copy into a solve-phase level");
-    if (debug_union()) verify_union_level(c, ms, srows, nS, alen.get(), &Ad);
-    check_structure(c, Ad, "union level matrix", false);
-    check_structure(c, Wd, "union interpolation", false);
-    if (ncoarse > 0) transpose(c, Wd, Wtd);
-    if (nS > 0) lv.nnz_C = read1(c, Ad.rp.get() + nCtot);
-    lv.A = std::move(Ad);
-    lv.W = std::move(Wd);
-    lv.Wt = std::move(Wtd);
-    built.push_back(std::move(lv));
-    if (ncoarse == 0) break;
+    exclusive_scan(c, alen.get(), b.arp.get(), b.nS);
+    exclusive_scan(c, wlen.get(), b.wrp.get(), b.nF);
+    row_stats(c, b.nS, b.arp.get(), b.aw64, b.asoff, stats.get() + 6 * l);
+    row_stats(c, b.nF, b.wrp.get(), b.ww64, b.wsoff, stats.get() + 6 * l + 2);
+    hipLaunchKernelGGL(k_u_sizes, dim3(1), dim3(1), 0, c->stream, (const int*)b.arp.get(), b.nS,
+                       b.nC, (const int*)b.wrp.get(), b.nF, (const int*)err, sizes.get() + 4 * l);
+    MGD_CHECK_LAUNCH();
   }
-  finalize_levels(c, built, *U, autotune);
-  {
+  const std::vector<int> sz = read_vec(c, sizes.get(), (size_t)nl * 4);
+  c->throw_device_errors(nl ? sz[4 * nl - 1] : 0, "stored order of the solve-phase levels");
+  // matrices in stored order
+  for (int l = 0; l < nl; ++l) {
+    StepScope st("solve-phase build: matrices of level " + std::to_string(l));
+    BuildLevel<T>& b = bl[l];
+    const UMember* dt = dtab.get() + b.tab;
+    ULevel<T>& lv = U->L[l];
+    if (sz[4 * l] != b.want_a || sz[4 * l + 2] != b.want_w)
+      fail(MGD_EHIP, "internal check failed: stored level matrix has " + std::to_string(sz[4 * l]) +
+                         " entries and W " + std::to_string(sz[4 * l + 2]) + ", their members " +
+                         std::to_string(b.want_a) + " and " + std::to_string(b.want_w) +
+                         step_suffix());
+    const bool coarsens = l + 1 < nl && b.n_coarse > 0;
+    lv.n = lv.nX = b.n;
+    lv.nS = b.nS;
+    lv.nC = b.nC;
+    lv.nnz_C = sz[4 * l + 1];
+    lv.nnz_F = b.want_a - lv.nnz_C;
+    lv.dinv.alloc(c, (size_t)std::max(b.nS, 1));
+    if (smoother == 1) lv.dgs.alloc(c, (size_t)std::max(b.nS, 1));
+    b.A.n_rows = b.nS;
+    b.A.n_cols = b.nS;
+    b.A.nnz = (int)b.want_a;
+    b.A.rp = std::move(b.arp);
+    b.A.ci.alloc(c, (size_t)std::max(b.A.nnz, 1));
+    b.A.v.alloc(c, (size_t)std::max(b.A.nnz, 1));
+    // lanes per copied row: about the mean row length
+#define MGD_ROWS(K, N_, AVG, ...)                                                                  \
+  if ((AVG) <= 10.0)                                                                               \
+    hipLaunchKernelGGL(K<8>, dim3(cdiv(N_, 32)), dim3(256), 0, c->stream, __VA_ARGS__);            \
+  else if ((AVG) <= 24.0)                                                                          \
+    hipLaunchKernelGGL(K<16>, dim3(cdiv(N_, 16)), dim3(256), 0, c->stream, __VA_ARGS__);           \
+  else                                                                                             \
+    hipLaunchKernelGGL(K<64>, dim3(cdiv(N_, 4)), dim3(256), 0, c->stream, __VA_ARGS__);            \
+  MGD_CHECK_LAUNCH()
+    if (b.nS > 0) {
+      const double avg = (double)b.A.nnz / b.nS;
+      MGD_ROWS(k_u_rows, b.nS, avg, b.nS, b.n, b.R, dt, (const int*)b.perm.get(),
+               (const int*)b.ext.get(), (const int*)b.A.rp.get(), b.A.ci.get(), b.A.v.get(), err);
+      hipLaunchKernelGGL(k_u_dinv<T>, dim3(cdiv(b.nS, 256)), dim3(256), 0, c->stream, b.nS,
+                         (const int*)b.A.rp.get(), (const int*)b.A.ci.get(),
+                         (const double*)b.A.v.get(), lv.dinv.get(), lv.dgs.get());
+      MGD_CHECK_LAUNCH();
+    }
+    check_structure_async(c, b.nS, b.nS, b.A.nnz, b.A.rp.get(), b.A.ci.get(), false, true);
+    // dense members: offsets in the extended order
+    for (int q = 0; q < b.R.nm; ++q) {
+      const UMember& m = tab[b.tab + q];
+      if (m.n == 0 || m.kind != 2) continue;
+      lv.dense.push_back({b.nS + m.dense_before, m.n, members[q]->inverse()});
+      lv.dense_max_n = std::max(lv.dense_max_n, m.n);
+      lv.dense_entries += (long long)m.n * m.n;
+    }
+    if (!lv.dense.empty()) {
+      lv.dense_dev.alloc(c, lv.dense.size());
+      copy_h2d(c, lv.dense_dev.get(), lv.dense.data(), lv.dense.size());
+    }
+    if (coarsens) {
+      BuildLevel<T>& nb = bl[l + 1];
+      MGD_REQUIRE(nb.n == b.n_coarse && b.nC == b.n_coarse,
+                  "internal: coarse level size differs from the C-block");
+      lv.nX_next = nb.n;
+      lv.nC_next = nb.nC;
+      lv.nS_next = nb.nS;
+      b.W.n_rows = b.nF;
+      b.W.n_cols = nb.n;
+      b.W.nnz = (int)b.want_w;
+      b.W.rp = std::move(b.wrp);
+      b.W.ci.alloc(c, (size_t)std::max(b.W.nnz, 1));
+      b.W.v.alloc(c, (size_t)std::max(b.W.nnz, 1));
+      if (b.nF > 0) {
+        const double avg = (double)b.W.nnz / b.nF;
+        MGD_ROWS(k_u_wrows, b.nF, avg, b.nC, b.nF, b.R, dt, (const int*)b.perm.get(),
+                 (const int*)nb.ext.get(), (const int*)b.W.rp.get(), b.W.ci.get(), b.W.v.get(),
+                 err);
+      }
+#undef MGD_ROWS
+      // C-block position -> level l+1 index; level l+1 index -> C-block position
+      lv.cmap.alloc(c, (size_t)std::max(b.nC, 1));
+      lv.cpos.alloc(c, (size_t)std::max(nb.n, 1));
+      fill<int>(c, lv.cpos.get(), 0, (size_t)nb.n);
+      hipLaunchKernelGGL(k_u_cmap, dim3(cdiv(b.nC, 256)), dim3(256), 0, c->stream, b.nC, nb.n, b.R,
+                         dt, (const int*)b.perm.get(), (const int*)nb.ext.get(), lv.cmap.get(),
+                         lv.cpos.get(), err);
+      hipLaunchKernelGGL(k_u_cmap_check, dim3(cdiv(b.nC, 256)), dim3(256), 0, c->stream, b.nC,
+                         (const int*)lv.cmap.get(), (const int*)lv.cpos.get(), err);
+      MGD_CHECK_LAUNCH();
+      check_structure_async(c, b.nF, nb.n, b.W.nnz, b.W.rp.get(), b.W.ci.get(), false, true);
+      // W^T: rows in level l+1 extended order, columns F indices ascending
+      transpose(c, b.W, b.Wt);
+      row_stats(c, b.Wt.n_rows, b.Wt.rp.get(), b.tw64, b.tsoff, stats.get() + 6 * l + 4);
+    }
+    if (debug_union()) verify_union_level(c, tab, b);
+  }
+  const std::vector<int> hs = read_vec(c, stats.get(), (size_t)nl * 6);
+  c->check_device_errors("stored-order matrices of the solve-phase levels");
+  layout_levels<T>(c, bl, hs.data(), *U, autotune);
+  if (nl > 0) {
     // level 0 seen from the natural side, for entry kernels that read their
     // inputs in natural order: the inverse permutation and d^-1 of C rows
     ULevel<T>& l0 = U->L[0];
     const int nX = l0.nX, g = cdiv(std::max(nX, 1), 256);
-    l0.iperm.alloc(c, (size_t)std::max(nX, 1));
+    l0.iperm = std::move(bl[0].ext);
     l0.dinv_nat.alloc(c, (size_t)std::max(nX, 1));
     if (nX > 0) {
-      hipLaunchKernelGGL(k_invert, dim3(g), dim3(256), 0, c->stream, nX,
-                         (const int*)l0.perm.get(), l0.iperm.get(), c->err_flag());
-      MGD_CHECK_LAUNCH();
       hipLaunchKernelGGL(k_dinv_nat<T>, dim3(g), dim3(256), 0, c->stream, nX, l0.nC,
                          (const int*)l0.iperm.get(), (const T*)l0.dinv.get(), l0.dinv_nat.get());
       MGD_CHECK_LAUNCH();
     }
-    c->check_device_errors("natural-order map of level 0");
   }
   U->build_tail(c);
+  c->check_device_errors("solve-phase build");
   c->sync();
   return U;
 }
@@ -2053,27 +2076,9 @@ void autotune_store(long long rows, long long nnz, int maxrow, bool fp32, int tp
   tune_save_locked();
 }
 
-__global__ void k_max_row(int n, const int* __restrict__ rp, int* __restrict__ out) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  int m = i < n ? rp[i + 1] - rp[i] : 0;
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) m = max(m, __shfl_xor(m, off, 64));
-  if ((threadIdx.x & 63) == 0 && m > 0) atomicMax(out, m);
-}
-
 // ---------------------------------------------------------------------------
-// stored-order finalisation and level layouts
+// level layouts
 // ---------------------------------------------------------------------------
-// SELL slice widths (64 x the longest row of each 64-row slice)
-__global__ void k_slice_width(int rows, const int* __restrict__ rp, int* __restrict__ w64) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  const int ns = (rows + 63) / 64;
-  if (s >= ns) return;
-  int m = 0;
-  const int r1 = min(rows, 64 * s + 64);
-  for (int r = 64 * s; r < r1; ++r) m = max(m, rp[r + 1] - rp[r]);
-  w64[s] = 64 * m;
-}
 template <typename T>
 __global__ void k_sell_fill(int rows, const int* __restrict__ rp, const int* __restrict__ ci,
                             const double* __restrict__ v, const int* __restrict__ off,
@@ -2103,15 +2108,16 @@ static int sell16_span() {
 // one); a side spanning more than `span` (<= 2^15 - 1) columns makes the
 // slice keep 32-bit columns (F base -1).  units[s]: the slice's code size in
 // 16-bit units.
-__global__ void k_sell16_bases(int rows, const int* __restrict__ rp, const int* __restrict__ ci,
-                               int split, int span, const int* __restrict__ off,
-                               int* __restrict__ rp4, int* __restrict__ units) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
+// One wave per slice, one lane per row.
+__global__ void __launch_bounds__(256) k_sell16_bases(int rows, const int* __restrict__ rp,
+                                                      const int* __restrict__ ci, int split,
+                                                      int span, const int* __restrict__ off,
+                                                      int* __restrict__ rp4,
+                                                      int* __restrict__ units) {
+  const int r = blockIdx.x * 256 + threadIdx.x, s = r >> 6;
   const int ns = (rows + 63) / 64;
-  if (s >= ns) return;
   int cmin = INT_MAX, cmax = -1, fmin = INT_MAX, fmax = -1;
-  const int r1 = min(rows, 64 * s + 64);
-  for (int r = 64 * s; r < r1; ++r)
+  if (r < rows)
     for (int e = rp[r]; e < rp[r + 1]; ++e) {
       const int j = ci[e];
       if (j < split) {
@@ -2122,6 +2128,14 @@ __global__ void k_sell16_bases(int rows, const int* __restrict__ rp, const int* 
         fmax = max(fmax, j);
       }
     }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    cmin = min(cmin, __shfl_xor(cmin, o, 64));
+    cmax = max(cmax, __shfl_xor(cmax, o, 64));
+    fmin = min(fmin, __shfl_xor(fmin, o, 64));
+    fmax = max(fmax, __shfl_xor(fmax, o, 64));
+  }
+  if ((threadIdx.x & 63) != 0 || s >= ns) return;
   const bool wide = (cmax >= 0 && cmax - cmin > span) || (fmax >= 0 && fmax - fmin > span);
   rp4[4 * s] = off[s];
   rp4[4 * s + 2] = cmax >= 0 ? cmin : 0;
@@ -2176,12 +2190,28 @@ __global__ void k_sell16_check(int rows, int ncols, const int* __restrict__ rp,
   }
 }
 
+// Longest row (longest[0]) and SELL layout of a CSR structure: slice widths in
+// w64, slice offsets in soff, the stored entries with padding in longest[1].
+static void row_stats(Ctx* c, int rows, const int* rp, DBuf<int>& w64, DBuf<int>& soff,
+                      int* longest) {
+  if (rows <= 0) return;
+  const int ns = cdiv(rows, 64);
+  w64.alloc(c, (size_t)ns);
+  soff.alloc(c, (size_t)ns + 1);
+  hipLaunchKernelGGL(k_row_stats, dim3(std::min(cdiv(rows, 256), kStatBlocks)), dim3(256), 0, c->stream, rows, rp,
+                     w64.get(), longest);
+  MGD_CHECK_LAUNCH();
+  exclusive_scan(c, w64.get(), soff.get(), ns);
+  copy_d2d(c, longest + 1, soff.get() + ns, 1);
+}
+
 // CSR (FP64 values) -> layout `fmt` with values in T; `self_pad` pads SELL rows
 // with their own index as column (square stored-order matrices), else column 0.
-// A SELL result becomes SELL16 when split16 >= 0 and every slice fits.
+// A SELL result (slice offsets soff, `stored` entries) becomes SELL16 when
+// split16 >= 0.
 template <typename T>
 static void to_layout(Ctx* c, const Csr<double>& M, int fmt, int tpr, bool self_pad,
-                      LMat<T>& out, int split16 = -1) {
+                      LMat<T>& out, const DBuf<int>& soff, long long stored, int split16 = -1) {
   out.rows = M.n_rows;
   out.nnz = M.nnz;
   out.fmt = fmt;
@@ -2195,16 +2225,12 @@ static void to_layout(Ctx* c, const Csr<double>& M, int fmt, int tpr, bool self_
     copy_d2d(c, out.ci.get(), M.ci.get(), (size_t)M.nnz);
     out.v.alloc(c, (size_t)std::max(M.nnz, 1));
     cast_copy<T, double>(c, out.v.get(), M.v.get(), (size_t)M.nnz, KC_VEC);
-    c->sync();
     return;
   }
   const int ns = cdiv(M.n_rows, 64);
-  DBuf<int> w64(c, (size_t)ns);
-  hipLaunchKernelGGL(k_slice_width, dim3(cdiv(ns, 256)), dim3(256), 0, c->stream, M.n_rows,
-                     (const int*)M.rp.get(), w64.get());
-  MGD_CHECK_LAUNCH();
   out.rp.alloc(c, (size_t)ns + 1);
-  out.stored = exclusive_scan_total(c, w64.get(), out.rp.get(), ns);
+  copy_d2d(c, out.rp.get(), soff.get(), (size_t)ns + 1);
+  out.stored = stored;
   out.ci.alloc(c, (size_t)std::max(out.stored, 1LL));
   out.v.alloc(c, (size_t)std::max(out.stored, 1LL));
   hipLaunchKernelGGL(k_sell_fill<T>, dim3(cdiv(M.n_rows, 256)), dim3(256), 0, c->stream,
@@ -2212,10 +2238,9 @@ static void to_layout(Ctx* c, const Csr<double>& M, int fmt, int tpr, bool self_
                      (const double*)M.v.get(), (const int*)out.rp.get(), self_pad ? 1 : 0,
                      out.ci.get(), out.v.get());
   MGD_CHECK_LAUNCH();
-  c->sync();
   if (split16 < 0 || M.nnz == 0) return;
   DBuf<int> rp4(c, 4 * (size_t)ns + 2), units(c, (size_t)ns), coff(c, (size_t)ns + 1);
-  hipLaunchKernelGGL(k_sell16_bases, dim3(cdiv(ns, 256)), dim3(256), 0, c->stream, M.n_rows,
+  hipLaunchKernelGGL(k_sell16_bases, dim3(cdiv(M.n_rows, 256)), dim3(256), 0, c->stream, M.n_rows,
                      (const int*)M.rp.get(), (const int*)M.ci.get(), split16, sell16_span(),
                      (const int*)out.rp.get(), rp4.get(), units.get());
   MGD_CHECK_LAUNCH();
@@ -2232,27 +2257,16 @@ static void to_layout(Ctx* c, const Csr<double>& M, int fmt, int tpr, bool self_
                      M.n_rows, M.n_cols, (const int*)M.rp.get(), (const int*)M.ci.get(),
                      (const int*)rp4.get(), (const int*)codes.get(), c->err_flag());
   MGD_CHECK_LAUNCH();
-  c->check_device_errors("16-bit sliced layout");
   out.rp = std::move(rp4);
   out.ci = std::move(codes);
   out.fmt = kFmtSELL16;
 }
-// padded size of the SELL layout of M (host-side estimate through the device widths)
-static long long sell_stored(Ctx* c, const Csr<double>& M) {
-  if (M.n_rows == 0) return 0;
-  const int ns = cdiv(M.n_rows, 64);
-  DBuf<int> w64(c, (size_t)ns), tmp(c, (size_t)ns + 1);
-  hipLaunchKernelGGL(k_slice_width, dim3(cdiv(ns, 256)), dim3(256), 0, c->stream, M.n_rows,
-                     (const int*)M.rp.get(), w64.get());
-  MGD_CHECK_LAUNCH();
-  return exclusive_scan_total(c, w64.get(), tmp.get(), ns);
-}
-
 template <typename T>
-static void tune_layout(Ctx* c, ULevel<T>& lv, const Csr<double>& A, int autotune, bool fp32);
+static void tune_layout(Ctx* c, ULevel<T>& lv, const BuildLevel<T>& b, const int* st, int autotune,
+                        bool fp32);
 template <typename T>
-static void tune_restrict(Ctx* c, const ULevel<T>& lv, int nS, int nC, int nCn,
-                          const Csr<double>& Wt, LMat<T>& out, int autotune, bool fp32);
+static void tune_restrict(Ctx* c, const ULevel<T>& lv, const BuildLevel<T>& b, const int* st,
+                          LMat<T>& out, int autotune, bool fp32);
 
 constexpr long long kFillLanes = 1 << 17;  // lanes that keep all compute units busy
 constexpr int kSellMinRows = 1 << 17;
@@ -2292,147 +2306,33 @@ static int transfer_default(const Csr<double>& M, long long sell_entries) {
   return std::max(small_level_tpr(M.n_rows, avg), default_tpr(avg));
 }
 template <typename T>
-static void layout_transfer(Ctx* c, const Csr<double>& M, LMat<T>& out, int split16) {
-  const int d = transfer_default(M, M.nnz > 0 && M.n_rows >= sell_min_rows() ? sell_stored(c, M) : 0);
+static void layout_transfer(Ctx* c, const Csr<double>& M, LMat<T>& out, const DBuf<int>& soff,
+                            long long stored, int split16) {
+  const int d = transfer_default(M, stored);
   if (d == 1000)
-    to_layout<T>(c, M, kFmtSELL, 1, false, out, sell16_enabled() ? split16 : -1);
+    to_layout<T>(c, M, kFmtSELL, 1, false, out, soff, stored, sell16_enabled() ? split16 : -1);
   else
-    to_layout<T>(c, M, kFmtCSR, d, false, out);
+    to_layout<T>(c, M, kFmtCSR, d, false, out, soff, stored);
 }
 
+// stats: per level the longest row and the SELL entries of A, W and W^T
 template <typename T>
-static void finalize_levels(Ctx* c, std::vector<BuildLevel<T>>& bl, Union<T>& U, int autotune) {
+static void layout_levels(Ctx* c, std::vector<BuildLevel<T>>& bl, const int* stats, Union<T>& U,
+                          int autotune) {
   const int nl = (int)bl.size();
-  int* err = c->err_flag();
-  // extended stored order (stored rows, then dense members' rows) and its inverse
-  std::vector<DBuf<int>> pext(nl), sinv(nl);
   for (int l = 0; l < nl; ++l) {
-    auto& b = bl[l];
-    pext[l].alloc(c, (size_t)std::max(b.n, 1));
-    sinv[l].alloc(c, (size_t)std::max(b.n, 1));
-    copy_d2d(c, pext[l].get(), b.perm.get(), (size_t)b.nS);
-    int pos = b.nS;
-    for (auto& d : b.dense) {
-      hipLaunchKernelGGL(k_iota, dim3(cdiv(d.n, 256)), dim3(256), 0, c->stream, d.n, d.off,
-                         pext[l].get() + pos);
-      MGD_CHECK_LAUNCH();
-      pos += d.n;
-    }
-    MGD_REQUIRE(pos == b.n, "internal: extended order does not cover the level");
-    if (b.n > 0) {
-      hipLaunchKernelGGL(k_invert, dim3(cdiv(b.n, 256)), dim3(256), 0, c->stream, b.n,
-                         (const int*)pext[l].get(), sinv[l].get(), err);
-      MGD_CHECK_LAUNCH();
-    }
-  }
-  c->check_device_errors("extended stored order");
-  U.L.clear();
-  U.L.resize(nl);
-  for (int l = 0; l < nl; ++l) {
-    StepScope st("solve-phase build: stored-order level " + std::to_string(l));
-    auto& b = bl[l];
+    StepScope st("solve-phase build: layouts of level " + std::to_string(l));
+    BuildLevel<T>& b = bl[l];
     ULevel<T>& lv = U.L[l];
-    lv.n = lv.nX = b.n;
-    lv.nS = b.nS;
-    lv.nC = b.nC;
-    lv.nnz_C = b.nnz_C;
-    lv.nnz_F = b.A.nnz - b.nnz_C;
-    lv.perm = std::move(pext[l]);
-    lv.dinv = std::move(b.dinv);
-    lv.dgs = std::move(b.dgs);
-    lv.cranges = std::move(b.cranges);
-    // columns of A in stored order (each member's rows only reference its own rows)
-    if (b.A.nnz > 0) {
-      hipLaunchKernelGGL(k_remap, dim3(cdiv(b.A.nnz, 256)), dim3(256), 0, c->stream,
-                         (long long)b.A.nnz, (const int*)sinv[l].get(), b.n, b.A.ci.get(), err);
-      MGD_CHECK_LAUNCH();
-    }
-    check_index_structure(c, b.A.n_rows, b.nS, b.A.nnz, b.A.rp.get(), b.A.ci.get(),
-                          "stored-order level matrix");
-    // dense members: offsets in the extended order
-    int pos = b.nS;
-    for (auto& d : b.dense) {
-      lv.dense.push_back({pos, d.n, d.inv});
-      lv.dense_max_n = std::max(lv.dense_max_n, d.n);
-      lv.dense_entries += (long long)d.n * d.n;
-      pos += d.n;
-    }
-    if (!lv.dense.empty()) {
-      lv.dense_dev.alloc(c, lv.dense.size());
-      copy_h2d(c, lv.dense_dev.get(), lv.dense.data(), lv.dense.size());
-    }
-    if (l + 1 < nl && b.n_coarse > 0) {
-      auto& nb = bl[l + 1];
-      MGD_REQUIRE(nb.n == b.n_coarse && b.nC == b.n_coarse,
-                  "internal: coarse level size differs from the C-block");
-      lv.nX_next = nb.n;
-      lv.nC_next = nb.nC;
-      lv.nS_next = nb.nS;
-      // W: columns to level l+1 extended order
-      if (b.W.nnz > 0) {
-        hipLaunchKernelGGL(k_remap, dim3(cdiv(b.W.nnz, 256)), dim3(256), 0, c->stream,
-                           (long long)b.W.nnz, (const int*)sinv[l + 1].get(), nb.n, b.W.ci.get(),
-                           err);
-        MGD_CHECK_LAUNCH();
-      }
-      // C-block position -> level l+1 index; level l+1 index -> C-block position
-      lv.cmap.alloc(c, (size_t)std::max(b.nC, 1));
-      lv.cpos.alloc(c, (size_t)std::max(nb.n, 1));
-      DBuf<int> cinv;
-      if (b.cnat.p) {
-        hipLaunchKernelGGL(k_compose, dim3(cdiv(b.nC, 256)), dim3(256), 0, c->stream, b.nC,
-                           (const int*)sinv[l + 1].get(), nb.n, (const int*)b.cnat.get(),
-                           lv.cmap.get(), err);
-        MGD_CHECK_LAUNCH();
-        cinv.alloc(c, (size_t)std::max(b.nC, 1));
-        hipLaunchKernelGGL(k_invert, dim3(cdiv(b.nC, 256)), dim3(256), 0, c->stream, b.nC,
-                           (const int*)b.cnat.get(), cinv.get(), err);
-        MGD_CHECK_LAUNCH();
-      } else {
-        copy_d2d(c, lv.cmap.get(), sinv[l + 1].get(), (size_t)b.nC);
-      }
-      // rows of W^T in level l+1 extended order
-      Csr<double> Wt2;
-      Wt2.n_rows = nb.n;
-      Wt2.n_cols = b.Wt.n_cols;
-      Wt2.nnz = b.Wt.nnz;
-      Wt2.rp.alloc(c, (size_t)nb.n + 1);
-      Wt2.ci.alloc(c, (size_t)std::max(b.Wt.nnz, 1));
-      Wt2.v.alloc(c, (size_t)std::max(b.Wt.nnz, 1));
-      {
-        // level l+1's extended order is pext[l+1] (moved into U.L[l+1] later)
-        const int* src = pext[l + 1].get();
-        if (b.cnat.p) {
-          hipLaunchKernelGGL(k_compose, dim3(cdiv(nb.n, 256)), dim3(256), 0, c->stream, nb.n,
-                             (const int*)cinv.get(), b.nC, src, lv.cpos.get(), err);
-          MGD_CHECK_LAUNCH();
-        } else {
-          copy_d2d(c, lv.cpos.get(), src, (size_t)nb.n);
-        }
-        DBuf<int> len(c, (size_t)nb.n + 1);
-        hipLaunchKernelGGL(k_gather_len, dim3(cdiv(nb.n, 256)), dim3(256), 0, c->stream, nb.n,
-                           (const int*)b.Wt.rp.get(), src, len.get());
-        MGD_CHECK_LAUNCH();
-        const int tot = exclusive_scan_total(c, len.get(), Wt2.rp.get(), nb.n);
-        MGD_REQUIRE(tot == b.Wt.nnz, "internal: permuted W^T lost entries");
-        hipLaunchKernelGGL(k_gather_rows, dim3(cdiv(nb.n, 256)), dim3(256), 0, c->stream, nb.n,
-                           (const int*)b.Wt.rp.get(), (const int*)b.Wt.ci.get(),
-                           (const double*)b.Wt.v.get(), src, (const int*)Wt2.rp.get(),
-                           Wt2.ci.get(), Wt2.v.get(), err);
-        MGD_CHECK_LAUNCH();
-      }
-      c->check_device_errors("transfer operators in stored order");
-      check_index_structure(c, b.W.n_rows, nb.n, b.W.nnz, b.W.rp.get(), b.W.ci.get(),
-                            "stored-order interpolation");
-      check_index_structure(c, Wt2.n_rows, b.nS - b.nC, Wt2.nnz, Wt2.rp.get(), Wt2.ci.get(),
-                            "stored-order restriction");
+    const int* s6 = stats + 6 * l;
+    if (lv.nX_next > 0) {
       // W gathers from three regions of the next level: 32-bit columns;
       // W^T's columns are F indices, one region
-      layout_transfer<T>(c, b.W, lv.W, -1);
-      tune_restrict<T>(c, lv, b.nS, b.nC, nb.nC, Wt2, lv.Wt, autotune, sizeof(T) == 4);
+      layout_transfer<T>(c, b.W, lv.W, b.wsoff, s6[3], -1);
+      tune_restrict<T>(c, lv, b, s6 + 4, lv.Wt, autotune, sizeof(T) == 4);
     }
-    c->check_device_errors("stored-order level");
-    tune_layout<T>(c, lv, b.A, autotune, sizeof(T) == 4);
+    tune_layout<T>(c, lv, b, s6, autotune, sizeof(T) == 4);
+    lv.perm = std::move(b.perm);
   }
   // workspace
   U.B.resize(nl);
@@ -2467,16 +2367,6 @@ constexpr int kTuneSell = 1000;
 constexpr int kTuneBsUnit = 100000;
 constexpr double kTuneMargin = 1.03;
 
-static int max_row_len(Ctx* c, int rows, const int* rp) {
-  DBuf<int> mr(c, 1);
-  fill<int>(c, mr.get(), 0, 1);
-  if (rows > 0) {
-    hipLaunchKernelGGL(k_max_row, dim3(cdiv(rows, 256)), dim3(256), 0, c->stream, rows, rp,
-                       mr.get());
-    MGD_CHECK_LAUNCH();
-  }
-  return read1(c, mr.get());
-}
 // candidate layouts: SELL while its padding stays within 2x, CSR with 1 lane
 // and with up to twice the mean row length in lanes, and the default
 static std::vector<int> tune_layouts(long long sell_entries, long long nnz, double avg, int dflt) {
@@ -2515,6 +2405,7 @@ static int tune_pick(Ctx* c, const std::vector<int>& layouts, int dflt, int reps
         MGD_HIP(hipEventElapsedTime(&t, e0, e1));
         ms = std::min(ms, t);
       }
+      c->sync();  // the candidate's predecessors go back to the allocator
       if (cand == dflt_value) t_dflt = ms;
       if (ms < best) {
         best = ms;
@@ -2533,20 +2424,22 @@ static int tune_reps(double bytes) {
 }
 
 template <typename T>
-static void tune_layout(Ctx* c, ULevel<T>& lv, const Csr<double>& A, int autotune, bool fp32) {
+static void tune_layout(Ctx* c, ULevel<T>& lv, const BuildLevel<T>& b, const int* stat,
+                        int autotune, bool fp32) {
+  const Csr<double>& A = b.A;
   if (lv.nS == 0) {
-    to_layout<T>(c, A, kFmtCSR, 1, true, lv.A);
+    to_layout<T>(c, A, kFmtCSR, 1, true, lv.A, b.asoff, 0);
     return;
   }
-  const int maxrow = max_row_len(c, lv.nS, A.rp.get());
+  const int maxrow = stat[0];
   const double avg = (double)A.nnz / lv.nS;
-  const long long st = sell_stored(c, A);
+  const long long st = stat[1];
   auto apply = [&](int value) {
     const int code = value % kTuneBsUnit, units = value / kTuneBsUnit;
     if (code == kTuneSell)
-      to_layout<T>(c, A, kFmtSELL, 1, true, lv.A, sell16_enabled() ? lv.nC : -1);
+      to_layout<T>(c, A, kFmtSELL, 1, true, lv.A, b.asoff, st, sell16_enabled() ? lv.nC : -1);
     else
-      to_layout<T>(c, A, kFmtCSR, code, true, lv.A);
+      to_layout<T>(c, A, kFmtCSR, code, true, lv.A, b.asoff, st);
     lv.A.bs = units ? 64 * units : 256;
   };
   const int cached = autotune_lookup(lv.nS, A.nnz, maxrow, fp32);
@@ -2582,19 +2475,22 @@ static void tune_layout(Ctx* c, ULevel<T>& lv, const Csr<double>& A, int autotun
 // restriction kernel timed into scratch vectors of the two levels' sizes
 // (cpos, the C-block position of each coarse row, is the level's own).
 template <typename T>
-static void tune_restrict(Ctx* c, const ULevel<T>& lv, int nS, int nC, int nCn,
-                          const Csr<double>& Wt, LMat<T>& out, int autotune, bool fp32) {
+static void tune_restrict(Ctx* c, const ULevel<T>& lv, const BuildLevel<T>& b, const int* stat,
+                          LMat<T>& out, int autotune, bool fp32) {
+  const Csr<double>& Wt = b.Wt;
+  const int nS = b.nS, nC = b.nC, nCn = lv.nC_next;
+  const int maxrow = stat[0];
+  const long long st = stat[1];
   if (Wt.n_rows == 0 || Wt.nnz == 0) {
-    layout_transfer<T>(c, Wt, out, 0);
+    layout_transfer<T>(c, Wt, out, b.tsoff, st, 0);
     return;
   }
-  const int maxrow = max_row_len(c, Wt.n_rows, Wt.rp.get());
   auto apply = [&](int value) {
     const int code = value % kTuneBsUnit, units = value / kTuneBsUnit;
     if (code == kTuneSell)
-      to_layout<T>(c, Wt, kFmtSELL, 1, false, out, sell16_enabled() ? 0 : -1);
+      to_layout<T>(c, Wt, kFmtSELL, 1, false, out, b.tsoff, st, sell16_enabled() ? 0 : -1);
     else
-      to_layout<T>(c, Wt, kFmtCSR, code, false, out);
+      to_layout<T>(c, Wt, kFmtCSR, code, false, out, b.tsoff, st);
     out.bs = units ? 64 * units : 256;
   };
   const int cached = autotune_lookup(Wt.n_rows, Wt.nnz, maxrow, fp32, "wt:");
@@ -2603,11 +2499,10 @@ static void tune_restrict(Ctx* c, const ULevel<T>& lv, int nS, int nC, int nCn,
     return;
   }
   if (!autotune || Wt.n_rows < tune_min_rows()) {
-    layout_transfer<T>(c, Wt, out, 0);
+    layout_transfer<T>(c, Wt, out, b.tsoff, st, 0);
     return;
   }
   const double avg = (double)Wt.nnz / Wt.n_rows;
-  const long long st = sell_stored(c, Wt);
   const int dflt = transfer_default(Wt, st);
   const int nXn = Wt.n_rows;
   DBuf<T> R(c, (size_t)std::max(nS, 1)), dn(c, (size_t)std::max(nCn, 1));

@@ -107,7 +107,7 @@ void exclusive_scan(Ctx* c, const int* in, int* out, int n) {
                      (const int*)sums_scan.get(), out);
   MGD_CHECK_LAUNCH();
   // temporaries are released only after the stream has consumed them
-  c->sync();
+  if (!c->defer) c->sync();
 }
 
 int exclusive_scan_total(Ctx* c, const int* in, int* out, int n) {
