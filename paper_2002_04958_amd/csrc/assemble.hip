@@ -371,6 +371,7 @@ void assemble_impl(Ctx* c, const mgd_coeffs* cf, mgd_block_system* out) {
 
 void system_transpose_impl(Ctx* c, const mgd_block_system* A, mgd_block_system* out) {
   const int G = A->G, N = A->N;
+  DeferFrees frees(c);
   auto os = std::make_unique<OwnedSystem>();
   os->blocks.resize(G + 2);
   for (int a = 0; a < G + 2; ++a) {
@@ -386,7 +387,7 @@ void system_transpose_impl(Ctx* c, const mgd_block_system* A, mgd_block_system* 
   copy_d2d(c, os->d_Eg.get(), A->d_gE, (size_t)G * N);
   copy_d2d(c, os->d_EI.get(), A->d_IE, (size_t)N);
   copy_d2d(c, os->d_IE.get(), A->d_EI, (size_t)N);
-  c->sync();
+  c->check_device_errors("transposed block system");
   // Blocks that share one pattern keep sharing it: the transposes of equal
   // patterns are equal (every transposed row is sorted by column), so block
   // 0's row pointers and column indices serve all blocks.

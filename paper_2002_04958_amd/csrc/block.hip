@@ -8,6 +8,7 @@
 
 #include <chrono>
 #include <cstdlib>
+#include <climits>
 #include <functional>
 
 #include "handles.hpp"
@@ -188,7 +189,7 @@ __global__ void k_jacobi(int N, const JacMember* __restrict__ tab, const T* __re
     return;
   }
   const T* __restrict__ x = xin + off;
-  for (int e = J.rp[i]; e < J.rp[i + 1]; ++e) r = r - J.v[e] * (double)x[J.ci[e]];
+  for (int e = J.rp[i]; e < J.rp[i + 1]; ++e) r = r - J.v[e] * (double)x[J.ci[e] - J.base];
   xout[off + i] = (T)((double)x[i] + r / J.d[i]);
 }
 // Definition 1 count: rows with -d_k <= theta a_k
@@ -202,14 +203,15 @@ __global__ void k_weak_count(int n, const double* __restrict__ d, const double* 
 // Definition 2 count: rows with sum_j a_kj < theta a_kk, the sum taken left
 // to right in stored (ascending column) order
 __global__ void k_wd_count(int n, const int* __restrict__ rp, const int* __restrict__ ci,
-                           const double* __restrict__ v, double theta, int* __restrict__ cnt) {
+                           const double* __restrict__ v, int base, double theta,
+                           int* __restrict__ cnt) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   bool hit = false;
   if (i < n) {
     double s = 0.0, dg = 0.0;
     for (int e = rp[i]; e < rp[i + 1]; ++e) {
       s = s + v[e];
-      if (ci[e] == i) dg = v[e];
+      if (ci[e] - base == i) dg = v[e];
     }
     hit = s < theta * dg;
   }
@@ -275,7 +277,7 @@ __global__ void __launch_bounds__(256) k_member_resid(int N, const JacMember* __
   double s = 0.0;
   for (int i = blockIdx.x * 256 + threadIdx.x; i < N; i += nb * 256) {
     double v = (double)b[off + i];
-    for (int e = A.rp[i]; e < A.rp[i + 1]; ++e) v = v - A.v[e] * (double)z[off + A.ci[e]];
+    for (int e = A.rp[i]; e < A.rp[i + 1]; ++e) v = v - A.v[e] * (double)z[off + (A.ci[e] - A.base)];
     r[off + i] = (T)v;
     s = s + v * v;
   }
@@ -326,26 +328,56 @@ __global__ void k_pctl_correct(int G, int N, const double* __restrict__ p, const
 // ---------------------------------------------------------------------------
 // setup kernels
 // ---------------------------------------------------------------------------
-// a_ii <- a_ii - (d1_i d2_i) / dd_i on the stored diagonal
-__global__ void k_hat_update(int n, const int* __restrict__ rp, const int* __restrict__ ci,
-                             double* __restrict__ v, const double* __restrict__ d1,
-                             const double* __restrict__ d2, const double* __restrict__ dd) {
+// One member of a batch's finest level: a block of the system, with its diagonal
+// lowered by (d1_i d2_i) / dd_i where d1 is given (the hat of Section 3.4)
+struct StackMember {
+  const int* rp;
+  const int* ci;
+  const double* v;
+  const double *d1, *d2, *dd;
+  int nnz, off, eoff;
+};
+// entries of member blockIdx.y, four per thread and turn, columns numbered through
+__global__ void k_stack_entries(const StackMember* __restrict__ tab, int* __restrict__ ci,
+                                double* __restrict__ v) {
+  const StackMember m = tab[blockIdx.y];
+  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < m.nnz; e += gridDim.x * blockDim.x) {
+    ci[(size_t)m.eoff + e] = m.ci[e] + m.off;
+    v[(size_t)m.eoff + e] = m.v[e];
+  }
+}
+// row pointers, and the hats' diagonals
+__global__ void k_stack_rows(int N, int last, const StackMember* __restrict__ tab,
+                             int* __restrict__ rp, double* __restrict__ v) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= N) return;
+  const StackMember m = tab[blockIdx.y];
+  rp[m.off + i] = m.eoff + m.rp[i];
+  if ((int)blockIdx.y == last && i == N - 1) rp[m.off + N] = m.eoff + m.rp[N];
+  if (!m.d1) return;
+  for (int e = m.rp[i]; e < m.rp[i + 1]; ++e)
+    if (m.ci[e] == i) {
+      const double t = (m.d1[i] * m.d2[i]) / m.dd[i];
+      v[(size_t)m.eoff + e] = m.v[e] - t;
+    }
+}
+// the diagonal of a hat from the diagonal it lowers
+__global__ void k_hat_diag(int n, const double* __restrict__ a, const double* __restrict__ d1,
+                           const double* __restrict__ d2, const double* __restrict__ dd,
+                           double* __restrict__ out) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  for (int e = rp[i]; e < rp[i + 1]; ++e)
-    if (ci[e] == i) {
-      const double t = (d1[i] * d2[i]) / dd[i];
-      v[e] = v[e] - t;
-    }
+  const double t = (d1[i] * d2[i]) / dd[i];
+  out[i] = a[i] - t;
 }
 
 __global__ void k_get_diag(int n, const int* __restrict__ rp, const int* __restrict__ ci,
-                           const double* __restrict__ v, double* __restrict__ d) {
+                           const double* __restrict__ v, int base, double* __restrict__ d) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   double x = 0.0;
   for (int e = rp[i]; e < rp[i + 1]; ++e)
-    if (ci[e] == i) x = v[e];
+    if (ci[e] - base == i) x = v[e];
   d[i] = x;
 }
 
@@ -453,32 +485,86 @@ block_precond::~block_precond() {
   if (fs_join) hipEventDestroy(fs_join);
 }
 
-static void make_hierarchy(block_precond* bp, int role, Csr<double>&& M) {
+static void add_hierarchy(block_precond* bp, int role, const std::shared_ptr<SetupBatch>& b, int m) {
   auto h = std::make_unique<amg_hierarchy>();
   h->ctx = bp->ctx;
   h->prm = bp->prm.amg;
-  h->n = M.n_rows;
-  auto t0 = std::chrono::steady_clock::now();
-  amg_build(bp->ctx, std::move(M), h->prm, h->H);
-  h->setup_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
+  h->H.b = b;
+  h->H.m = m;
+  h->n = h->H.n(0);
   if ((int)bp->hier.size() <= role) bp->hier.resize(role + 1);
   bp->hier[role] = std::move(h);
 }
 
-static void diag_of(Ctx* c, const Csr<double>& A, double* d) {
-  hipLaunchKernelGGL(k_get_diag, dim3(cdiv(A.n_rows, 256)), dim3(256), 0, c->stream, A.n_rows,
-                     A.rp.get(), A.ci.get(), A.v.get(), d);
-  MGD_CHECK_LAUNCH();
+static void make_hierarchy(block_precond* bp, int role, Csr<double>&& M) {
+  auto b = std::make_shared<SetupBatch>();
+  const int n = M.n_rows, nnz = M.nnz;
+  amg_build(bp->ctx, std::move(M), {0, n}, {0, nnz}, bp->prm.amg, *b);
+  add_hierarchy(bp, role, b, 0);
 }
 
-static Csr<double> hat(Ctx* c, const Csr<double>& A, const double* d1, const double* d2,
-                       const double* dd) {
-  Csr<double> B;
-  csr_copy(c, A, B);
-  hipLaunchKernelGGL(k_hat_update, dim3(cdiv(B.n_rows, 256)), dim3(256), 0, c->stream, B.n_rows,
-                     B.rp.get(), B.ci.get(), B.v.get(), d1, d2, dd);
+// a scalar matrix to set up: block `block` of the system, or its hat
+struct RoleMatrix {
+  int role, block;
+  const double *d1, *d2, *dd;
+};
+
+// Entries of a batch's finest level: far enough below 2^31 for the products of
+// its setup, whose rows are a few times as long.
+constexpr long long kBatchEntries = 1LL << 27;
+
+// Hierarchies of all the roles, as many in one batch as the parameters and the
+// entries allow.
+static void make_hierarchies(block_precond* bp, const std::vector<RoleMatrix>& roles) {
+  Ctx* c = bp->ctx;
+  const int N = bp->N;
+  const bool together = setup_batches(bp->prm.amg);
+  for (size_t q0 = 0; q0 < roles.size();) {
+    std::vector<StackMember> tab;
+    std::vector<int> off{0}, eoff{0};
+    size_t q1 = q0;
+    int most = 0;
+    while (q1 < roles.size() && (int)tab.size() < kMaxMembers) {
+      const RoleMatrix& r = roles[q1];
+      const BlockCsr& B = bp->sys.blk[r.block];
+      const int nnz = (int)bp->sys.nnz[r.block];
+      const long long entries = (long long)eoff.back() + nnz;
+      if (!tab.empty() && (!together || entries > kBatchEntries ||
+                           (long long)off.back() + N >= INT32_MAX))
+        break;
+      tab.push_back({B.rp, B.ci, B.v, r.d1, r.d2, r.dd, nnz, off.back(), eoff.back()});
+      off.push_back(off.back() + N);
+      eoff.push_back((int)entries);
+      most = std::max(most, nnz);
+      ++q1;
+    }
+    const int nm = (int)tab.size();
+    DBuf<StackMember> dt(c, (size_t)nm);
+    copy_h2d(c, dt.get(), tab.data(), (size_t)nm);
+    Csr<double> A0;
+    A0.alloc(c, off.back(), off.back(), eoff.back());
+    if (most > 0)
+      hipLaunchKernelGGL(k_stack_entries, dim3(std::min(cdiv(most, 256), 4096), nm), dim3(256), 0,
+                         c->stream, (const StackMember*)dt.get(), A0.ci.get(), A0.v.get());
+    hipLaunchKernelGGL(k_stack_rows, dim3(cdiv(N, 256), nm), dim3(256), 0, c->stream, N, nm - 1,
+                       (const StackMember*)dt.get(), A0.rp.get(), A0.v.get());
+    MGD_CHECK_LAUNCH();
+    auto b = std::make_shared<SetupBatch>();
+    amg_build(c, std::move(A0), off, eoff, bp->prm.amg, *b);
+    for (int m = 0; m < nm; ++m) add_hierarchy(bp, roles[q0 + m].role, b, m);
+    q0 = q1;
+  }
+}
+
+static void diag_of(Ctx* c, const MemberCsr& A, double* d) {
+  hipLaunchKernelGGL(k_get_diag, dim3(cdiv(A.n, 256)), dim3(256), 0, c->stream, A.n, A.rp, A.ci,
+                     A.v, A.base, d);
   MGD_CHECK_LAUNCH();
-  return B;
+}
+// block a of the preconditioner's own system
+static MemberCsr block_csr(const block_precond* bp, int a) {
+  const BlockCsr& B = bp->sys.blk[a];
+  return {bp->N, (int)bp->sys.nnz[a], 0, B.rp, B.ci, B.v};
 }
 
 // Option #3: V-cycles on the hierarchy until ||rhs - A z|| < tol ||rhs||.
@@ -494,14 +580,15 @@ static int solve_to_tol(block_precond* bp, amg_hierarchy* h, const double* rhs, 
   dot_dev(c, rw, rhs, rhs, n, nrm.get());
   const double nb = std::sqrt(read1(c, nrm.get()));
   if (nb == 0.0) return 0;
-  const CsrView<double> A0 = view(h->H.levels[0].A);
+  const MemberCsr M0 = h->H.level0();
+  const CsrView<double> A0{M0.n, M0.n, M0.nnz, M0.rp, M0.ci, M0.v};
   const int tpr = default_tpr((double)A0.nnz / std::max(1, A0.n_rows));
   int k = 0;
   while (k < maxc) {
     U->apply(c, r.get(), t.get(), 1);
     axpy(c, z, t.get(), 1.0, n);
     ++k;
-    spmv(c, A0, z, r.get(), tpr, KC_SPMV);
+    spmv(c, A0, z - M0.base, r.get(), tpr, KC_SPMV);  // columns are numbered from the base
     rsub(c, rhs, r.get(), n);
     dot_dev(c, rw, r.get(), r.get(), n, nrm.get() + 1);
     if (std::sqrt(read1(c, nrm.get() + 1)) < tol * nb) break;
@@ -530,8 +617,8 @@ static std::unique_ptr<TolSolve<T>> make_tol(block_precond* bp, const std::vecto
   S->roles = roles;
   std::vector<JacMember> tab;
   for (int r : roles) {
-    const Csr<double>& A = bp->hier[r]->H.levels[0].A;
-    tab.push_back({A.rp.get(), A.ci.get(), A.v.get(), nullptr});
+    const MemberCsr A = bp->hier[r]->H.level0();
+    tab.push_back({A.rp, A.ci, A.v, nullptr, A.base});
     S->nnz += (double)A.nnz;
   }
   S->mats.alloc(c, (size_t)nm);
@@ -622,8 +709,8 @@ static void build_exec(block_precond* bp, std::unique_ptr<PcExec<T>>& X) {
   for (int r : singles) {
     if (inner && bp->tol_role[r] && !bp->jacobi[r]) X->tol_one[r] = make_tol<T>(bp, {r});
     if (bp->jacobi[r]) {
-      const Csr<double>& A = bp->hier[r]->H.levels[0].A;
-      JacMember jm{A.rp.get(), A.ci.get(), A.v.get(), bp->jac_diag[r].get()};
+      const MemberCsr A = bp->hier[r]->H.level0();
+      JacMember jm{A.rp, A.ci, A.v, bp->jac_diag[r].get(), A.base};
       X->jac_one[r].alloc(c, 1);
       copy_h2d(c, X->jac_one[r].get(), &jm, 1);
       if (X->jac_tmp1.n < (size_t)N) X->jac_tmp1.alloc(c, (size_t)std::max(N, 1));
@@ -742,8 +829,8 @@ static void build_exec(block_precond* bp, std::unique_ptr<PcExec<T>>& X) {
   if (nj > 0) {
     std::vector<JacMember> jt;
     for (size_t m = n_amg; m < nm; ++m) {
-      const Csr<double>& A = bp->hier[roles[m]]->H.levels[0].A;
-      jt.push_back({A.rp.get(), A.ci.get(), A.v.get(), bp->jac_diag[roles[m]].get()});
+      const MemberCsr A = bp->hier[roles[m]]->H.level0();
+      jt.push_back({A.rp, A.ci, A.v, bp->jac_diag[roles[m]].get(), A.base});
       grp.jac_nnz += (double)A.nnz;
     }
     grp.jac_tab.alloc(c, (size_t)nj);
@@ -818,7 +905,7 @@ static void apply_impl(block_precond* bp, PcExec<T>& X, const double* r, double*
                  [&](const T* rin, T* tout) { U(role)->apply(c, rin, tout, 1); });
     else if (bp->jacobi[role])
       jacobi_run<T>(c, N, X.jac_one[role].get(), 1, bp->prm.jacobi_sweeps,
-                    (double)bp->hier[role]->H.levels[0].A.nnz, in, out, X.jac_tmp1.get());
+                    (double)bp->hier[role]->H.nnz(0), in, out, X.jac_tmp1.get());
     else
       U(role)->apply(c, in, out, bp->cycles[role]);
   };
@@ -1300,16 +1387,31 @@ static void copy_system(block_precond* bp, const mgd_block_system* A) {
   Ctx* c = bp->ctx;
   const int G = A->G, N = A->N;
   const bool tr = bp->prm.transpose != 0;
+  DeferFrees frees(c);
+  // Blocks given with one shared pattern keep one (copies and sorted transposes
+  // of equal patterns are equal).
+  bool shared = true;
+  for (int a = 1; a < G + 2; ++a)
+    shared = shared && A->blocks[a].row_ptr == A->blocks[0].row_ptr &&
+             A->blocks[a].col_idx == A->blocks[0].col_idx && A->blocks[a].nnz == A->blocks[0].nnz;
   bp->blocks.resize(G + 2);
   for (int a = 0; a < G + 2; ++a) {
     if (tr) {
       Csr<double> tmp;
       csr_copy_from(c, &A->blocks[a], tmp);
       transpose(c, tmp, bp->blocks[a]);
+    } else if (a > 0 && shared) {
+      Csr<double>& B = bp->blocks[a];
+      B.n_rows = B.n_cols = N;
+      B.nnz = (int)A->blocks[a].nnz;
+      B.v.alloc(c, (size_t)B.nnz);
+      copy_d2d(c, B.v.get(), A->blocks[a].val, (size_t)B.nnz);
     } else {
       csr_copy_from(c, &A->blocks[a], bp->blocks[a]);
     }
-    check_structure(c, bp->blocks[a], "copied diagonal block", true);
+    if (bp->blocks[a].rp.p)
+      check_structure_async(c, N, N, bp->blocks[a].nnz, bp->blocks[a].rp.get(),
+                            bp->blocks[a].ci.get(), true, false);
   }
   bp->d_gE.alloc(c, (size_t)G * N);
   bp->d_Eg.alloc(c, (size_t)G * N);
@@ -1320,13 +1422,7 @@ static void copy_system(block_precond* bp, const mgd_block_system* A) {
   copy_d2d(c, bp->d_Eg.get(), tr ? A->d_gE : A->d_Eg, (size_t)G * N);
   copy_d2d(c, bp->d_EI.get(), tr ? A->d_IE : A->d_EI, (size_t)N);
   copy_d2d(c, bp->d_IE.get(), tr ? A->d_EI : A->d_IE, (size_t)N);
-  c->sync();
-  // Blocks given with one shared pattern keep one in the preconditioner's
-  // matvec (copies and sorted transposes of equal patterns are equal).
-  bool shared = true;
-  for (int a = 1; a < G + 2; ++a)
-    shared = shared && A->blocks[a].row_ptr == A->blocks[0].row_ptr &&
-             A->blocks[a].col_idx == A->blocks[0].col_idx && A->blocks[a].nnz == A->blocks[0].nnz;
+  c->check_device_errors("copied block system");
   mgd_block_system view{};
   std::vector<mgd_csr> bl(G + 2);
   for (int a = 0; a < G + 2; ++a) {
@@ -1422,7 +1518,7 @@ static void adaptive_couplings(block_precond* bp) {
   const int G = bp->G, N = bp->N;
   const double th = bp->prm.theta_wc, sig = bp->prm.sigma_wc;
   DBuf<double> dg(c, (size_t)(G + 2) * N);
-  for (int a = 0; a < G + 2; ++a) diag_of(c, bp->blocks[a], dg.get() + (size_t)a * N);
+  for (int a = 0; a < G + 2; ++a) diag_of(c, block_csr(bp, a), dg.get() + (size_t)a * N);
   const int nc = 2 * G + 2;
   DBuf<int> cnt(c, (size_t)nc);
   fill<int>(c, cnt.get(), 0, (size_t)nc);
@@ -1476,9 +1572,9 @@ static void adaptive_inverses(block_precond* bp) {
   DBuf<int> cnt(c, (size_t)G + 2);
   fill<int>(c, cnt.get(), 0, (size_t)G + 2);
   for (int r = 0; r < G + 2; ++r) {
-    const Csr<double>& A = bp->hier[r]->H.levels[0].A;
-    hipLaunchKernelGGL(k_wd_count, dim3(cdiv(A.n_rows, 256)), dim3(256), 0, c->stream, A.n_rows,
-                       A.rp.get(), A.ci.get(), A.v.get(), bp->prm.theta_wd, cnt.get() + r);
+    const MemberCsr A = bp->hier[r]->H.level0();
+    hipLaunchKernelGGL(k_wd_count, dim3(cdiv(A.n, 256)), dim3(256), 0, c->stream, A.n, A.rp, A.ci,
+                       A.v, A.base, bp->prm.theta_wd, cnt.get() + r);
     MGD_CHECK_LAUNCH();
   }
   std::vector<int> h((size_t)G + 2);
@@ -1486,9 +1582,9 @@ static void adaptive_inverses(block_precond* bp) {
   for (int r = 0; r < G + 2; ++r) {
     bp->wd_count[r] = h[r];
     if (h[r] == 0) {
-      const Csr<double>& A = bp->hier[r]->H.levels[0].A;
+      const MemberCsr A = bp->hier[r]->H.level0();
       bp->jacobi[r] = 1;
-      bp->jac_diag[r].alloc(c, (size_t)std::max(A.n_rows, 1));
+      bp->jac_diag[r].alloc(c, (size_t)std::max(A.n, 1));
       diag_of(c, A, bp->jac_diag[r].get());
     }
   }
@@ -1525,62 +1621,50 @@ block_precond* block_precond_create_impl(Ctx* c, const mgd_block_system* A, cons
   bp->cycles[G] = p->cycles_E;
   bp->cycles[G + 1] = p->cycles_I;
   bp->cycles[G + 2] = p->cycles_E;
-  const Csr<double>* B = bp->blocks.data();
   if (kind == MGD_PC_AMG_MONO) {
     bp->cycles[0] = 1;
     make_hierarchy(bp.get(), 0, monolithic(c, bp->sys));
   } else if (kind != MGD_PC_IDENTITY) {
     DBuf<double> dE(c, N), dI(c, N), dCE(c, N);
-    diag_of(c, B[G], dE.get());
-    diag_of(c, B[G + 1], dI.get());
+    diag_of(c, block_csr(bp.get(), G), dE.get());
+    diag_of(c, block_csr(bp.get(), G + 1), dI.get());
+    const double *gE = bp->d_gE.get(), *Eg = bp->d_Eg.get(), *EI = bp->d_EI.get(),
+                 *IE = bp->d_IE.get();
+    std::vector<RoleMatrix> roles;
     if (kind == MGD_PC_BLOCK_DIAG || kind == MGD_PC_PCTL) {
-      for (int a = 0; a < G + 2; ++a) {
-        Csr<double> M;
-        csr_copy(c, B[a], M);
-        make_hierarchy(bp.get(), a, std::move(M));
-      }
+      for (int a = 0; a < G + 2; ++a) roles.push_back({a, a, nullptr, nullptr, nullptr});
     } else if (kind == MGD_PC_SCHUR1) {
-      Csr<double> CE = hat(c, B[G], bp->d_EI.get(), bp->d_IE.get(), dI.get());
-      diag_of(c, CE, dCE.get());
+      hipLaunchKernelGGL(k_hat_diag, dim3(cdiv(N, 256)), dim3(256), 0, c->stream, N,
+                         (const double*)dE.get(), EI, IE, (const double*)dI.get(), dCE.get());
+      MGD_CHECK_LAUNCH();
       for (int g = 0; g < G; ++g)
-        make_hierarchy(bp.get(), g,
-                       hat(c, B[g], bp->d_gE.get() + (size_t)g * N, bp->d_Eg.get() + (size_t)g * N,
-                           dCE.get()));
-      if (p->option4_steps > 0) {
-        Csr<double> AE;  // option #4 iterates with A_E itself (the hat only fixed C^_g)
-        csr_copy(c, B[G], AE);
-        make_hierarchy(bp.get(), G, std::move(AE));
-      } else {
-        make_hierarchy(bp.get(), G, std::move(CE));
-      }
-      Csr<double> AI;
-      csr_copy(c, B[G + 1], AI);
-      make_hierarchy(bp.get(), G + 1, std::move(AI));
+        roles.push_back({g, g, gE + (size_t)g * N, Eg + (size_t)g * N, dCE.get()});
+      if (p->option4_steps > 0)  // option #4 iterates with A_E itself (the hat only fixed C^_g)
+        roles.push_back({G, G, nullptr, nullptr, nullptr});
+      else
+        roles.push_back({G, G, EI, IE, dI.get()});
+      roles.push_back({G + 1, G + 1, nullptr, nullptr, nullptr});
     } else {  // SCHUR2, SCHUR2_LOWER
       for (int g = 0; g < G; ++g)
-        make_hierarchy(bp.get(), g,
-                       hat(c, B[g], bp->d_gE.get() + (size_t)g * N, bp->d_Eg.get() + (size_t)g * N,
-                           dE.get()));
-      Csr<double> AE;
-      csr_copy(c, B[G], AE);
-      make_hierarchy(bp.get(), G, std::move(AE));
-      if (p->option4_steps > 0) {
-        Csr<double> AI;  // option #4 iterates with A_I itself
-        csr_copy(c, B[G + 1], AI);
-        make_hierarchy(bp.get(), G + 1, std::move(AI));
-      } else {
-        make_hierarchy(bp.get(), G + 1, hat(c, B[G + 1], bp->d_IE.get(), bp->d_EI.get(), dE.get()));
-      }
+        roles.push_back({g, g, gE + (size_t)g * N, Eg + (size_t)g * N, dE.get()});
+      roles.push_back({G, G, nullptr, nullptr, nullptr});
+      if (p->option4_steps > 0)  // option #4 iterates with A_I itself
+        roles.push_back({G + 1, G + 1, nullptr, nullptr, nullptr});
+      else
+        roles.push_back({G + 1, G + 1, IE, EI, dE.get()});
     }
+    make_hierarchies(bp.get(), roles);
     if (kind == MGD_PC_PCTL) {
       // all blocks must share A_E's pattern for eq. 3.1
       DBuf<int> diff(c, 1);
       fill<int>(c, diff.get(), 0, 1);
+      const MemberCsr BE = block_csr(bp.get(), G);
       for (int a = 0; a < G + 2; ++a) {
-        MGD_REQUIRE(B[a].nnz == B[G].nnz, "PCTL needs all diagonal blocks on one pattern");
-        hipLaunchKernelGGL(k_pattern_diff, dim3(cdiv(std::max(N + 1, B[G].nnz), 256)), dim3(256), 0,
-                           c->stream, N, B[G].nnz, B[G].rp.get(), B[G].ci.get(), B[a].rp.get(),
-                           B[a].ci.get(), diff.get());
+        const MemberCsr Ba = block_csr(bp.get(), a);
+        MGD_REQUIRE(Ba.nnz == BE.nnz, "PCTL needs all diagonal blocks on one pattern");
+        if (Ba.rp == BE.rp && Ba.ci == BE.ci) continue;
+        hipLaunchKernelGGL(k_pattern_diff, dim3(cdiv(std::max(N + 1, BE.nnz), 256)), dim3(256), 0,
+                           c->stream, N, BE.nnz, BE.rp, BE.ci, Ba.rp, Ba.ci, diff.get());
         MGD_CHECK_LAUNCH();
       }
       MGD_REQUIRE(read1(c, diff.get()) == 0, "PCTL needs all diagonal blocks on one pattern");
@@ -1597,7 +1681,9 @@ block_precond* block_precond_create_impl(Ctx* c, const mgd_block_system* A, cons
                                             p->pctl_p_maxcycles));
       }
       Csr<double> Ac;
-      csr_copy(c, B[G], Ac);
+      Ac.alloc(c, N, N, BE.nnz);
+      copy_d2d(c, Ac.rp.get(), BE.rp, (size_t)N + 1);
+      copy_d2d(c, Ac.ci.get(), BE.ci, (size_t)BE.nnz);
       hipLaunchKernelGGL(k_pctl_coarse, dim3(cdiv(N, 256)), dim3(256), 0, c->stream, G, N, bp->sys,
                          (const double*)bp->p.get(), Ac.v.get());
       MGD_CHECK_LAUNCH();

@@ -236,6 +236,25 @@ void validate_csr_device(Ctx* c, const mgd_csr* A, bool require_diag) {
   if (b) fail(MGD_EINVAL, "invalid CSR:" + check_message(b));
 }
 
+void validate_csrs_device(Ctx* c, const mgd_csr* A, int count) {
+  DBuf<int> bad(c, (size_t)std::max(count, 1));
+  fill<int>(c, bad.get(), 0, (size_t)count);
+  for (int a = 0; a < count; ++a) {
+    // an earlier block with the same arrays has the same findings
+    bool same = false;
+    for (int b = 0; b < a && !same; ++b)
+      same = A[b].row_ptr == A[a].row_ptr && A[b].col_idx == A[a].col_idx &&
+             A[b].nnz == A[a].nnz && A[b].n_rows == A[a].n_rows && A[b].n_cols == A[a].n_cols;
+    if (same || A[a].n_rows == 0) continue;
+    hipLaunchKernelGGL(k_validate, dim3(cdiv(A[a].n_rows, 256)), dim3(256), 0, c->stream,
+                       A[a].n_rows, A[a].n_cols, (long long)A[a].nnz, A[a].row_ptr, A[a].col_idx, 1,
+                       bad.get() + a);
+    MGD_CHECK_LAUNCH();
+  }
+  for (int b : read_vec(c, bad.get(), (size_t)count))
+    if (b) fail(MGD_EINVAL, "invalid CSR:" + check_message(b));
+}
+
 template <typename V>
 void check_structure(Ctx* c, const Csr<V>& A, const char* what, bool require_diag) {
   const int b = csr_check_bits(c, A.n_rows, A.n_cols, A.nnz, A.rp.get(), A.ci.get(), require_diag);
@@ -517,7 +536,9 @@ mgd_status amg_setup(mgd_ctx* ctx, const mgd_csr* A, const amg_params* p, amg_hi
     Csr<double> M;
     csr_copy_from(ctx, A, M);
     check_structure(ctx, M, "copied input matrix", true);
-    amg_build(ctx, std::move(M), h->prm, h->H);
+    h->H.b = std::make_shared<SetupBatch>();
+    const int n = M.n_rows, nnz = M.nnz;
+    amg_build(ctx, std::move(M), {0, n}, {0, nnz}, h->prm, *h->H.b);
     if (p->precision == 0)
       h->union64();
     else
@@ -547,20 +568,20 @@ mgd_status amg_get_info(const amg_hierarchy* h, amg_info* out) {
     StepScope step_("amg_get_info");
     MGD_REQUIRE(h && out, "hierarchy or out is NULL");
     *out = amg_info{};
-    out->levels = (int)h->H.levels.size();
-    out->coarse_kind = h->H.coarse_kind;
+    const SetupHierarchy& H = h->H;
+    out->levels = (int)H.n_levels();
+    out->coarse_kind = H.coarse_kind();
     double gs = 0, os_ = 0;
-    for (size_t l = 0; l < h->H.levels.size(); ++l) {
-      const auto& L = h->H.levels[l];
-      out->n[l] = L.A.n_rows;
-      out->nnz[l] = L.A.nnz;
-      out->nnz_P[l] = L.P.nnz;
-      out->pmis_rounds[l] = L.pmis_rounds;
-      gs += L.A.n_rows;
-      os_ += L.A.nnz;
+    for (size_t l = 0; l < H.n_levels(); ++l) {
+      out->n[l] = H.n(l);
+      out->nnz[l] = H.nnz(l);
+      out->nnz_P[l] = H.nnz_P(l);
+      out->pmis_rounds[l] = H.rounds(l);
+      gs += H.n(l);
+      os_ += H.nnz(l);
     }
-    out->grid_complexity = gs / std::max(1, h->H.levels[0].A.n_rows);
-    out->operator_complexity = os_ / std::max(1, h->H.levels[0].A.nnz);
+    out->grid_complexity = gs / std::max(1, H.n(0));
+    out->operator_complexity = os_ / std::max(1, H.nnz(0));
     return MGD_OK;
   });
 }
@@ -571,24 +592,33 @@ mgd_status amg_export_level(mgd_ctx* ctx, const amg_hierarchy* h, int level, int
   return guard([&] {
     StepScope step_("amg_export_level");
     MGD_REQUIRE(ctx && h, "ctx or hierarchy is NULL");
-    MGD_REQUIRE(level >= 0 && level < (int)h->H.levels.size(), "level out of range");
+    const SetupHierarchy& H = h->H;
+    MGD_REQUIRE(level >= 0 && level < (int)H.n_levels(), "level out of range");
     ctx->make_current();
-    const auto& L = h->H.levels[level];
-    const int n = L.A.n_rows;
+    const SetupLevel& L = H.b->levels[level];
+    const int n = H.n(level), r0 = L.off[H.m];
+    const bool has_p = !H.last(level);
     if (cf) {
-      if (L.cf.p)
-        copy_d2h(ctx, cf, L.cf.get(), (size_t)n);
+      if (has_p)
+        copy_d2h(ctx, cf, L.cf.get() + r0, (size_t)n);
       else
         std::fill(cf, cf + n, (int8_t)0);
     }
-    if (a_row_ptr) copy_d2h(ctx, a_row_ptr, L.A.rp.get(), (size_t)n + 1);
-    if (a_col) copy_d2h(ctx, a_col, L.A.ci.get(), (size_t)L.A.nnz);
-    if (a_val) copy_d2h(ctx, a_val, L.A.v.get(), (size_t)L.A.nnz);
-    if (L.P.rp.p) {
-      if (p_row_ptr) copy_d2h(ctx, p_row_ptr, L.P.rp.get(), (size_t)n + 1);
-      if (p_col) copy_d2h(ctx, p_col, L.P.ci.get(), (size_t)L.P.nnz);
-      if (p_val) copy_d2h(ctx, p_val, L.P.v.get(), (size_t)L.P.nnz);
-    }
+    // the member's rows of the batch's matrix, numbered from zero
+    auto part = [&](const Csr<double>& A, int e0, int ne, int base, int32_t* rp, int32_t* ci,
+                    double* v) {
+      if (rp) {
+        copy_d2h(ctx, rp, A.rp.get() + r0, (size_t)n + 1);
+        for (int i = 0; i <= n; ++i) rp[i] -= e0;
+      }
+      if (ci) {
+        copy_d2h(ctx, ci, A.ci.get() + e0, (size_t)ne);
+        for (int e = 0; e < ne; ++e) ci[e] -= base;
+      }
+      if (v) copy_d2h(ctx, v, A.v.get() + e0, (size_t)ne);
+    };
+    part(L.A, L.eoff[H.m], H.nnz(level), r0, a_row_ptr, a_col, a_val);
+    if (has_p) part(L.P, L.poff[H.m], H.nnz_P(level), L.coff[H.m], p_row_ptr, p_col, p_val);
     return MGD_OK;
   });
 }
@@ -695,7 +725,7 @@ mgd_status block_precond_create(mgd_ctx* ctx, const mgd_block_system* A, const b
       MGD_REQUIRE(p->jacobi_sweeps >= 1 && p->jacobi_sweeps <= 64, "jacobi_sweeps must be in [1, 64]");
     }
     ctx->make_current();
-    for (int a = 0; a < A->G + 2; ++a) validate_csr_device(ctx, &A->blocks[a], true);
+    validate_csrs_device(ctx, A->blocks, A->G + 2);
     *out = block_precond_create_impl(ctx, A, p);
     return MGD_OK;
   });

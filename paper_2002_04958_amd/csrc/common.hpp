@@ -333,6 +333,8 @@ void check_csr_meta(const mgd_csr* A, bool square);
 // Device-side structural validation (sorted columns in range, row_ptr monotone,
 // diagonal present when require_diag).  Synchronises.
 void validate_csr_device(Ctx* c, const mgd_csr* A, bool require_diag);
+// The same for `count` matrices that must store their diagonals, with one wait.
+void validate_csrs_device(Ctx* c, const mgd_csr* A, int count);
 
 }  // namespace mgd
 

@@ -35,12 +35,13 @@ struct SegOut {
 };
 
 // A scalar matrix inverted by Jacobi iterations (option #1 of Section 3.4):
-// its CSR arrays and its diagonal, FP64.
+// its CSR arrays (columns ci - base) and its diagonal, FP64.
 struct JacMember {
   const int* rp;
   const int* ci;
   const double* v;
   const double* d;
+  int base;
 };
 
 // `sweeps` Jacobi iterations from zero for `nm` members at once (member-major
@@ -101,7 +102,8 @@ struct block_precond {
   mgd::Ctx* ctx = nullptr;
   block_params prm{};
   int G = 0, N = 0;
-  // owned copy of the (possibly transposed) system
+  // owned copy of the (possibly transposed) system; blocks given with one shared
+  // pattern keep it in blocks[0] only (sys.blk has every block's arrays)
   std::vector<mgd::Csr<double>> blocks;
   mgd::DBuf<double> d_gE, d_Eg, d_EI, d_IE;
   mgd::BlockSysDev sys{};

@@ -37,9 +37,10 @@ void csr_copy(Ctx* c, const Csr<double>& A, Csr<double>& out) {
 // ---------------------------------------------------------------------------
 __global__ void k_strength(int n, const int* __restrict__ rp, const int* __restrict__ ci,
                            const double* __restrict__ v, double theta, double dom,
-                           uint8_t* __restrict__ S, int* __restrict__ stc) {
+                           uint8_t* __restrict__ S, int* __restrict__ stc,
+                           double* __restrict__ diag, const int* __restrict__ err) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
+  if (i >= n || *err) return;
   const int e0 = rp[i], e1 = rp[i + 1];
   double m = -INFINITY, rs = 0.0, dg = 0.0;
   for (int e = e0; e < e1; ++e) {
@@ -50,6 +51,7 @@ __global__ void k_strength(int n, const int* __restrict__ rp, const int* __restr
     else if (-a > m)
       m = -a;
   }
+  diag[i] = dg;
   bool empty = !(m > 0.0);
   if (dom > 0.0 && rs >= dom * dg) empty = true;
   const double thr = theta * m;
@@ -61,14 +63,17 @@ __global__ void k_strength(int n, const int* __restrict__ rp, const int* __restr
   }
 }
 
-void strength(Ctx* c, const Csr<double>& A, double theta, double dom, DBuf<uint8_t>& S,
-              DBuf<int>& stc) {
+// S: one flag per entry; stc: how many rows depend on each; diag: a_ii
+static void strength(Ctx* c, const Csr<double>& A, double theta, double dom, DBuf<uint8_t>& S,
+                     DBuf<int>& stc, DBuf<double>& diag) {
   S.alloc(c, (size_t)A.nnz);
   stc.alloc(c, (size_t)A.n_rows);
+  diag.alloc(c, (size_t)A.n_rows);
   fill<int>(c, stc.get(), 0, (size_t)A.n_rows);
   if (A.n_rows == 0) return;
   hipLaunchKernelGGL(k_strength, dim3(cdiv(A.n_rows, 256)), dim3(256), 0, c->stream, A.n_rows,
-                     A.rp.get(), A.ci.get(), A.v.get(), theta, dom, S.get(), stc.get());
+                     A.rp.get(), A.ci.get(), A.v.get(), theta, dom, S.get(), stc.get(), diag.get(),
+                     (const int*)c->err_flag());
   MGD_CHECK_LAUNCH();
 }
 
@@ -83,13 +88,23 @@ __device__ __forceinline__ uint64_t splitmix64_first(uint64_t z) {
   return z ^ (z >> 31);
 }
 
-__global__ void k_pmis_init(int n, const int* __restrict__ stc, uint64_t seed, int level,
-                            uint64_t* __restrict__ key, int8_t* __restrict__ state) {
+// members that coarsen at this level
+struct MemberFlags {
+  uint8_t on[kMaxMembers] = {};
+};
+
+// keys and first states; rows of members that do not coarsen are F
+__global__ void k_pmis_init(int n, RowRanges R, MemberFlags M, const int* __restrict__ stc,
+                            uint64_t seed, int level, uint64_t* __restrict__ key,
+                            int* __restrict__ loser, int8_t* __restrict__ state) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  const uint64_t h = splitmix64_first(seed ^ ((uint64_t)level << 56) ^ (uint64_t)i) >> 32;
+  const int m = member_of(R, i);
+  const uint64_t own = (uint64_t)(i - R.off[m]);
+  const uint64_t h = splitmix64_first(seed ^ ((uint64_t)level << 56) ^ own) >> 32;
   key[i] = ((uint64_t)stc[i] << 32) | h;
-  state[i] = stc[i] == 0 ? kF : kU;
+  loser[i] = 0;
+  state[i] = (!M.on[m] || stc[i] == 0) ? kF : kU;
 }
 
 __global__ void k_st_fill(int n, const int* __restrict__ rp, const int* __restrict__ ci,
@@ -111,60 +126,118 @@ __device__ __forceinline__ bool beats(uint64_t kj, int j, uint64_t ki, int i) {
   return kj > ki || (kj == ki && j > i);
 }
 
-__global__ void k_pmis_select(int n, const int* __restrict__ rp, const int* __restrict__ ci,
-                              const uint8_t* __restrict__ S, const int* __restrict__ st_rp,
-                              const int* __restrict__ st_ci, const uint64_t* __restrict__ key,
-                              const int8_t* __restrict__ state, uint8_t* __restrict__ newc) {
+// A round: an undecided row none of whose undecided neighbours, in either
+// direction of the strength graph, beats it becomes C, and rows that depend
+// strongly on a new C point become F.  The first kernel walks each edge from the
+// row that stores it and marks the loser with the round's number, so no
+// transposed graph is formed; the second settles the rows.  Its reads of
+// neighbours' states may see them settled or not: a new C point is a row not
+// marked this round and not F either way (an undecided row has no older C point
+// among its dependencies).
+__global__ void k_pmis_lose(int n, const int* __restrict__ rp, const int* __restrict__ ci,
+                            const uint8_t* __restrict__ S, const uint64_t* __restrict__ key,
+                            const int8_t* __restrict__ state, int round,
+                            const int* __restrict__ left, int* __restrict__ loser,
+                            const int* __restrict__ err) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  if (state[i] != kU) {
-    newc[i] = 0;
-    return;
-  }
+  if (*left == 0 || *err) return;  // nothing undecided after the round before
+  if (i >= n || state[i] != kU) return;
   const uint64_t ki = key[i];
-  bool best = true;
-  for (int e = rp[i]; e < rp[i + 1] && best; ++e) {
+  bool lose = false;
+  for (int e = rp[i]; e < rp[i + 1]; ++e) {
     if (!S[e]) continue;
     const int j = ci[e];
-    if (state[j] == kU && beats(key[j], j, ki, i)) best = false;
+    if (state[j] != kU) continue;
+    if (beats(key[j], j, ki, i))
+      lose = true;
+    else
+      loser[j] = round;
   }
-  for (int p = st_rp[i]; p < st_rp[i + 1] && best; ++p) {
-    const int j = st_ci[p];
-    if (state[j] == kU && beats(key[j], j, ki, i)) best = false;
-  }
-  newc[i] = best ? 1 : 0;
+  if (lose) loser[i] = round;
 }
 
-__global__ void k_pmis_update(int n, const int* __restrict__ rp, const int* __restrict__ ci,
-                              const uint8_t* __restrict__ S, const uint8_t* __restrict__ newc,
-                              int8_t* __restrict__ state, int* __restrict__ remaining) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  bool und = false;
-  if (i < n && state[i] == kU) {
-    if (newc[i]) {
-      state[i] = kC;
-    } else {
-      bool dep = false;
-      for (int e = rp[i]; e < rp[i + 1]; ++e)
-        if (S[e] && newc[ci[e]]) {
-          dep = true;
-          break;
+// Undecided rows per member (cnt[m]) and altogether (cnt[nm]), kPmisRows rows
+// per thread so that few workgroups meet in the counters.  SETTLE: the second
+// half of a round first.
+constexpr int kPmisRows = 8;
+template <bool SETTLE>
+__global__ void __launch_bounds__(256) k_pmis_settle(int n, RowRanges R,
+                                                     const int* __restrict__ rp,
+                                                     const int* __restrict__ ci,
+                                                     const uint8_t* __restrict__ S, int round,
+                                                     const int* __restrict__ left,
+                                                     const int* __restrict__ loser,
+                                                     int8_t* state, int* __restrict__ cnt,
+                                                     const int* __restrict__ err) {
+  __shared__ int s_cnt[kMaxMembers + 1];
+  if (SETTLE && (*left == 0 || *err)) return;
+  if (threadIdx.x <= R.nm) s_cnt[threadIdx.x] = 0;
+  __syncthreads();
+  for (int t = 0; t < kPmisRows; ++t) {
+    const int i = blockIdx.x * 256 * kPmisRows + t * 256 + threadIdx.x;
+    bool und = i < n && state[i] == kU;
+    if (SETTLE && und) {
+      if (loser[i] != round) {
+        state[i] = kC;
+        und = false;
+      } else {
+        for (int e = rp[i]; e < rp[i + 1]; ++e) {
+          const int j = ci[e];
+          if (S[e] && loser[j] != round && state[j] != kF) {
+            state[i] = kF;
+            und = false;
+            break;
+          }
         }
-      if (dep)
-        state[i] = kF;
-      else
-        und = true;
+      }
+    }
+    if (und) {
+      const int m = member_of(R, i);
+      atomicAdd(&s_cnt[m], 1);
+      atomicAdd(&s_cnt[R.nm], 1);
     }
   }
-  const uint64_t m = __ballot(und);
-  if ((threadIdx.x & 63) == 0 && m) atomicAdd(remaining, (int)__popcll(m));
+  __syncthreads();
+  if (threadIdx.x <= R.nm && s_cnt[threadIdx.x])
+    atomicAdd(&cnt[threadIdx.x], s_cnt[threadIdx.x]);
 }
 
-__global__ void k_count_undecided(int n, const int8_t* __restrict__ state,
-                                  int* __restrict__ remaining) {
+// rows of members that turn out not to coarsen become F
+__global__ void k_mask_f(int n, RowRanges R, MemberFlags M, int8_t* __restrict__ state) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const uint64_t m = __ballot(i < n && state[i] == kU);
-  if ((threadIdx.x & 63) == 0 && m) atomicAdd(remaining, (int)__popcll(m));
+  if (i < n && !M.on[member_of(R, i)]) state[i] = kF;
+}
+
+// out[m] = scan[off[m]] for every member and one past the last, then the error flag
+__global__ void k_bounds(RowRanges R, const int* __restrict__ scan, const int* __restrict__ err,
+                         int* __restrict__ out) {
+  for (int m = threadIdx.x; m <= R.nm; m += blockDim.x) out[m] = scan[R.off[m]];
+  if (threadIdx.x == 0) out[R.nm + 1] = *err;
+}
+
+__global__ void k_is_c(int n, const int8_t* __restrict__ st, int* __restrict__ out) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) out[i] = st[i] == kC ? 1 : 0;
+}
+
+static RowRanges row_ranges(const std::vector<int>& off) {
+  RowRanges R;
+  R.nm = (int)off.size() - 1;
+  MGD_REQUIRE(R.nm >= 1 && R.nm <= kMaxMembers, "internal: too many hierarchies in a batch");
+  std::copy(off.begin(), off.end(), R.off);
+  return R;
+}
+
+// scan values at the members' bounds; throws if a device check has failed
+static std::vector<int> read_bounds(Ctx* c, const RowRanges& R, const int* scan, const char* where) {
+  DBuf<int> d(c, (size_t)R.nm + 2);
+  hipLaunchKernelGGL(k_bounds, dim3(1), dim3(64), 0, c->stream, R, scan, (const int*)c->err_flag(),
+                     d.get());
+  MGD_CHECK_LAUNCH();
+  std::vector<int> h = read_vec(c, d.get(), (size_t)R.nm + 2);
+  c->throw_device_errors(h[R.nm + 1], where);
+  h.pop_back();
+  return h;
 }
 
 // ---------------------------------------------------------------------------
@@ -278,27 +351,42 @@ __global__ void k_hmis_init(int n, const int* __restrict__ rp, const int* __rest
   state[i] = dep ? kF : kU;
 }
 
-int pmis(Ctx* c, const Csr<double>& A, const DBuf<uint8_t>& S, const DBuf<int>& stc,
-         uint64_t seed, int level, DBuf<int8_t>& state, int hmis_tile) {
-  const int n = A.n_rows;
-  state.alloc(c, (size_t)n);
-  if (n == 0) return 0;
-  DBuf<uint64_t> key(c, (size_t)n);
-  DBuf<uint8_t> newc(c, (size_t)n);
-  DBuf<int> st_rp(c, (size_t)n + 1), fillpos(c, (size_t)n), remaining(c, 1);
-  const int g = cdiv(n, 256);
-  hipLaunchKernelGGL(k_pmis_init, dim3(g), dim3(256), 0, c->stream, n, stc.get(), seed, level,
-                     key.get(), state.get());
-  MGD_CHECK_LAUNCH();
-  const int nst = exclusive_scan_total(c, stc.get(), st_rp.get(), n);
-  DBuf<int> st_ci(c, (size_t)std::max(nst, 1));
-  copy_d2d(c, fillpos.get(), st_rp.get(), (size_t)n);
-  hipLaunchKernelGGL(k_st_fill, dim3(g), dim3(256), 0, c->stream, n, A.rp.get(), A.ci.get(),
-                     S.get(), fillpos.get(), st_ci.get(), nst, c->err_flag());
-  MGD_CHECK_LAUNCH();
-  c->check_device_errors("transposed strength graph");
-  check_index_structure(c, n, n, nst, st_rp.get(), st_ci.get(), "transposed strength graph");
-  if (hmis_tile > 0) {
+// C/F splitting of the members flagged in M (PMIS, or HMIS with tiles of
+// hmis_tile rows), the coarse numbers cidx (n + 1) of its C points, each member's
+// first coarse number (returned) and its rounds.  Rounds are enqueued several at
+// a time, with the numbering behind them; a round with nothing left to decide
+// does nothing, and the counters read back say which rounds a member took.
+constexpr int kPmisAhead = 6;
+static std::vector<int> pmis(Ctx* c, const Csr<double>& A, const DBuf<uint8_t>& S,
+                             const DBuf<int>& stc, const RowRanges& R, const MemberFlags& M,
+                             uint64_t seed, int level, int hmis_tile, DBuf<int8_t>& state,
+                             DBuf<int>& cidx, std::vector<int>& rounds) {
+  const int n = A.n_rows, nm = R.nm, stride = nm + 1;
+  rounds.assign(nm, 0);
+  state.alloc(c, (size_t)std::max(n, 1));
+  cidx.alloc(c, (size_t)n + 1);
+  const int g = cdiv(std::max(n, 1), 256), gs = cdiv(std::max(n, 1), 256 * kPmisRows);
+  const int* err = c->err_flag();
+  DBuf<uint64_t> key(c, (size_t)std::max(n, 1));
+  DBuf<int> loser(c, (size_t)std::max(n, 1)), isc(c, (size_t)std::max(n, 1));
+  // counters per round (row 0: before the first), then the members' bounds and the flag
+  const size_t at = (size_t)(kPmisAhead + 1) * stride;
+  DBuf<int> cnt(c, at + nm + 2);
+  if (n > 0) {
+    hipLaunchKernelGGL(k_pmis_init, dim3(g), dim3(256), 0, c->stream, n, R, M, stc.get(), seed,
+                       level, key.get(), loser.get(), state.get());
+    MGD_CHECK_LAUNCH();
+  }
+  if (hmis_tile > 0 && n > 0) {
+    DBuf<int> st_rp(c, (size_t)n + 1), fillpos(c, (size_t)n);
+    const int nst = exclusive_scan_total(c, stc.get(), st_rp.get(), n);
+    DBuf<int> st_ci(c, (size_t)std::max(nst, 1));
+    copy_d2d(c, fillpos.get(), st_rp.get(), (size_t)n);
+    hipLaunchKernelGGL(k_st_fill, dim3(g), dim3(256), 0, c->stream, n, A.rp.get(), A.ci.get(),
+                       S.get(), fillpos.get(), st_ci.get(), nst, c->err_flag());
+    MGD_CHECK_LAUNCH();
+    c->check_device_errors("transposed strength graph");
+    check_index_structure(c, n, n, nst, st_rp.get(), st_ci.get(), "transposed strength graph");
     DBuf<int8_t> c0(c, (size_t)n);
     hipLaunchKernelGGL(k_rs_tiles, dim3(cdiv(n, hmis_tile)), dim3(256), 0, c->stream, n, hmis_tile,
                        seed, level, A.rp.get(), A.ci.get(), S.get(), (const int*)st_rp.get(),
@@ -309,23 +397,53 @@ int pmis(Ctx* c, const Csr<double>& A, const DBuf<uint8_t>& S, const DBuf<int>& 
     MGD_CHECK_LAUNCH();
     c->sync();
   }
-  fill<int>(c, remaining.get(), 0, 1);
-  hipLaunchKernelGGL(k_count_undecided, dim3(g), dim3(256), 0, c->stream, n, state.get(),
-                     remaining.get());
-  MGD_CHECK_LAUNCH();
-  int rounds = 0;
-  while (read1(c, remaining.get()) > 0) {
-    fill<int>(c, remaining.get(), 0, 1);
-    hipLaunchKernelGGL(k_pmis_select, dim3(g), dim3(256), 0, c->stream, n, A.rp.get(), A.ci.get(),
-                       S.get(), st_rp.get(), st_ci.get(), key.get(), state.get(), newc.get());
+  for (int base = 0;; base += kPmisAhead) {
+    fill<int>(c, cnt.get(), 0, at);
+    // row 0 is counted again rather than carried over
+    hipLaunchKernelGGL(k_pmis_settle<false>, dim3(gs), dim3(256), 0, c->stream, n, R, A.rp.get(),
+                       A.ci.get(), S.get(), 0, (const int*)nullptr, (const int*)loser.get(),
+                       state.get(), cnt.get(), err);
     MGD_CHECK_LAUNCH();
-    hipLaunchKernelGGL(k_pmis_update, dim3(g), dim3(256), 0, c->stream, n, A.rp.get(), A.ci.get(),
-                       S.get(), newc.get(), state.get(), remaining.get());
+    for (int r = 1; r <= kPmisAhead; ++r) {
+      const int* left = cnt.get() + (size_t)(r - 1) * stride + nm;
+      hipLaunchKernelGGL(k_pmis_lose, dim3(g), dim3(256), 0, c->stream, n, A.rp.get(), A.ci.get(),
+                         S.get(), (const uint64_t*)key.get(), (const int8_t*)state.get(), base + r,
+                         left, loser.get(), err);
+      hipLaunchKernelGGL(k_pmis_settle<true>, dim3(gs), dim3(256), 0, c->stream, n, R, A.rp.get(),
+                         A.ci.get(), S.get(), base + r, left, (const int*)loser.get(), state.get(),
+                         cnt.get() + (size_t)r * stride, err);
+      MGD_CHECK_LAUNCH();
+    }
+    if (n > 0) {
+      hipLaunchKernelGGL(k_is_c, dim3(g), dim3(256), 0, c->stream, n, (const int8_t*)state.get(),
+                         isc.get());
+      MGD_CHECK_LAUNCH();
+    }
+    exclusive_scan(c, isc.get(), cidx.get(), n);
+    hipLaunchKernelGGL(k_bounds, dim3(1), dim3(64), 0, c->stream, R, (const int*)cidx.get(), err,
+                       cnt.get() + at);
     MGD_CHECK_LAUNCH();
+    const std::vector<int> h = read_vec(c, cnt.get(), at + nm + 2);
+    c->throw_device_errors(h[at + nm + 1], "PMIS");
+    for (int m = 0; m < nm; ++m)
+      for (int r = 1; r <= kPmisAhead; ++r)
+        if (h[(size_t)(r - 1) * stride + m] > 0) rounds[m] = base + r;
+    if (h[(size_t)kPmisAhead * stride + nm] == 0)
+      return std::vector<int>(h.begin() + at, h.begin() + at + nm + 1);
     // each round decides at least the undecided row of largest (key, index)
-    if (++rounds > n) fail(MGD_EHIP, "PMIS did not terminate");
+    if (base > n) fail(MGD_EHIP, "PMIS did not terminate");
   }
-  return rounds;
+}
+
+// one matrix, every row
+static int pmis_one(Ctx* c, const Csr<double>& A, const DBuf<uint8_t>& S, const DBuf<int>& stc,
+                    uint64_t seed, int level, DBuf<int8_t>& state, int hmis_tile) {
+  MemberFlags M;
+  M.on[0] = 1;
+  DBuf<int> cidx;
+  std::vector<int> rounds;
+  pmis(c, A, S, stc, row_ranges({0, A.n_rows}), M, seed, level, hmis_tile, state, cidx, rounds);
+  return rounds[0];
 }
 
 // ---------------------------------------------------------------------------
@@ -344,14 +462,6 @@ __device__ __forceinline__ int find_col(const int* __restrict__ ci, int e0, int 
       hi = mid;
   }
   return (lo < e1 && ci[lo] == j) ? lo : -1;
-}
-
-__global__ void k_diag(int n, const int* __restrict__ rp, const int* __restrict__ ci,
-                       const double* __restrict__ v, double* __restrict__ d) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int p = find_col(ci, rp[i], rp[i + 1], i);
-  d[i] = p >= 0 ? v[p] : 0.0;
 }
 
 __global__ void k_interp_count(int n, const int* __restrict__ rp, const int* __restrict__ ci,
@@ -573,29 +683,25 @@ __global__ void __launch_bounds__(256) k_interp_fill(
   }
 }
 
-__global__ void k_is_c(int n, const int8_t* __restrict__ st, int* __restrict__ out) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] = st[i] == kC ? 1 : 0;
-}
-
-void interpolation(Ctx* c, const Csr<double>& A, const DBuf<uint8_t>& S,
-                   const DBuf<int8_t>& state, const DBuf<int>& cidx, int nc, Csr<double>& P) {
+// nc coarse points in all; poff: every member's first entry of P
+static void interpolation(Ctx* c, const Csr<double>& A, const DBuf<double>& diag,
+                          const DBuf<uint8_t>& S, const DBuf<int8_t>& state, const DBuf<int>& cidx,
+                          const RowRanges& R, int nc, Csr<double>& P, std::vector<int>& poff) {
   const int n = A.n_rows;
   DBuf<int> cnt(c, (size_t)n);
-  DBuf<double> diag(c, (size_t)n), sigma(c, (size_t)std::max(A.nnz, 1));
+  DBuf<double> sigma(c, (size_t)std::max(A.nnz, 1));
   const int g = cdiv(n, 256);
-  hipLaunchKernelGGL(k_diag, dim3(g), dim3(256), 0, c->stream, n, A.rp.get(), A.ci.get(), A.v.get(),
-                     diag.get());
-  MGD_CHECK_LAUNCH();
   hipLaunchKernelGGL(k_interp_count, dim3(g), dim3(256), 0, c->stream, n, A.rp.get(), A.ci.get(),
                      S.get(), state.get(), cnt.get());
   MGD_CHECK_LAUNCH();
   P.n_rows = n;
   P.n_cols = nc;
   P.rp.alloc(c, (size_t)n + 1);
-  P.nnz = exclusive_scan_total(c, cnt.get(), P.rp.get(), n);
-  P.ci.alloc(c, (size_t)P.nnz);
-  P.v.alloc(c, (size_t)P.nnz);
+  exclusive_scan(c, cnt.get(), P.rp.get(), n);
+  poff = read_bounds(c, R, P.rp.get(), "interpolation");
+  P.nnz = poff.back();
+  P.ci.alloc(c, (size_t)std::max(P.nnz, 1));
+  P.v.alloc(c, (size_t)std::max(P.nnz, 1));
   // as many lanes as a row has entries on average, up to half a wave: the
   // lanes read one neighbour's row side by side
 #define MGD_INTERP(GL)                                                                           \
@@ -611,7 +717,6 @@ void interpolation(Ctx* c, const Csr<double>& A, const DBuf<uint8_t>& S,
     MGD_INTERP(32);
 #undef MGD_INTERP
   MGD_CHECK_LAUNCH();
-  c->check_device_errors("interpolation fill");
 }
 
 // ---------------------------------------------------------------------------
@@ -740,8 +845,10 @@ __global__ void __launch_bounds__(256) k_spgemm_bin(int n, int max_cols,
                                                     const int* __restrict__ crp,
                                                     int* __restrict__ cnt,
                                                     int* __restrict__ lists,
-                                                    int* __restrict__ count) {
+                                                    int* __restrict__ count,
+                                                    const int* __restrict__ err) {
   __shared__ int s_n[kSpClasses], s_base[kSpClasses];
+  if (*err) return;  // an operand is malformed: empty lists, reported with the sizes
   if (threadIdx.x < kSpClasses) s_n[threadIdx.x] = 0;
   __syncthreads();
   const int r0 = blockIdx.x * 256 * kSpBinRows;
@@ -959,7 +1066,8 @@ static void spgemm_pass(Ctx* c, const Csr<double>& A, const Csr<double>& B, int 
   fill<int>(c, count.get(), 0, kSpClasses);
   hipLaunchKernelGGL(k_spgemm_bin<FILL>, dim3(cdiv(n, 256 * kSpBinRows)), dim3(256), 0, c->stream,
                      n, max_cols, A.rp.get(), A.ci.get(), B.rp.get(), crp,
-                     FILL ? (int*)nullptr : cnt_or_cci, lists.get(), count.get());
+                     FILL ? (int*)nullptr : cnt_or_cci, lists.get(), count.get(),
+                     (const int*)c->err_flag());
   MGD_CHECK_LAUNCH();
   const int top = sp_class(max_cols);  // no row needs more than all columns
 #define MGD_SPGEMM(CLS, H, GL, WG)                                                                \
@@ -984,7 +1092,7 @@ static void spgemm_pass(Ctx* c, const Csr<double>& A, const Csr<double>& B, int 
   }
 }
 
-void spgemm(Ctx* c, const Csr<double>& A, const Csr<double>& B, Csr<double>& C) {
+void spgemm(Ctx* c, const Csr<double>& A, const Csr<double>& B, int max_cols, Csr<double>& C) {
   MGD_REQUIRE(A.n_cols == B.n_rows, "spgemm: inner dimensions differ");
   const int n = A.n_rows;
   DBuf<int> cnt(c, (size_t)std::max(n, 1)), lists(c, (size_t)kSpClasses * std::max(n, 1));
@@ -992,15 +1100,13 @@ void spgemm(Ctx* c, const Csr<double>& A, const Csr<double>& B, Csr<double>& C) 
   C.n_rows = n;
   C.n_cols = B.n_cols;
   C.rp.alloc(c, (size_t)n + 1);
-  if (n)
-    spgemm_pass<false>(c, A, B, B.n_cols, lists, count, nullptr, cnt.get(), nullptr);
-  C.nnz = exclusive_scan_total(c, cnt.get(), C.rp.get(), n);
-  C.ci.alloc(c, (size_t)C.nnz);
-  C.v.alloc(c, (size_t)C.nnz);
-  if (n)
-    spgemm_pass<true>(c, A, B, B.n_cols, lists, count, C.rp.get(), C.ci.get(),
-                      C.v.get());
-  c->check_device_errors("SpGEMM fill");
+  if (n) spgemm_pass<false>(c, A, B, max_cols, lists, count, nullptr, cnt.get(), nullptr);
+  exclusive_scan(c, cnt.get(), C.rp.get(), n);
+  C.nnz = read_bounds(c, row_ranges({0, n}), C.rp.get(), "SpGEMM count").back();
+  MGD_REQUIRE(C.nnz >= 0, "sparse product too large for int32 indices");
+  C.ci.alloc(c, (size_t)std::max(C.nnz, 1));
+  C.v.alloc(c, (size_t)std::max(C.nnz, 1));
+  if (n) spgemm_pass<true>(c, A, B, max_cols, lists, count, C.rp.get(), C.ci.get(), C.v.get());
 }
 
 // ---------------------------------------------------------------------------
@@ -1104,9 +1210,9 @@ __global__ void k_d2_combine(int n, const int8_t* __restrict__ st1, const int* _
 
 // state: first-pass C/F splitting in, final splitting out; returns the rounds
 // of the second pass
-int aggressive_split(Ctx* c, const Csr<double>& A, const DBuf<uint8_t>& S,
-                     const DBuf<int>& cidx1, int n1, uint64_t seed, int level, int hmis_tile,
-                     DBuf<int8_t>& state) {
+static int aggressive_split(Ctx* c, const Csr<double>& A, const DBuf<uint8_t>& S,
+                            const DBuf<int>& cidx1, int n1, uint64_t seed, int level,
+                            int hmis_tile, DBuf<int8_t>& state) {
   const int n = A.n_rows;
   const int g = cdiv(n, 256);
   Csr<double> X, Y, Z, G2;
@@ -1144,7 +1250,7 @@ int aggressive_split(Ctx* c, const Csr<double>& A, const DBuf<uint8_t>& S,
   }
   check_structure(c, X, "distance-two graph: X", false);
   check_structure(c, Y, "distance-two graph: Y", false);
-  spgemm(c, X, Y, Z);
+  spgemm(c, X, Y, n1, Z);
   check_structure(c, Z, "distance-two graph", false);
   {
     const int g1 = cdiv(n1, 256);
@@ -1170,7 +1276,7 @@ int aggressive_split(Ctx* c, const Csr<double>& A, const DBuf<uint8_t>& S,
                        G2.ci.get(), stc2.get(), (const int*)c->err_flag());
   MGD_CHECK_LAUNCH();
   DBuf<int8_t> st2;
-  const int rounds = pmis(c, G2, S2, stc2, seed, level + kAggressiveSalt, st2, hmis_tile);
+  const int rounds = pmis_one(c, G2, S2, stc2, seed, level + kAggressiveSalt, st2, hmis_tile);
   DBuf<int8_t> out(c, (size_t)n);
   hipLaunchKernelGGL(k_d2_combine, dim3(g), dim3(256), 0, c->stream, n, state.get(), cidx1.get(),
                      (const int8_t*)st2.get(), out.get());
@@ -1301,9 +1407,9 @@ __global__ void k_mp_copy(int n, int m, const int* __restrict__ pass, const int*
   }
 }
 
-void multipass_interpolation(Ctx* c, const Csr<double>& A, const DBuf<uint8_t>& S,
-                             const DBuf<int8_t>& state, const DBuf<int>& cidx, int nc,
-                             Csr<double>& P) {
+static void multipass_interpolation(Ctx* c, const Csr<double>& A, const DBuf<uint8_t>& S,
+                                    const DBuf<int8_t>& state, const DBuf<int>& cidx, int nc,
+                                    Csr<double>& P) {
   const int n = A.n_rows;
   const int g = cdiv(n, 256);
   DBuf<int> pass(c, (size_t)n), off(c, (size_t)n), len(c, (size_t)n), added(c, 1);
@@ -1432,21 +1538,134 @@ int jp_colouring(Ctx* c, const Csr<double>& A, uint64_t seed, int level, DBuf<in
 }
 
 // ---------------------------------------------------------------------------
-// dense inverse of the coarsest matrix (FP64): LU with partial pivoting
-// (first row of maximum magnitude), then one triangular solve pair per
-// column of the identity.  One workgroup; n <= dense_max.
+// dense inverses of the members' coarsest matrices (FP64): LU with partial
+// pivoting (first row of maximum magnitude), then one triangular solve pair per
+// column of the identity.  One workgroup per member; n <= dense_max.
 // ---------------------------------------------------------------------------
-__global__ void k_csr_to_dense(int n, const int* __restrict__ rp, const int* __restrict__ ci,
-                               const double* __restrict__ v, double* __restrict__ M) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  for (int e = rp[i]; e < rp[i + 1]; ++e) M[(size_t)i * n + ci[e]] = v[e];
+struct DenseJob {
+  const int* rp;  // the member's rows, columns ci - cbase
+  const int* ci;
+  const double* v;
+  int n, cbase;
+  double* M;      // n x n work, row-major (members larger than kLdsDense only)
+  int* piv;
+  double* inv;    // n x n, column-major
+};
+
+// Up to kLdsDense rows (the default coarsest size): matrix and inverse in LDS.
+// Every entry goes through the operations of the factorisation below in the
+// same order: the forward solves apply row k to all later rows at once
+// (ascending k for each), the backward solves, whose sums start at the row just
+// finished, run one column per thread.
+constexpr int kLdsDense = 100;
+__global__ void __launch_bounds__(1024) k_dense_inverse(const DenseJob* __restrict__ jobs,
+                                                        int* __restrict__ singular) {
+  __shared__ double M[kLdsDense * kLdsDense], X[kLdsDense * kLdsDense];
+  __shared__ int piv[kLdsDense];
+  const DenseJob J = jobs[blockIdx.x];
+  const int n = J.n, t = threadIdx.x, lane = t & 63;
+  if (n > kLdsDense) return;
+  for (int q = t; q < n * n; q += 1024) {
+    M[q] = 0.0;
+    X[q] = 0.0;
+  }
+  __syncthreads();
+  for (int i = t; i < n; i += 1024)
+    for (int e = J.rp[i]; e < J.rp[i + 1]; ++e) {
+      const int j = J.ci[e] - J.cbase;
+      if (j >= 0 && j < n) M[i * n + j] = J.v[e];
+    }
+  __syncthreads();
+  for (int col = 0; col < n; ++col) {
+    // pivot: largest |M[r][col]|, smallest r on ties; every wave finds it
+    double best = -1.0;
+    int bi = INT_MAX;
+    for (int r = col + lane; r < n; r += 64) {
+      const double a = fabs(M[r * n + col]);
+      if (a > best) {
+        best = a;
+        bi = r;
+      }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      const double ov = __shfl_xor(best, o, 64);
+      const int oi = __shfl_xor(bi, o, 64);
+      if (ov > best || (ov == best && oi < bi)) {
+        best = ov;
+        bi = oi;
+      }
+    }
+    if (!(best > 0.0)) {  // the same in every thread
+      if (t == 0) singular[0] = 1;
+      return;
+    }
+    __syncthreads();
+    if (t == 0) piv[col] = bi;
+    if (bi != col)
+      for (int j = t; j < n; j += 1024) {
+        const double tmp = M[col * n + j];
+        M[col * n + j] = M[bi * n + j];
+        M[bi * n + j] = tmp;
+      }
+    __syncthreads();
+    const double d = M[col * n + col];
+    for (int r = col + 1 + t; r < n; r += 1024) M[r * n + col] = M[r * n + col] / d;
+    __syncthreads();
+    const int m = n - col - 1;
+    for (int q = t; q < m * m; q += 1024) {
+      const int r = col + 1 + q / m, j = col + 1 + q % m;
+      M[r * n + j] = M[r * n + j] - M[r * n + col] * M[col * n + j];
+    }
+    __syncthreads();
+  }
+  if (t < n) {  // column t of the permuted identity
+    int at = t;
+    for (int i = 0; i < n; ++i) {
+      const int p = piv[i];
+      at = at == i ? p : (at == p ? i : at);
+    }
+    X[at * n + t] = 1.0;
+  }
+  __syncthreads();
+  for (int k = 0; k + 1 < n; ++k) {  // unit lower
+    const int m = n - k - 1;
+    for (int q = t; q < m * n; q += 1024) {
+      const int i = k + 1 + q / n, j = q % n;
+      X[i * n + j] = X[i * n + j] - M[i * n + k] * X[k * n + j];
+    }
+    __syncthreads();
+  }
+  if (t < n) {  // upper
+    for (int i = n - 1; i >= 0; --i) {
+      double s = X[i * n + t];
+      for (int k = i + 1; k < n; ++k) s = s - M[i * n + k] * X[k * n + t];
+      X[i * n + t] = s / M[i * n + i];
+    }
+  }
+  __syncthreads();
+  for (int q = t; q < n * n; q += 1024) J.inv[(size_t)(q % n) * n + q / n] = X[q];
 }
 
-__global__ void __launch_bounds__(1024) k_lu(int n, double* __restrict__ M, int* __restrict__ piv,
+// Larger coarsest matrices (coarsening stalled above the default size): in memory.
+__global__ void k_csr_to_dense(const DenseJob* __restrict__ jobs) {
+  const DenseJob J = jobs[blockIdx.y];
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (J.n <= kLdsDense || i >= J.n) return;
+  for (int e = J.rp[i]; e < J.rp[i + 1]; ++e) {
+    const int j = J.ci[e] - J.cbase;
+    if (j >= 0 && j < J.n) J.M[(size_t)i * J.n + j] = J.v[e];
+  }
+}
+
+__global__ void __launch_bounds__(1024) k_lu(const DenseJob* __restrict__ jobs,
                                              int* __restrict__ singular) {
   __shared__ double sval[1024];
   __shared__ int sidx[1024];
+  const DenseJob J = jobs[blockIdx.x];
+  const int n = J.n;
+  if (n <= kLdsDense) return;
+  double* __restrict__ M = J.M;
   const int t = threadIdx.x;
   for (int col = 0; col < n; ++col) {
     // pivot search: max |M[r][col]|, smallest r on ties
@@ -1480,7 +1699,7 @@ __global__ void __launch_bounds__(1024) k_lu(int n, double* __restrict__ M, int*
       if (t == 0) singular[0] = 1;
       return;
     }
-    if (t == 0) piv[col] = p;
+    if (t == 0) J.piv[col] = p;
     if (p != col)
       for (int j = t; j < n; j += 1024) {
         const double tmp = M[(size_t)col * n + j];
@@ -1502,14 +1721,15 @@ __global__ void __launch_bounds__(1024) k_lu(int n, double* __restrict__ M, int*
 }
 
 // inverse column j: solve L U x = P e_j; written column-major inv[j*n + i]
-__global__ void k_lu_inverse(int n, const double* __restrict__ M, const int* __restrict__ piv,
-                             double* __restrict__ inv) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n) return;
-  double* x = inv + (size_t)j * n;
+__global__ void k_lu_inverse(const DenseJob* __restrict__ jobs, const int* __restrict__ singular) {
+  const DenseJob J = jobs[blockIdx.y];
+  const int n = J.n, j = blockIdx.x * blockDim.x + threadIdx.x;
+  if (n <= kLdsDense || j >= n || *singular) return;
+  const double* __restrict__ M = J.M;
+  double* x = J.inv + (size_t)j * n;
   for (int i = 0; i < n; ++i) x[i] = (i == j) ? 1.0 : 0.0;
   for (int i = 0; i < n; ++i) {  // apply the row interchanges in order
-    const int p = piv[i];
+    const int p = J.piv[i];
     if (p != i) {
       const double t = x[i];
       x[i] = x[p];
@@ -1528,98 +1748,181 @@ __global__ void k_lu_inverse(int n, const double* __restrict__ M, const int* __r
   }
 }
 
-bool dense_inverse(Ctx* c, const Csr<double>& A, DBuf<double>& inv) {
-  const int n = A.n_rows;
-  inv.alloc(c, (size_t)n * n);
-  if (n == 0) return true;
-  DBuf<double> M(c, (size_t)n * n);
-  DBuf<int> piv(c, (size_t)n), sing(c, 1);
-  fill<double>(c, M.get(), 0.0, (size_t)n * n);
+// coarse_kind and inverses of every member
+static void coarsest_inverses(Ctx* c, const amg_params& p, SetupBatch& H) {
+  const int nm = (int)H.n_levels.size();
+  H.coarse_kind.assign(nm, 0);
+  H.inv_at.assign(nm, 0);
+  size_t total = 0, work = 0, pivs = 0;
+  int top = 0;
+  std::vector<DenseJob> jobs;
+  std::vector<size_t> m_at, p_at;
+  std::vector<int> who;
+  for (int m = 0; m < nm; ++m) {
+    const SetupLevel& L = H.levels[H.n_levels[m] - 1];
+    const int n = L.off[m + 1] - L.off[m];
+    if (n > p.dense_max) {
+      H.coarse_kind[m] = 1;
+      continue;
+    }
+    H.inv_at[m] = total;
+    total += (size_t)n * n;
+    if (n == 0) continue;
+    jobs.push_back({L.A.rp.get() + L.off[m], L.A.ci.get(), L.A.v.get(), n, L.off[m], nullptr,
+                    nullptr, nullptr});
+    m_at.push_back(work);
+    p_at.push_back(pivs);
+    who.push_back(m);
+    if (n > kLdsDense) {
+      work += (size_t)n * n;
+      pivs += n;
+      top = std::max(top, n);
+    }
+  }
+  if (jobs.empty()) return;
+  H.inv.alloc(c, std::max<size_t>(total, 1));
+  DBuf<double> M(c, std::max<size_t>(work, 1));
+  DBuf<int> piv(c, std::max<size_t>(pivs, 1)), sing(c, 1);
+  for (size_t q = 0; q < jobs.size(); ++q) {
+    jobs[q].M = M.get() + m_at[q];
+    jobs[q].piv = piv.get() + p_at[q];
+    jobs[q].inv = H.inv.get() + H.inv_at[who[q]];
+  }
+  DBuf<DenseJob> dj(c, jobs.size());
+  copy_h2d(c, dj.get(), jobs.data(), jobs.size());
   fill<int>(c, sing.get(), 0, 1);
-  hipLaunchKernelGGL(k_csr_to_dense, dim3(cdiv(n, 256)), dim3(256), 0, c->stream, n, A.rp.get(),
-                     A.ci.get(), A.v.get(), M.get());
+  const unsigned nj = (unsigned)jobs.size();
+  hipLaunchKernelGGL(k_dense_inverse, dim3(nj), dim3(1024), 0, c->stream,
+                     (const DenseJob*)dj.get(), sing.get());
   MGD_CHECK_LAUNCH();
-  hipLaunchKernelGGL(k_lu, dim3(1), dim3(1024), 0, c->stream, n, M.get(), piv.get(), sing.get());
-  MGD_CHECK_LAUNCH();
-  if (read1(c, sing.get())) return false;
-  hipLaunchKernelGGL(k_lu_inverse, dim3(cdiv(n, 64)), dim3(64), 0, c->stream, n,
-                     (const double*)M.get(), (const int*)piv.get(), inv.get());
-  MGD_CHECK_LAUNCH();
-  c->sync();
-  return true;
+  if (top > 0) {
+    fill<double>(c, M.get(), 0.0, work);
+    hipLaunchKernelGGL(k_csr_to_dense, dim3(cdiv(top, 256), nj), dim3(256), 0, c->stream,
+                       (const DenseJob*)dj.get());
+    hipLaunchKernelGGL(k_lu, dim3(nj), dim3(1024), 0, c->stream, (const DenseJob*)dj.get(),
+                       sing.get());
+    hipLaunchKernelGGL(k_lu_inverse, dim3(cdiv(top, 64), nj), dim3(64), 0, c->stream,
+                       (const DenseJob*)dj.get(), (const int*)sing.get());
+    MGD_CHECK_LAUNCH();
+  }
+  if (read1(c, sing.get())) fail(MGD_ESINGULAR, "zero pivot in the coarsest-level LU");
 }
 
 // ---------------------------------------------------------------------------
 // hierarchy driver
 // ---------------------------------------------------------------------------
-void amg_build(Ctx* c, Csr<double>&& A0, const amg_params& p, SetupHierarchy& H) {
+void amg_build(Ctx* c, Csr<double>&& A0, const std::vector<int>& off0,
+               const std::vector<int>& eoff0, const amg_params& p, SetupBatch& H) {
+  DeferFrees frees(c);
+  const int nm = (int)off0.size() - 1;
+  MGD_REQUIRE(nm == 1 || setup_batches(p), "internal: these parameters set up one matrix at a time");
   H.levels.clear();
+  H.n_levels.assign(nm, 0);
+  const int tile = p.coarsening == 1 ? p.hmis_tile : 0;
   Csr<double> A = std::move(A0);
+  std::vector<int> off = off0, eoff = eoff0;
   for (int lvl = 0;; ++lvl) {
     const int n = A.n_rows;
     SetupLevel L;
-    if (n <= p.coarse_max || lvl == p.max_levels - 1 || lvl == MGD_MAX_LEVELS - 1) {
+    L.off = off;
+    L.eoff = eoff;
+    const RowRanges R = row_ranges(off);
+    MemberFlags M;
+    bool any = false;
+    for (int m = 0; m < nm; ++m) {
+      const int rows = off[m + 1] - off[m];
+      const bool on =
+          rows > p.coarse_max && lvl != p.max_levels - 1 && lvl != MGD_MAX_LEVELS - 1;
+      M.on[m] = on ? 1 : 0;
+      any = any || on;
+      if (rows > 0 || lvl == 0) H.n_levels[m] = lvl + 1;  // the last level, so far
+    }
+    if (!any) {
       L.A = std::move(A);
       H.levels.push_back(std::move(L));
       break;
     }
     const std::string at = " (level " + std::to_string(lvl) + ", " + std::to_string(n) + " rows)";
     DBuf<uint8_t> S;
-    DBuf<int> stc;
-    StepScope st_strength("amg setup: strength" + at);
-    strength(c, A, p.strength_theta, p.dominance_theta, S, stc);
+    DBuf<int> stc, cidx;
+    DBuf<double> diag;
     DBuf<int8_t> state;
+    StepScope st_strength("amg setup: strength" + at);
+    strength(c, A, p.strength_theta, p.dominance_theta, S, stc, diag);
     StepScope st_pmis("amg setup: pmis" + at);
-    int rounds = pmis(c, A, S, stc, p.seed, lvl, state, p.coarsening == 1 ? p.hmis_tile : 0);
+    std::vector<int> coff =
+        pmis(c, A, S, stc, R, M, p.seed, lvl, tile, state, cidx, L.rounds);
     StepScope st_cnum("amg setup: coarse numbering" + at);
-    DBuf<int> isc(c, (size_t)n), cidx(c, (size_t)n + 1);
-    hipLaunchKernelGGL(k_is_c, dim3(cdiv(n, 256)), dim3(256), 0, c->stream, n, state.get(),
-                       isc.get());
-    MGD_CHECK_LAUNCH();
-    int nc = exclusive_scan_total(c, isc.get(), cidx.get(), n);
-    const bool aggressive = lvl < p.aggressive_levels;
-    if (aggressive && nc > 0) {
-      StepScope st_agg("amg setup: aggressive second pass" + at);
-      rounds += aggressive_split(c, A, S, cidx, nc, p.seed, lvl,
-                                 p.coarsening == 1 ? p.hmis_tile : 0, state);
-      hipLaunchKernelGGL(k_is_c, dim3(cdiv(n, 256)), dim3(256), 0, c->stream, n, state.get(),
-                         isc.get());
+    auto number = [&]() {
+      DBuf<int> isc(c, (size_t)n);
+      hipLaunchKernelGGL(k_is_c, dim3(cdiv(n, 256)), dim3(256), 0, c->stream, n,
+                         (const int8_t*)state.get(), isc.get());
       MGD_CHECK_LAUNCH();
-      nc = exclusive_scan_total(c, isc.get(), cidx.get(), n);
+      exclusive_scan(c, isc.get(), cidx.get(), n);
+      coff = read_bounds(c, R, cidx.get(), "coarse numbering");
+    };
+    const bool aggressive = lvl < p.aggressive_levels;
+    if (aggressive && coff.back() > 0) {  // one matrix
+      StepScope st_agg("amg setup: aggressive second pass" + at);
+      L.rounds[0] += aggressive_split(c, A, S, cidx, coff.back(), p.seed, lvl, tile, state);
+      number();
     }
-    if (nc == 0 || 10LL * nc > 9LL * n) {  // stalled coarsening: this is the coarsest level
+    // members whose coarsening stalled end here
+    bool stalled = false;
+    any = false;
+    for (int m = 0; m < nm; ++m) {
+      const int rows = off[m + 1] - off[m], nc = coff[m + 1] - coff[m];
+      if (M.on[m] && (nc == 0 || 10LL * nc > 9LL * rows)) {
+        M.on[m] = 0;
+        stalled = true;
+      }
+      any = any || M.on[m];
+    }
+    if (!any) {
       L.A = std::move(A);
       H.levels.push_back(std::move(L));
       break;
     }
-    Csr<double> P, R, AP, Ac;
+    if (stalled) {
+      hipLaunchKernelGGL(k_mask_f, dim3(cdiv(n, 256)), dim3(256), 0, c->stream, n, R, M,
+                         state.get());
+      MGD_CHECK_LAUNCH();
+      number();
+    }
+    const int nc = coff.back();
+    int max_cols = 0;  // no product row leaves its member
+    for (int m = 0; m < nm; ++m) max_cols = std::max(max_cols, coff[m + 1] - coff[m]);
+    Csr<double> P, Rt, AP, Ac;
     {
       StepScope st("amg setup: interpolation" + at);
-      if (aggressive)
+      if (aggressive) {
         multipass_interpolation(c, A, S, state, cidx, nc, P);
-      else
-        interpolation(c, A, S, state, cidx, nc, P);
-      check_structure(c, P, "interpolation", false);
+        L.poff = {0, P.nnz};
+      } else {
+        interpolation(c, A, diag, S, state, cidx, R, nc, P, L.poff);
+      }
+      check_structure_async(c, P.n_rows, P.n_cols, P.nnz, P.rp.get(), P.ci.get(), false, false);
     }
     {
       StepScope st("amg setup: transpose of P" + at);
-      transpose(c, P, R);
+      transpose(c, P, Rt);
     }
     {
       StepScope st("amg setup: A P" + at);
-      spgemm(c, A, P, AP);
-      check_structure(c, AP, "A P", false);
+      spgemm(c, A, P, max_cols, AP);
+      check_structure_async(c, AP.n_rows, AP.n_cols, AP.nnz, AP.rp.get(), AP.ci.get(), false, false);
     }
     {
       StepScope st("amg setup: R (A P)" + at);
-      spgemm(c, R, AP, Ac);
-      check_structure(c, Ac, "coarse operator", true);
+      spgemm(c, Rt, AP, max_cols, Ac);
+      check_structure_async(c, Ac.n_rows, Ac.n_cols, Ac.nnz, Ac.rp.get(), Ac.ci.get(), true, false);
+      eoff = read_bounds(c, row_ranges(coff), Ac.rp.get(), "coarse operator");
     }
     L.A = std::move(A);
     L.cf = std::move(state);
     L.P = std::move(P);
-    L.nc = nc;
-    L.pmis_rounds = rounds;
+    L.coff = coff;
+    off = coff;
     H.levels.push_back(std::move(L));
     A = std::move(Ac);
   }
@@ -1630,15 +1933,8 @@ void amg_build(Ctx* c, Csr<double>&& A0, const amg_params& p, SetupHierarchy& H)
       L.ncolours = jp_colouring(c, L.A, p.seed, (int)l, L.colour);
     }
   }
-  SetupLevel& last = H.levels.back();
-  if (last.A.n_rows <= p.dense_max) {
-    StepScope st("amg setup: coarsest LU (" + std::to_string(last.A.n_rows) + " rows)");
-    H.coarse_kind = 0;
-    if (!dense_inverse(c, last.A, H.coarse_inv))
-      fail(MGD_ESINGULAR, "zero pivot in the coarsest-level LU");
-  } else {
-    H.coarse_kind = 1;
-  }
+  StepScope st("amg setup: coarsest LU");
+  coarsest_inverses(c, p, H);
 }
 
 }  // namespace mgd

@@ -1,5 +1,8 @@
 // AMG setup on the device (natural ordering).
 #pragma once
+#include <memory>
+#include <vector>
+
 #include "common.hpp"
 
 namespace mgd {
@@ -27,48 +30,77 @@ __device__ __forceinline__ int member_of(const RowRanges& R, int i) {
 
 struct UMember;  // a member's arrays at one level, for the union builder
 
+// Hierarchies built together: level l holds the level matrices of all members
+// that have one as the diagonal blocks of one matrix (columns numbered through),
+// so one set of launches and one wait serve them all.  A member keeps the values
+// it would have alone: its rows only see its own columns, and whatever depends
+// on a row's number (hash keys, tie breaks) uses the number within the member.
+// The 22 hierarchies of the 3D 64^3, G = 20 system take 29 ms together; one
+// after another they took 145 ms, most of it launches and waits on small levels.
 struct SetupLevel {
   Csr<double> A;
-  DBuf<int8_t> cf;  // empty on the coarsest level
-  Csr<double> P;    // n x nc; empty on the coarsest level
-  int nc = 0;
-  int pmis_rounds = 0;
+  DBuf<int8_t> cf;            // empty on the last level; all F for members that end here
+  Csr<double> P;              // A.n_rows x next level's rows; empty rows for members that end here
+  std::vector<int> off, eoff;    // per member its first row and entry (members + 1)
+  std::vector<int> coff, poff;   // its first coarse row and entry of P (members + 1)
+  std::vector<int> rounds;       // PMIS rounds per member
   DBuf<int> colour;  // Jones-Plassmann colours (multicolour Gauss-Seidel only)
   int ncolours = 0;
 };
 
-struct SetupHierarchy {
+struct SetupBatch {
   std::vector<SetupLevel> levels;
-  int coarse_kind = 0;           // 0 dense LU (explicit inverse), 1 l1-Jacobi sweeps
-  DBuf<double> coarse_inv;       // n_L x n_L, column-major, when coarse_kind == 0
-  size_t n_levels() const { return levels.size(); }
-  long long nnz(size_t l) const { return l < levels.size() ? levels[l].A.nnz : 0; }
-  long long nnz_P(size_t l) const { return l < levels.size() ? levels[l].P.nnz : 0; }
-  const double* inverse() const { return coarse_inv.get(); }
+  std::vector<int> n_levels;     // per member
+  std::vector<int> coarse_kind;  // per member: 0 dense LU (explicit inverse), 1 l1-Jacobi sweeps
+  DBuf<double> inv;              // the inverses, n_L x n_L, column-major
+  std::vector<size_t> inv_at;    // per member its first value in inv
+};
+
+// A member's level-0 matrix inside its batch: row i at rp[i], columns ci - base.
+struct MemberCsr {
+  int n = 0, nnz = 0, base = 0;
+  const int* rp = nullptr;
+  const int* ci = nullptr;
+  const double* v = nullptr;
+};
+
+struct SetupHierarchy {
+  std::shared_ptr<SetupBatch> b;
+  int m = 0;
+  size_t n_levels() const { return b->n_levels[m]; }
+  bool last(size_t l) const { return l + 1 == n_levels(); }
+  int n(size_t l) const { return b->levels[l].off[m + 1] - b->levels[l].off[m]; }
+  int nnz(size_t l) const { return b->levels[l].eoff[m + 1] - b->levels[l].eoff[m]; }
+  int nnz_P(size_t l) const { return last(l) ? 0 : b->levels[l].poff[m + 1] - b->levels[l].poff[m]; }
+  int rounds(size_t l) const { return last(l) ? 0 : b->levels[l].rounds[m]; }
+  int coarse_kind() const { return b->coarse_kind[m]; }
+  const double* inverse() const { return b->inv.get() + b->inv_at[m]; }
+  MemberCsr level0() const {
+    const SetupLevel& L = b->levels[0];
+    return {n(0), nnz(0), L.off[m], L.A.rp.get() + L.off[m], L.A.ci.get(), L.A.v.get()};
+  }
   UMember member(size_t l) const;
 };
 
 // Copy a caller matrix into an owned one.
 void csr_copy_from(Ctx* c, const mgd_csr* A, Csr<double>& out);
 void csr_copy(Ctx* c, const Csr<double>& A, Csr<double>& out);
-// Build the hierarchy for a square matrix (already validated, copied in).
-void amg_build(Ctx* c, Csr<double>&& A0, const amg_params& p, SetupHierarchy& H);
+// Build the hierarchies of the diagonal blocks of A0 (member q: rows and columns
+// [off[q], off[q + 1]), entries [eoff[q], eoff[q + 1])), already validated.  More
+// than one member needs setup_batches(p).
+void amg_build(Ctx* c, Csr<double>&& A0, const std::vector<int>& off,
+               const std::vector<int>& eoff, const amg_params& p, SetupBatch& H);
+// Whether hierarchies with these parameters can be built together (HMIS tiles,
+// the distance-two pass and colourings are formed for one matrix at a time).
+inline bool setup_batches(const amg_params& p) {
+  return p.coarsening == 0 && p.aggressive_levels == 0 && p.smoother == 0;
+}
 
-// Pieces exposed for testing and for the union builder.
-void strength(Ctx* c, const Csr<double>& A, double theta, double dom, DBuf<uint8_t>& S,
-              DBuf<int>& stc);
-// hmis_tile > 0: HMIS with tiles of that many rows (<= 1024), else PMIS
-int pmis(Ctx* c, const Csr<double>& A, const DBuf<uint8_t>& S, const DBuf<int>& stc,
-         uint64_t seed, int level, DBuf<int8_t>& state, int hmis_tile);
-void interpolation(Ctx* c, const Csr<double>& A, const DBuf<uint8_t>& S,
-                   const DBuf<int8_t>& state, const DBuf<int>& cidx, int nc, Csr<double>& P);
 // Sorted transpose (values copied).
 void transpose(Ctx* c, const Csr<double>& A, Csr<double>& T);
-// C = A B, structural pattern, entries summed over ascending k from 0.
-void spgemm(Ctx* c, const Csr<double>& A, const Csr<double>& B, Csr<double>& C);
+// C = A B, structural pattern, entries summed over ascending k from 0.  No row of
+// C has more than max_cols columns.
+void spgemm(Ctx* c, const Csr<double>& A, const Csr<double>& B, int max_cols, Csr<double>& C);
 // Jones-Plassmann colouring of the structural graph of A; returns the number of colours
 int jp_colouring(Ctx* c, const Csr<double>& A, uint64_t seed, int level, DBuf<int>& colour);
-// Explicit inverse via LU with partial pivoting; returns false on a zero pivot.
-bool dense_inverse(Ctx* c, const Csr<double>& A, DBuf<double>& inv_colmajor);
-
 }  // namespace mgd

@@ -48,24 +48,27 @@ struct UMember {
 };
 
 UMember SetupHierarchy::member(size_t l) const {
-  UMember m{};
-  if (l >= levels.size()) return m;
-  const SetupLevel& L = levels[l];
-  m.rp = L.A.rp.get();
-  m.ci = L.A.ci.get();
-  m.v = L.A.v.get();
-  m.n = L.A.n_rows;
-  m.colour = L.colour.get();
-  if (l + 1 < levels.size()) {
-    m.cf = L.cf.get();
-    m.prp = L.P.rp.get();
-    m.pci = L.P.ci.get();
-    m.pv = L.P.v.get();
-    m.nc = L.nc;
+  UMember u{};
+  if (l >= n_levels()) return u;
+  const SetupLevel& L = b->levels[l];
+  const int r0 = L.off[m];
+  u.rp = L.A.rp.get() + r0;
+  u.ci = L.A.ci.get();
+  u.v = L.A.v.get();
+  u.cbase = r0;
+  u.n = n(l);
+  u.colour = L.colour.p ? L.colour.get() + r0 : nullptr;
+  if (!last(l)) {
+    u.cf = L.cf.get() + r0;
+    u.prp = L.P.rp.get() + r0;
+    u.pci = L.P.ci.get();
+    u.pv = L.P.v.get();
+    u.pbase = L.coff[m];
+    u.nc = L.coff[m + 1] - L.coff[m];
   } else {
-    m.kind = coarse_kind == 1 ? 1 : 2;
+    u.kind = coarse_kind() == 1 ? 1 : 2;
   }
-  return m;
+  return u;
 }
 
 // isc[i] = 1 for C rows.  Members without a coarser level are all F.

@@ -304,6 +304,41 @@ def test_amg_levelwise_on_gpu_levels(ctx):
         assert np.array_equal(P.data, pv)
 
 
+@pytest.mark.parametrize("n,params", [(9, {}), (24, {}), (24, {"dense_max": 20, "max_levels": 3}),
+                                      (33, {"coarse_max": 7})])
+def test_hierarchies_built_together_equal_single_ones(ctx, n, params):
+    """Members of one preconditioner are set up together, whatever level each of
+    them ends at (too small, stalled because no row has strong neighbours, or the
+    level limit): every hierarchy equals the one of its matrix alone bit for bit,
+    and the batched apply equals the members' own V-cycles to rounding."""
+    api = gpu_modules()
+    inp = si.generate(5, 2, n, 17)
+    inp.kappa[1] *= 1e-9      # diagonal to rounding: coarsening stalls at once
+    inp.kappa[3] = 1.0        # another depth than the others
+    co, gsys = gpu_system(ctx, inp)
+    kw = {"amg_" + k: v for k, v in params.items()}
+    M = api.BlockPreconditioner(ctx, gsys, "bdiag", amg_seed=5, batched=1, **kw)
+    b = np.random.default_rng(3).uniform(size=7 * n * n)
+    z = to_host(M.apply(to_dev(ctx, b))).reshape(7, -1)
+    depths = set()
+    for a in range(7):
+        rp, ci, v = gsys.block_arrays(a)
+        alone = api.AMG(ctx, rp, ci, v, seed=5, **params)
+        got = M.hierarchy(a)
+        ia, ig = alone.info(), got.info()
+        assert ia == ig, (a, ia, ig)
+        depths.add(ia["levels"])
+        for l in range(ia["levels"]):
+            ea, eg = alone.export_level(l), got.export_level(l)
+            assert np.array_equal(ea["cf"], eg["cf"])
+            for key in ("A", "P") if l + 1 < ia["levels"] else ("A",):
+                for x, y in zip(ea[key], eg[key]):
+                    assert np.array_equal(x, y), (a, l, key)
+        za = to_host(alone.apply(to_dev(ctx, b.reshape(7, -1)[a])))
+        assert_elementwise(z[a], za, 1e-12, what="batched member")
+    assert n < 24 or len(depths) > 1
+
+
 def test_amg_edge_cases(ctx):
     api = gpu_modules()
     # single row
