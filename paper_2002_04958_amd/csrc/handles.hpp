@@ -132,7 +132,7 @@ struct block_precond {
   std::vector<int> inner_cycles;
   std::unique_ptr<mgd::PcExec<double>> x64;
   std::unique_ptr<mgd::PcExec<float>> x32;
-  // graph cache keyed by (r, z)
+  // graph cache keyed by (r, z); null after the first use, which launches directly
   std::map<std::pair<const void*, void*>, hipGraphExec_t> graphs;
   // whole flexible-GMRES steps (apply, matvec, Gram-Schmidt) keyed by every
   // pointer and size their launches use

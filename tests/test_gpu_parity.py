@@ -889,6 +889,36 @@ def test_gmres_step_graph_matches_direct(ctx, kind, precision, restart):
         assert float((b * 2.0).sum()) == float((b * 2.0).sum())
 
 
+@pytest.mark.parametrize("kind,precision", [("schur2", 1), ("schur1", 0), ("pctl", 1), ("bdiag", 0)])
+def test_first_use_launches_then_graphs_are_equal(ctx, kind, precision):
+    """With use_graph the first use of a pair of buffers (or of a GMRES step) runs
+    its launches directly, the second captures them, later ones replay: the same
+    bits each time, with other work and synchronisations between, and equal to a
+    preconditioner without graphs."""
+    import torch
+    api = gpu_modules()
+    inp = si.generate(3, 2, 20, 44)
+    co, gsys = gpu_system(ctx, inp)
+    kw = dict(amg_seed=5, batched=1, amg_precision=precision)
+    M = api.BlockPreconditioner(ctx, gsys, kind, use_graph=1, **kw)
+    Md = api.BlockPreconditioner(ctx, gsys, kind, use_graph=0, **kw)
+    r = to_dev(ctx, inp.b)
+    want = to_host(Md.apply(r))
+    z = torch.empty_like(r)
+    for _ in range(4):
+        z.fill_(7.0)
+        M.apply(r, z)
+        assert np.array_equal(to_host(z), want)
+        torch.cuda.synchronize()
+    xs = []
+    for _ in range(4):
+        x, res = api.gmres(ctx, gsys, M, r, rtol=1e-9)
+        assert res.converged
+        xs.append((to_host(x), res.iters))
+        torch.cuda.synchronize()
+    assert all(np.array_equal(x, xs[0][0]) and i == xs[0][1] for x, i in xs)
+
+
 def test_gmres_no_preconditioner_and_nonflexible(ctx):
     api = gpu_modules()
     inp = si.generate(1, 2, 12, 5)
