@@ -4,6 +4,7 @@
 #include <algorithm>
 #include <array>
 #include <chrono>
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <fstream>
@@ -113,10 +114,23 @@ __global__ void k_u_check(int n, const int* __restrict__ ext, const int* __restr
 
 constexpr int kSortWindow = 128;  // two 64-row slices: less padding, gathers stay local
 
-// Rows of the C-block and of the F-block in order of decreasing length (stable)
-// within windows of kSortWindow rows, one workgroup per window: a row's rank is
-// the number of longer rows, and of equally long ones before it.
-__global__ void __launch_bounds__(kSortWindow) k_u_window_sort(int nC, int nS, int nwC, RowRanges R,
+// Windows of the length order: segment q holds rows [row[q], row[q + 1]) and
+// windows [win[q], win[q + 1]), the last one cut at the segment's end.
+struct SortWindows {
+  int nseg = 0;
+  int win[2 * kMaxMembers + 1] = {}, row[2 * kMaxMembers + 1] = {};
+  void add(int rows) {
+    if (rows <= 0) return;
+    win[nseg + 1] = win[nseg] + cdiv(rows, kSortWindow);
+    row[nseg + 1] = row[nseg] + rows;
+    ++nseg;
+  }
+};
+
+// Rows of each segment in order of decreasing length (stable) within windows of
+// kSortWindow rows, one workgroup per window: a row's rank is the number of
+// longer rows, and of equally long ones before it.
+__global__ void __launch_bounds__(kSortWindow) k_u_window_sort(SortWindows W, RowRanges R,
                                                                const UMember* __restrict__ tab,
                                                                int* __restrict__ ext,
                                                                int* __restrict__ perm,
@@ -124,8 +138,10 @@ __global__ void __launch_bounds__(kSortWindow) k_u_window_sort(int nC, int nS, i
   __shared__ int lens[kSortWindow];
   if (*err) return;
   const int b = blockIdx.x, t = threadIdx.x;
-  const int w0 = b < nwC ? b * kSortWindow : nC + (b - nwC) * kSortWindow;
-  const int w1 = min(b < nwC ? nC : nS, w0 + kSortWindow);
+  int q = 0;
+  while (q + 1 < W.nseg && W.win[q + 1] <= b) ++q;
+  const int w0 = W.row[q] + (b - W.win[q]) * kSortWindow;
+  const int w1 = min(W.row[q + 1], w0 + kSortWindow);
   int i = 0, len = -1;
   if (w0 + t < w1) {
     i = perm[w0 + t];
@@ -316,6 +332,7 @@ struct BuildLevel {
   int n = 0, nS = 0, nC = 0, nF = 0, n_coarse = 0;
   RowRanges R;
   size_t tab = 0;            // its members in the device table
+  bool bottom = false;       // runs one member per workgroup (or may, see build_bottom)
   long long want_a = 0, want_w = 0;  // entries the stored matrix and W must end with
   DBuf<int> ext, perm;       // natural -> extended stored order, and back
   DBuf<int> arp, wrp;
@@ -325,6 +342,23 @@ struct BuildLevel {
 template <typename T>
 static void layout_levels(Ctx* c, std::vector<BuildLevel<T>>& bl, const int* stats, Union<T>& U,
                           int autotune);
+template <typename T>
+static void build_bottom(Ctx* c, std::vector<BuildLevel<T>>& bl, const std::vector<UMember>& tab,
+                         int cand, const int* widths_dev, const std::vector<int>& widths,
+                         Union<T>& U);
+template <typename T>
+static std::vector<int> bot_widths(Ctx* c, const std::vector<BuildLevel<T>>& bl,
+                                   const std::vector<UMember>& tab, int cand, DBuf<int>& out);
+static long long sell_min_rows();
+static long long tune_min_rows();
+constexpr int kBotRows = 2048;
+// rows of a member in the F-block (F points, or a relaxed last level)
+static int f_rows(const UMember& m) { return m.kind == 0 ? m.n - m.nc : (m.kind == 1 ? m.n : 0); }
+
+static long long env_ll(const char* name, long long dflt) {
+  const char* e = std::getenv(name);
+  return e && *e ? std::atoll(e) : dflt;
+}
 
 // Host-side verification of a union level (MGD_DEBUG_UNION=1): the map is a
 // permutation and every stored row equals its source row.  Throws with the
@@ -459,6 +493,17 @@ std::unique_ptr<Union<T>> build_union(Ctx* c, const std::vector<const SetupHiera
   const int nl = (int)bl.size();
   DBuf<UMember> dtab(c, std::max<size_t>(tab.size(), 1));
   copy_h2d(c, dtab.get(), tab.data(), tab.size());
+  // first level from which every member is small enough for one workgroup
+  int cand = nl;
+  if (smoother != 1)
+    while (cand > 0) {
+      const BuildLevel<T>& b = bl[cand - 1];
+      // (levels whose layouts may be tuned or sliced are not, tuned now or before)
+      bool ok = b.nS < std::min(sell_min_rows(), tune_min_rows());
+      for (int q = 0; q < b.R.nm; ++q) ok = ok && tab[b.tab + q].n <= kBotRows;
+      if (!ok) break;
+      --cand;
+    }
   U->L.resize(nl);
   int* err = c->err_flag();
   // maps and row lengths of every level
@@ -494,9 +539,17 @@ std::unique_ptr<Union<T>> build_union(Ctx* c, const std::vector<const SetupHiera
       c->check_device_errors("stored-row map of a solve-phase level");
       colour_order(c, b, dt, U->L[l].cranges);
     } else if (b.nS > 0 && l > 0) {
-      const int nwC = cdiv(b.nC, kSortWindow), nwF = cdiv(b.nF, kSortWindow);
-      hipLaunchKernelGGL(k_u_window_sort, dim3(nwC + nwF), dim3(kSortWindow), 0, c->stream, b.nC,
-                         b.nS, nwC, b.R, dt, b.ext.get(), b.perm.get(), (const int*)err);
+      // levels that may run one member per workgroup keep a member's rows together
+      SortWindows win;
+      if (l >= cand) {
+        for (int q = 0; q < b.R.nm; ++q) win.add(tab[b.tab + q].nc);
+        for (int q = 0; q < b.R.nm; ++q) win.add(f_rows(tab[b.tab + q]));
+      } else {
+        win.add(b.nC);
+        win.add(b.nF);
+      }
+      hipLaunchKernelGGL(k_u_window_sort, dim3(win.win[win.nseg]), dim3(kSortWindow), 0, c->stream,
+                         win, b.R, dt, b.ext.get(), b.perm.get(), (const int*)err);
       MGD_CHECK_LAUNCH();
     }
     DBuf<int> alen(c, (size_t)std::max(b.nS, 1)), wlen(c, (size_t)std::max(b.nF, 1));
@@ -610,8 +663,11 @@ std::unique_ptr<Union<T>> build_union(Ctx* c, const std::vector<const SetupHiera
     }
     if (debug_union()) verify_union_level(c, tab, b);
   }
+  DBuf<int> widths;  // slice widths of each member's rows at the candidate bottom levels
+  const std::vector<int> hw = bot_widths(c, bl, tab, cand, widths);
   const std::vector<int> hs = read_vec(c, stats.get(), (size_t)nl * 6);
   c->check_device_errors("stored-order matrices of the solve-phase levels");
+  build_bottom<T>(c, bl, tab, cand, widths.get(), hw, *U);
   layout_levels<T>(c, bl, hs.data(), *U, autotune);
   if (nl > 0) {
     // level 0 seen from the natural side, for entry kernels that read their
@@ -628,7 +684,6 @@ std::unique_ptr<Union<T>> build_union(Ctx* c, const std::vector<const SetupHiera
   }
   U->build_tail(c);
   c->check_device_errors("solve-phase build");
-  c->sync();
   return U;
 }
 
@@ -1166,6 +1221,422 @@ __global__ void k_axpy_t(int n, const T* __restrict__ x, T* __restrict__ y) {
 }
 
 // ---------------------------------------------------------------------------
+// the bottom of a cycle: one workgroup per member
+// ---------------------------------------------------------------------------
+// A cycle's small levels are a chain of dependent launches of 2 to 5 us each
+// (six per level), whose work is a few hundred nanoseconds.  One workgroup runs
+// the whole chain for its member between barriers of its own, with the same
+// arithmetic as per-level launches with one lane per row.  What bounds it is one
+// compute unit's instruction issue (a wave's instruction takes four cycles), so
+// the layout is chosen for few instructions per entry: 64-row slices stored
+// column by column (C rows and F rows in slices of their own), every address a
+// constant step from the last, rows padded to the slice's even width with zero
+// values; iterates in one buffer, so a column is its position.  The three lower
+// levels of a 64^2 hierarchy (FP64) take 40 us as 13 launches, 33 us here with
+// rows in CSR order (25 instructions per entry) and 20 us as slices.  A Schur1
+// apply at 2D 101^2, G = 5 went from 777 to 507 us by it, a PCTL apply at 2D
+// 256^2, G = 20 from 644 to 561 us.
+extern __shared__ __align__(16) unsigned char bot_sm[];
+
+// an array of a level, in the LDS copy or in memory
+template <bool IN, typename U>
+__device__ __forceinline__ const U* bot_at(const unsigned char* __restrict__ g, unsigned o) {
+  if (IN) return reinterpret_cast<const U*>(bot_sm + o);
+  return reinterpret_cast<const U*>(g + o);
+}
+
+// K entries of the lane's row, their loads together, added in order
+template <int K, typename T>
+__device__ __forceinline__ T bot_part(const uint16_t* ci, const T* v, const T* x, T s) {
+  int j[K];
+  T a[K], xv[K];
+#pragma unroll
+  for (int q = 0; q < K; ++q) {
+    j[q] = ci[64 * q];
+    a[q] = v[64 * q];
+  }
+#pragma unroll
+  for (int q = 0; q < K; ++q) xv[q] = x[j[q]];
+#pragma unroll
+  for (int q = 0; q < K; ++q) s += a[q] * xv[q];
+  return s;
+}
+// the lane's row of slice `sl`
+template <bool IN, typename T>
+__device__ __forceinline__ T bot_row(const unsigned char* __restrict__ g, const BotOp& op,
+                                     const T* x, int sl, int lane) {
+  const uint16_t* so = bot_at<true, uint16_t>(g, op.so);
+  const int o = __builtin_amdgcn_readfirstlane(so[sl]);
+  int w = __builtin_amdgcn_readfirstlane(so[sl + 1]) - o;
+  const uint16_t* ci = bot_at<IN, uint16_t>(g, op.co) + 64 * o + lane;
+  const T* v = bot_at<IN, T>(g, op.vo) + 64 * o + lane;
+  T s = 0;
+  if (!IN) {
+    // from memory: sixteen columns' loads in flight, cut at the (scalar) width
+    for (; w > 0; w -= 16, ci += 1024, v += 1024) {
+      int j[16];
+      T a[16], xv[16];
+#pragma unroll
+      for (int q = 0; q < 16; q += 2)
+        if (q < w) {
+          j[q] = ci[64 * q];
+          j[q + 1] = ci[64 * q + 64];
+          a[q] = v[64 * q];
+          a[q + 1] = v[64 * q + 64];
+        }
+#pragma unroll
+      for (int q = 0; q < 16; q += 2)
+        if (q < w) {
+          xv[q] = x[j[q]];
+          xv[q + 1] = x[j[q + 1]];
+        }
+#pragma unroll
+      for (int q = 0; q < 16; q += 2)
+        if (q < w) {
+          s += a[q] * xv[q];
+          s += a[q + 1] * xv[q + 1];
+        }
+    }
+    return s;
+  }
+  for (; w >= 8; w -= 8, ci += 512, v += 512) s = bot_part<8>(ci, v, x, s);
+  if (w >= 4) {
+    s = bot_part<4>(ci, v, x, s);
+    w -= 4;
+    ci += 256;
+    v += 256;
+  }
+  if (w >= 2) s = bot_part<2>(ci, v, x, s);
+  return s;
+}
+
+// one operation: a wave per slice
+template <int NT, bool IN, typename T>
+__device__ __forceinline__ void bot_rows(const unsigned char* __restrict__ g, const BotOp& op,
+                                         T* vec) {
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint16_t* map = bot_at<true, uint16_t>(g, op.map);
+  const T* dv = bot_at<true, T>(g, op.dv);
+  const T* x = vec + op.x;
+  // a half-sweep's new values wait for every row to have read the old ones: in a
+  // register while a wave has one slice, else at op.out
+  const bool one = op.s1 - op.s0 <= NT / 64;
+  T keep = 0;
+  int kept = -1;
+  for (int sl = op.s0 + w; sl < op.s1; sl += NT / 64) {
+    // slices [0, sC) hold rows [0, rC), the others the rows from rC on
+    const bool first = sl < op.sC;
+    const int r = first ? 64 * sl + lane : op.rC + 64 * (sl - op.sC) + lane;
+    const int rs = min(r, (first ? op.rC : op.rows) - 1);  // a row of the slice
+    if (op.kind == kBotHalf || op.kind == kBotFHalf0) {
+      const T old = op.kind == kBotHalf ? vec[op.x + rs] : (T)0;
+      const T bk = vec[op.b + rs], dk = dv[rs];
+      const T s = bot_row<IN>(g, op, x, sl, lane);
+      keep = old + (bk - s) * dk;
+      kept = r == rs ? r : -1;
+      if (!one && r == rs) vec[op.out + r] = keep;
+    } else if (op.kind == kBotResid) {
+      const T bk = vec[op.b + rs];
+      const T s = bot_row<IN>(g, op, x, sl, lane);
+      if (r == rs) vec[op.out + r] = bk - s;
+    } else if (op.kind == kBotRestrict) {
+      const T rc = vec[op.b + map[rs]], dk = dv[min(rs, op.nd)];
+      const T s = bot_row<IN>(g, op, x, sl, lane);
+      const T bb = rc + s;
+      if (r == rs) {
+        vec[op.out + r] = bb;
+        vec[op.out2 + r] = r < op.nC ? bb * dk : (T)0;
+      }
+    } else {  // kBotProlong: F rows, in place
+      const T xk = vec[op.out + rs];
+      const T s = bot_row<IN>(g, op, x, sl, lane);
+      if (r == rs) vec[op.out + r] = xk + s;
+    }
+  }
+  if (op.kind == kBotProlong)  // C rows: their coarse points' values
+    for (int k = threadIdx.x; k < op.nC; k += NT) vec[op.out2 + k] += x[map[k]];
+  if (op.kind == kBotHalf || op.kind == kBotFHalf0) {
+    __syncthreads();
+    if (one) {
+      if (kept >= 0) vec[op.x + kept] = keep;
+      return;
+    }
+    for (int sl = op.s0 + w; sl < op.s1; sl += NT / 64) {
+      const bool first = sl < op.sC;
+      const int r = first ? 64 * sl + lane : op.rC + 64 * (sl - op.sC) + lane;
+      if (r < (first ? op.rC : op.rows)) vec[op.x + r] = vec[op.out + r];
+    }
+  }
+}
+
+// x = A^{-1} b of a dense last level: k_dense's sums (four quarters of the
+// columns, added in order), NT / 256 64-row chunks at a time
+template <int NT, bool IN, typename T>
+__device__ __forceinline__ void bot_dense(const unsigned char* __restrict__ g, const BotOp& op,
+                                          T* vec, double (*part)[4][64]) {
+  const double* inv = bot_at<IN, double>(g, op.vo);
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), q = w & 3, h = w >> 2;
+  const int n = op.rows, quarter = (n + 3) / 4;
+  const int j0 = min(n, q * quarter), j1 = min(n, j0 + quarter);
+  for (int c0 = 0; c0 < n; c0 += 64 * (NT / 256)) {
+    const int i = c0 + 64 * h + lane;
+    double s = 0.0;
+    if (i < n) {
+      int j = j0;
+      for (; j + 16 <= j1; j += 16) {
+        double a[16], x[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+          a[k] = inv[(j + k) * n + i];
+          x[k] = (double)vec[op.b + j + k];
+        }
+#pragma unroll
+        for (int k = 0; k < 16; ++k) s += a[k] * x[k];
+      }
+      if (j < j1) {  // the rest: loads past it repeat the last column and are not added
+        double a[16], x[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+          const int jk = min(j + k, j1 - 1);
+          a[k] = inv[jk * n + i];
+          x[k] = (double)vec[op.b + jk];
+        }
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+          if (j + k < j1) s += a[k] * x[k];
+      }
+    }
+    part[h][q][lane] = s;
+    __syncthreads();
+    if (q == 0 && i < n)
+      vec[op.out + i] =
+          (T)(((part[h][0][lane] + part[h][1][lane]) + part[h][2][lane]) + part[h][3][lane]);
+    __syncthreads();
+  }
+}
+
+template <typename T, int NT>
+__global__ void __launch_bounds__(NT) k_bottom(const BotMember* __restrict__ mem,
+                                               const unsigned char* __restrict__ buf,
+                                               const T* __restrict__ B, T* __restrict__ X) {
+  __shared__ double part[NT / 256][4][64];
+  const BotMember m = mem[blockIdx.x];
+  const unsigned char* __restrict__ g = buf + m.buf;
+  T* vec = reinterpret_cast<T*>(bot_sm + m.vec_at);
+  const int t = threadIdx.x;
+  auto place = [&](int i) { return i < m.nC ? m.cb + i : m.fb + (i - m.nC); };
+  // the right-hand side, its diagonals and the member's data, all in flight
+  constexpr int kPer = kBotRows / NT;
+  T bb[kPer], dd[kPer];
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int i = t + k * NT;
+    bb[k] = i < m.n ? B[place(i)] : (T)0;
+    dd[k] = i < m.nC ? bot_at<false, T>(g, m.dv)[i] : (T)0;
+  }
+  for (unsigned i0 = 16 * t; i0 < m.lds; i0 += 5 * 16 * NT) {
+    uint4 c[5];
+#pragma unroll
+    for (int k = 0; k < 5; ++k)
+      c[k] = *reinterpret_cast<const uint4*>(g + min(i0 + k * 16 * NT, m.lds - 16));
+#pragma unroll
+    for (int k = 0; k < 5; ++k)
+      if (i0 + k * 16 * NT < m.lds) *reinterpret_cast<uint4*>(bot_sm + i0 + k * 16 * NT) = c[k];
+  }
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int i = t + k * NT;
+    if (i < m.n) {
+      vec[i] = bb[k];
+      vec[m.n + i] = i < m.nC ? bb[k] * dd[k] : (T)0;
+    }
+  }
+  __syncthreads();
+  for (int p = 0; p < m.nops; ++p) {
+    // the operation, from LDS into scalars
+    BotOp op;
+    {
+      constexpr int kWords = sizeof(BotOp) / 4;
+      const int* src = reinterpret_cast<const int*>(bot_sm + m.ops) + p * kWords;
+      int w[kWords];
+#pragma unroll
+      for (int k = 0; k < kWords; ++k) w[k] = __builtin_amdgcn_readfirstlane(src[k]);
+      __builtin_memcpy(&op, w, sizeof(op));
+    }
+    if (op.kind == kBotDense) {
+      if (op.in)
+        bot_dense<NT, true, T>(g, op, vec, part);
+      else
+        bot_dense<NT, false, T>(g, op, vec, part);
+    } else {
+      if (op.in)
+        bot_rows<NT, true, T>(g, op, vec);
+      else
+        bot_rows<NT, false, T>(g, op, vec);
+      __syncthreads();
+    }
+  }
+  for (int i = t; i < m.n; i += NT) X[place(i)] = vec[m.n + i];
+}
+
+// Even widths of the 64-row slices of member blockIdx.x's rows at one level: of
+// A (C rows, then F rows), of W (F rows) and of W^T (the next level's rows), at
+// out[blockIdx.x][matrix][slice]; the slices of a matrix are counted by its rows.
+constexpr int kBotSlices = 2 * (kBotRows / 64) / 2 + 4;
+struct BotRows {       // a member's place in a level's extended stored order
+  int cb, fb, db, nC, nF, kind;
+};
+__global__ void __launch_bounds__(256) k_bot_widths(const BotRows* __restrict__ at,
+                                                    const BotRows* __restrict__ next, int nC_u,
+                                                    const int* __restrict__ arp,
+                                                    const int* __restrict__ wrp,
+                                                    const int* __restrict__ trp,
+                                                    int* __restrict__ out) {
+  const BotRows m = at[blockIdx.x];
+  int* o = out + (size_t)blockIdx.x * 3 * kBotSlices;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int sC = (m.nC + 63) / 64, sF = (m.nF + 63) / 64;
+  auto emit = [&](int mat, int sl, int len) {
+#pragma unroll
+    for (int f = 32; f > 0; f >>= 1) len = max(len, __shfl_xor(len, f, 64));
+    if (lane == 0) o[mat * kBotSlices + sl] = (len + 1) & ~1;
+  };
+  if (m.kind == 2) return;
+  for (int sl = wave; sl < sC + sF; sl += 4) {
+    const int r = sl < sC ? 64 * sl + lane : 64 * (sl - sC) + lane;
+    const int k = sl < sC ? m.cb + r : m.fb + r;
+    const bool in = r < (sl < sC ? m.nC : m.nF);
+    emit(0, sl, in ? arp[k + 1] - arp[k] : 0);
+  }
+  if (m.kind != 0) return;
+  for (int sl = wave; sl < sF; sl += 4) {
+    const int r = 64 * sl + lane, k = m.fb - nC_u + r;
+    emit(1, sl, r < m.nF ? wrp[k + 1] - wrp[k] : 0);
+  }
+  const BotRows x = next[blockIdx.x];
+  for (int sl = wave; sl < sC; sl += 4) {  // the next level's rows: as many as C rows here
+    const int r = 64 * sl + lane;
+    const int k = x.kind == 2 ? x.db + r : (r < x.nC ? x.cb + r : x.fb + (r - x.nC));
+    emit(2, sl, r < m.nC ? trp[k + 1] - trp[k] : 0);
+  }
+}
+
+// Packs member blockIdx.y's rows of one bottom level: local rows and columns,
+// values in T.
+struct BotPack {
+  unsigned char* buf;  // the member's part
+  BotLevel L;
+  BotRows at, next;
+  const double* inv;
+  int q;               // the member's row of the slice widths
+};
+// local row of extended stored index k
+__device__ __forceinline__ int bot_local(int k, int nC_u, int nS_u, const BotRows& m) {
+  return k < nC_u ? k - m.cb : (k < nS_u ? m.nC + k - m.fb : k - m.db);
+}
+template <typename T>
+__global__ void k_bot_pack(const BotPack* __restrict__ tab, int nC, int nS, int nCn, int nSn,
+                           const int* __restrict__ widths, const int* __restrict__ arp,
+                           const int* __restrict__ aci, const double* __restrict__ av,
+                           const int* __restrict__ wrp, const int* __restrict__ wci,
+                           const double* __restrict__ wv, const int* __restrict__ trp,
+                           const int* __restrict__ tci, const double* __restrict__ tv,
+                           const T* __restrict__ dinv, const int* __restrict__ cmap,
+                           const int* __restrict__ cpos, int* __restrict__ err) {
+  const BotPack p = tab[blockIdx.y];
+  const BotLevel L = p.L;
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  unsigned char* g = p.buf;
+  if (L.kind == 2) {
+    double* inv = reinterpret_cast<double*>(g + L.vA);
+    for (int e = i; e < L.n * L.n; e += gridDim.x * blockDim.x) inv[e] = p.inv[e];
+    return;
+  }
+  const int* wd = widths + (size_t)p.q * 3 * kBotSlices;
+  bool bad = false;
+  // one row of matrix `mat` into slice sl, lane ln: entry(e, column, value)
+  auto put = [&](int mat, int sl, int ln, int len, int pad, unsigned co, unsigned vo, auto entry) {
+    int o = 0;
+    for (int k = 0; k < sl; ++k) o += wd[mat * kBotSlices + k];
+    const int w = wd[mat * kBotSlices + sl];
+    bad = bad || len > w;
+    uint16_t* ci = reinterpret_cast<uint16_t*>(g + co) + 64 * o + ln;
+    T* v = reinterpret_cast<T*>(g + vo) + 64 * o + ln;
+    for (int e = 0; e < w; ++e) {
+      int j = pad;
+      double a = 0.0;
+      if (e < len) entry(e, j, a);
+      ci[64 * e] = (uint16_t)j;
+      v[64 * e] = (T)a;
+    }
+  };
+  auto offsets = [&](int mat, int ns, unsigned so) {  // one thread per slice offset
+    if (i > ns) return;
+    int o = 0;
+    for (int k = 0; k < i; ++k) o += wd[mat * kBotSlices + k];
+    reinterpret_cast<uint16_t*>(g + so)[i] = (uint16_t)o;
+  };
+  const int nF = L.n - L.nC, sC = (L.nC + 63) / 64, sF = (nF + 63) / 64;
+  offsets(0, sC + sF, L.sA);
+  // the slice's 64 lanes, those past its last row with rows of padding
+  if (i < 64 * (sC + sF)) {
+    const int sl = i >> 6, ln = i & 63;
+    const bool c = sl < sC;
+    const int r = c ? i : i - 64 * sC;  // row of its block
+    const bool in = r < (c ? L.nC : nF);
+    const int k = (c ? p.at.cb : p.at.fb) + (in ? r : 0), row = c ? r : L.nC + r;
+    put(0, sl, ln, in ? arp[k + 1] - arp[k] : 0, in ? row : 0, L.cA, L.vA,
+        [&](int e, int& j, double& a) {
+          j = bot_local(aci[arp[k] + e], nC, nS, p.at);
+          a = av[arp[k] + e];
+          bad = bad || j < 0 || j >= L.n;
+        });
+    if (in) reinterpret_cast<T*>(g + L.dv)[row] = dinv[k];
+  }
+  if (L.kind == 0) {
+    const int f0 = p.at.fb - nC;
+    offsets(1, sF, L.sW);
+    offsets(2, sC, L.sT);
+    if (i < 64 * sF) {
+      const bool in = i < nF;
+      const int k = f0 + (in ? i : 0);
+      put(1, i >> 6, i & 63, in ? wrp[k + 1] - wrp[k] : 0, 0, L.cW, L.vW,
+          [&](int e, int& j, double& a) {
+            j = bot_local(wci[wrp[k] + e], nCn, nSn, p.next);
+            a = wv[wrp[k] + e];
+            bad = bad || j < 0 || j >= L.nn;
+          });
+    }
+    if (i < 64 * sC) {
+      const bool in = i < L.nn;
+      const int r = in ? i : 0;
+      const BotRows& x = p.next;
+      const int k = x.kind == 2 ? x.db + r : (r < x.nC ? x.cb + r : x.fb + (r - x.nC));
+      put(2, i >> 6, i & 63, in ? trp[k + 1] - trp[k] : 0, 0, L.cT, L.vT,
+          [&](int e, int& j, double& a) {
+            const int f = tci[trp[k] + e] - f0;  // local F row, read from the residual
+            j = L.nC + f;
+            a = tv[trp[k] + e];
+            bad = bad || f < 0 || f >= nF;
+          });
+      if (in) {
+        const int cl = cpos[k] - p.at.cb;
+        bad = bad || cl < 0 || cl >= L.nC;
+        reinterpret_cast<uint16_t*>(g + L.cp)[i] = (uint16_t)cl;
+      }
+    }
+    if (i < L.nC) {
+      const int j = bot_local(cmap[p.at.cb + i], nCn, nSn, p.next);
+      bad = bad || j < 0 || j >= L.nn;
+      reinterpret_cast<uint16_t*>(g + L.cm)[i] = (uint16_t)j;
+    }
+  }
+  if (bad) atomicOr(err, 32);
+}
+
+// ---------------------------------------------------------------------------
 // persistent tail: every level from a threshold down (and back up) in one
 // launch.  Each phase does what the per-level kernel of the same name does,
 // with the same arithmetic, over a grid-stride loop; phases are separated by
@@ -1548,7 +2019,7 @@ void Union<T>::vcycle(Ctx* c, T* z) {
   std::vector<int> cc(nl, 0), cf(nl, 0);
   auto Xb = [&](int l, int which) -> T* { return which ? X1[l].get() : X0[l].get(); };
   t_prof_members = members;
-  const int lt = tail_from >= 0 ? tail_from : nl;
+  const int lt = bot_from >= 0 ? bot_from : (tail_from >= 0 ? tail_from : nl);
   for (int l = 0; l < lt; ++l) {
     t_prof_level = l;
     ULevel<T>& lv = L[l];
@@ -1611,7 +2082,21 @@ void Union<T>::vcycle(Ctx* c, T* z) {
       MGD_CHECK_LAUNCH();
     }
   }
-  if (lt < nl) {  // levels lt .. nl-1, down and up, in one launch
+  if (bot_from >= 0) {  // levels lt .. nl-1, down and up, one workgroup per member
+    t_prof_level = lt;
+    ProfScope ps(c, cls_of(lt, KC_SMOOTH_L0), bot_bytes,
+                 ksym(c, "k_bottom", {type_name<T>(), std::to_string(bot_threads)}) + level_tag());
+    auto bottom = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(bot_members), dim3(bot_threads), bot_lds, c->stream,
+                         (const BotMember*)bot_mem.get(), (const unsigned char*)bot_buf.get(),
+                         (const T*)B[lt].get(), X0[lt].get());
+    };
+    if (bot_threads == 1024)
+      bottom(k_bottom<T, 1024>);
+    else
+      bottom(k_bottom<T, 512>);
+    MGD_CHECK_LAUNCH();
+  } else if (lt < nl) {  // levels lt .. nl-1, down and up, in one launch
     t_prof_level = lt;
     ProfScope ps(c, KC_VCYCLE_COARSE, tail_bytes, ksym(c, "k_tail", {type_name<T>()}) + level_tag(),
                  tail_bytes_csr);
@@ -1679,6 +2164,15 @@ void Union<T>::vcycle(Ctx* c, T* z) {
       MGD_CHECK_LAUNCH();
     }
   }
+  if (lt == 0 && bot_from == 0) {  // the whole cycle was the bottom: its result is in X0
+    out_cc = out_cf = 0;
+    if (!z) return;
+    ULevel<T>& lv = L[0];
+    hipLaunchKernelGGL(k_out<T>, dim3(cdiv(lv.nX, 256)), dim3(256), 0, c->stream, lv.nX,
+                       gather_cfd<T>(X0[0].get(), X0[0].get(), X0[0].get(), lv.nC, lv.nS),
+                       (const int*)lv.perm.get(), z);
+    MGD_CHECK_LAUNCH();
+  }
 }
 
 // Levels from which the persistent tail takes over: the first level from
@@ -1690,10 +2184,6 @@ void Union<T>::vcycle(Ctx* c, T* z) {
 // resident at once.
 constexpr int kTailRows = 0;
 constexpr int kTailBlocks = 256;
-static long long env_ll(const char* name, long long dflt) {
-  const char* e = std::getenv(name);
-  return e && *e ? std::atoll(e) : dflt;
-}
 
 // The phase table of vcycle() for levels >= tail_from, recorded with the same
 // buffer choices (the two iterate buffers of every level start at X0 in each
@@ -1703,7 +2193,7 @@ void Union<T>::build_tail(Ctx* c) {
   tail_from = -1;
   const int nl = (int)L.size();
   const long long rows = env_ll("MGD_TAIL_ROWS", kTailRows);
-  if (gs || n_pre < 1 || rows <= 0 || nl < 2) return;
+  if (gs || n_pre < 1 || rows <= 0 || nl < 2 || bot_from >= 0) return;
   int lt = nl;
   while (lt > 1 && L[lt - 1].nX <= rows) --lt;
   if (lt >= nl) return;
@@ -2318,6 +2808,381 @@ static void layout_transfer(Ctx* c, const Csr<double>& M, LMat<T>& out, const DB
     to_layout<T>(c, M, kFmtCSR, d, false, out, soff, stored);
 }
 
+// The operations of a member's cycle over its levels lev[0 .. n), the same as
+// Union::vcycle's launches; tmp: values shared by the levels (the residual, and
+// the new values of a half-sweep).
+static void bot_program(const BotLevel* lev, int n, int n_pre, int n_post, int tmp,
+                        std::vector<BotOp>& ops) {
+  auto on_A = [&](int l, int kind) {
+    const BotLevel& L = lev[l];
+    BotOp o{};
+    o.kind = kind;
+    o.in = L.in_lds;
+    o.sC = cdiv(L.nC, 64);
+    o.rC = L.nC;
+    o.rows = L.n;
+    o.s1 = o.sC + cdiv(L.n - L.nC, 64);
+    o.so = L.sA;
+    o.co = L.cA;
+    o.vo = L.vA;
+    o.x = L.vec + L.n;
+    o.b = L.vec;
+    o.out = tmp;
+    o.dv = o.map = L.dv;
+    o.nd = L.n - 1;
+    return o;
+  };
+  auto half = [&](int l, bool F, int kind) {
+    BotOp o = on_A(l, kind);
+    if (F)
+      o.s0 = o.sC;
+    else
+      o.s1 = o.sC;
+    if (o.s1 > o.s0) ops.push_back(o);
+  };
+  for (int l = 0; l < n; ++l) {
+    const BotLevel& L = lev[l];
+    if (L.kind == 2) {
+      BotOp o{};
+      o.kind = kBotDense;
+      o.in = L.in_lds;
+      o.rows = L.n;
+      o.vo = L.vA;
+      o.b = L.vec;
+      o.out = L.vec + L.n;
+      ops.push_back(o);
+      break;
+    }
+    half(l, true, kBotFHalf0);
+    for (int s = 1; s < n_pre; ++s) {
+      half(l, false, kBotHalf);
+      half(l, true, kBotHalf);
+    }
+    if (L.kind != 0) continue;
+    ops.push_back(on_A(l, kBotResid));
+    const BotLevel& N = lev[l + 1];
+    BotOp r{};
+    r.kind = kBotRestrict;
+    r.in = L.in_lds;
+    r.sC = r.s1 = cdiv(L.nn, 64);
+    r.rC = r.rows = L.nn;
+    r.so = L.sT;
+    r.co = L.cT;
+    r.vo = L.vT;
+    r.x = r.b = tmp;
+    r.map = L.cp;
+    r.out = N.vec;
+    r.out2 = N.vec + N.n;
+    r.nC = N.nC;
+    r.dv = N.nC > 0 ? N.dv : L.dv;
+    r.nd = N.nC > 0 ? N.n - 1 : 0;
+    ops.push_back(r);
+  }
+  for (int l = n - 1; l >= 0; --l) {
+    const BotLevel& L = lev[l];
+    if (L.kind == 2) continue;
+    if (L.kind == 0) {
+      const BotLevel& N = lev[l + 1];
+      BotOp o{};
+      o.kind = kBotProlong;
+      o.in = L.in_lds;
+      o.sC = o.s1 = cdiv(L.n - L.nC, 64);
+      o.rC = o.rows = L.n - L.nC;
+      o.so = L.sW;
+      o.co = L.cW;
+      o.vo = L.vW;
+      o.x = N.vec + N.n;
+      o.b = L.vec;
+      o.dv = L.dv;
+      o.map = L.cm;
+      o.nC = L.nC;
+      o.out = L.vec + L.n + L.nC;
+      o.out2 = L.vec + L.n;
+      ops.push_back(o);
+    }
+    for (int s = 0; s < n_post; ++s) {
+      half(l, true, kBotHalf);
+      half(l, false, kBotHalf);
+    }
+  }
+}
+
+// The bottom of the cycle (BotLevel, k_bottom): the levels from which on every
+// member has at most kBotRows rows, if any of them coarsens (a lone dense level
+// stays with k_dense).  MGD_BOTTOM=0 (or MGD_TAIL_ROWS, whose launch takes these
+// levels instead) keeps per-level launches, with one lane per row there: the
+// same bits.  With members of at most 0 (no bottom), 300, 600, 1200 and 2048 rows
+// an apply took, in us: 2D 101^2 G = 5 Schur1 777, 728, 605, 509, 507; 2D 64^2
+// Schur2 303, 197, 203, 170, 169; 3D 20^3 G = 3 Schur2 447, 486, 335, 329, 347
+// (its 300-row bottom has one short level); batched 2D 256^2 G = 20 PCTL 644, 589,
+// 588, 561, 561.  Above 2048 rows a matrix outgrows LDS and 16 rows a lane would
+// be in sequence.  The limit on entries (2048 rows: 8192, 16384, 32768 and 65536
+// of them) gave 580, 513, 509, 507 on the first of these, and 20.6, 19.8, 19.3,
+// 19.2 ms on a solve at 2D 256^2, G = 20.
+// While the finest level leaves compute units free beside a concurrent block
+// matvec (one workgroup per 512 rows), a member takes a whole unit; above that,
+// 512 threads and 110 KB, which fit beside a workgroup of the matvec.
+constexpr long long kBotWholeRows = 512 * 192;
+constexpr unsigned kBotLdsWhole = 150 * 1024, kBotLdsShared = 110 * 1024;
+constexpr int kBotEntries = 1 << 16;  // stored entries of a matrix and member
+constexpr int kBotDenseRows = 256;  // larger dense levels are spread over workgroups
+
+// places of the members in a level's extended stored order
+template <typename T>
+static std::vector<BotRows> bot_rows_of(const BuildLevel<T>& b, const std::vector<UMember>& tab) {
+  std::vector<BotRows> v;
+  int cb = 0, fb = b.nC;
+  for (int q = 0; q < b.R.nm; ++q) {
+    const UMember& m = tab[b.tab + q];
+    v.push_back({cb, fb, b.nS + m.dense_before, m.nc, f_rows(m), m.kind});
+    cb += m.nc;
+    fb += f_rows(m);
+  }
+  return v;
+}
+
+template <typename T>
+static std::vector<int> bot_widths(Ctx* c, const std::vector<BuildLevel<T>>& bl,
+                                   const std::vector<UMember>& tab, int cand, DBuf<int>& out) {
+  const int nl = (int)bl.size(), nm = nl ? bl[0].R.nm : 0;
+  if (cand >= nl) return {};
+  const size_t per = (size_t)nm * 3 * kBotSlices;
+  out.alloc(c, per * (nl - cand));
+  fill<int>(c, out.get(), 0, per * (nl - cand));
+  std::vector<BotRows> at;
+  for (int l = cand; l <= nl; ++l) {
+    std::vector<BotRows> r(nm);
+    if (l < nl) r = bot_rows_of(bl[l], tab);
+    at.insert(at.end(), r.begin(), r.end());
+  }
+  DBuf<BotRows> dev(c, at.size());
+  copy_h2d(c, dev.get(), at.data(), at.size());
+  for (int l = cand; l < nl; ++l) {
+    if (bl[l].nS == 0) continue;
+    const BotRows* d = dev.get() + (size_t)(l - cand) * nm;
+    hipLaunchKernelGGL(k_bot_widths, dim3(nm), dim3(256), 0, c->stream, d, d + nm, bl[l].nC,
+                       (const int*)bl[l].A.rp.get(), (const int*)bl[l].W.rp.get(),
+                       (const int*)bl[l].Wt.rp.get(), out.get() + per * (l - cand));
+    MGD_CHECK_LAUNCH();
+  }
+  return read_vec(c, out.get(), per * (nl - cand));
+}
+
+template <typename T>
+static void build_bottom(Ctx* c, std::vector<BuildLevel<T>>& bl, const std::vector<UMember>& tab,
+                         int cand, const int* widths_dev, const std::vector<int>& widths,
+                         Union<T>& U) {
+  const int nl = (int)bl.size(), nm = nl ? bl[0].R.nm : 0;
+  if (U.gs || U.n_pre < 1 || cand >= nl) return;
+  int rows0 = 0;
+  for (int q = 0; q < nm; ++q) rows0 = std::max(rows0, tab[bl[0].tab + q].n);
+  const bool whole = rows0 <= kBotWholeRows;
+  const unsigned budget = whole ? kBotLdsWhole : kBotLdsShared;
+  auto wid = [&](int l, int q, int mat) {
+    return widths.data() + (((size_t)(l - cand) * nm + q) * 3 + mat) * kBotSlices;
+  };
+  auto sum = [](const int* w, int n) {
+    int s = 0;
+    for (int k = 0; k < n; ++k) s += w[k];
+    return s;
+  };
+  // slice columns (64 stored entries each) of the member's A, W and W^T
+  auto stored = [&](int l, int q, int mat) {
+    const UMember& m = tab[bl[l].tab + q];
+    const int sC = cdiv(m.nc, 64), sF = cdiv(f_rows(m), 64);
+    if (m.n == 0 || m.kind == 2) return 0;
+    if (mat > 0 && m.kind != 0) return 0;
+    return sum(wid(l, q, mat), mat == 0 ? sC + sF : (mat == 1 ? sF : sC));
+  };
+  int lt = nl;
+  while (lt > cand) {
+    bool ok = true;
+    for (int q = 0; q < nm; ++q) {
+      const UMember& m = tab[bl[lt - 1].tab + q];
+      for (int mat = 0; mat < 3; ++mat) ok = ok && 64 * stored(lt - 1, q, mat) <= kBotEntries;
+      ok = ok && (m.kind != 2 || m.n <= kBotDenseRows);
+    }
+    if (!ok) break;
+    --lt;
+  }
+  // vectors and index arrays of every member in LDS
+  for (; lt < nl; ++lt) {
+    bool fits = true;
+    for (int q = 0; q < nm; ++q) {
+      size_t v = 0, top = 0, small = 0;
+      for (int l = lt; l < nl; ++l) {
+        const size_t n = tab[bl[l].tab + q].n;
+        v += 2 * n;
+        top = std::max(top, n);
+        small += n * (sizeof(T) + 4) + 6 * kBotSlices + 128;
+        small += (2 * (U.n_pre + U.n_post) + 3) * sizeof(BotOp);
+      }
+      fits = fits && (v + top) * sizeof(T) + small <= budget;
+    }
+    if (fits) break;
+  }
+  bool coarsens = false;
+  for (int l = lt; l < nl; ++l) coarsens = coarsens || bl[l].n_coarse > 0;
+  if (!coarsens) return;
+  for (int l = lt; l < nl; ++l) bl[l].bottom = bl[l].nS > 0;
+  const char* off = std::getenv("MGD_BOTTOM");
+  if ((off && off[0] == '0') || env_ll("MGD_TAIL_ROWS", 0) > 0) return;
+  std::vector<BotMember> mem;
+  std::vector<std::vector<BotOp>> progs;
+  std::vector<BotPack> pack;            // level by level
+  std::vector<size_t> first(nl + 1, 0);
+  std::vector<std::vector<BotLevel>> levs;
+  std::vector<int> who;
+  size_t total = 0;
+  for (int q = 0; q < nm; ++q) {
+    if (tab[bl[lt].tab + q].n == 0) continue;
+    BotMember M{};
+    M.buf = total;
+    int last = lt;
+    while (last + 1 < nl && tab[bl[last + 1].tab + q].n > 0 && tab[bl[last].tab + q].kind == 0) ++last;
+    std::vector<BotLevel> lev(last - lt + 1);
+    int vec = 0, top = 0;
+    for (int l = lt; l <= last; ++l) {
+      const UMember& m = tab[bl[l].tab + q];
+      BotLevel& L = lev[l - lt];
+      L.n = m.n;
+      L.kind = m.kind;
+      L.nC = L.nn = m.kind == 0 ? m.nc : 0;
+      L.vec = vec;
+      vec += 2 * m.n;
+      top = std::max(top, m.n);
+    }
+    const int tmp = vec;
+    const unsigned vbytes = (unsigned)(((size_t)(vec + top) * sizeof(T) + 15) / 16 * 16);
+    unsigned at = 0;
+    auto take = [&](size_t bytes) {
+      const unsigned o = at;
+      at += (unsigned)((bytes + 7) / 8 * 8);
+      return o;
+    };
+    // in LDS in any case: the index arrays and diagonals
+    for (int l = last; l >= lt; --l) {
+      BotLevel& L = lev[l - lt];
+      if (L.kind == 2) continue;
+      const int sC = cdiv(L.nC, 64), sF = cdiv(L.n - L.nC, 64);
+      L.dv = take(L.n * sizeof(T));
+      L.sA = take(2 * (size_t)(sC + sF + 1));
+      L.sW = take(2 * (size_t)(sF + 1));
+      L.sT = take(2 * (size_t)(sC + 1));
+      L.cm = take(2 * (size_t)L.nC);
+      L.cp = take(2 * (size_t)L.nn);
+    }
+    at = (at + 15) / 16 * 16;
+    M.ops = at;
+    {
+      std::vector<BotOp> count;  // as many as the program will have
+      bot_program(lev.data(), (int)lev.size(), U.n_pre, U.n_post, tmp, count);
+      M.nops = (int)count.size();
+    }
+    at += (unsigned)((M.nops * sizeof(BotOp) + 15) / 16 * 16);
+    M.lds = at;
+    // then, while there is room, the matrices (read four times a cycle), the
+    // coarsest first, and the dense inverse (read once)
+    bool room = true;
+    auto place = [&](BotLevel& L) {
+      at = (at + 15) / 16 * 16;
+      room = room && at + vbytes <= budget;
+      L.in_lds = room ? 1 : 0;
+      if (room) M.lds = at;
+    };
+    for (int l = last; l >= lt; --l) {
+      BotLevel& L = lev[l - lt];
+      if (L.kind == 2) continue;
+      const size_t nA = 64 * (size_t)stored(l, q, 0), nW = 64 * (size_t)stored(l, q, 1),
+                   nT = 64 * (size_t)stored(l, q, 2);
+      L.vA = take(nA * sizeof(T));
+      L.vW = take(nW * sizeof(T));
+      L.vT = take(nT * sizeof(T));
+      L.cA = take(2 * nA);
+      L.cW = take(2 * nW);
+      L.cT = take(2 * nT);
+      place(L);
+    }
+    if (lev.back().kind == 2) {
+      lev.back().vA = take(sizeof(double) * (size_t)lev.back().n * lev.back().n);
+      place(lev.back());
+    }
+    M.vec_at = M.lds;
+    U.bot_lds = std::max(U.bot_lds, M.lds + vbytes);
+    U.bot_bytes += at + 2.0 * lev[0].n * sizeof(T);
+    total += (at + 255) / 256 * 256;
+    M.n = lev[0].n;
+    M.nC = lev[0].nC;
+    M.dv = lev[0].dv;
+    progs.emplace_back();
+    bot_program(lev.data(), (int)lev.size(), U.n_pre, U.n_post, tmp, progs.back());
+    mem.push_back(M);
+    levs.push_back(std::move(lev));
+    who.push_back(q);
+  }
+  U.bot_buf.alloc(c, std::max<size_t>(total, 16));
+  for (int l = lt; l < nl; ++l) {
+    first[l] = pack.size();
+    const std::vector<BotRows> at = bot_rows_of(bl[l], tab);
+    std::vector<BotRows> next(nm);
+    if (l + 1 < nl) next = bot_rows_of(bl[l + 1], tab);
+    for (size_t k = 0; k < mem.size(); ++k) {
+      const int q = who[k];
+      if (l - lt >= (int)levs[k].size()) continue;
+      if (l == lt) {
+        mem[k].cb = at[q].cb;
+        mem[k].fb = at[q].kind == 2 ? at[q].db : at[q].fb;
+      }
+      BotPack P{};
+      P.buf = U.bot_buf.get() + mem[k].buf;
+      P.L = levs[k][l - lt];
+      P.at = at[q];
+      P.next = next[q];
+      P.q = (l - cand) * nm + q;
+      if (P.L.kind == 2) {
+        for (const DenseDev& d : U.L[l].dense)
+          if (d.off == at[q].db) P.inv = d.inv;
+        MGD_REQUIRE(P.inv, "internal: dense member without an inverse");
+      }
+      pack.push_back(P);
+    }
+  }
+  first[nl] = pack.size();
+  U.bot_mem.alloc(c, mem.size());
+  copy_h2d(c, U.bot_mem.get(), mem.data(), mem.size());
+  for (size_t k = 0; k < mem.size(); ++k)
+    MGD_HIP(hipMemcpyAsync(U.bot_buf.get() + mem[k].buf + mem[k].ops, progs[k].data(),
+                           progs[k].size() * sizeof(BotOp), hipMemcpyHostToDevice, c->stream));
+  DBuf<BotPack> dp(c, pack.size());
+  copy_h2d(c, dp.get(), pack.data(), pack.size());
+  for (int l = lt; l < nl; ++l) {
+    const unsigned cnt = (unsigned)(first[l + 1] - first[l]);
+    if (!cnt) continue;
+    const BuildLevel<T>& b = bl[l];
+    const BuildLevel<T>* nb = l + 1 < nl ? &bl[l + 1] : nullptr;
+    int rows = 1;
+    for (size_t k = first[l]; k < first[l + 1]; ++k)
+      rows = std::max(rows, 64 * (cdiv(pack[k].L.nC, 64) + cdiv(pack[k].L.n - pack[k].L.nC, 64) + 1));
+    hipLaunchKernelGGL(k_bot_pack<T>, dim3(cdiv(rows, 256), cnt), dim3(256), 0, c->stream,
+                       (const BotPack*)(dp.get() + first[l]), b.nC, b.nS, nb ? nb->nC : 0,
+                       nb ? nb->nS : 0, widths_dev, (const int*)b.A.rp.get(),
+                       (const int*)b.A.ci.get(), (const double*)b.A.v.get(),
+                       (const int*)b.W.rp.get(), (const int*)b.W.ci.get(),
+                       (const double*)b.W.v.get(), (const int*)b.Wt.rp.get(),
+                       (const int*)b.Wt.ci.get(), (const double*)b.Wt.v.get(),
+                       (const T*)U.L[l].dinv.get(), (const int*)U.L[l].cmap.get(),
+                       (const int*)U.L[l].cpos.get(), c->err_flag());
+    MGD_CHECK_LAUNCH();
+  }
+  c->check_device_errors("packed bottom levels");
+  const void* kernel = whole ? reinterpret_cast<const void*>(&k_bottom<T, 1024>)
+                             : reinterpret_cast<const void*>(&k_bottom<T, 512>);
+  MGD_HIP(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)budget));
+  U.bot_threads = whole ? 1024 : 512;
+  U.bot_members = (int)mem.size();
+  U.bot_from = lt;
+}
+
 // stats: per level the longest row and the SELL entries of A, W and W^T
 template <typename T>
 static void layout_levels(Ctx* c, std::vector<BuildLevel<T>>& bl, const int* stats, Union<T>& U,
@@ -2328,6 +3193,23 @@ static void layout_levels(Ctx* c, std::vector<BuildLevel<T>>& bl, const int* sta
     BuildLevel<T>& b = bl[l];
     ULevel<T>& lv = U.L[l];
     const int* s6 = stats + 6 * l;
+    const bool packed = U.bot_from >= 0 && l >= U.bot_from;  // in bot_buf instead
+    if (b.bottom && (!packed || l == 0)) {
+      // one lane per row, so that per-level launches add a row's entries in the
+      // bottom's order (and, at level 0, the residual between cycles, which is
+      // always a launch of its own)
+      to_layout<T>(c, b.A, kFmtCSR, 1, true, lv.A, b.asoff, 0);
+      if (lv.nX_next > 0 && !packed) {
+        to_layout<T>(c, b.W, kFmtCSR, 1, false, lv.W, b.wsoff, 0);
+        to_layout<T>(c, b.Wt, kFmtCSR, 1, false, lv.Wt, b.tsoff, 0);
+      }
+      lv.perm = std::move(b.perm);
+      continue;
+    }
+    if (packed) {
+      lv.perm = std::move(b.perm);
+      continue;
+    }
     if (lv.nX_next > 0) {
       // W gathers from three regions of the next level: 32-bit columns;
       // W^T's columns are F indices, one region
@@ -2345,6 +3227,7 @@ static void layout_levels(Ctx* c, std::vector<BuildLevel<T>>& bl, const int* sta
   U.n0 = nl ? U.L[0].nX : 0;
   for (int l = 0; l < nl; ++l) {
     auto& lv = U.L[l];
+    if (U.bot_from >= 0 && l > U.bot_from) break;  // in LDS
     U.B[l].alloc(c, (size_t)std::max(lv.nX, 1));
     U.X0[l].alloc(c, (size_t)std::max(lv.nX, 1));
     U.X1[l].alloc(c, (size_t)std::max(lv.nX, 1));

@@ -118,6 +118,48 @@ struct TailOp {
   int ndense, dchunks;
 };
 
+// The bottom of a union's cycle: from level bot_from down (and back up), each
+// member's levels run in one workgroup of their own (members do not couple, so
+// nothing waits for other workgroups), its vectors and as many of its matrices
+// as fit in LDS.  Byte offsets are into the member's part of Union::bot_buf, the
+// coarsest level first; rows are local, C rows then F rows.
+struct BotLevel {
+  int n, nC, nn;            // rows, C rows, rows at the next level
+  int kind;                 // 0 coarsens, 1 relaxed last level, 2 dense last level
+  unsigned vA, vW, vT;      // values in 64-row slices: level matrix (dense: the inverse, FP64),
+                            // W, W^T
+  unsigned cA, cW, cT;      // 16-bit local columns
+  unsigned sA, sW, sT;      // 16-bit slice offsets, in columns of a slice
+  unsigned dv;              // 1 / l1 diagonal
+  unsigned cm, cp;          // C row -> next level's row, and back
+  int vec;                  // first of its vector values: b, then the iterate
+  int in_lds;
+};
+// One operation of a member's cycle: slices [s0, s1) of one matrix times the
+// vector x, and what becomes of the sums.  Vector positions are counted in values
+// from the member's first.
+enum : int { kBotFHalf0 = 0, kBotHalf, kBotResid, kBotRestrict, kBotProlong, kBotDense };
+struct BotOp {
+  int kind, in;             // in: entries in LDS
+  int s0, s1;
+  int sC, rC, rows;         // slices [0, sC) hold rows [0, rC), the rest rows [rC, rows)
+  unsigned so, co, vo;      // slice offsets, columns, values (dense: the inverse)
+  int x, b, out, out2;      // vector, right-hand side, result; restrict: the next level's
+                            // iterate, prolong: the C rows
+  unsigned dv, map;         // 1 / diagonal; restrict, prolong: the C rows' map
+  int nd, nC;               // last row of dv; restrict: the next level's, prolong: this level's C rows
+};
+struct BotMember {
+  unsigned long long buf;   // its part of bot_buf
+  unsigned lds;             // leading bytes of it copied into LDS (a multiple of 16)
+  unsigned vec_at;          // LDS byte offset of its vectors
+  unsigned ops;             // LDS byte offset of its operations
+  int nops;
+  int n, nC;                // rows and C rows at level bot_from
+  int cb, fb;               // its first C row there, and its first F (or dense) row
+  unsigned dv;              // 1 / diagonal of that level
+};
+
 // A union's level-0 result left in stored order: member m's row i sits at
 // stored index k = iperm[m N + i] of the C region (k < nC), the F region
 // (k < nS) or the dense rows (each region in a buffer of its own, indexed by k)
@@ -148,6 +190,14 @@ struct Union {
   DBuf<TailOp<T>> tail_ops;
   DBuf<unsigned> tail_sync;  // barrier counters (reset by the last workgroup out)
   void build_tail(Ctx* c);
+
+  // bottom: levels >= bot_from run as one launch of a workgroup per member
+  // (bot_from < 0: no bottom)
+  int bot_from = -1, bot_members = 0, bot_threads = 512;
+  unsigned bot_lds = 0;          // LDS of the largest member
+  double bot_bytes = 0;
+  DBuf<unsigned char> bot_buf;
+  DBuf<BotMember> bot_mem;
 
   // z = k V-cycles on b (zero initial guess); b, z natural level-0 vectors.
   void apply(Ctx* c, const T* b, T* z, int cycles);

@@ -1302,6 +1302,48 @@ def test_persistent_tail_matches_level_launches(ctx, monkeypatch, precision, blo
     assert ai == bi and np.array_equal(ax, bx)
 
 
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("n,params", [
+    (9, {}),                                       # the whole cycle is the bottom
+    (12, {"n_pre": 2, "n_post": 3}),
+    (33, {"coarse_max": 7}),                       # several levels in LDS
+    (33, {"coarse_max": 300}),                     # a dense level of several 64-row chunks
+    (60, {"dense_max": 20, "max_levels": 4, "n_post": 0}),  # relaxed last levels
+    (96, {}),                                      # levels above the bottom
+])
+def test_bottom_levels_equal_level_launches(ctx, monkeypatch, n, params, precision):
+    """The bottom levels in one workgroup per member against one launch per level
+    and phase (MGD_BOTTOM=0): the same bits, for one hierarchy with one and three
+    cycles and for the members of a preconditioner, which end at different levels."""
+    api = gpu_modules()
+    inp = si.generate(4, 2, n, 23)
+    inp.kappa[1] *= 1e-9      # coarsening stalls at the finest level
+    inp.kappa[2] = 30.0
+    co, gsys = gpu_system(ctx, inp)
+    arrs = gsys.block_arrays(0)
+    b = np.random.default_rng(8).uniform(size=6 * n * n)
+    out = []
+    for bottom in ("1", "0"):
+        monkeypatch.setenv("MGD_BOTTOM", bottom)
+        g = api.AMG(ctx, *arrs, seed=3, precision=precision, **params)
+        ctx.reset_kernel_stats()
+        ctx.set_profiling(True)
+        v1 = to_host(g.apply(to_dev(ctx, b[:n * n])))
+        ctx.set_profiling(False)
+        ran = any(k.startswith("k_bottom") for k in ctx.kernel_symbol_stats())
+        assert ran == (bottom == "1" and g.info()["levels"] > 1)
+        v3 = to_host(g.apply(to_dev(ctx, b[:n * n]), cycles=3))
+        kw = {"amg_" + k: v for k, v in params.items()}
+        zs = []
+        for kind in ("bdiag", "schur2"):
+            M = api.BlockPreconditioner(ctx, gsys, kind, amg_seed=3, batched=1,
+                                        amg_precision=precision, **kw)
+            zs.append(to_host(M.apply(to_dev(ctx, b))))
+        out.append([v1, v3] + zs)
+    for x, y in zip(*out):
+        assert np.isfinite(x).all() and np.array_equal(x, y)
+
+
 # ---------------------------------------------------------------------------
 # level-layout autotuning
 # ---------------------------------------------------------------------------
