@@ -2789,12 +2789,19 @@ static int small_level_tpr(long long rows, double avg) {
   while (t < 64 && rows * t < kFillLanes && t < avg) t *= 2;
   return t;
 }
+// Padding up to which a large matrix is stored as SELL without timing it.  Its
+// 2-byte columns and unit-stride loads pay for padding that CSR does not read:
+// with 1.3, 1.4, 1.5, 1.6 and 2.0 a solve at 3D 64^3, G = 20 (lower levels pad
+// by 1.34 and 1.46) took 52.0, 48.8, 48.2, 48.2 and 48.2 ms with FP32
+// hierarchies and 66.9, 62.2, 61.9, 61.9, 61.8 ms with FP64, at 3D 80^3, G = 2
+// 32.6, 31.8, 31.8, 31.8, 31.8 ms; 2D 256^2 and 512^2 were the same throughout.
+constexpr double kSellPad = 1.5;
 // interpolation / restriction layout: SELL for large matrices with little
 // padding (sell_entries: the SELL layout's stored entries), otherwise CSR with
 // enough lanes per row; the result is kTuneSell (1000) or the lanes per row
 static int transfer_default(const Csr<double>& M, long long sell_entries) {
   const double avg = M.n_rows ? (double)M.nnz / M.n_rows : 1.0;
-  if (M.nnz > 0 && M.n_rows >= sell_min_rows() && sell_entries <= (long long)(1.5 * M.nnz))
+  if (M.nnz > 0 && M.n_rows >= sell_min_rows() && sell_entries <= (long long)(kSellPad * M.nnz))
     return 1000;
   return std::max(small_level_tpr(M.n_rows, avg), default_tpr(avg));
 }
@@ -3240,7 +3247,7 @@ static void layout_levels(Ctx* c, std::vector<BuildLevel<T>>& bl, const int* sta
 // row) key as code + (threads per workgroup / 64) * kTuneBsUnit, code 1000 =
 // SELL, t = CSR with t lanes per row (a value below kTuneBsUnit keeps 256
 // threads); without a cached choice and with autotuning off, SELL when
-// padding stays within 30%, else CSR with a lane count from the mean row
+// padding stays within kSellPad, else CSR with a lane count from the mean row
 // length, on 256-thread workgroups.  Autotuning times the residual kernel for
 // every layout with 64, 128 and 256 threads per workgroup (rows per workgroup
 // = threads / lanes per row; 64-row slices for SELL): the best of three runs
@@ -3334,8 +3341,8 @@ static void tune_layout(Ctx* c, ULevel<T>& lv, const BuildLevel<T>& b, const int
     return;
   }
   // enough lanes to occupy the device on small levels (a lane per row serialises
-  // long rows), SELL when the level is large and its padding small
-  const int dflt = (lv.nS >= sell_min_rows() && st <= (long long)(1.3 * A.nnz))
+  // long rows), SELL when the level is large and its padding within kSellPad
+  const int dflt = (lv.nS >= sell_min_rows() && st <= (long long)(kSellPad * A.nnz))
                        ? kTuneSell
                        : std::max(small_level_tpr(lv.nS, avg), default_tpr(avg));
   if (!autotune || lv.nS < tune_min_rows()) {
