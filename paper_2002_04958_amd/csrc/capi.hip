@@ -62,43 +62,117 @@ const char* kernel_class_name(int c) {
   return (c >= 0 && c < KC_COUNT) ? names[c] : "?";
 }
 
-void* Ctx::dmalloc(size_t bytes) {
+void* Ctx::raw_alloc(size_t bytes) {
+  if (has_alloc) return alloc.alloc(bytes, (void*)stream, alloc.user);
   void* p = nullptr;
+  if (hipMalloc(&p, bytes) == hipSuccess) return p;
+  (void)hipGetLastError();
+  return nullptr;
+}
+void Ctx::raw_free(void* p) {
+  if (has_alloc)
+    alloc.free(p, (void*)stream, alloc.user);
+  else
+    (void)hipFree(p);
+}
+void* Ctx::dmalloc(size_t bytes) {
   if (no_alloc)
     fail(MGD_EINVAL, "a device allocation of " + std::to_string(bytes) +
                          " bytes was requested inside a no-allocation call");
-  if (has_alloc) {
-    p = alloc.alloc(bytes, (void*)stream, alloc.user);
-    if (!p) fail(MGD_ENOMEM, "allocator callback returned NULL for " + std::to_string(bytes) + " bytes");
-    return p;
-  }
-  hipError_t e = hipMalloc(&p, bytes);
-  if (e != hipSuccess) {
-    (void)hipGetLastError();
-    fail(MGD_ENOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
-  }
+  if (void* p = defer ? pool_take(bytes) : nullptr) return p;
+  void* p = raw_alloc(bytes);
+  if (!p)
+    fail(MGD_ENOMEM, (has_alloc ? "allocator callback returned NULL for " : "hipMalloc of ") +
+                         std::to_string(bytes) + (has_alloc ? " bytes" : " bytes failed"));
   return p;
 }
 void Ctx::free_dead() {
   std::vector<void*> d;
   d.swap(dead);
-  for (void* p : d) {
-    if (has_alloc)
-      alloc.free(p, (void*)stream, alloc.user);
-    else
-      (void)hipFree(p);
-  }
+  for (void* p : d) release(p);
 }
 void Ctx::dfree(void* p) {
   if (!p) return;
-  if (defer) {
+  if (defer)
     dead.push_back(p);
+  else
+    release(p);
+}
+void* Ctx::pool_take(size_t bytes) {
+  constexpr size_t kPoolChunk = size_t(4) << 20, kPoolMost = size_t(512) << 10;
+  if (bytes > kPoolMost) return nullptr;
+  bytes = (bytes + 255) / 256 * 256;
+  std::unique_lock<std::mutex> lock(pool.mu);
+  auto take = [&](char* base, Pool::Chunk& ch) -> void* {
+    for (auto g = ch.gaps.begin(); g != ch.gaps.end(); ++g) {
+      if (g->second < bytes) continue;
+      char* p = base + g->first;
+      if (g->second > bytes) ch.gaps.emplace(g->first + bytes, g->second - bytes);
+      ch.gaps.erase(g);
+      pool.size[p] = bytes;
+      ++ch.live;
+      return p;
+    }
+    return nullptr;
+  };
+  for (auto& [at, ch] : pool.chunks)
+    if (void* p = take(at, ch)) return p;
+  lock.unlock();  // a callback may wait for the interpreter
+  char* base = static_cast<char*>(raw_alloc(kPoolChunk));
+  if (!base) return nullptr;
+  lock.lock();
+  Pool::Chunk& ch = pool.chunks[base];
+  ch.gaps.emplace(0, kPoolChunk);
+  return take(base, ch);
+}
+void Ctx::release(void* q) {
+  char* p = static_cast<char*>(q);
+  std::unique_lock<std::mutex> lock(pool.mu);
+  auto s = pool.size.find(p);
+  if (s == pool.size.end()) {
+    lock.unlock();
+    raw_free(p);
     return;
   }
-  if (has_alloc)
-    alloc.free(p, (void*)stream, alloc.user);
-  else
-    (void)hipFree(p);
+  auto it = std::prev(pool.chunks.upper_bound(p));
+  Pool::Chunk& ch = it->second;
+  size_t at = (size_t)(p - it->first), n = s->second;
+  pool.size.erase(s);
+  auto next = ch.gaps.lower_bound(at);  // joined with the gaps on either side
+  if (next != ch.gaps.end() && next->first == at + n) {
+    n += next->second;
+    next = ch.gaps.erase(next);
+  }
+  if (next != ch.gaps.begin()) {
+    auto before = std::prev(next);
+    if (before->first + before->second == at) {
+      at = before->first;
+      n += before->second;
+      ch.gaps.erase(before);
+    }
+  }
+  ch.gaps.emplace(at, n);
+  if (--ch.live == 0 && !defer) {
+    char* base = it->first;
+    pool.chunks.erase(it);
+    lock.unlock();
+    raw_free(base);
+  }
+}
+void Ctx::pool_trim() {
+  std::vector<void*> empty;
+  {
+    std::lock_guard<std::mutex> lock(pool.mu);
+    for (auto it = pool.chunks.begin(); it != pool.chunks.end();) {
+      if (it->second.live == 0) {
+        empty.push_back(it->first);
+        it = pool.chunks.erase(it);
+      } else {
+        ++it;
+      }
+    }
+  }
+  for (void* p : empty) raw_free(p);
 }
 void* Ctx::host_stage(size_t bytes) {
   if (no_alloc && bytes > pinned_bytes) {

@@ -6,9 +6,12 @@
 #include <cstdint>
 #include <cstring>
 #include <initializer_list>
+#include <map>
 #include <memory>
+#include <mutex>
 #include <stdexcept>
 #include <string>
+#include <unordered_map>
 #include <utility>
 #include <vector>
 
@@ -112,6 +115,23 @@ struct Ctx {
   // frees held back until the stream has been waited for (DeferFrees)
   int defer = 0;
   std::vector<void*> dead;
+  // Small buffers of a DeferFrees scope come out of chunks of kPoolChunk bytes
+  // and go back to their chunk; a chunk without buffers goes back to the
+  // allocator (at the end of the scope, or with its last buffer after it).  A
+  // buffer is given out again only for work on the same stream, as by a caching
+  // allocator.  A setup takes about 600 buffers, mostly of small levels, and each
+  // was a callback into torch's allocator and back in host time that a small
+  // setup is bound by: a hierarchy at 2D 1024^2 takes 7.6 instead of 8.0 ms, a
+  // time step at 2D 100^2, G = 4 14.1 instead of 14.9 ms.
+  struct Pool {
+    struct Chunk {
+      size_t live = 0;
+      std::map<size_t, size_t> gaps;  // offset -> bytes
+    };
+    std::mutex mu;  // a handle may be closed by another thread
+    std::map<char*, Chunk> chunks;
+    std::unordered_map<char*, size_t> size;  // of the buffers given out
+  } pool;
   int64_t launches[KC_COUNT] = {};
   double ms[KC_COUNT] = {};
   double bytes[KC_COUNT] = {};
@@ -119,6 +139,11 @@ struct Ctx {
 
   void* dmalloc(size_t bytes);
   void dfree(void* p);
+  void* raw_alloc(size_t bytes);  // null on failure
+  void raw_free(void* p);
+  void* pool_take(size_t bytes);  // null: too large, or no memory for a chunk
+  void release(void* p);          // to its chunk, or to the allocator
+  void pool_trim();               // empty chunks back to the allocator
   void* host_stage(size_t bytes);  // pinned buffer of at least `bytes`
   void sync() {
     MGD_HIP(hipStreamSynchronize(stream));
@@ -149,10 +174,12 @@ struct DeferFrees {
   DeferFrees(const DeferFrees&) = delete;
   DeferFrees& operator=(const DeferFrees&) = delete;
   ~DeferFrees() {
-    if (--c->defer == 0 && !c->dead.empty()) {
+    if (--c->defer > 0) return;
+    if (!c->dead.empty()) {
       (void)hipStreamSynchronize(c->stream);
       c->free_dead();
     }
+    c->pool_trim();
   }
 };
 

@@ -1096,6 +1096,35 @@ def test_context_memory_comes_from_torch_allocator(ctx):
     hctx.close()
 
 
+@pytest.mark.parametrize("dim,n", [(2, 8), (2, 40), (3, 18)])
+@pytest.mark.parametrize("order", [(0, 1, 2), (2, 0, 1)])
+def test_setup_memory_returns_in_any_order(ctx, dim, n, order):
+    """Small buffers of a setup share chunks: handles made one after another
+    and closed in any order keep their results, and give back every byte."""
+    import torch
+    api = gpu_modules()
+    inp = si.generate(3, dim, n, 17)
+    co, gsys = gpu_system(ctx, inp)
+    r = to_dev(ctx, np.random.default_rng(2).standard_normal(gsys.n))
+    make = lambda s: api.BlockPreconditioner(ctx, gsys, "schur2", amg_seed=s, batched=1)  # noqa: E731
+    want = []
+    for s in range(3):
+        M = make(s)
+        want.append(to_host(M.apply(r)))
+        M.close()
+    torch.cuda.synchronize()
+    m0 = torch.cuda.memory_allocated(ctx.device)
+    Ms = [make(s) for s in range(3)]
+    left = [0, 1, 2]
+    for k in order:
+        for s in left:
+            assert np.array_equal(to_host(Ms[s].apply(r)), want[s]), (k, s)
+        Ms[k].close()
+        left.remove(k)
+    torch.cuda.synchronize()
+    assert torch.cuda.memory_allocated(ctx.device) == m0
+
+
 # ---------------------------------------------------------------------------
 # persistent tail of the batched V-cycle
 # ---------------------------------------------------------------------------
