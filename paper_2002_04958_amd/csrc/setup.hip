@@ -811,33 +811,45 @@ void transpose(Ctx* c, const Csr<double>& A, Csr<double>& T) {
 // reaches, ascending, with the value 0 + a_ik1 b_k1j + a_ik2 b_k2j + ... over
 // the row's entries in ascending k.
 //
-// A row is collected in a hash table in LDS by a group of GL lanes: the row's
-// entries k in turn, the lanes side by side over row k of B.  The columns of one
-// row of B are distinct, so no two lanes meet in a slot, and a slot gets its
-// terms in ascending k: the sum above, term by term.  Rows are sorted into
-// classes by the table they need (load at most 3/4): from the sum of their B
-// rows' lengths before the columns are counted, from the count itself before
-// the values are formed, and from the number of columns that exist at all in
-// both.  The kernels of a class walk its list with a grid of at most kSpGrid
-// workgroups and read the list's length on the device, so classes without rows
-// cost an empty launch and no readback.  Rows too long for the largest table are
-// formed one range of columns after another.  One lane per row merging the
-// B rows' heads through memory took 200 ms of a step with new coefficients at
-// 3D 64^3, G = 20 (22 hierarchies); the tables take 38 ms.
+// A row is collected in a hash table in LDS by a group of GL lanes.  The lanes
+// take the products of GL entries k of the row side by side (a search among the
+// entries' running totals gives each lane its entry), find their slots together,
+// and add one entry's products after the other's: the columns of one row of B
+// are distinct, so no two lanes meet in a slot, and a slot gets its terms in
+// ascending k, the sum above term by term.  With the lanes over one row of B at a
+// time, one to four of eight worked at the finest level.
+//
+// Rows are sorted into classes by the table they need (load at most 3/4): from
+// the sum of their B rows' lengths before the columns are counted, from the
+// count itself before the values are formed, and from the number of columns that
+// exist at all in both.  What bounds a row is instructions and the LDS its table
+// takes from other waves, hence the small first table (24 columns hold nearly
+// every row of A P and the Galerkin rows of the first levels) and 16-byte
+// accesses where a table is cleared, read out and ranked.  The kernels of a class
+// walk its list with a grid of at most kSpGrid workgroups and read the list's
+// length on the device, so classes without rows cost an empty launch and no
+// readback.  Rows too long for the largest table are formed one range of columns
+// after another.
+//
+// At 3D 64^3, G = 20 (22 hierarchies), products of a setup: one lane per row
+// merging the B rows' heads through memory 200 ms; tables from 64 slots, lanes
+// over one row of B 9.9 ms; tables from 32 slots 8.4; products side by side 6.0;
+// 16-byte accesses 5.2.
 // ---------------------------------------------------------------------------
 constexpr int kSpClasses = 5;             // four table sizes, then ranges of columns
-constexpr int kSpTable[4] = {64, 256, 1024, 4096};
 constexpr int kSpGrid = 4096;
-constexpr int kSpBinRows = 8;             // rows per thread of the sorting kernel
+// rows per thread of the sorting kernel: few where the rows' walks over A bound
+// it (at 276K rows 8 took 145 us), many where the workgroups meet in the counters
+constexpr int kSpBinFew = 2, kSpBinMany = 8, kSpBinManyFrom = 1 << 21;
 
 __host__ __device__ constexpr int sp_class(int cols) {
-  return cols <= 48 ? 0 : cols <= 192 ? 1 : cols <= 768 ? 2 : cols <= 3072 ? 3 : 4;
+  return cols <= 24 ? 0 : cols <= 96 ? 1 : cols <= 384 ? 2 : cols <= 3072 ? 3 : 4;
 }
 
 // lists[c * n ...] = the rows of class c, count[c] their number.  COUNTED: the
 // class from crp's row lengths, else from the B rows' total length; rows
 // without entries are in no list (cnt[i] = 0 for them before the count).
-template <bool COUNTED>
+template <bool COUNTED, int ROWS>
 __global__ void __launch_bounds__(256) k_spgemm_bin(int n, int max_cols,
                                                     const int* __restrict__ arp,
                                                     const int* __restrict__ aci,
@@ -851,10 +863,10 @@ __global__ void __launch_bounds__(256) k_spgemm_bin(int n, int max_cols,
   if (*err) return;  // an operand is malformed: empty lists, reported with the sizes
   if (threadIdx.x < kSpClasses) s_n[threadIdx.x] = 0;
   __syncthreads();
-  const int r0 = blockIdx.x * 256 * kSpBinRows;
-  int cls[kSpBinRows], pos[kSpBinRows];
+  const int r0 = blockIdx.x * 256 * ROWS;
+  int cls[ROWS], pos[ROWS];
 #pragma unroll
-  for (int t = 0; t < kSpBinRows; ++t) {
+  for (int t = 0; t < ROWS; ++t) {
     const int i = r0 + t * 256 + threadIdx.x;
     cls[t] = -1;
     pos[t] = 0;
@@ -886,9 +898,17 @@ __global__ void __launch_bounds__(256) k_spgemm_bin(int n, int max_cols,
     s_base[threadIdx.x] = s_n[threadIdx.x] ? atomicAdd(&count[threadIdx.x], s_n[threadIdx.x]) : 0;
   __syncthreads();
 #pragma unroll
-  for (int t = 0; t < kSpBinRows; ++t)
+  for (int t = 0; t < ROWS; ++t)
     if (cls[t] >= 0)
       lists[(size_t)cls[t] * n + s_base[cls[t]] + pos[t]] = r0 + t * 256 + threadIdx.x;
+}
+
+// Between LDS accesses of one wave to places other lanes wrote: the hardware
+// does them in program order, this keeps the compiler to it.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 template <int H, int GL, int WG, bool FILL>
@@ -898,54 +918,74 @@ __global__ void __launch_bounds__(WG) k_spgemm_hash(
     const int* __restrict__ bci, const double* __restrict__ bv, const int* __restrict__ crp,
     int* __restrict__ cnt_or_cci, double* __restrict__ cv, int* __restrict__ err) {
   constexpr int kGroups = WG / GL, kMost = 3 * H / 4;
-  constexpr int kShift = 32 - (H == 64 ? 6 : H == 256 ? 8 : H == 1024 ? 10 : 12);
-  __shared__ int s_key[kGroups][H];
-  __shared__ double s_val[FILL ? kGroups : 1][FILL ? H : 1];
-  __shared__ int s_col[FILL ? kGroups : 1][FILL ? kMost : 1];
+  constexpr int kShift = 32 - (H == 32 ? 5 : H == 128 ? 7 : H == 512 ? 9 : 12);
+  constexpr int kQuads = H / (4 * GL);  // int4s of a table per lane
+  __shared__ int4 s_key4[kGroups][H / 4];
+  __shared__ double2 s_val2[FILL ? kGroups : 1][FILL ? H / 2 : 1];
+  __shared__ int4 s_col4[FILL ? kGroups : 1][FILL ? kMost / 4 : 1];
   __shared__ uint16_t s_slot[FILL ? kGroups : 1][FILL ? kMost : 1];
   const int grp = threadIdx.x / GL, lane = threadIdx.x % GL;
   const int sh = (threadIdx.x & 63) / GL * GL;
   const uint64_t gm = (GL == 64 ? ~0ull : ((1ull << (GL & 63)) - 1)) << sh;
   // volatile: a group's lanes are in one wave, whose LDS operations are done in
   // program order; no barrier is needed between them
-  volatile int* key = s_key[grp];
-  volatile double* val = s_val[FILL ? grp : 0];
-  volatile int* col = s_col[FILL ? grp : 0];
+  int* keys = reinterpret_cast<int*>(s_key4[grp]);
+  volatile int* key = keys;
+  volatile double* val = reinterpret_cast<double*>(s_val2[FILL ? grp : 0]);
+  volatile int* col = reinterpret_cast<int*>(s_col4[FILL ? grp : 0]);
   volatile uint16_t* slot = s_slot[FILL ? grp : 0];
   const int nr = *count;
   for (int r = blockIdx.x * kGroups + grp; r < nr; r += gridDim.x * kGroups) {
     const int i = list[r];
     const int e0 = arp[i], e1 = arp[i + 1];
-    for (int s = lane; s < H; s += GL) {
-      key[s] = -1;
-      if (FILL) val[s] = 0.0;
+#pragma unroll
+    for (int s = 0; s < kQuads; ++s) {
+      s_key4[grp][s * GL + lane] = make_int4(-1, -1, -1, -1);
+      if (FILL) {
+        s_val2[grp][2 * s * GL + lane] = make_double2(0.0, 0.0);
+        s_val2[grp][(2 * s + 1) * GL + lane] = make_double2(0.0, 0.0);
+      }
     }
+    wave_lds_fence();
     int fresh = 0;
     bool lost = false;
     for (int b = e0; b < e1; b += GL) {
+      // GL entries of the row, then the products of all of them side by side
       const int e = b + lane;
-      int f0 = 0, f1 = 0;
+      int f0 = 0, len = 0;
       double a = 0.0;
       if (e < e1) {
         const int k = aci[e];
         f0 = brp[k];
-        f1 = brp[k + 1];
+        len = brp[k + 1] - f0;
         if (FILL) a = av[e];
       }
-      const int cnt = min(GL, e1 - b);
-      for (int q = 0; q < cnt; ++q) {
-        const int k0 = __shfl(f0, q, GL), k1 = __shfl(f1, q, GL);
+      int upto = len;  // products of the entries up to the lane's
+#pragma unroll
+      for (int o = 1; o < GL; o <<= 1) {
+        const int t = __shfl_up(upto, o, GL);
+        if (lane >= o) upto += t;
+      }
+      const int total = __shfl(upto, GL - 1, GL), from = f0 - (upto - len);
+      for (int p0 = 0; p0 < total; p0 += GL) {
+        const int p = p0 + lane;
+        int q = 0;  // the entry product p belongs to
+#pragma unroll
+        for (int o = GL / 2; o > 0; o >>= 1)
+          if (__shfl(upto, q + o - 1, GL) <= p) q += o;
+        const int f = __shfl(from, q, GL) + p;
         const double aq = FILL ? __shfl(a, q, GL) : 0.0;
-        for (int f = k0 + lane; f < k1; f += GL) {
+        int h = -1;
+        double x = 0.0;
+        if (p < total) {
           const int j = bci[f];
-          double x = 0.0;
-          if (FILL) x = bv[f];
-          int h = (int)(((unsigned)j * 2654435769u) >> kShift);
+          if (FILL) x = aq * bv[f];
+          h = (int)(((unsigned)j * 2654435769u) >> kShift);
           int tries = 0;
           for (; tries < H; ++tries) {  // a table is at most 3/4 full
             int at = key[h];
             if (at == -1) {
-              at = atomicCAS(&s_key[grp][h], -1, j);
+              at = atomicCAS(&keys[h], -1, j);
               if (at == -1) {
                 ++fresh;
                 break;
@@ -956,9 +996,13 @@ __global__ void __launch_bounds__(WG) k_spgemm_hash(
           }
           if (tries == H) {
             lost = true;
-            continue;
+            h = -1;
           }
-          if (FILL) val[h] = val[h] + aq * x;
+        }
+        if (FILL) {  // one entry's products after the other's
+          const int last = __shfl(q, min(GL, total - p0) - 1, GL);
+          for (int t = __shfl(q, 0, GL); t <= last; ++t)
+            if (q == t && h >= 0) val[h] = val[h] + x;
         }
       }
     }
@@ -970,29 +1014,41 @@ __global__ void __launch_bounds__(WG) k_spgemm_hash(
       continue;
     }
     // the columns present, in slot order, then each at its rank
+    wave_lds_fence();
     int m = 0;
-    for (int s0 = 0; s0 < H; s0 += GL) {
-      const int k = key[s0 + lane];
-      const uint64_t w = (__ballot(k >= 0) & gm) >> sh;
-      const int at = m + (int)__popcll(w & ((1ull << lane) - 1));
-      if (k >= 0 && at < kMost) {
-        col[at] = k;
-        slot[at] = (uint16_t)(s0 + lane);
+#pragma unroll
+    for (int s = 0; s < kQuads; ++s) {
+      const int4 k4 = s_key4[grp][s * GL + lane];
+      const int k[4] = {k4.x, k4.y, k4.z, k4.w};
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const uint64_t w = (__ballot(k[t] >= 0) & gm) >> sh;
+        const int at = m + (int)__popcll(w & ((1ull << lane) - 1));
+        if (k[t] >= 0 && at < kMost) {
+          col[at] = k[t];
+          slot[at] = (uint16_t)(4 * (s * GL + lane) + t);
+        }
+        m += (int)__popcll(w);
       }
-      m += (int)__popcll(w);
     }
     const int o = crp[i];
     if (m != crp[i + 1] - o || m > kMost) {  // another number of columns than were counted
       if (lane == 0) atomicOr(err, 2);
       continue;
     }
+    if (lane < (-m & 3)) col[m + lane] = INT_MAX;  // m <= kMost, a multiple of 4
+    wave_lds_fence();
     for (int t = lane; t < m; t += GL) {
       const int k = col[t];
       int rank = 0;
-      for (int u = 0; u < m; ++u) rank += col[u] < k ? 1 : 0;
+      for (int u = 0; u < (m + 3) / 4; ++u) {
+        const int4 c4 = s_col4[grp][u];
+        rank += (c4.x < k) + (c4.y < k) + (c4.z < k) + (c4.w < k);
+      }
       cnt_or_cci[o + rank] = k;
       cv[o + rank] = val[slot[t]];
     }
+    wave_lds_fence();
   }
 }
 
@@ -1064,11 +1120,16 @@ static void spgemm_pass(Ctx* c, const Csr<double>& A, const Csr<double>& B, int 
                         DBuf<int>& lists, DBuf<int>& count, const int* crp, int* cnt_or_cci, double* cv) {
   const int n = A.n_rows;
   fill<int>(c, count.get(), 0, kSpClasses);
-  hipLaunchKernelGGL(k_spgemm_bin<FILL>, dim3(cdiv(n, 256 * kSpBinRows)), dim3(256), 0, c->stream,
-                     n, max_cols, A.rp.get(), A.ci.get(), B.rp.get(), crp,
-                     FILL ? (int*)nullptr : cnt_or_cci, lists.get(), count.get(),
-                     (const int*)c->err_flag());
-  MGD_CHECK_LAUNCH();
+  auto bin = [&](auto kernel, int rows) {
+    hipLaunchKernelGGL(kernel, dim3(cdiv(n, 256 * rows)), dim3(256), 0, c->stream, n, max_cols,
+                       A.rp.get(), A.ci.get(), B.rp.get(), crp, FILL ? (int*)nullptr : cnt_or_cci,
+                       lists.get(), count.get(), (const int*)c->err_flag());
+    MGD_CHECK_LAUNCH();
+  };
+  if (n < kSpBinManyFrom)
+    bin(k_spgemm_bin<FILL, kSpBinFew>, kSpBinFew);
+  else
+    bin(k_spgemm_bin<FILL, kSpBinMany>, kSpBinMany);
   const int top = sp_class(max_cols);  // no row needs more than all columns
 #define MGD_SPGEMM(CLS, H, GL, WG)                                                                \
   if (CLS <= top) {                                                                               \
@@ -1078,9 +1139,9 @@ static void spgemm_pass(Ctx* c, const Csr<double>& A, const Csr<double>& B, int 
                        B.rp.get(), B.ci.get(), B.v.get(), crp, cnt_or_cci, cv, c->err_flag());    \
     MGD_CHECK_LAUNCH();                                                                           \
   }
-  MGD_SPGEMM(0, 64, 8, 256)
-  MGD_SPGEMM(1, 256, 32, 256)
-  MGD_SPGEMM(2, 1024, 64, 256)
+  MGD_SPGEMM(0, 32, 8, 256)
+  MGD_SPGEMM(1, 128, 16, 256)
+  MGD_SPGEMM(2, 512, 64, 256)
   MGD_SPGEMM(3, 4096, 64, 64)
 #undef MGD_SPGEMM
   if (top == 4) {
