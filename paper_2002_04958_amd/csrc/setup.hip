@@ -10,6 +10,7 @@
 
 #include <algorithm>
 #include <climits>
+#include <type_traits>
 
 #include "kernels.hpp"
 #include "setup.hpp"
@@ -35,27 +36,53 @@ void csr_copy(Ctx* c, const Csr<double>& A, Csr<double>& out) {
 // ---------------------------------------------------------------------------
 // strength of connection
 // ---------------------------------------------------------------------------
-__global__ void k_strength(int n, const int* __restrict__ rp, const int* __restrict__ ci,
-                           const double* __restrict__ v, double theta, double dom,
-                           uint8_t* __restrict__ S, int* __restrict__ stc,
-                           double* __restrict__ diag, const int* __restrict__ err) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+// GL lanes per row read its entries side by side, the row sum adds them in
+// order (it decides dominance).  One lane per row, 64 rows apart in every load,
+// took 2.3 ms for the five levels of a setup at 3D 64^3, G = 20 (1.3 ms for the
+// 1.6M rows of 17 entries at the second); this takes 0.76 ms.
+template <int GL>
+__global__ void __launch_bounds__(256) k_strength(int n, const int* __restrict__ rp,
+                                                  const int* __restrict__ ci,
+                                                  const double* __restrict__ v, double theta,
+                                                  double dom, uint8_t* __restrict__ S,
+                                                  int* __restrict__ stc,
+                                                  double* __restrict__ diag,
+                                                  const int* __restrict__ err) {
+  const int i = blockIdx.x * (256 / GL) + threadIdx.x / GL, lane = threadIdx.x % GL;
   if (i >= n || *err) return;
   const int e0 = rp[i], e1 = rp[i + 1];
   double m = -INFINITY, rs = 0.0, dg = 0.0;
-  for (int e = e0; e < e1; ++e) {
-    const double a = v[e];
-    rs = rs + a;
-    if (ci[e] == i)
-      dg = a;
-    else if (-a > m)
-      m = -a;
+  bool has = false;
+  for (int b = e0; b < e1; b += GL) {
+    const int e = b + lane;
+    double a = 0.0;
+    if (e < e1) {
+      a = v[e];
+      if (ci[e] == i) {
+        dg = a;
+        has = true;
+      } else if (-a > m) {
+        m = -a;
+      }
+    }
+    const int cnt = min(GL, e1 - b);
+    for (int q = 0; q < cnt; ++q) rs = rs + __shfl(a, q, GL);
   }
-  diag[i] = dg;
+#pragma unroll
+  for (int o = GL / 2; o > 0; o >>= 1) {
+    const double om = __shfl_xor(m, o, GL), od = __shfl_xor(dg, o, GL);
+    const int oh = __shfl_xor((int)has, o, GL);
+    if (om > m) m = om;
+    if (!has && oh) {
+      dg = od;
+      has = true;
+    }
+  }
+  if (lane == 0) diag[i] = dg;
   bool empty = !(m > 0.0);
   if (dom > 0.0 && rs >= dom * dg) empty = true;
   const double thr = theta * m;
-  for (int e = e0; e < e1; ++e) {
+  for (int e = e0 + lane; e < e1; e += GL) {
     const int j = ci[e];
     const bool s = !empty && j != i && (-v[e] >= thr);
     S[e] = s ? 1 : 0;
@@ -71,10 +98,16 @@ static void strength(Ctx* c, const Csr<double>& A, double theta, double dom, DBu
   diag.alloc(c, (size_t)A.n_rows);
   fill<int>(c, stc.get(), 0, (size_t)A.n_rows);
   if (A.n_rows == 0) return;
-  hipLaunchKernelGGL(k_strength, dim3(cdiv(A.n_rows, 256)), dim3(256), 0, c->stream, A.n_rows,
-                     A.rp.get(), A.ci.get(), A.v.get(), theta, dom, S.get(), stc.get(), diag.get(),
-                     (const int*)c->err_flag());
-  MGD_CHECK_LAUNCH();
+  auto launch = [&](auto kernel, int lanes) {
+    hipLaunchKernelGGL(kernel, dim3(cdiv(A.n_rows, 256 / lanes)), dim3(256), 0, c->stream,
+                       A.n_rows, A.rp.get(), A.ci.get(), A.v.get(), theta, dom, S.get(), stc.get(),
+                       diag.get(), (const int*)c->err_flag());
+    MGD_CHECK_LAUNCH();
+  };
+  if (A.nnz <= 10LL * A.n_rows)
+    launch(k_strength<8>, 8);
+  else
+    launch(k_strength<16>, 16);
 }
 
 // ---------------------------------------------------------------------------
@@ -134,72 +167,161 @@ __device__ __forceinline__ bool beats(uint64_t kj, int j, uint64_t ki, int i) {
 // neighbours' states may see them settled or not: a new C point is a row not
 // marked this round and not F either way (an undecided row has no older C point
 // among its dependencies).
-__global__ void k_pmis_lose(int n, const int* __restrict__ rp, const int* __restrict__ ci,
-                            const uint8_t* __restrict__ S, const uint64_t* __restrict__ key,
-                            const int8_t* __restrict__ state, int round,
-                            const int* __restrict__ left, int* __restrict__ loser,
-                            const int* __restrict__ err) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (*left == 0 || *err) return;  // nothing undecided after the round before
-  if (i >= n || state[i] != kU) return;
-  const uint64_t ki = key[i];
-  bool lose = false;
-  for (int e = rp[i]; e < rp[i + 1]; ++e) {
-    if (!S[e]) continue;
-    const int j = ci[e];
-    if (state[j] != kU) continue;
-    if (beats(key[j], j, ki, i))
-      lose = true;
-    else
-      loser[j] = round;
+//
+// A round walks the list of rows the last one left undecided, kPmisLanes lanes
+// per row (a workgroup past the list's end exits), and the second kernel writes
+// the next list, in any order.  With a lane per row and every row visited, and
+// two counters per undecided row in LDS, the rounds of a setup at 3D 64^3, G = 20
+// took 3.7 ms and those of a hierarchy at 2D 1024^2 1.06 ms; now 2.3 and 0.75 ms.
+constexpr int kPmisLanes = 8;
+__global__ void __launch_bounds__(256) k_pmis_lose(
+    const int* __restrict__ list, const int* __restrict__ left, const int* __restrict__ rp,
+    const int* __restrict__ ci, const uint8_t* __restrict__ S, const uint64_t* __restrict__ key,
+    const int8_t* __restrict__ state, int round, int* __restrict__ loser,
+    const int* __restrict__ err) {
+  constexpr int kRows = 256 / kPmisLanes, kBatch = 4;
+  const int nl = *left, lane = threadIdx.x % kPmisLanes;
+  if (*err) return;
+  // a group's rows in a pass, whose loads wait for each other together
+  const int per = nl > (int)gridDim.x * kRows ? kBatch : 1;
+  for (int p0 = blockIdx.x * kRows * per; p0 < nl; p0 += gridDim.x * kRows * per) {
+    int i[kBatch], f0[kBatch], f1[kBatch];
+    uint64_t ki[kBatch];
+    bool lose[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const int p = p0 + kRows * u + threadIdx.x / kPmisLanes;
+      i[u] = u < per && p < nl ? list[p] : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      f0[u] = f1[u] = 0;
+      ki[u] = 0;
+      lose[u] = false;
+      if (i[u] < 0) continue;
+      f0[u] = rp[i[u]] + lane;
+      f1[u] = rp[i[u] + 1];
+      ki[u] = key[i[u]];
+    }
+    for (bool more = true; __any(more);) {
+      more = false;
+      int j[kBatch];
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) j[u] = f0[u] < f1[u] && S[f0[u]] ? ci[f0[u]] : -1;
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u)
+        if (j[u] >= 0 && state[j[u]] != kU) j[u] = -1;
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) {
+        if (j[u] >= 0) {
+          if (beats(key[j[u]], j[u], ki[u], i[u]))
+            lose[u] = true;
+          else
+            loser[j[u]] = round;
+        }
+        f0[u] += kPmisLanes;
+        more = more || f0[u] < f1[u];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u)
+      if (lose[u]) loser[i[u]] = round;
   }
-  if (lose) loser[i] = round;
 }
 
-// Undecided rows per member (cnt[m]) and altogether (cnt[nm]), kPmisRows rows
-// per thread so that few workgroups meet in the counters.  SETTLE: the second
-// half of a round first.
-constexpr int kPmisRows = 8;
-template <bool SETTLE>
+// The undecided rows: list[0 .. cnt[nm]), and a flag per member that has any
+// (cnt[m]).  SETTLE: of the rows in `from`, after the second half of a round;
+// otherwise of all n.  A workgroup takes 256 * CHUNKS rows at a time and adds to
+// the list once for all of them: few workgroups meet in the counter.
+template <bool SETTLE, int CHUNKS>
 __global__ void __launch_bounds__(256) k_pmis_settle(int n, RowRanges R,
+                                                     const int* __restrict__ from,
+                                                     const int* __restrict__ left,
                                                      const int* __restrict__ rp,
                                                      const int* __restrict__ ci,
                                                      const uint8_t* __restrict__ S, int round,
-                                                     const int* __restrict__ left,
-                                                     const int* __restrict__ loser,
-                                                     int8_t* state, int* __restrict__ cnt,
+                                                     const int* __restrict__ loser, int8_t* state,
+                                                     int* __restrict__ list, int* __restrict__ cnt,
                                                      const int* __restrict__ err) {
-  __shared__ int s_cnt[kMaxMembers + 1];
-  if (SETTLE && (*left == 0 || *err)) return;
-  if (threadIdx.x <= R.nm) s_cnt[threadIdx.x] = 0;
-  __syncthreads();
-  for (int t = 0; t < kPmisRows; ++t) {
-    const int i = blockIdx.x * 256 * kPmisRows + t * 256 + threadIdx.x;
-    bool und = i < n && state[i] == kU;
-    if (SETTLE && und) {
-      if (loser[i] != round) {
-        state[i] = kC;
-        und = false;
+  __shared__ int s_any[kMaxMembers], s_n, s_base;
+  constexpr int kRows = 256 / kPmisLanes;
+  const int nl = SETTLE ? *left : n;
+  // rows of a workgroup at a time; one per lane group where the list is short
+  const bool thin = SETTLE && nl <= (int)gridDim.x * kRows;
+  const int per = thin ? kRows : 256 * CHUNKS;
+  if (*err || (int)blockIdx.x * per >= nl) return;
+  const int grp = threadIdx.x / kPmisLanes, lane = threadIdx.x % kPmisLanes;
+  const int sh = (threadIdx.x & 63) / kPmisLanes * kPmisLanes;
+  constexpr uint64_t kGroup = (1ull << kPmisLanes) - 1;
+  if (threadIdx.x < R.nm) s_any[threadIdx.x] = 0;
+  for (int p0 = blockIdx.x * per; p0 < nl; p0 += gridDim.x * per) {
+    if (threadIdx.x == 0) s_n = 0;
+    __syncthreads();
+    int row[CHUNKS], pos[CHUNKS];  // undecided rows, -1: none
+#pragma unroll
+    for (int t = 0; t < CHUNKS; ++t) {
+      row[t] = -1;
+      if (!SETTLE) {
+        const int i = p0 + 256 * t + threadIdx.x;
+        if (i < n && state[i] == kU) row[t] = i;
       } else {
-        for (int e = rp[i]; e < rp[i + 1]; ++e) {
-          const int j = ci[e];
-          if (S[e] && loser[j] != round && state[j] != kF) {
-            state[i] = kF;
-            und = false;
-            break;
+        // kPmisLanes rows of the group together: their loads wait for each other
+        // four deep once, not once per row
+        int i[kPmisLanes], f0[kPmisLanes], f1[kPmisLanes];  // f1 = -1: a winner
+        bool hit[kPmisLanes];
+#pragma unroll
+        for (int u = 0; u < kPmisLanes; ++u) {
+          const int p = p0 + 256 * t + kRows * u + grp;
+          i[u] = p < nl && (!thin || t + u == 0) ? from[p] : -1;
+        }
+#pragma unroll
+        for (int u = 0; u < kPmisLanes; ++u) {
+          f0[u] = f1[u] = 0;
+          if (i[u] < 0) continue;
+          f0[u] = rp[i[u]] + lane;
+          f1[u] = loser[i[u]] == round ? rp[i[u] + 1] : -1;
+        }
+#pragma unroll
+        for (int u = 0; u < kPmisLanes; ++u) hit[u] = false;
+        for (bool more = true; __any(more);) {
+          more = false;
+          int j[kPmisLanes];
+#pragma unroll
+          for (int u = 0; u < kPmisLanes; ++u)
+            j[u] = f0[u] < f1[u] && S[f0[u]] ? ci[f0[u]] : -1;
+#pragma unroll
+          for (int u = 0; u < kPmisLanes; ++u) {
+            if (j[u] >= 0 && loser[j[u]] != round && state[j[u]] != kF) hit[u] = true;
+            f0[u] += kPmisLanes;
+            more = more || (f0[u] < f1[u] && !hit[u]);
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < kPmisLanes; ++u) {
+          const bool f = ((__ballot(hit[u]) >> sh) & kGroup) != 0;
+          if (i[u] < 0) continue;
+          if (f1[u] < 0 || f) {
+            if (lane == 0) state[i[u]] = f ? kF : kC;
+          } else if (lane == u) {
+            row[t] = i[u];
           }
         }
       }
+      const uint64_t w = __ballot(row[t] >= 0);
+      int base = 0;
+      if ((threadIdx.x & 63) == 0 && w) base = atomicAdd(&s_n, (int)__popcll(w));
+      pos[t] = __shfl(base, 0, 64) + (int)__popcll(w & ((1ull << (threadIdx.x & 63)) - 1));
+      if (row[t] >= 0) s_any[member_of(R, row[t])] = 1;
     }
-    if (und) {
-      const int m = member_of(R, i);
-      atomicAdd(&s_cnt[m], 1);
-      atomicAdd(&s_cnt[R.nm], 1);
-    }
+    __syncthreads();
+    if (threadIdx.x == 0) s_base = s_n ? atomicAdd(&cnt[R.nm], s_n) : 0;
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < CHUNKS; ++t)
+      if (row[t] >= 0) list[s_base + pos[t]] = row[t];
   }
   __syncthreads();
-  if (threadIdx.x <= R.nm && s_cnt[threadIdx.x])
-    atomicAdd(&cnt[threadIdx.x], s_cnt[threadIdx.x]);
+  if (threadIdx.x < R.nm && s_any[threadIdx.x]) cnt[threadIdx.x] = 1;
 }
 
 // rows of members that turn out not to coarsen become F
@@ -357,6 +479,9 @@ __global__ void k_hmis_init(int n, const int* __restrict__ rp, const int* __rest
 // a time, with the numbering behind them; a round with nothing left to decide
 // does nothing, and the counters read back say which rounds a member took.
 constexpr int kPmisAhead = 6;
+// A row per lane group while kPmisThinGrid workgroups hold the list: rows of 30
+// entries eight to a group took 34 us a round however few were left.
+constexpr int kPmisGrid = 16384, kPmisThinGrid = 2048, kPmisManyFrom = 1 << 20;
 static std::vector<int> pmis(Ctx* c, const Csr<double>& A, const DBuf<uint8_t>& S,
                              const DBuf<int>& stc, const RowRanges& R, const MemberFlags& M,
                              uint64_t seed, int level, int hmis_tile, DBuf<int8_t>& state,
@@ -365,13 +490,13 @@ static std::vector<int> pmis(Ctx* c, const Csr<double>& A, const DBuf<uint8_t>& 
   rounds.assign(nm, 0);
   state.alloc(c, (size_t)std::max(n, 1));
   cidx.alloc(c, (size_t)n + 1);
-  const int g = cdiv(std::max(n, 1), 256), gs = cdiv(std::max(n, 1), 256 * kPmisRows);
+  const int g = cdiv(std::max(n, 1), 256);
   const int* err = c->err_flag();
   DBuf<uint64_t> key(c, (size_t)std::max(n, 1));
   DBuf<int> loser(c, (size_t)std::max(n, 1)), isc(c, (size_t)std::max(n, 1));
   // counters per round (row 0: before the first), then the members' bounds and the flag
   const size_t at = (size_t)(kPmisAhead + 1) * stride;
-  DBuf<int> cnt(c, at + nm + 2);
+  DBuf<int> cnt(c, at + nm + 2), lists(c, (size_t)2 * std::max(n, 1));
   if (n > 0) {
     hipLaunchKernelGGL(k_pmis_init, dim3(g), dim3(256), 0, c->stream, n, R, M, stc.get(), seed,
                        level, key.get(), loser.get(), state.get());
@@ -397,22 +522,37 @@ static std::vector<int> pmis(Ctx* c, const Csr<double>& A, const DBuf<uint8_t>& 
     MGD_CHECK_LAUNCH();
     c->sync();
   }
+  // settles round r (or lists the rows there are) and counts into the row of
+  // counters behind `before`'s
+  auto settle = [&](auto settles, int r, const int* from, int* list, int* before) {
+    constexpr bool kSettle = decltype(settles)::value;
+    auto launch = [&](auto kernel, int chunks) {
+      const int g = std::max(cdiv(n, 256 * chunks),  // short lists with a row per lane group
+                             std::min(cdiv(n, 256 / kPmisLanes), kPmisThinGrid));
+      hipLaunchKernelGGL(kernel, dim3(std::clamp(g, 1, kPmisGrid)), dim3(256), 0,
+                         c->stream, n, R, from, (const int*)before, A.rp.get(), A.ci.get(),
+                         S.get(), r, (const int*)loser.get(), state.get(), list,
+                         kSettle ? before + 1 : before, err);
+      MGD_CHECK_LAUNCH();
+    };
+    if (n < kPmisManyFrom)
+      launch(k_pmis_settle<kSettle, 1>, 1);
+    else
+      launch(k_pmis_settle<kSettle, 4>, 4);
+  };
   for (int base = 0;; base += kPmisAhead) {
     fill<int>(c, cnt.get(), 0, at);
     // row 0 is counted again rather than carried over
-    hipLaunchKernelGGL(k_pmis_settle<false>, dim3(gs), dim3(256), 0, c->stream, n, R, A.rp.get(),
-                       A.ci.get(), S.get(), 0, (const int*)nullptr, (const int*)loser.get(),
-                       state.get(), cnt.get(), err);
-    MGD_CHECK_LAUNCH();
+    settle(std::false_type{}, 0, nullptr, lists.get(), cnt.get());
     for (int r = 1; r <= kPmisAhead; ++r) {
-      const int* left = cnt.get() + (size_t)(r - 1) * stride + nm;
-      hipLaunchKernelGGL(k_pmis_lose, dim3(g), dim3(256), 0, c->stream, n, A.rp.get(), A.ci.get(),
+      const int* from = lists.get() + (size_t)((r - 1) & 1) * n;
+      int* before = cnt.get() + (size_t)(r - 1) * stride + nm;
+      hipLaunchKernelGGL(k_pmis_lose, dim3(std::clamp(cdiv(n, 256 / kPmisLanes), 1, kPmisGrid)),
+                         dim3(256), 0, c->stream, from, (const int*)before, A.rp.get(), A.ci.get(),
                          S.get(), (const uint64_t*)key.get(), (const int8_t*)state.get(), base + r,
-                         left, loser.get(), err);
-      hipLaunchKernelGGL(k_pmis_settle<true>, dim3(gs), dim3(256), 0, c->stream, n, R, A.rp.get(),
-                         A.ci.get(), S.get(), base + r, left, (const int*)loser.get(), state.get(),
-                         cnt.get() + (size_t)r * stride, err);
+                         loser.get(), err);
       MGD_CHECK_LAUNCH();
+      settle(std::true_type{}, base + r, from, lists.get() + (size_t)(r & 1) * n, before);
     }
     if (n > 0) {
       hipLaunchKernelGGL(k_is_c, dim3(g), dim3(256), 0, c->stream, n, (const int8_t*)state.get(),

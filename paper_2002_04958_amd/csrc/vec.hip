@@ -50,14 +50,23 @@ __global__ void __launch_bounds__(256) k_tile_sums(const int* __restrict__ in, i
   if (threadIdx.x == 0) sums[blockIdx.x] = lds[0] + lds[1] + lds[2] + lds[3];
 }
 
-// Exclusive scan of one tile with an additive base; writes out[i] for
-// i < n and, from the block holding the last element, out[n] = total.
+// Exclusive scan of one tile on top of the sums of the tiles before it (null: the
+// first tile only); writes out[i] for i < n and, from the block holding the last
+// element, out[n] = total.  Every workgroup adds up the tile sums for itself: a
+// scan of the sums in between would be another dependent launch.
 __global__ void __launch_bounds__(256) k_tile_scan(const int* __restrict__ in, int n,
-                                                   const int* __restrict__ base_of_tile,
+                                                   const int* __restrict__ tile_sums,
                                                    int* __restrict__ out) {
   __shared__ int lds[256];
+  __shared__ int s_before[4];
   const long base = (long)blockIdx.x * kScanTile;
   const int t = threadIdx.x;
+  int before = 0;
+  if (tile_sums)
+    for (int k = t; k < (int)blockIdx.x; k += 256) before += tile_sums[k];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off, 64);
+  if ((t & 63) == 0) s_before[t >> 6] = before;
   int v[8];
   int s = 0;
 #pragma unroll
@@ -75,7 +84,7 @@ __global__ void __launch_bounds__(256) k_tile_scan(const int* __restrict__ in, i
     lds[t] += add;
     __syncthreads();
   }
-  int run = (t ? lds[t - 1] : 0) + (base_of_tile ? base_of_tile[blockIdx.x] : 0);
+  int run = (t ? lds[t - 1] : 0) + s_before[0] + s_before[1] + s_before[2] + s_before[3];
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
     long i = base + t * 8 + k;
@@ -99,12 +108,11 @@ void exclusive_scan(Ctx* c, const int* in, int* out, int n) {
     MGD_CHECK_LAUNCH();
     return;
   }
-  DBuf<int> sums(c, tiles), sums_scan(c, (size_t)tiles + 1);
+  DBuf<int> sums(c, tiles);
   hipLaunchKernelGGL(k_tile_sums, dim3(tiles), dim3(256), 0, c->stream, in, n, sums.get());
   MGD_CHECK_LAUNCH();
-  exclusive_scan(c, sums.get(), sums_scan.get(), tiles);
   hipLaunchKernelGGL(k_tile_scan, dim3(tiles), dim3(256), 0, c->stream, in, n,
-                     (const int*)sums_scan.get(), out);
+                     (const int*)sums.get(), out);
   MGD_CHECK_LAUNCH();
   // temporaries are released only after the stream has consumed them
   if (!c->defer) c->sync();

@@ -285,6 +285,29 @@ def test_amg_setup_long_rows_bit_exact(ctx, n, weak, strong):
     _compare_hierarchies(g, H, exact_values=True)
 
 
+@pytest.mark.parametrize("n", [255, 300, 1030])
+def test_first_level_of_many_rows_bit_exact(ctx, n):
+    """Lists of undecided rows longer than one row per lane group (65,536 rows),
+    several chunks per workgroup (2^20 rows): strength, C/F splitting and P of
+    the first level bit for bit the oracle's."""
+    api = gpu_modules()
+    rng = np.random.default_rng(n)
+    lap = sp.diags([-np.ones(n - 1), 2.0 * np.ones(n), -np.ones(n - 1)], [-1, 0, 1])
+    A = sp.csr_matrix(sp.kron(sp.eye(n), lap) + sp.kron(lap, sp.eye(n)))
+    w = sp.diags(rng.uniform(0.5, 2.0, n * n))
+    A = sp.csr_matrix(w @ A @ w + sp.diags(rng.uniform(0.0, 0.2, n * n)))
+    A.sort_indices()
+    g = api.AMG(ctx, A.indptr, A.indices, A.data, seed=3, max_levels=2)
+    e = g.export_level(0)
+    S = oamg.strength(A, 0.25, 0.9)
+    cf = oamg.pmis(A, S, 3, 0)
+    assert np.array_equal(cf, e["cf"])
+    P = oamg.interpolation(A, S, cf)
+    prp, pci, pv = e["P"]
+    assert np.array_equal(P.indptr, prp) and np.array_equal(P.indices, pci)
+    assert np.array_equal(P.data, pv)
+
+
 def test_amg_levelwise_on_gpu_levels(ctx):
     """Binding test: the oracle's strength, PMIS and interpolation applied to
     each GPU level matrix give the GPU's C/F splitting and P bit for bit."""
