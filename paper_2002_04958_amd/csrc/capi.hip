@@ -88,15 +88,20 @@ void* Ctx::dmalloc(size_t bytes) {
 }
 void Ctx::free_dead() {
   std::vector<void*> d;
-  d.swap(dead);
+  {
+    std::lock_guard<std::mutex> lock(pool.mu);
+    d.swap(dead);
+  }
   for (void* p : d) release(p);
 }
 void Ctx::dfree(void* p) {
   if (!p) return;
-  if (defer)
+  if (defer) {
+    std::lock_guard<std::mutex> lock(pool.mu);
     dead.push_back(p);
-  else
+  } else {
     release(p);
+  }
 }
 void* Ctx::pool_take(size_t bytes) {
   constexpr size_t kPoolChunk = size_t(4) << 20, kPoolMost = size_t(512) << 10;

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstdint>
 #include <cstring>
 #include <initializer_list>
@@ -112,9 +113,10 @@ struct Ctx {
   std::vector<Pending> pending;
   std::vector<hipEvent_t> event_pool;
   int* dev_err = nullptr;  // set by in-kernel bounds checks
-  // frees held back until the stream has been waited for (DeferFrees)
-  int defer = 0;
-  std::vector<void*> dead;
+  // frees held back until the stream has been waited for (DeferFrees); a handle
+  // may be closed by another thread meanwhile (a collector that runs there)
+  std::atomic<int> defer{0};
+  std::vector<void*> dead;  // under pool.mu
   // Small buffers of a DeferFrees scope come out of chunks of kPoolChunk bytes
   // and go back to their chunk; a chunk without buffers goes back to the
   // allocator (at the end of the scope, or with its last buffer after it).  A
@@ -128,7 +130,7 @@ struct Ctx {
       size_t live = 0;
       std::map<size_t, size_t> gaps;  // offset -> bytes
     };
-    std::mutex mu;  // a handle may be closed by another thread
+    std::mutex mu;
     std::map<char*, Chunk> chunks;
     std::unordered_map<char*, size_t> size;  // of the buffers given out
   } pool;
@@ -147,7 +149,7 @@ struct Ctx {
   void* host_stage(size_t bytes);  // pinned buffer of at least `bytes`
   void sync() {
     MGD_HIP(hipStreamSynchronize(stream));
-    if (!dead.empty()) free_dead();
+    free_dead();
   }
   void free_dead();
   void make_current() { MGD_HIP(hipSetDevice(device)); }
@@ -175,7 +177,12 @@ struct DeferFrees {
   DeferFrees& operator=(const DeferFrees&) = delete;
   ~DeferFrees() {
     if (--c->defer > 0) return;
-    if (!c->dead.empty()) {
+    bool left;
+    {
+      std::lock_guard<std::mutex> lock(c->pool.mu);
+      left = !c->dead.empty();
+    }
+    if (left) {
       (void)hipStreamSynchronize(c->stream);
       c->free_dead();
     }
