@@ -1148,6 +1148,31 @@ def test_setup_memory_returns_in_any_order(ctx, dim, n, order):
     assert torch.cuda.memory_allocated(ctx.device) == m0
 
 
+def test_handles_closed_by_another_thread_during_setup(ctx):
+    """A handle may be closed by another thread (a collector that runs there)
+    while a setup holds its frees back: both end, with the same results."""
+    import threading
+    api = gpu_modules()
+    inp = si.generate(3, 2, 24, 17)
+    co, gsys = gpu_system(ctx, inp)
+    r = to_dev(ctx, np.random.default_rng(2).standard_normal(gsys.n))
+    make = lambda: api.BlockPreconditioner(ctx, gsys, "schur2", amg_seed=1, batched=1)  # noqa: E731
+    M = make()
+    want = to_host(M.apply(r))
+    old = [make() for _ in range(12)]
+
+    def close():
+        for m in old:
+            m.close()
+    t = threading.Thread(target=close)
+    t.start()
+    new = [make() for _ in range(6)]
+    t.join()
+    for m in new:
+        assert np.array_equal(to_host(m.apply(r)), want)
+        m.close()
+
+
 # ---------------------------------------------------------------------------
 # persistent tail of the batched V-cycle
 # ---------------------------------------------------------------------------
