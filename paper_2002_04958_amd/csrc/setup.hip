@@ -978,9 +978,14 @@ void transpose(Ctx* c, const Csr<double>& A, Csr<double>& T) {
 // ---------------------------------------------------------------------------
 constexpr int kSpClasses = 5;             // four table sizes, then ranges of columns
 constexpr int kSpGrid = 4096;
-// rows per thread of the sorting kernel: few where the rows' walks over A bound
-// it (at 276K rows 8 took 145 us), many where the workgroups meet in the counters
-constexpr int kSpBinFew = 2, kSpBinMany = 8, kSpBinManyFrom = 1 << 21;
+// Rows per thread of the sorting kernel: few where the rows' walks over A bound
+// it (at 276K rows 8 took 145 us; one up to 2^19, for a workgroup per compute
+// unit), many where the workgroups meet in the counters,
+// one addition after the other.  For the same reason a workgroup has 1024 threads:
+// with 256 sorting the rows of A P took 34.6 and 27.2 us at 2^20 rows (before and
+// after the count), with 1024 16.9 and 10.2.
+constexpr int kSpBinFew = 2, kSpBinMany = 8, kSpBinWg = 1024;
+constexpr int kSpBinFewFrom = 1 << 19, kSpBinManyFrom = 1 << 21;
 
 __host__ __device__ constexpr int sp_class(int cols) {
   return cols <= 24 ? 0 : cols <= 96 ? 1 : cols <= 384 ? 2 : cols <= 3072 ? 3 : 4;
@@ -990,7 +995,7 @@ __host__ __device__ constexpr int sp_class(int cols) {
 // class from crp's row lengths, else from the B rows' total length; rows
 // without entries are in no list (cnt[i] = 0 for them before the count).
 template <bool COUNTED, int ROWS>
-__global__ void __launch_bounds__(256) k_spgemm_bin(int n, int max_cols,
+__global__ void __launch_bounds__(kSpBinWg) k_spgemm_bin(int n, int max_cols,
                                                     const int* __restrict__ arp,
                                                     const int* __restrict__ aci,
                                                     const int* __restrict__ brp,
@@ -1003,11 +1008,11 @@ __global__ void __launch_bounds__(256) k_spgemm_bin(int n, int max_cols,
   if (*err) return;  // an operand is malformed: empty lists, reported with the sizes
   if (threadIdx.x < kSpClasses) s_n[threadIdx.x] = 0;
   __syncthreads();
-  const int r0 = blockIdx.x * 256 * ROWS;
+  const int r0 = blockIdx.x * kSpBinWg * ROWS;
   int cls[ROWS], pos[ROWS];
 #pragma unroll
   for (int t = 0; t < ROWS; ++t) {
-    const int i = r0 + t * 256 + threadIdx.x;
+    const int i = r0 + t * kSpBinWg + threadIdx.x;
     cls[t] = -1;
     pos[t] = 0;
     if (i < n) {
@@ -1040,7 +1045,7 @@ __global__ void __launch_bounds__(256) k_spgemm_bin(int n, int max_cols,
 #pragma unroll
   for (int t = 0; t < ROWS; ++t)
     if (cls[t] >= 0)
-      lists[(size_t)cls[t] * n + s_base[cls[t]] + pos[t]] = r0 + t * 256 + threadIdx.x;
+      lists[(size_t)cls[t] * n + s_base[cls[t]] + pos[t]] = r0 + t * kSpBinWg + threadIdx.x;
 }
 
 // Between LDS accesses of one wave to places other lanes wrote: the hardware
@@ -1261,12 +1266,14 @@ static void spgemm_pass(Ctx* c, const Csr<double>& A, const Csr<double>& B, int 
   const int n = A.n_rows;
   fill<int>(c, count.get(), 0, kSpClasses);
   auto bin = [&](auto kernel, int rows) {
-    hipLaunchKernelGGL(kernel, dim3(cdiv(n, 256 * rows)), dim3(256), 0, c->stream, n, max_cols,
+    hipLaunchKernelGGL(kernel, dim3(cdiv(n, kSpBinWg * rows)), dim3(kSpBinWg), 0, c->stream, n, max_cols,
                        A.rp.get(), A.ci.get(), B.rp.get(), crp, FILL ? (int*)nullptr : cnt_or_cci,
                        lists.get(), count.get(), (const int*)c->err_flag());
     MGD_CHECK_LAUNCH();
   };
-  if (n < kSpBinManyFrom)
+  if (n < kSpBinFewFrom)
+    bin(k_spgemm_bin<FILL, 1>, 1);
+  else if (n < kSpBinManyFrom)
     bin(k_spgemm_bin<FILL, kSpBinFew>, kSpBinFew);
   else
     bin(k_spgemm_bin<FILL, kSpBinMany>, kSpBinMany);

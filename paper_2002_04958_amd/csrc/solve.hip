@@ -186,12 +186,14 @@ __global__ void k_u_len(int nC, int nS, RowRanges R, const UMember* __restrict__
 }
 
 // 64 x the longest row of every 64-row slice, and the longest row of all: one
-// wave per slice, at most kStatBlocks workgroups so that few of them meet in the
-// one maximum
-constexpr int kStatBlocks = 1024;
+// wave per slice.  What bounds it are the additions to the one maximum, about
+// 12 ns each one after the other: one per workgroup, of at most kStatBlocks, and
+// none that would not raise it.  One per wave of 1024 workgroups took 48 us at
+// 2^20 rows, this 5.6 us.
+constexpr int kStatBlocks = 512;
 __global__ void __launch_bounds__(256) k_row_stats(int rows, const int* __restrict__ rp,
-                                                   int* __restrict__ w64,
-                                                   int* __restrict__ longest) {
+                                                   int* __restrict__ w64, int* longest) {
+  __shared__ int s_most[4];
   int most = 0;
   const int ns = (rows + 63) / 64;
   for (int s = blockIdx.x * 4 + (threadIdx.x >> 6); s < ns; s += gridDim.x * 4) {
@@ -202,7 +204,14 @@ __global__ void __launch_bounds__(256) k_row_stats(int rows, const int* __restri
     if ((threadIdx.x & 63) == 0) w64[s] = 64 * m;
     most = max(most, m);
   }
-  if ((threadIdx.x & 63) == 0 && most > 0) atomicMax(longest, most);
+  if ((threadIdx.x & 63) == 0) s_most[threadIdx.x >> 6] = most;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    most = max(max(s_most[0], s_most[1]), max(s_most[2], s_most[3]));
+    // a value read late only costs an addition
+    if (most > __hip_atomic_load(longest, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicMax(longest, most);
+  }
 }
 
 // sizes of one level for the readback (slots may be absent)
