@@ -476,7 +476,7 @@ block_precond::~block_precond() {
   for (auto& kv : graphs)
     if (kv.second) hipGraphExecDestroy(kv.second);
   for (auto& kv : step_graphs)
-    if (kv.second) hipGraphExecDestroy(kv.second);
+    if (kv.second.exec) hipGraphExecDestroy(kv.second.exec);
   if (aux) hipStreamDestroy(aux);
   if (ev_in) hipEventDestroy(ev_in);
   if (ev_out) hipEventDestroy(ev_out);
@@ -1222,20 +1222,17 @@ void block_precond_apply_dispatch(block_precond* bp, const double* r, double* z)
   block_precond_graph_launch(bp, r, z);
 }
 
-template <typename Map>
-static void drop_graphs(Map& graphs) {
-  for (auto& kv : graphs)
-    if (kv.second) (void)hipGraphExecDestroy(kv.second);
-  graphs.clear();
-}
-
 // Direct launches on the first use of (r, z), a graph from the second on.
 void block_precond_graph_launch(block_precond* bp, const double* r, double* z) {
   Ctx* c = bp->ctx;
   auto key = std::make_pair((const void*)r, (void*)z);
   auto it = bp->graphs.find(key);
   if (it == bp->graphs.end()) {
-    if (bp->graphs.size() >= 256) drop_graphs(bp->graphs);
+    if (bp->graphs.size() >= 256) {
+      for (auto& kv : bp->graphs)
+        if (kv.second) (void)hipGraphExecDestroy(kv.second);
+      bp->graphs.clear();
+    }
     bp->graphs.emplace(key, nullptr);
     block_precond_apply_impl(bp, r, z);
     return;
@@ -1344,11 +1341,16 @@ bool block_precond_step_graphable(const block_precond* bp) {
 
 // Runs `body` (launches only, everything allocated beforehand, the apply in
 // its direct form) as one graph for `key`, which must hold every pointer and size
-// the launches use.  The first use of a key runs the launches themselves and the
-// second captures them: a preconditioner made for one solve, as in a loop whose
-// coefficients change, uses most keys once, and a step graph costs more to
-// instantiate and destroy (0.2 + 0.45 ms) than it saves once.  On the null stream the graph
-// runs on a private stream ordered after and before the caller's work.
+// the launches use.  The first kStepDirect uses of a key run the launches
+// themselves, the next one captures them: a step graph costs 0.2 + 0.45 ms to
+// instantiate and destroy, and a preconditioner made for one solve, as in a loop
+// whose coefficients change, uses a key once for every restart cycle its
+// iterations reach.  Captured at the second use a time step at 3D 64^3, G = 20 (38
+// iterations, 8 steps used twice) took 82.3 ms, at the fourth 78.2; solves with a
+// kept preconditioner were the same (2D 256^2 19.37 and 19.31 ms, 3D 64^3 55.7 and
+// 55.5).  On the null stream the graph runs on a private
+// stream ordered after and before the caller's work.
+constexpr int kStepDirect = 3;
 void block_precond_step_launch(block_precond* bp, const std::vector<uintptr_t>& key,
                                const std::function<void()>& body) {
   Ctx* c = bp->ctx;
@@ -1366,10 +1368,18 @@ void block_precond_step_launch(block_precond* bp, const std::vector<uintptr_t>& 
   try {
     auto it = bp->step_graphs.find(key);
     if (it == bp->step_graphs.end()) {
-      if (bp->step_graphs.size() >= 256) drop_graphs(bp->step_graphs);
-      bp->step_graphs.emplace(key, nullptr);
+      if (bp->step_graphs.size() >= 256) {
+        for (auto& kv : bp->step_graphs)
+          if (kv.second.exec) (void)hipGraphExecDestroy(kv.second.exec);
+        bp->step_graphs.clear();
+      }
+      it = bp->step_graphs.emplace(key, block_precond::StepGraph{}).first;
+    }
+    hipGraphExec_t& exec = it->second.exec;
+    if (it->second.uses < kStepDirect) {
+      ++it->second.uses;
       body();
-    } else if (!it->second) {
+    } else if (!exec) {
       hipGraph_t g = nullptr;
       MGD_HIP(hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed));
       try {
@@ -1380,12 +1390,12 @@ void block_precond_step_launch(block_precond* bp, const std::vector<uintptr_t>& 
         throw;
       }
       MGD_HIP(hipStreamEndCapture(c->stream, &g));
-      const hipError_t made = hipGraphInstantiate(&it->second, g, nullptr, nullptr, 0);
+      const hipError_t made = hipGraphInstantiate(&exec, g, nullptr, nullptr, 0);
       (void)hipGraphDestroy(g);
       MGD_HIP(made);
-      MGD_HIP(hipGraphLaunch(it->second, c->stream));
+      MGD_HIP(hipGraphLaunch(exec, c->stream));
     } else {
-      MGD_HIP(hipGraphLaunch(it->second, c->stream));
+      MGD_HIP(hipGraphLaunch(exec, c->stream));
     }
   } catch (...) {
     c->stream = user;

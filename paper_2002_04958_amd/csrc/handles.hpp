@@ -136,7 +136,11 @@ struct block_precond {
   std::map<std::pair<const void*, void*>, hipGraphExec_t> graphs;
   // whole flexible-GMRES steps (apply, matvec, Gram-Schmidt) keyed by every
   // pointer and size their launches use
-  std::map<std::vector<uintptr_t>, hipGraphExec_t> step_graphs;
+  struct StepGraph {
+    int uses = 0;  // launched directly so far
+    hipGraphExec_t exec = nullptr;
+  };
+  std::map<std::vector<uintptr_t>, StepGraph> step_graphs;
   // GMRES steps with Schur2: the block matvec of z overlaps the last E solve
   hipStream_t ovl_stream = nullptr;
   hipEvent_t ovl_fork = nullptr, ovl_join = nullptr;

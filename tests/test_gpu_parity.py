@@ -942,6 +942,26 @@ def test_first_use_launches_then_graphs_are_equal(ctx, kind, precision):
     assert all(np.array_equal(x, xs[0][0]) and i == xs[0][1] for x, i in xs)
 
 
+@pytest.mark.parametrize("kind,restart", [("schur2", 30), ("pctl", 4), ("bdiag", 30)])
+def test_step_graphs_after_direct_uses_are_equal(ctx, kind, restart):
+    """The first uses of a GMRES step launch directly, the next captures, later
+    ones replay; short restart cycles reach that inside one solve.  Every solve
+    gives the same bits, with other work and synchronisations between."""
+    import torch
+    api = gpu_modules()
+    inp = si.generate(3, 2, 20, 44)
+    co, gsys = gpu_system(ctx, inp)
+    M = api.BlockPreconditioner(ctx, gsys, kind, amg_seed=5, batched=1, use_graph=1)
+    Md = api.BlockPreconditioner(ctx, gsys, kind, amg_seed=5, batched=1, use_graph=0)
+    r = to_dev(ctx, inp.b)
+    xd, rd = api.gmres(ctx, gsys, Md, r, rtol=1e-9, restart=restart)
+    for _ in range(7):
+        x, res = api.gmres(ctx, gsys, M, r, rtol=1e-9, restart=restart)
+        assert res.converged and res.iters == rd.iters
+        assert np.array_equal(to_host(x), to_host(xd))
+        torch.cuda.synchronize()
+
+
 def test_gmres_no_preconditioner_and_nonflexible(ctx):
     api = gpu_modules()
     inp = si.generate(1, 2, 12, 5)
