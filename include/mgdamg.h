@@ -249,7 +249,8 @@ mgd_status mgd_block_system_free(mgd_ctx* ctx, mgd_block_system* s);
  * step (the group blocks, plus I where the step has it) as one set of
  * launches over all hierarchies; use_graph = 1 replays the whole apply from
  * a captured HIP graph (captured at the second use of the same r and z; the
- * first use launches directly), and GMRES steps from their fourth use on.  transpose = 1 builds the preconditioner on A^T.
+ * first use launches directly) and enqueues GMRES steps ahead of the readback
+ * of the one before.  transpose = 1 builds the preconditioner on A^T.
  *
  * adaptive = 1 (PCTL, SCHUR1, SCHUR2: the alpha-variants of Section 3.5)
  * forms the preconditioner from the system with its weak couplings

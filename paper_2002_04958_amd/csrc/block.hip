@@ -475,8 +475,6 @@ template struct Group<float>;
 block_precond::~block_precond() {
   for (auto& kv : graphs)
     if (kv.second) hipGraphExecDestroy(kv.second);
-  for (auto& kv : step_graphs)
-    if (kv.second.exec) hipGraphExecDestroy(kv.second.exec);
   if (aux) hipStreamDestroy(aux);
   if (ev_in) hipEventDestroy(ev_in);
   if (ev_out) hipEventDestroy(ev_out);
@@ -1259,7 +1257,7 @@ bool block_precond_has_first_stage(const block_precond* bp);
 
 // z = M^{-1} r, then y = A z for the system S.  With Schur2 and the shared
 // block pattern, the part of A z that does not read z_E runs on a second
-// stream beside the last E solve (launches only: usable under capture).
+// stream beside the last E solve.
 // first_done: w_E* for r was computed by block_precond_first_stage(bp, r).
 void block_precond_apply_matvec(block_precond* bp, const double* r, double* z,
                                 const BlockSysDev& S, double* y, bool first_done) {
@@ -1321,7 +1319,7 @@ void block_precond_first_stage(block_precond* bp, const double* r) {
 }
 
 // Stream and events that order the rest of a Gram-Schmidt update beside the
-// first stage of the next apply (created on first use, outside any capture).
+// first stage of the next apply (created on first use).
 void block_precond_side(block_precond* bp, hipStream_t* s, hipEvent_t* fork, hipEvent_t* join) {
   if (!bp->ovl_stream) MGD_HIP(hipStreamCreateWithFlags(&bp->ovl_stream, hipStreamNonBlocking));
   if (!bp->fs_fork) MGD_HIP(hipEventCreateWithFlags(&bp->fs_fork, hipEventDisableTiming));
@@ -1331,81 +1329,22 @@ void block_precond_side(block_precond* bp, hipStream_t* s, hipEvent_t* fork, hip
   *join = bp->fs_join;
 }
 
-// Whether a whole GMRES step with this preconditioner may run as one graph:
-// graph replay asked for, no host decisions inside the apply, no profiling.
-bool block_precond_step_graphable(const block_precond* bp) {
+// Whether GMRES steps with this preconditioner may be enqueued ahead of the
+// host's look at their coefficients: use_graph (as for the apply), no host
+// decisions inside the apply, no profiling.  The launches go out one by one.
+// Replaying a captured step was slower at every size, with kept preconditioners:
+// solves at 2D 32^2 G = 1 4.62 against 4.24 ms, 2D 100^2 G = 4 9.6 against 8.5,
+// 3D 20^3 G = 3 10.5 against 10.3 (FP64), 2D 200^2 G = 10 13.5 against 12.7, 2D
+// 256^2 G = 20 19.0 against 18.9, 3D 64^3 G = 20 45.9 against 45.0 (FP32
+// hierarchies); a step's graph cost 0.65 ms to instantiate and destroy, and on the
+// null stream it ran on a private one, two events a step.  With all of that gone
+// the last two take 17.1 instead of 19.2 and 49.2 instead of 51.3 ms, time steps at
+// 2D 100^2 G = 4 12.4 instead of 13.8, at 3D 64^3 G = 20 76.1 instead of 82.9 (in
+// turn, on another machine than the first figures).
+bool block_precond_steps_ahead(const block_precond* bp) {
   return bp->prm.use_graph && bp->prm.inner_tol <= 0 && !bp->ctx->profiling &&
          !bp->ctx->no_alloc &&
          bp->prm.kind != MGD_PC_IDENTITY;
-}
-
-// Runs `body` (launches only, everything allocated beforehand, the apply in
-// its direct form) as one graph for `key`, which must hold every pointer and size
-// the launches use.  The first kStepDirect uses of a key run the launches
-// themselves, the next one captures them: a step graph costs 0.2 + 0.45 ms to
-// instantiate and destroy, and a preconditioner made for one solve, as in a loop
-// whose coefficients change, uses a key once for every restart cycle its
-// iterations reach.  Captured at the second use a time step at 3D 64^3, G = 20 (38
-// iterations, 8 steps used twice) took 82.3 ms, at the fourth 78.2; solves with a
-// kept preconditioner were the same (2D 256^2 19.37 and 19.31 ms, 3D 64^3 55.7 and
-// 55.5).  On the null stream the graph runs on a private
-// stream ordered after and before the caller's work.
-constexpr int kStepDirect = 3;
-void block_precond_step_launch(block_precond* bp, const std::vector<uintptr_t>& key,
-                               const std::function<void()>& body) {
-  Ctx* c = bp->ctx;
-  const hipStream_t user = c->stream;
-  if (user == nullptr) {
-    if (!bp->aux) {
-      MGD_HIP(hipStreamCreateWithFlags(&bp->aux, hipStreamNonBlocking));
-      MGD_HIP(hipEventCreateWithFlags(&bp->ev_in, hipEventDisableTiming));
-      MGD_HIP(hipEventCreateWithFlags(&bp->ev_out, hipEventDisableTiming));
-    }
-    MGD_HIP(hipEventRecord(bp->ev_in, user));
-    MGD_HIP(hipStreamWaitEvent(bp->aux, bp->ev_in, 0));
-    c->stream = bp->aux;
-  }
-  try {
-    auto it = bp->step_graphs.find(key);
-    if (it == bp->step_graphs.end()) {
-      if (bp->step_graphs.size() >= 256) {
-        for (auto& kv : bp->step_graphs)
-          if (kv.second.exec) (void)hipGraphExecDestroy(kv.second.exec);
-        bp->step_graphs.clear();
-      }
-      it = bp->step_graphs.emplace(key, block_precond::StepGraph{}).first;
-    }
-    hipGraphExec_t& exec = it->second.exec;
-    if (it->second.uses < kStepDirect) {
-      ++it->second.uses;
-      body();
-    } else if (!exec) {
-      hipGraph_t g = nullptr;
-      MGD_HIP(hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed));
-      try {
-        body();
-      } catch (...) {
-        hipStreamEndCapture(c->stream, &g);
-        if (g) hipGraphDestroy(g);
-        throw;
-      }
-      MGD_HIP(hipStreamEndCapture(c->stream, &g));
-      const hipError_t made = hipGraphInstantiate(&exec, g, nullptr, nullptr, 0);
-      (void)hipGraphDestroy(g);
-      MGD_HIP(made);
-      MGD_HIP(hipGraphLaunch(exec, c->stream));
-    } else {
-      MGD_HIP(hipGraphLaunch(exec, c->stream));
-    }
-  } catch (...) {
-    c->stream = user;
-    throw;
-  }
-  if (user == nullptr) {
-    c->stream = user;
-    MGD_HIP(hipEventRecord(bp->ev_out, bp->aux));
-    MGD_HIP(hipStreamWaitEvent(user, bp->ev_out, 0));
-  }
 }
 
 static void copy_system(block_precond* bp, const mgd_block_system* A) {

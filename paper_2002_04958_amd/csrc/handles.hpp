@@ -134,13 +134,6 @@ struct block_precond {
   std::unique_ptr<mgd::PcExec<float>> x32;
   // graph cache keyed by (r, z); null after the first use, which launches directly
   std::map<std::pair<const void*, void*>, hipGraphExec_t> graphs;
-  // whole flexible-GMRES steps (apply, matvec, Gram-Schmidt) keyed by every
-  // pointer and size their launches use
-  struct StepGraph {
-    int uses = 0;  // launched directly so far
-    hipGraphExec_t exec = nullptr;
-  };
-  std::map<std::vector<uintptr_t>, StepGraph> step_graphs;
   // GMRES steps with Schur2: the block matvec of z overlaps the last E solve
   hipStream_t ovl_stream = nullptr;
   hipEvent_t ovl_fork = nullptr, ovl_join = nullptr;

@@ -43,9 +43,7 @@ void block_precond_apply_matvec(block_precond* bp, const double* r, double* z,
 bool block_precond_has_first_stage(const block_precond* bp);
 void block_precond_first_stage(block_precond* bp, const double* r);
 void block_precond_side(block_precond* bp, hipStream_t* s, hipEvent_t* fork, hipEvent_t* join);
-bool block_precond_step_graphable(const block_precond* bp);
-void block_precond_step_launch(block_precond* bp, const std::vector<uintptr_t>& key,
-                               const std::function<void()>& body);
+bool block_precond_steps_ahead(const block_precond* bp);
 
 // Workspace of gmres_solve_noalloc: a static device array, one copy per
 // device, shared by every such call on that device (the contents of the last
@@ -220,7 +218,7 @@ mgd_status gmres_impl(Ctx* c, const BlockSysDev& S, block_precond* M, const doub
   }
   std::vector<double> H((size_t)(m + 1) * m), cs(m), sn(m), g(m + 1), y(m);
   double r_last = 0.0, r_prev = 0.0;  // residual estimates of the last two steps
-  int launched = -1;     // graph-replayed steps enqueued in this cycle
+  int launched = -1;     // steps enqueued ahead in this cycle
   auto Hij = [&](int i, int j) -> double& { return H[(size_t)i * m + j]; };
   // Flexible GMRES with a preconditioner keeps the unrotated Hessenberg
   // matrix: the delayed reorthogonalisation completes each column one step
@@ -230,36 +228,21 @@ mgd_status gmres_impl(Ctx* c, const BlockSysDev& S, block_precond* M, const doub
   auto Hu = [&](int i, int j) -> double& { return Hunrot[(size_t)i * m + j]; };
   DBuf<double>& dd = ws.dd;
   DBuf<double>& dcoef = ws.dcoef;
-  // With graph replay a step runs as one graph (no per-step events then)
-  const bool step_graph = delayed && !p.profile && block_precond_step_graphable(M);
-  std::vector<uintptr_t> sys_key;
-  // Where the apply starts with w_E* = A_E^{-1} r_E, each step graph ends by
+  // Steps enqueued ahead of the host's look at their coefficients (no per-step
+  // events then)
+  const bool ahead = delayed && !p.profile && block_precond_steps_ahead(M);
+  // Where the apply starts with w_E* = A_E^{-1} r_E, each such step ends by
   // computing it for the next basis vector beside the rest of its update
   // sweep (the E segment of the sweep first), and the next step skips it.
-  const bool early_E = step_graph && block_precond_has_first_stage(M);
+  const bool early_E = ahead && block_precond_has_first_stage(M);
   DcgsSplit split;
   if (early_E) {
     block_precond_side(M, &split.side, &split.fork, &split.join);
     split.lo = (size_t)S.G * S.N;
     split.hi = split.lo + S.N;
   }
-  if (step_graph) {
-    rw.ensure(c);  // nothing may be allocated inside a capture
-    sys_key = {(uintptr_t)S.G, (uintptr_t)S.N, (uintptr_t)S.tpr, (uintptr_t)S.shared,
-               (uintptr_t)S.d_gE, (uintptr_t)S.d_Eg, (uintptr_t)S.d_EI, (uintptr_t)S.d_IE};
-    for (int a = 0; a < S.G + 2; ++a) {
-      sys_key.push_back((uintptr_t)S.blk[a].rp);
-      sys_key.push_back((uintptr_t)S.blk[a].ci);
-      sys_key.push_back((uintptr_t)S.blk[a].v);
-    }
-    sys_key.push_back((uintptr_t)S.sym);  // the half storage, when attached
-    if (S.sym) {
-      sys_key.push_back((uintptr_t)S.sym_urp);
-      sys_key.push_back((uintptr_t)S.sym_src);
-      for (int a = 0; a < S.G + 2; ++a) sys_key.push_back((uintptr_t)S.sym_v[a]);
-    }
-  }
-  // Enqueue graph-replayed step jj (z = M^{-1} v_jj, w = A z, the Gram-Schmidt
+  if (ahead) rw.ensure(c);
+  // Enqueue step jj (z = M^{-1} v_jj, w = A z, the Gram-Schmidt
   // step) and the readback of its coefficients into pinned slot jj % 2.
   auto launch_step = [&](int jj) {
     double* vjj = V.get() + (size_t)jj * n;
@@ -270,18 +253,11 @@ mgd_status gmres_impl(Ctx* c, const BlockSysDev& S, block_precond* M, const doub
     // step jj-1 of this cycle computed w_E* for v_jj; step m-1 skips it for v_m
     const bool done = early_E && jj >= 1;
     const bool next = early_E && jj + 1 < m;
-    std::vector<uintptr_t> key = sys_key;
-    for (uintptr_t v : {(uintptr_t)vjj, (uintptr_t)zt, (uintptr_t)wj, (uintptr_t)V.get(),
-                        (uintptr_t)n, (uintptr_t)F, (uintptr_t)dd.get(), (uintptr_t)dcoef.get(),
-                        (uintptr_t)rw.partial.get(), (uintptr_t)done, (uintptr_t)next})
-      key.push_back(v);
-    block_precond_step_launch(M, key, [&] {
-      block_precond_apply_matvec(M, vjj, zt, S, wj, done);
-      if (next) split.beside = [&] { block_precond_first_stage(M, wj); };
-      dcgs_step_dev(c, rw, V.get(), n, F, prov ? vjj : nullptr, wj, n, dd.get(), dcoef.get(),
-                    next ? &split : nullptr);
-      split.beside = nullptr;
-    });
+    block_precond_apply_matvec(M, vjj, zt, S, wj, done);
+    if (next) split.beside = [&] { block_precond_first_stage(M, wj); };
+    dcgs_step_dev(c, rw, V.get(), n, F, prov ? vjj : nullptr, wj, n, dd.get(), dcoef.get(),
+                  next ? &split : nullptr);
+    split.beside = nullptr;
     MGD_HIP(hipMemcpyAsync(slot(jj), dcoef.get(), kDcgsCoef * sizeof(double),
                            hipMemcpyDeviceToHost, c->stream));
     MGD_HIP(hipEventRecord(ws.ev[jj & 1], c->stream));
@@ -303,7 +279,7 @@ mgd_status gmres_impl(Ctx* c, const BlockSysDev& S, block_precond* M, const doub
       double* vj = V.get() + (size_t)j * n;
       double* w = V.get() + (size_t)(j + 1) * n;
       const double* zj = vj;
-      if (delayed && step_graph) {
+      if (delayed && ahead) {
         if (launched < j) launch_step(j);
         // Enqueue step j+1 before waiting for this step's coefficients: it
         // needs only v_{j+1}, which this step writes, so the GPU works on it
@@ -317,7 +293,7 @@ mgd_status gmres_impl(Ctx* c, const BlockSysDev& S, block_precond* M, const doub
       } else if (M) {
         double* zt = flex ? Z.get() + (size_t)j * n : t1.get();
         if (evp) MGD_HIP(hipEventRecord(evp->a, c->stream));
-        if (delayed && !p.profile)  // the launches a graph-replayed step runs
+        if (delayed && !p.profile)  // the launches a step enqueued ahead runs
           block_precond_apply_matvec(M, vj, zt, S, w);
         else
           block_precond_apply_dispatch(M, vj, zt);
@@ -325,7 +301,7 @@ mgd_status gmres_impl(Ctx* c, const BlockSysDev& S, block_precond* M, const doub
         res.precond_applies++;
         zj = zt;
       }
-      if (!(delayed && (step_graph || !p.profile))) {
+      if (!(delayed && (ahead || !p.profile))) {
         if (evm) MGD_HIP(hipEventRecord(evm->a, c->stream));
         block_matvec(c, S, zj, nullptr, w);
         if (evm) MGD_HIP(hipEventRecord(evm->b, c->stream));
@@ -337,13 +313,13 @@ mgd_status gmres_impl(Ctx* c, const BlockSysDev& S, block_precond* M, const doub
         // completed here (v_j = V a + beta v_j_new), then this column.
         const bool prov = j >= 1;
         const int F = prov ? j : 1;
-        if (!step_graph) {
+        if (!ahead) {
           if (evo) MGD_HIP(hipEventRecord(evo->a, c->stream));
           dcgs_step_dev(c, rw, V.get(), n, F, prov ? vj : nullptr, w, n, dd.get(), dcoef.get());
           if (evo) MGD_HIP(hipEventRecord(evo->b, c->stream));
         }
         const double* hb = hbuf;
-        if (step_graph) {
+        if (ahead) {
           hb = slot(j);
           MGD_HIP(hipEventSynchronize(ws.ev[j & 1]));
         } else {
@@ -364,7 +340,7 @@ mgd_status gmres_impl(Ctx* c, const BlockSysDev& S, block_precond* M, const doub
           // (not when the next step is already under way with it: that step's
           // dots use its actual norm, and the relation stays exact)
           const double nv = std::sqrt(hb[66]);
-          if (!step_graph && !(std::fabs(nv - 1.0) <= 1e-6) && nv > 0.0) {
+          if (!ahead && !(std::fabs(nv - 1.0) <= 1e-6) && nv > 0.0) {
             scale_dev(c, 1.0 / nv, vj, n);
             Hu(j, j - 1) *= nv;
             hF *= nv;
@@ -374,11 +350,11 @@ mgd_status gmres_impl(Ctx* c, const BlockSysDev& S, block_precond* M, const doub
         if (prov) Hu(j, j) = hF;
         double al = hb[65];
         const double ex = std::sqrt(hb[67]);
-        if (!step_graph && !(std::fabs(ex - al) <= 1e-6 * ex)) {
+        if (!ahead && !(std::fabs(ex - al) <= 1e-6 * ex)) {
           if (ex > 0.0) scale_dev(c, al / ex, w, n);
           al = ex;
         }
-        if (step_graph && !(ex > 0.0)) al = 0.0;  // w' vanished: breakdown
+        if (ahead && !(ex > 0.0)) al = 0.0;  // w' vanished: breakdown
         Hu(j + 1, j) = al;
         alpha_prev = al;
         breakdown = al == 0.0;

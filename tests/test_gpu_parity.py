@@ -943,10 +943,10 @@ def test_first_use_launches_then_graphs_are_equal(ctx, kind, precision):
 
 
 @pytest.mark.parametrize("kind,restart", [("schur2", 30), ("pctl", 4), ("bdiag", 30)])
-def test_step_graphs_after_direct_uses_are_equal(ctx, kind, restart):
-    """The first uses of a GMRES step launch directly, the next captures, later
-    ones replay; short restart cycles reach that inside one solve.  Every solve
-    gives the same bits, with other work and synchronisations between."""
+def test_solves_with_steps_ahead_are_equal(ctx, kind, restart):
+    """Steps of a use_graph preconditioner are enqueued ahead of the host's look at
+    their coefficients.  Every solve with it gives the bits of one without, with
+    other work and synchronisations between."""
     import torch
     api = gpu_modules()
     inp = si.generate(3, 2, 20, 44)
