@@ -247,10 +247,10 @@ mgd_status mgd_block_system_free(mgd_ctx* ctx, mgd_block_system* s);
  * 3.4): cycles_rad for group blocks, cycles_E for E blocks (and A_c),
  * cycles_I for I blocks.  batched = 1 applies the independent V-cycles of a
  * step (the group blocks, plus I where the step has it) as one set of
- * launches over all hierarchies; use_graph = 1 replays the whole apply from
- * a captured HIP graph (captured at the second use of the same r and z; the
- * first use launches directly) and enqueues GMRES steps ahead of the readback
- * of the one before.  transpose = 1 builds the preconditioner on A^T.
+ * launches over all hierarchies; use_graph = 1 enqueues each GMRES step ahead
+ * of the readback of the one before (the option's name is from a time when
+ * steps and applies were replayed as HIP graphs, which was slower).
+ * transpose = 1 builds the preconditioner on A^T.
  *
  * adaptive = 1 (PCTL, SCHUR1, SCHUR2: the alpha-variants of Section 3.5)
  * forms the preconditioner from the system with its weak couplings
@@ -388,7 +388,7 @@ mgd_status gmres_solve(mgd_ctx* ctx, const mgd_block_system* A, block_precond* M
  * n = (G+2) N, m = restart.  Sizes that do not fit return MGD_EINVAL before
  * any launch (with m = 30 and a flexible preconditioned solve, up to about
  * 137,000 unknowns); profile = 1 returns MGD_EINVAL.  Preconditioner applies
- * run as direct launches (a use_graph preconditioner is not replayed here)
+ * and steps wait for the readback of the one before (use_graph is ignored)
  * and the whole solve stays on the context stream.  Every call on one device
  * shares that device's array and leaves its contents behind: calls that
  * overlap on one device race, so run them on one stream or one at a time.

@@ -473,11 +473,6 @@ template struct Group<float>;
 // block_precond
 // ===========================================================================
 block_precond::~block_precond() {
-  for (auto& kv : graphs)
-    if (kv.second) hipGraphExecDestroy(kv.second);
-  if (aux) hipStreamDestroy(aux);
-  if (ev_in) hipEventDestroy(ev_in);
-  if (ev_out) hipEventDestroy(ev_out);
   if (ovl_stream) hipStreamDestroy(ovl_stream);
   if (ovl_fork) hipEventDestroy(ovl_fork);
   if (ovl_join) hipEventDestroy(ovl_join);
@@ -1179,78 +1174,12 @@ static void apply_impl(block_precond* bp, PcExec<T>& X, const double* r, double*
   bp->matvecs_last = nmv;
 }
 
-void block_precond_graph_launch(block_precond* bp, const double* r, double* z);
 
 void block_precond_apply_impl(block_precond* bp, const double* r, double* z) {
   if (bp->prm.amg.precision == 1 && bp->prm.kind != MGD_PC_IDENTITY)
     apply_impl<float>(bp, *bp->x32, r, z);
   else
     apply_impl<double>(bp, *bp->x64, r, z);
-}
-
-void block_precond_apply_dispatch(block_precond* bp, const double* r, double* z) {
-  Ctx* c = bp->ctx;
-  if (!bp->prm.use_graph || c->profiling || c->no_alloc || bp->prm.inner_tol > 0) {
-    block_precond_apply_impl(bp, r, z);
-    return;
-  }
-  // Capture and replay need a real stream: on the null stream the graph runs
-  // on a private non-blocking stream ordered after and before the caller's.
-  const hipStream_t user = c->stream;
-  if (user == nullptr) {
-    if (!bp->aux) {
-      MGD_HIP(hipStreamCreateWithFlags(&bp->aux, hipStreamNonBlocking));
-      MGD_HIP(hipEventCreateWithFlags(&bp->ev_in, hipEventDisableTiming));
-      MGD_HIP(hipEventCreateWithFlags(&bp->ev_out, hipEventDisableTiming));
-    }
-    MGD_HIP(hipEventRecord(bp->ev_in, user));
-    MGD_HIP(hipStreamWaitEvent(bp->aux, bp->ev_in, 0));
-    c->stream = bp->aux;
-    try {
-      block_precond_graph_launch(bp, r, z);
-    } catch (...) {
-      c->stream = user;
-      throw;
-    }
-    c->stream = user;
-    MGD_HIP(hipEventRecord(bp->ev_out, bp->aux));
-    MGD_HIP(hipStreamWaitEvent(user, bp->ev_out, 0));
-    return;
-  }
-  block_precond_graph_launch(bp, r, z);
-}
-
-// Direct launches on the first use of (r, z), a graph from the second on.
-void block_precond_graph_launch(block_precond* bp, const double* r, double* z) {
-  Ctx* c = bp->ctx;
-  auto key = std::make_pair((const void*)r, (void*)z);
-  auto it = bp->graphs.find(key);
-  if (it == bp->graphs.end()) {
-    if (bp->graphs.size() >= 256) {
-      for (auto& kv : bp->graphs)
-        if (kv.second) (void)hipGraphExecDestroy(kv.second);
-      bp->graphs.clear();
-    }
-    bp->graphs.emplace(key, nullptr);
-    block_precond_apply_impl(bp, r, z);
-    return;
-  }
-  if (!it->second) {
-    hipGraph_t g = nullptr;
-    MGD_HIP(hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed));
-    try {
-      block_precond_apply_impl(bp, r, z);
-    } catch (...) {
-      hipStreamEndCapture(c->stream, &g);
-      if (g) hipGraphDestroy(g);
-      throw;
-    }
-    MGD_HIP(hipStreamEndCapture(c->stream, &g));
-    const hipError_t made = hipGraphInstantiate(&it->second, g, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(g);
-    MGD_HIP(made);
-  }
-  MGD_HIP(hipGraphLaunch(it->second, c->stream));
 }
 
 bool block_precond_has_first_stage(const block_precond* bp);
@@ -1330,17 +1259,17 @@ void block_precond_side(block_precond* bp, hipStream_t* s, hipEvent_t* fork, hip
 }
 
 // Whether GMRES steps with this preconditioner may be enqueued ahead of the
-// host's look at their coefficients: use_graph (as for the apply), no host
-// decisions inside the apply, no profiling.  The launches go out one by one.
-// Replaying a captured step was slower at every size, with kept preconditioners:
-// solves at 2D 32^2 G = 1 4.62 against 4.24 ms, 2D 100^2 G = 4 9.6 against 8.5,
-// 3D 20^3 G = 3 10.5 against 10.3 (FP64), 2D 200^2 G = 10 13.5 against 12.7, 2D
-// 256^2 G = 20 19.0 against 18.9, 3D 64^3 G = 20 45.9 against 45.0 (FP32
-// hierarchies); a step's graph cost 0.65 ms to instantiate and destroy, and on the
-// null stream it ran on a private one, two events a step.  With all of that gone
-// the last two take 17.1 instead of 19.2 and 49.2 instead of 51.3 ms, time steps at
-// 2D 100^2 G = 4 12.4 instead of 13.8, at 3D 64^3 G = 20 76.1 instead of 82.9 (in
-// turn, on another machine than the first figures).
+// host's look at their coefficients: use_graph, no host
+// decisions inside the apply, no profiling.
+//
+// Applies and steps are launched one by one.  As graphs, on a private stream when
+// the caller's was the null stream, both were slower at every size, in us per
+// PCTL, Schur2 and block-diagonal apply of a kept preconditioner: 2D 32^2 G = 1
+// 122, 106, 53 replayed against 85, 72, 24; 2D 100^2 G = 4 276, 236, 104 against
+// 209, 181, 69; 2D 256^2 G = 20 560, 434, 250 against 485, 370, 205; 3D 64^3 G =
+// 10 1035, 891, 628 against 948, 817, 583.  Solves with FP32 hierarchies took 19.2
+// against 17.1 ms at 2D 256^2 G = 20, 51.3 against 49.2 at 3D 64^3 G = 20, and a
+// graph cost 0.65 ms to instantiate and destroy.
 bool block_precond_steps_ahead(const block_precond* bp) {
   return bp->prm.use_graph && bp->prm.inner_tol <= 0 && !bp->ctx->profiling &&
          !bp->ctx->no_alloc &&

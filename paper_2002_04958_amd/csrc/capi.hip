@@ -14,7 +14,7 @@ using namespace mgd;
 
 // implemented in other translation units
 block_precond* block_precond_create_impl(Ctx* c, const mgd_block_system* A, const block_params* p);
-void block_precond_apply_dispatch(block_precond* bp, const double* r, double* z);
+void block_precond_apply_impl(block_precond* bp, const double* r, double* z);
 mgd_status gmres_impl(Ctx* c, const BlockSysDev& S, block_precond* M, const double* b, double* x,
                       const gmres_params& p, gmres_result& res);
 void assemble_impl(Ctx* c, const mgd_coeffs* cf, mgd_block_system* out);
@@ -817,7 +817,7 @@ mgd_status block_precond_apply(mgd_ctx* ctx, block_precond* M, const double* r, 
     MGD_REQUIRE(M->ctx == ctx, "preconditioner belongs to another context");
     MGD_REQUIRE(r && z && (const void*)r != (const void*)z, "r, z must be distinct and non-NULL");
     ctx->make_current();
-    block_precond_apply_dispatch(M, r, z);
+    block_precond_apply_impl(M, r, z);
     return MGD_OK;
   });
 }

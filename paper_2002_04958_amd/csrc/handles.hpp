@@ -132,8 +132,6 @@ struct block_precond {
   std::vector<int> inner_cycles;
   std::unique_ptr<mgd::PcExec<double>> x64;
   std::unique_ptr<mgd::PcExec<float>> x32;
-  // graph cache keyed by (r, z); null after the first use, which launches directly
-  std::map<std::pair<const void*, void*>, hipGraphExec_t> graphs;
   // GMRES steps with Schur2: the block matvec of z overlaps the last E solve
   hipStream_t ovl_stream = nullptr;
   hipEvent_t ovl_fork = nullptr, ovl_join = nullptr;
@@ -146,8 +144,6 @@ struct block_precond {
   // first_stage: 0 whole apply, 1 only that solve, 2 the apply without it
   hipEvent_t fs_fork = nullptr, fs_join = nullptr;
   int first_stage = 0;
-  hipStream_t aux = nullptr;  // graph stream when the context stream is the null stream
-  hipEvent_t ev_in = nullptr, ev_out = nullptr;
   int inverses_last = 0, matvecs_last = 0;
   double setup_ms = 0;
   ~block_precond();

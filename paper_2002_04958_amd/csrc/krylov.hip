@@ -18,8 +18,6 @@
 
 using namespace mgd;
 
-void block_precond_apply_dispatch(block_precond* bp, const double* r, double* z);
-
 struct EvPair {
   hipEvent_t a = nullptr, b = nullptr;
   EvPair() {
@@ -296,7 +294,7 @@ mgd_status gmres_impl(Ctx* c, const BlockSysDev& S, block_precond* M, const doub
         if (delayed && !p.profile)  // the launches a step enqueued ahead runs
           block_precond_apply_matvec(M, vj, zt, S, w);
         else
-          block_precond_apply_dispatch(M, vj, zt);
+          block_precond_apply_impl(M, vj, zt);
         if (evp) MGD_HIP(hipEventRecord(evp->b, c->stream));
         res.precond_applies++;
         zj = zt;
@@ -444,7 +442,7 @@ mgd_status gmres_impl(Ctx* c, const BlockSysDev& S, block_precond* M, const doub
     } else {
       fill<double>(c, t1.get(), 0.0, n);
       combine_dev(c, V.get(), n, k, yd, t1.get(), n);
-      block_precond_apply_dispatch(M, t1.get(), t2.get());
+      block_precond_apply_impl(M, t1.get(), t2.get());
       res.precond_applies++;
       axpy(c, x, t2.get(), 1.0, n);
     }
