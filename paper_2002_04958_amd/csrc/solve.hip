@@ -2961,15 +2961,18 @@ static void bot_program(const BotLevel* lev, int n, int n_pre, int n_post, int t
 // Schur2 303, 197, 203, 170, 169; 3D 20^3 G = 3 Schur2 447, 486, 335, 329, 347
 // (its 300-row bottom has one short level); batched 2D 256^2 G = 20 PCTL 644, 589,
 // 588, 561, 561.  Above 2048 rows a matrix outgrows LDS and 16 rows a lane would
-// be in sequence.  The limit on entries (2048 rows: 8192, 16384, 32768 and 65536
-// of them) gave 580, 513, 509, 507 on the first of these, and 20.6, 19.8, 19.3,
-// 19.2 ms on a solve at 2D 256^2, G = 20.
+// be in sequence.  A matrix is limited to what LDS could hold (values and 16-bit
+// columns): past it one compute unit reads it from L2 four times a cycle.  With
+// limits of 2^14 (FP64's, nearly), 2^15 and 2^16 entries FP64 applies of one hierarchy with long rows took 176, 174 and 187
+// us (2D 101^2 G = 20), 360, 379 and 379 us (3D 46^3 G = 6; 355 with launches), on
+// the first of the cases above 504, 500 and 500, an FP32 solve at 2D 256^2 G = 20
+// 18.7, 18.6 and 18.6 ms.
 // While the finest level leaves compute units free beside a concurrent block
 // matvec (one workgroup per 512 rows), a member takes a whole unit; above that,
 // 512 threads and 110 KB, which fit beside a workgroup of the matvec.
 constexpr long long kBotWholeRows = 512 * 192;
 constexpr unsigned kBotLdsWhole = 150 * 1024, kBotLdsShared = 110 * 1024;
-constexpr int kBotEntries = 1 << 16;  // stored entries of a matrix and member
+constexpr long long kBotMatrix = 160 * 1024;  // bytes of a matrix and member
 constexpr int kBotDenseRows = 256;  // larger dense levels are spread over workgroups
 
 // places of the members in a level's extended stored order
@@ -3044,7 +3047,7 @@ static void build_bottom(Ctx* c, std::vector<BuildLevel<T>>& bl, const std::vect
     bool ok = true;
     for (int q = 0; q < nm; ++q) {
       const UMember& m = tab[bl[lt - 1].tab + q];
-      for (int mat = 0; mat < 3; ++mat) ok = ok && 64 * stored(lt - 1, q, mat) <= kBotEntries;
+      for (int mat = 0; mat < 3; ++mat) ok = ok && 64LL * stored(lt - 1, q, mat) * (long long)(sizeof(T) + 2) <= kBotMatrix;
       ok = ok && (m.kind != 2 || m.n <= kBotDenseRows);
     }
     if (!ok) break;
