@@ -86,6 +86,21 @@ void* Ctx::dmalloc(size_t bytes) {
                          std::to_string(bytes) + (has_alloc ? " bytes" : " bytes failed"));
   return p;
 }
+hipError_t Ctx::drain() {
+  std::vector<void*> d;
+  {
+    std::lock_guard<std::mutex> lock(pool.mu);
+    d.swap(dead);
+  }
+  const hipError_t e = hipStreamSynchronize(stream);
+  if (e != hipSuccess) {  // nothing is known to have finished
+    std::lock_guard<std::mutex> lock(pool.mu);
+    dead.insert(dead.end(), d.begin(), d.end());
+    return e;
+  }
+  for (void* p : d) release(p);
+  return e;
+}
 void Ctx::free_dead() {
   std::vector<void*> d;
   {

@@ -147,11 +147,12 @@ struct Ctx {
   void release(void* p);          // to its chunk, or to the allocator
   void pool_trim();               // empty chunks back to the allocator
   void* host_stage(size_t bytes);  // pinned buffer of at least `bytes`
-  void sync() {
-    MGD_HIP(hipStreamSynchronize(stream));
-    free_dead();
-  }
-  void free_dead();
+  void sync() { MGD_HIP(drain()); }
+  // Waits for the stream and releases what was held back before the wait: a
+  // buffer another thread lets go while this one waits may still be in use by
+  // work enqueued after the wait began, and stays held.
+  hipError_t drain();
+  void free_dead();  // everything held back; the stream is idle
   void make_current() { MGD_HIP(hipSetDevice(device)); }
   int* err_flag();                           // device int, zero until a check fails
   void check_device_errors(const char* where);  // synchronises; throws when set
@@ -182,10 +183,7 @@ struct DeferFrees {
       std::lock_guard<std::mutex> lock(c->pool.mu);
       left = !c->dead.empty();
     }
-    if (left) {
-      (void)hipStreamSynchronize(c->stream);
-      c->free_dead();
-    }
+    if (left) (void)c->drain();
     c->pool_trim();
   }
 };
