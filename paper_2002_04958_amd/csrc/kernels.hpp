@@ -10,9 +10,12 @@ constexpr int kBlock = 256;     // default workgroup size (4 wavefronts of 64)
 constexpr int kRedBlocks = 1024; // fixed partial count of deterministic reductions
 
 // ---- scans (int32) -----------------------------------------------------------
-// out[0..n]: out[i] = sum_{j<i} in[j], out[n] = total.  No synchronisation.
+// out[0..n]: out[i] = sum_{j<i} in[j], out[n] = total, of values >= 0.  Where int32
+// cannot hold the total, out[n] = kScanTooLarge and nothing else in out may be
+// used.  No synchronisation inside a DeferFrees scope.
+constexpr int kScanTooLarge = -1;
 void exclusive_scan(Ctx* c, const int* in, int* out, int n);
-// Same, then returns the total (synchronises).
+// Same, then returns the total (synchronises); MGD_EINVAL where it is too large.
 int exclusive_scan_total(Ctx* c, const int* in, int* out, int n);
 
 // ---- fills / casts ---------------------------------------------------------

@@ -201,7 +201,7 @@ __global__ void __launch_bounds__(256) k_row_stats(int rows, const int* __restri
     int m = k < rows ? rp[k + 1] - rp[k] : 0;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) m = max(m, __shfl_xor(m, off, 64));
-    if ((threadIdx.x & 63) == 0) w64[s] = 64 * m;
+    if ((threadIdx.x & 63) == 0) w64[s] = (int)min(64LL * m, (long long)INT_MAX);
     most = max(most, m);
   }
   if ((threadIdx.x & 63) == 0) s_most[threadIdx.x >> 6] = most;
@@ -2722,7 +2722,8 @@ __global__ void k_sell16_check(int rows, int ncols, const int* __restrict__ rp,
 }
 
 // Longest row (longest[0]) and SELL layout of a CSR structure: slice widths in
-// w64, slice offsets in soff, the stored entries with padding in longest[1].
+// w64, slice offsets in soff, the stored entries with padding in longest[1]
+// (kScanTooLarge where int32 cannot hold them: soff is of no use then).
 static void row_stats(Ctx* c, int rows, const int* rp, DBuf<int>& w64, DBuf<int>& soff,
                       int* longest) {
   if (rows <= 0) return;
@@ -2775,7 +2776,9 @@ static void to_layout(Ctx* c, const Csr<double>& M, int fmt, int tpr, bool self_
                      (const int*)M.rp.get(), (const int*)M.ci.get(), split16, sell16_span(),
                      (const int*)out.rp.get(), rp4.get(), units.get());
   MGD_CHECK_LAUNCH();
-  const long long total = exclusive_scan_total(c, units.get(), coff.get(), ns);
+  exclusive_scan(c, units.get(), coff.get(), ns);
+  const long long total = read1(c, coff.get() + ns);
+  if (total < 0) return;  // codes past int32: the 32-bit columns stay
   hipLaunchKernelGGL(k_sell16_coff, dim3(cdiv(ns + 1, 256)), dim3(256), 0, c->stream, ns,
                      (const int*)coff.get(), rp4.get());
   MGD_CHECK_LAUNCH();
@@ -2834,6 +2837,9 @@ static int small_level_tpr(long long rows, double avg) {
 // hierarchies and 66.9, 62.2, 61.9, 61.9, 61.8 ms with FP64, at 3D 80^3, G = 2
 // 32.6, 31.8, 31.8, 31.8, 31.8 ms; 2D 256^2 and 512^2 were the same throughout.
 constexpr double kSellPad = 1.5;
+// entries of a SELL layout; one that int32 cannot index is more than any limit
+constexpr long long kSellTooLarge = 1LL << 62;
+static long long sell_entries_of(int stat) { return stat < 0 ? kSellTooLarge : stat; }
 // interpolation / restriction layout: SELL for large matrices with little
 // padding (sell_entries: the SELL layout's stored entries), otherwise CSR with
 // enough lanes per row; the result is kTuneSell (1000) or the lanes per row
@@ -3261,7 +3267,7 @@ static void layout_levels(Ctx* c, std::vector<BuildLevel<T>>& bl, const int* sta
     if (lv.nX_next > 0) {
       // W gathers from three regions of the next level: 32-bit columns;
       // W^T's columns are F indices, one region
-      layout_transfer<T>(c, b.W, lv.W, b.wsoff, s6[3], -1);
+      layout_transfer<T>(c, b.W, lv.W, b.wsoff, sell_entries_of(s6[3]), -1);
       tune_restrict<T>(c, lv, b, s6 + 4, lv.Wt, autotune, sizeof(T) == 4);
     }
     tune_layout<T>(c, lv, b, s6, autotune, sizeof(T) == 4);
@@ -3367,7 +3373,7 @@ static void tune_layout(Ctx* c, ULevel<T>& lv, const BuildLevel<T>& b, const int
   }
   const int maxrow = stat[0];
   const double avg = (double)A.nnz / lv.nS;
-  const long long st = stat[1];
+  const long long st = sell_entries_of(stat[1]);
   auto apply = [&](int value) {
     const int code = value % kTuneBsUnit, units = value / kTuneBsUnit;
     if (code == kTuneSell)
@@ -3377,7 +3383,7 @@ static void tune_layout(Ctx* c, ULevel<T>& lv, const BuildLevel<T>& b, const int
     lv.A.bs = units ? 64 * units : 256;
   };
   const int cached = autotune_lookup(lv.nS, A.nnz, maxrow, fp32);
-  if (cached > 0) {
+  if (cached > 0 && !(st == kSellTooLarge && cached % kTuneBsUnit == kTuneSell)) {
     apply(cached);
     return;
   }
@@ -3414,7 +3420,7 @@ static void tune_restrict(Ctx* c, const ULevel<T>& lv, const BuildLevel<T>& b, c
   const Csr<double>& Wt = b.Wt;
   const int nS = b.nS, nC = b.nC, nCn = lv.nC_next;
   const int maxrow = stat[0];
-  const long long st = stat[1];
+  const long long st = sell_entries_of(stat[1]);
   if (Wt.n_rows == 0 || Wt.nnz == 0) {
     layout_transfer<T>(c, Wt, out, b.tsoff, st, 0);
     return;
@@ -3428,7 +3434,7 @@ static void tune_restrict(Ctx* c, const ULevel<T>& lv, const BuildLevel<T>& b, c
     out.bs = units ? 64 * units : 256;
   };
   const int cached = autotune_lookup(Wt.n_rows, Wt.nnz, maxrow, fp32, "wt:");
-  if (cached > 0) {
+  if (cached > 0 && !(st == kSellTooLarge && cached % kTuneBsUnit == kTuneSell)) {
     apply(cached);
     return;
   }

@@ -4,6 +4,8 @@
 // grid-stride loop, reduce each workgroup with wavefront shuffles and LDS,
 // and sum the per-workgroup partials in index order in a second kernel, so
 // the result depends only on n, never on scheduling.
+#include <climits>
+
 #include "kernels.hpp"
 
 namespace mgd {
@@ -35,10 +37,10 @@ __device__ __forceinline__ double block_sum256(double v, double* lds /*[4]*/) {
 constexpr int kScanTile = 2048;  // 256 threads x 8 items
 
 __global__ void __launch_bounds__(256) k_tile_sums(const int* __restrict__ in, int n,
-                                                   int* __restrict__ sums) {
-  __shared__ int lds[4];
+                                                   long long* __restrict__ sums) {
+  __shared__ long long lds[4];
   const long base = (long)blockIdx.x * kScanTile;
-  int s = 0;
+  long long s = 0;
   for (int k = threadIdx.x; k < kScanTile; k += 256) {
     long i = base + k;
     if (i < n) s += in[i];
@@ -52,23 +54,24 @@ __global__ void __launch_bounds__(256) k_tile_sums(const int* __restrict__ in, i
 
 // Exclusive scan of one tile on top of the sums of the tiles before it (null: the
 // first tile only); writes out[i] for i < n and, from the block holding the last
-// element, out[n] = total.  Every workgroup adds up the tile sums for itself: a
-// scan of the sums in between would be another dependent launch.
+// element, out[n] = total, or kScanTooLarge where int32 cannot hold it (the sums
+// are 64-bit, so a total past 2^32 is seen too).  Every workgroup adds up the tile
+// sums for itself: a scan of the sums in between would be another dependent launch.
 __global__ void __launch_bounds__(256) k_tile_scan(const int* __restrict__ in, int n,
-                                                   const int* __restrict__ tile_sums,
+                                                   const long long* __restrict__ tile_sums,
                                                    int* __restrict__ out) {
-  __shared__ int lds[256];
-  __shared__ int s_before[4];
+  __shared__ long long lds[256];
+  __shared__ long long s_before[4];
   const long base = (long)blockIdx.x * kScanTile;
   const int t = threadIdx.x;
-  int before = 0;
+  long long before = 0;
   if (tile_sums)
     for (int k = t; k < (int)blockIdx.x; k += 256) before += tile_sums[k];
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off, 64);
   if ((t & 63) == 0) s_before[t >> 6] = before;
   int v[8];
-  int s = 0;
+  long long s = 0;
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
     long i = base + t * 8 + k;
@@ -79,18 +82,18 @@ __global__ void __launch_bounds__(256) k_tile_scan(const int* __restrict__ in, i
   __syncthreads();
   // Hillis-Steele inclusive scan over 256 thread sums
   for (int off = 1; off < 256; off <<= 1) {
-    int add = (t >= off) ? lds[t - off] : 0;
+    const long long add = (t >= off) ? lds[t - off] : 0;
     __syncthreads();
     lds[t] += add;
     __syncthreads();
   }
-  int run = (t ? lds[t - 1] : 0) + s_before[0] + s_before[1] + s_before[2] + s_before[3];
+  long long run = (t ? lds[t - 1] : 0) + s_before[0] + s_before[1] + s_before[2] + s_before[3];
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
     long i = base + t * 8 + k;
-    if (i < n) out[i] = run;
+    if (i < n) out[i] = (int)run;
     run += v[k];
-    if (i == n - 1) out[n] = run;
+    if (i == n - 1) out[n] = run <= INT_MAX ? (int)run : kScanTooLarge;
   }
 }
 
@@ -108,11 +111,11 @@ void exclusive_scan(Ctx* c, const int* in, int* out, int n) {
     MGD_CHECK_LAUNCH();
     return;
   }
-  DBuf<int> sums(c, tiles);
+  DBuf<long long> sums(c, tiles);
   hipLaunchKernelGGL(k_tile_sums, dim3(tiles), dim3(256), 0, c->stream, in, n, sums.get());
   MGD_CHECK_LAUNCH();
   hipLaunchKernelGGL(k_tile_scan, dim3(tiles), dim3(256), 0, c->stream, in, n,
-                     (const int*)sums.get(), out);
+                     (const long long*)sums.get(), out);
   MGD_CHECK_LAUNCH();
   // temporaries are released only after the stream has consumed them
   if (!c->defer) c->sync();
@@ -120,7 +123,9 @@ void exclusive_scan(Ctx* c, const int* in, int* out, int n) {
 
 int exclusive_scan_total(Ctx* c, const int* in, int* out, int n) {
   exclusive_scan(c, in, out, n);
-  return read1(c, out + (n > 0 ? n : 0));
+  const int total = read1(c, out + (n > 0 ? n : 0));
+  MGD_REQUIRE(total >= 0, "matrix too large for int32 indices");
+  return total;
 }
 
 // ---------------------------------------------------------------------------

@@ -1542,3 +1542,76 @@ def test_autotune_layouts_and_cache(ctx, monkeypatch, tmp_path, precision):
                        capture_output=True, text=True, timeout=240, env=dict(os.environ))
     assert p.returncode == 0, p.stderr[-2000:]
     assert np.array_equal(np.load(out), z)
+
+
+# ---------------------------------------------------------------------------
+# totals past int32
+# ---------------------------------------------------------------------------
+def test_product_past_int32_is_refused(ctx):
+    """A P of 120,000 rows, each with all of the 51,884 coarse columns (a
+    chain whose rows couple weakly to 120 hubs, each with strong couplings to its
+    share of the rows): 1.45 times 2^32 entries, a total that reads 1.9e9 in 32
+    bits.  It is refused by its count; a setup that fits follows."""
+    api = gpu_modules()
+    n, K = 120000, 120
+    rng = np.random.default_rng(5)
+    hubs = np.linspace(100, n - 100, K).astype(int)
+    i = np.arange(n)
+    rows, cols = [i[:-1], i[1:]], [i[1:], i[:-1]]
+    vals = [-rng.uniform(0.9, 1.1, n - 1), -rng.uniform(0.9, 1.1, n - 1)]
+    for h, own in zip(hubs, np.array_split(rng.permutation(n), K)):
+        own = own[np.abs(own - h) > 1]
+        rows.append(np.full(own.size, h))
+        cols.append(own)
+        vals.append(-rng.uniform(0.9, 1.1, own.size))
+        w = i[np.abs(i - h) > 1]
+        rows.append(w)
+        cols.append(np.full(w.size, h))
+        vals.append(np.full(w.size, -1e-4))
+    A = sp.csr_matrix((np.concatenate(vals), (np.concatenate(rows), np.concatenate(cols))),
+                      shape=(n, n))
+    A = sp.csr_matrix(A + sp.diags(0.01 - np.asarray(A.sum(1)).reshape(-1)))
+    A.sort_indices()
+    with pytest.raises(RuntimeError, match="too large for int32"):
+        api.AMG(ctx, A.indptr, A.indices, A.data, seed=3)
+    B = oracle_system(si.generate(1, 2, 12, 3)).monolithic()
+    _compare_hierarchies(api.AMG(ctx, B.indptr, B.indices, B.data, seed=3),
+                         oamg.setup(B, oamg.AMGParams(seed=3)))
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_padding_past_int32_keeps_rows_unsliced(ctx, precision):
+    """One row of 8,300 entries in each 64-row slice of a 2^18-row matrix: sliced
+    it would hold 2^18 * 8,300 > 2^31 entries, so it stays in rows.  One
+    relaxed level: sweeps equal the oracle's."""
+    api = gpu_modules()
+    n, L = 1 << 18, 8300
+    rng = np.random.default_rng(8)
+    long_rows = np.arange(17, n, 64)
+    i = np.arange(n)
+    short = np.setdiff1d(i, long_rows)
+    start = np.minimum(long_rows, n - L)
+    lens = np.full(n, 2)
+    lens[long_rows] = L
+    rp = np.concatenate([[0], np.cumsum(lens)])
+    ci = np.empty(rp[-1], dtype=np.int64)
+    left = np.where(short > 0, short - 1, 1)
+    ci[rp[short]] = np.minimum(short, left)
+    ci[rp[short] + 1] = np.maximum(short, left)
+    ci[(rp[long_rows][:, None] + np.arange(L)).reshape(-1)] = (start[:, None]
+                                                               + np.arange(L)).reshape(-1)
+    v = -rng.uniform(0.5, 1.0, rp[-1])
+    diag = ci == np.repeat(i, lens)
+    assert diag.sum() == n
+    v[diag] = 1.05 * lens
+    A = sp.csr_matrix((v, ci, rp), shape=(n, n))
+    assert 64 * int(lens.reshape(-1, 64).max(axis=1).astype(np.int64).sum()) > 2 ** 31
+    g = api.AMG(ctx, A.indptr, A.indices, A.data, seed=1, max_levels=1, precision=precision)
+    assert g.info()["levels"] == 1 and g.info()["coarse_kind"] == 1
+    H = oamg.setup(A, oamg.AMGParams(seed=1, max_levels=1))
+    b = rng.uniform(size=n)
+    z = to_host(g.apply(to_dev(ctx, b)))
+    # the oracle adds 8,300 terms in sequence: at most 8300 eps sum |a_ij x_j| / a_ii
+    # a sweep, of the largest entry's size here; FP32 as in the V-cycle parity
+    assert_elementwise(z, oamg.vcycle(H, b), 5e-5 if precision else 5e-12, floor=1.0,
+                       what="unsliced rows")
