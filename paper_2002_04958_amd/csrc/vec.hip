@@ -35,6 +35,10 @@ __device__ __forceinline__ double block_sum256(double v, double* lds /*[4]*/) {
 // scan
 // ---------------------------------------------------------------------------
 constexpr int kScanTile = 2048;  // 256 threads x 8 items
+// Tiles up to which a workgroup adds up the tile sums before its own (us, scans of
+// 2^20, 2^22, 2^24, 2^26 and 2^28 values): 11, 26, 98, 583, 5005; with the bases
+// from a launch of their own 14, 30, 108, 426, 1616.
+constexpr int kScanOwnBase = 8192;
 
 __global__ void __launch_bounds__(256) k_tile_sums(const int* __restrict__ in, int n,
                                                    long long* __restrict__ sums) {
@@ -52,11 +56,43 @@ __global__ void __launch_bounds__(256) k_tile_sums(const int* __restrict__ in, i
   if (threadIdx.x == 0) sums[blockIdx.x] = lds[0] + lds[1] + lds[2] + lds[3];
 }
 
+// The tile sums become each tile's base, the sum of all tiles before it: one
+// workgroup, 1024 tiles at a time.
+__global__ void __launch_bounds__(1024) k_tile_bases(long long* __restrict__ sums, int tiles) {
+  __shared__ long long s_wave[16];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  long long carry = 0;
+  for (int k0 = 0; k0 < tiles; k0 += 1024) {
+    const int k = k0 + t;
+    const long long x = k < tiles ? sums[k] : 0;
+    long long upto = x;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const long long y = __shfl_up(upto, off, 64);
+      if (lane >= off) upto += y;
+    }
+    if (lane == 63) s_wave[w] = upto;
+    __syncthreads();
+    long long before = carry, all = 0;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      if (q < w) before += s_wave[q];
+      all += s_wave[q];
+    }
+    if (k < tiles) sums[k] = before + upto - x;
+    carry += all;
+    __syncthreads();
+  }
+}
+
 // Exclusive scan of one tile on top of the sums of the tiles before it (null: the
 // first tile only); writes out[i] for i < n and, from the block holding the last
 // element, out[n] = total, or kScanTooLarge where int32 cannot hold it (the sums
-// are 64-bit, so a total past 2^32 is seen too).  Every workgroup adds up the tile
-// sums for itself: a scan of the sums in between would be another dependent launch.
+// are 64-bit, so a total past 2^32 is seen too).  Up to kScanOwnBase tiles every
+// workgroup adds up the tile sums for itself, which saves a dependent launch; BASES:
+// k_tile_bases has done it, as all workgroups' reads together grow with the square
+// of the tiles.
+template <bool BASES>
 __global__ void __launch_bounds__(256) k_tile_scan(const int* __restrict__ in, int n,
                                                    const long long* __restrict__ tile_sums,
                                                    int* __restrict__ out) {
@@ -65,8 +101,11 @@ __global__ void __launch_bounds__(256) k_tile_scan(const int* __restrict__ in, i
   const long base = (long)blockIdx.x * kScanTile;
   const int t = threadIdx.x;
   long long before = 0;
-  if (tile_sums)
+  if (BASES) {
+    if (t == 0) before = tile_sums[blockIdx.x];
+  } else if (tile_sums) {
     for (int k = t; k < (int)blockIdx.x; k += 256) before += tile_sums[k];
+  }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off, 64);
   if ((t & 63) == 0) s_before[t >> 6] = before;
@@ -107,15 +146,22 @@ void exclusive_scan(Ctx* c, const int* in, int* out, int n) {
   }
   const int tiles = cdiv(n, kScanTile);
   if (tiles == 1) {
-    hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(256), 0, c->stream, in, n, nullptr, out);
+    hipLaunchKernelGGL(k_tile_scan<false>, dim3(1), dim3(256), 0, c->stream, in, n, nullptr, out);
     MGD_CHECK_LAUNCH();
     return;
   }
   DBuf<long long> sums(c, tiles);
   hipLaunchKernelGGL(k_tile_sums, dim3(tiles), dim3(256), 0, c->stream, in, n, sums.get());
   MGD_CHECK_LAUNCH();
-  hipLaunchKernelGGL(k_tile_scan, dim3(tiles), dim3(256), 0, c->stream, in, n,
-                     (const long long*)sums.get(), out);
+  if (tiles <= kScanOwnBase) {
+    hipLaunchKernelGGL(k_tile_scan<false>, dim3(tiles), dim3(256), 0, c->stream, in, n,
+                       (const long long*)sums.get(), out);
+  } else {
+    hipLaunchKernelGGL(k_tile_bases, dim3(1), dim3(1024), 0, c->stream, sums.get(), tiles);
+    MGD_CHECK_LAUNCH();
+    hipLaunchKernelGGL(k_tile_scan<true>, dim3(tiles), dim3(256), 0, c->stream, in, n,
+                       (const long long*)sums.get(), out);
+  }
   MGD_CHECK_LAUNCH();
   // temporaries are released only after the stream has consumed them
   if (!c->defer) c->sync();

@@ -1615,3 +1615,29 @@ def test_padding_past_int32_keeps_rows_unsliced(ctx, precision):
     # a sweep, of the largest entry's size here; FP32 as in the V-cycle parity
     assert_elementwise(z, oamg.vcycle(H, b), 5e-5 if precision else 5e-12, floor=1.0,
                        what="unsliced rows")
+
+
+# ---------------------------------------------------------------------------
+# scans of many tiles
+# ---------------------------------------------------------------------------
+def test_scan_of_more_tiles_than_own_bases(ctx):
+    """A chain of 8192 * 2048 + 1 rows, one past the scans in which a workgroup
+    adds up the tile sums before its own: coarse numbers and row pointers of P are
+    the running sums of the C/F splitting's counts."""
+    api = gpu_modules()
+    n = 8192 * 2048 + 1
+    rp = np.empty(n + 1, dtype=np.int32)
+    rp[0], rp[1:-1], rp[-1] = 0, 3 * np.arange(1, n) - 1, 3 * n - 2
+    ci = np.repeat(np.arange(n, dtype=np.int32), 3)
+    ci += np.tile(np.array([-1, 0, 1], dtype=np.int32), n)
+    v = np.tile(np.array([-1.0, 2.0, -1.0]), n)
+    g = api.AMG(ctx, rp, ci[1:-1], v[1:-1], seed=3, max_levels=2)
+    e = g.export_level(0)
+    c = e["cf"] == 1
+    neighbours = np.zeros(n, dtype=np.int64)
+    neighbours[1:] += c[:-1]
+    neighbours[:-1] += c[1:]
+    prp, pci, pv = e["P"]
+    assert np.array_equal(prp, np.concatenate([[0], np.cumsum(np.where(c, 1, neighbours))]))
+    assert g.info()["n"][1] == c.sum()
+    assert np.array_equal(pci[prp[:-1][c]], np.arange(c.sum()))
