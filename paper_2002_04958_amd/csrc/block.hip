@@ -337,7 +337,7 @@ struct StackMember {
   const double *d1, *d2, *dd;
   int nnz, off, eoff;
 };
-// entries of member blockIdx.y, four per thread and turn, columns numbered through
+// entries of member blockIdx.y, columns numbered through
 __global__ void k_stack_entries(const StackMember* __restrict__ tab, int* __restrict__ ci,
                                 double* __restrict__ v) {
   const StackMember m = tab[blockIdx.y];
@@ -508,46 +508,67 @@ struct RoleMatrix {
 // its setup, whose rows are a few times as long.
 constexpr long long kBatchEntries = 1LL << 27;
 
-// Hierarchies of all the roles, as many in one batch as the parameters and the
-// entries allow.
-static void make_hierarchies(block_precond* bp, const std::vector<RoleMatrix>& roles) {
+// The stacked matrices of `tab` (member m: rows [off[m], off[m + 1]), entries from
+// eoff[m]) and their hierarchies, with one wait for the temporaries of the stack.
+static std::shared_ptr<SetupBatch> build_batch(block_precond* bp,
+                                               const std::vector<StackMember>& tab,
+                                               const std::vector<int>& off,
+                                               const std::vector<int>& eoff) {
   Ctx* c = bp->ctx;
+  DeferFrees frees(c);
+  const int N = bp->N, nm = (int)tab.size();
+  int most = 0;
+  for (const StackMember& m : tab) most = std::max(most, m.nnz);
+  DBuf<StackMember> dt(c, (size_t)nm);
+  copy_h2d(c, dt.get(), tab.data(), (size_t)nm);
+  Csr<double> A0;
+  A0.alloc(c, off.back(), off.back(), eoff.back());
+  if (most > 0)
+    hipLaunchKernelGGL(k_stack_entries, dim3(std::min(cdiv(most, 256), 4096), nm), dim3(256), 0,
+                       c->stream, (const StackMember*)dt.get(), A0.ci.get(), A0.v.get());
+  hipLaunchKernelGGL(k_stack_rows, dim3(cdiv(N, 256), nm), dim3(256), 0, c->stream, N, nm - 1,
+                     (const StackMember*)dt.get(), A0.rp.get(), A0.v.get());
+  MGD_CHECK_LAUNCH();
+  auto b = std::make_shared<SetupBatch>();
+  amg_build(c, std::move(A0), off, eoff, bp->prm.amg, *b);
+  return b;
+}
+
+// Hierarchies of all the roles, as many in one batch as the parameters, the
+// entries and the memory allow: a batch holds the products and temporaries of all
+// its members at once and counts their entries in one int32, so one that does not
+// fit is taken in halves, down to single members.
+static void make_hierarchies(block_precond* bp, const std::vector<RoleMatrix>& roles) {
   const int N = bp->N;
   const bool together = setup_batches(bp->prm.amg);
+  size_t limit = together ? kMaxMembers : 1;
   for (size_t q0 = 0; q0 < roles.size();) {
     std::vector<StackMember> tab;
     std::vector<int> off{0}, eoff{0};
-    size_t q1 = q0;
-    int most = 0;
-    while (q1 < roles.size() && (int)tab.size() < kMaxMembers) {
-      const RoleMatrix& r = roles[q1];
+    for (size_t q = q0; q < roles.size() && tab.size() < limit; ++q) {
+      const RoleMatrix& r = roles[q];
       const BlockCsr& B = bp->sys.blk[r.block];
       const int nnz = (int)bp->sys.nnz[r.block];
       const long long entries = (long long)eoff.back() + nnz;
-      if (!tab.empty() && (!together || entries > kBatchEntries ||
-                           (long long)off.back() + N >= INT32_MAX))
+      if (!tab.empty() &&
+          (entries > kBatchEntries || (long long)off.back() + N >= INT32_MAX))
         break;
       tab.push_back({B.rp, B.ci, B.v, r.d1, r.d2, r.dd, nnz, off.back(), eoff.back()});
       off.push_back(off.back() + N);
       eoff.push_back((int)entries);
-      most = std::max(most, nnz);
-      ++q1;
     }
-    const int nm = (int)tab.size();
-    DBuf<StackMember> dt(c, (size_t)nm);
-    copy_h2d(c, dt.get(), tab.data(), (size_t)nm);
-    Csr<double> A0;
-    A0.alloc(c, off.back(), off.back(), eoff.back());
-    if (most > 0)
-      hipLaunchKernelGGL(k_stack_entries, dim3(std::min(cdiv(most, 256), 4096), nm), dim3(256), 0,
-                         c->stream, (const StackMember*)dt.get(), A0.ci.get(), A0.v.get());
-    hipLaunchKernelGGL(k_stack_rows, dim3(cdiv(N, 256), nm), dim3(256), 0, c->stream, N, nm - 1,
-                       (const StackMember*)dt.get(), A0.rp.get(), A0.v.get());
-    MGD_CHECK_LAUNCH();
-    auto b = std::make_shared<SetupBatch>();
-    amg_build(c, std::move(A0), off, eoff, bp->prm.amg, *b);
-    for (int m = 0; m < nm; ++m) add_hierarchy(bp, roles[q0 + m].role, b, m);
-    q0 = q1;
+    const size_t nm = tab.size();
+    std::shared_ptr<SetupBatch> b;
+    try {
+      b = build_batch(bp, tab, off, eoff);
+    } catch (const Error& e) {
+      if (nm == 1 || (e.code != MGD_ENOMEM && e.code != MGD_EINVAL)) throw;
+      (void)hipGetLastError();  // an allocator's failed attempt
+      limit = (nm + 1) / 2;
+      continue;
+    }
+    for (size_t m = 0; m < nm; ++m) add_hierarchy(bp, roles[q0 + m].role, b, (int)m);
+    q0 += nm;
   }
 }
 

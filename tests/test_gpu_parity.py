@@ -1168,6 +1168,82 @@ def test_setup_memory_returns_in_any_order(ctx, dim, n, order):
     assert torch.cuda.memory_allocated(ctx.device) == m0
 
 
+class _LimitedAllocator:
+    """Device memory from torch, in requests of at most `most` bytes (None: any);
+    `largest` is the largest request so far, `peak` the most bytes held at once.
+    The 4 MB chunks that small buffers come from are neither refused nor counted
+    as requests."""
+    CHUNK = 4 << 20
+
+    def __init__(self, api):
+        self.api, self.make = api, api._torch_allocator
+        self.most, self.largest, self.refused = None, 0, 0
+        self.held, self.size, self.peak = 0, {}, 0
+
+    def __call__(self, device):
+        cbs, _ = self.make(device)
+
+        def alloc(nbytes, stream, user):
+            if self.most is not None and nbytes > self.most and nbytes != self.CHUNK:
+                self.refused += 1
+                return None
+            p = cbs[0](nbytes, stream, user)
+            if nbytes != self.CHUNK:
+                self.largest = max(self.largest, nbytes)
+            self.size[p] = nbytes
+            self.held += nbytes
+            self.peak = max(self.peak, self.held)
+            return p
+
+        def free(ptr, stream, user):
+            self.held -= self.size.pop(ptr)
+            cbs[1](ptr, stream, user)
+
+        mine = (self.api.L.ALLOC_FN(alloc), self.api.L.FREE_FN(free))
+        return (cbs, mine), self.api.L.mgd_allocator(mine[0], mine[1], None)
+
+
+def test_setup_together_shrinks_to_the_memory(monkeypatch):
+    """Where the allocator refuses what setting up all members together asks for,
+    fewer are taken at once, with the same hierarchies bit for bit; what one
+    member alone cannot have is refused as before."""
+    api = gpu_modules()
+    lim = _LimitedAllocator(api)
+    monkeypatch.setattr(api, "_torch_allocator", lim)
+    c = api.Context(0)
+    inp = si.generate(9, 2, 160, 17)   # a member's level matrix is past the chunks' sizes
+    co, gsys = gpu_system(c, inp)
+    r = to_dev(c, np.random.default_rng(2).standard_normal(gsys.n))
+    rp, ci, v = gsys.block_arrays(9)
+    lim.largest = 0
+    api.AMG(c, rp, ci, v, seed=5).close()
+    one = lim.largest
+    lim.largest = 0
+    M = api.BlockPreconditioner(c, gsys, "schur2", amg_seed=5)
+    assert one > 0 and lim.largest > 6 * one
+    want = to_host(M.apply(r))
+    M.close()
+    for factor in (5, 3):
+        lim.most, lim.refused = factor * one, 0
+        M = api.BlockPreconditioner(c, gsys, "schur2", amg_seed=5)
+        assert lim.refused
+        lim.most = None
+        assert np.array_equal(to_host(M.apply(r)), want)
+        M.close()
+    held = lim.held
+    lim.most = one // 2
+    with pytest.raises(RuntimeError, match="MGD_ENOMEM"):
+        api.BlockPreconditioner(c, gsys, "schur2", amg_seed=5)
+    lim.most = None
+    assert lim.held == held
+    M = api.BlockPreconditioner(c, gsys, "schur2", amg_seed=5)
+    assert np.array_equal(to_host(M.apply(r)), want)
+    M.close()
+    gsys.close()
+    c.close()
+    assert lim.held == 0
+
+
 def test_handles_closed_by_another_thread_during_setup(ctx):
     """A handle may be closed by another thread (a collector that runs there)
     while a setup holds its frees back: both end, with the same results."""
