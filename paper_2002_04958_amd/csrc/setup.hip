@@ -1199,11 +1199,13 @@ __global__ void __launch_bounds__(WG) k_spgemm_hash(
 
 // Rows of the last class, one wave per row: the columns kSpRange at a time, each
 // range in an array indexed by column (the row's products are read again for
-// every range), so the columns come out in order without a search or a sort.
+// every range), so the columns come out in order without a search or a sort.  Only
+// ranges between the row's first and last column are walked: in a matrix of
+// several members a row reaches its own member's columns.
 constexpr int kSpRange = 4096;
 template <bool FILL>
 __global__ void __launch_bounds__(64) k_spgemm_range(
-    const int* __restrict__ list, const int* __restrict__ count, int n_cols,
+    const int* __restrict__ list, const int* __restrict__ count,
     const int* __restrict__ arp, const int* __restrict__ aci, const double* __restrict__ av,
     const int* __restrict__ brp, const int* __restrict__ bci, const double* __restrict__ bv,
     const int* __restrict__ crp, int* __restrict__ cnt_or_cci, double* __restrict__ cv,
@@ -1219,7 +1221,20 @@ __global__ void __launch_bounds__(64) k_spgemm_range(
     const int e0 = arp[i], e1 = arp[i + 1];
     int out = FILL ? crp[i] : 0;
     const int oend = FILL ? crp[i + 1] : INT_MAX;
-    for (long long lo = 0; lo < n_cols; lo += kSpRange) {
+    int first = INT_MAX, last = -1;  // B's rows are sorted
+    for (int e = e0 + lane; e < e1; e += 64) {
+      const int k = aci[e], f0 = brp[k], f1 = brp[k + 1];
+      if (f0 < f1) {
+        first = min(first, bci[f0]);
+        last = max(last, bci[f1 - 1]);
+      }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      first = min(first, __shfl_xor(first, o, 64));
+      last = max(last, __shfl_xor(last, o, 64));
+    }
+    for (long long lo = first; lo <= last; lo += kSpRange) {
       for (int s = lane; s < kSpRange / 32; s += 64) bits[s] = 0;
       if (FILL)
         for (int s = lane; s < kSpRange; s += 64) val[s] = 0.0;
@@ -1294,7 +1309,7 @@ static void spgemm_pass(Ctx* c, const Csr<double>& A, const Csr<double>& B, int 
   if (top == 4) {
     hipLaunchKernelGGL(k_spgemm_range<FILL>, dim3(std::min(n, kSpGrid)), dim3(64), 0, c->stream,
                        (const int*)lists.get() + (size_t)4 * n, (const int*)count.get() + 4,
-                       B.n_cols, A.rp.get(), A.ci.get(), A.v.get(), B.rp.get(), B.ci.get(),
+                       A.rp.get(), A.ci.get(), A.v.get(), B.rp.get(), B.ci.get(),
                        B.v.get(), crp, cnt_or_cci, cv, c->err_flag());
     MGD_CHECK_LAUNCH();
   }

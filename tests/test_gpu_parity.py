@@ -362,6 +362,36 @@ def test_hierarchies_built_together_equal_single_ones(ctx, n, params):
     assert n < 24 or len(depths) > 1
 
 
+def test_long_rows_of_members_set_up_together(ctx):
+    """Product rows of more columns than the largest table, in several members at
+    once: each row's ranges of columns lie within its own member's, and every
+    hierarchy equals the one of its matrix alone bit for bit."""
+    import torch
+    api = gpu_modules()
+    n, G = 130, 3
+    mats = [_hub_matrix(n, (2500, 4200, 9000 + 700 * a), (5,), 11 + a) for a in range(G + 2)]
+    dev = ctx.device
+    rng = np.random.default_rng(4)
+    N = n * n
+    s = api.BlockSystem.from_tensors(
+        ctx, G, N, [(torch.as_tensor(A.indptr.astype(np.int32)).to(dev),
+                     torch.as_tensor(A.indices.astype(np.int32)).to(dev),
+                     torch.as_tensor(A.data).to(dev)) for A in mats],
+        *[1e-3 * rng.standard_normal(k * N) for k in (G, G, 1, 1)])
+    M = api.BlockPreconditioner(ctx, s, "bdiag", amg_seed=4, amg_max_levels=3,
+                               amg_dense_max=100, batched=1)
+    for a, A in enumerate(mats):
+        alone = api.AMG(ctx, A.indptr, A.indices, A.data, seed=4, max_levels=3, dense_max=100)
+        got = M.hierarchy(a)
+        assert alone.info() == got.info()
+        for l in range(3):
+            ea, eg = alone.export_level(l), got.export_level(l)
+            assert np.array_equal(ea["cf"], eg["cf"])
+            for key in ("A", "P") if l < 2 else ("A",):
+                for x, y in zip(ea[key], eg[key]):
+                    assert np.array_equal(x, y), (a, l, key)
+
+
 def test_amg_edge_cases(ctx):
     api = gpu_modules()
     # single row
