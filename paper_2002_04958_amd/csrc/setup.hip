@@ -591,6 +591,14 @@ static int pmis_one(Ctx* c, const Csr<double>& A, const DBuf<uint8_t>& S, const 
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ int sgn(double x) { return (x > 0.0) - (x < 0.0); }
 
+// Between LDS accesses of one wave to places other lanes wrote: the hardware
+// does them in program order, this keeps the compiler to it.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // position of column j in the sorted row [e0, e1), or -1
 __device__ __forceinline__ int find_col(const int* __restrict__ ci, int e0, int e1, int j) {
   int lo = e0, hi = e1;
@@ -709,12 +717,12 @@ __global__ void __launch_bounds__(256) k_interp_fill(
   const int grp = threadIdx.x / GL, lane = threadIdx.x % GL;
   const int i = blockIdx.x * kGroups + grp;
   if (i >= n) return;
-  // volatile: the lanes of a group exchange data through these without a
-  // barrier; they are in one wave, whose LDS operations are done in order
-  volatile int* col = s_col[grp];
-  volatile int* hit = s_hit[grp];
-  volatile double* num = s_num[grp];
-  volatile double* ahs = s_ah[grp];
+  // the lanes of a group exchange data through these without a barrier: they are
+  // in one wave, with a wave_lds_fence between
+  int* col = s_col[grp];
+  int* hit = s_hit[grp];
+  double* num = s_num[grp];
+  double* ahs = s_ah[grp];
   const int p = prp[i], pend = prp[i + 1], m = pend - p;
   if (st[i] == kC) {
     if (lane) return;
@@ -763,6 +771,7 @@ __global__ void __launch_bounds__(256) k_interp_fill(
     if (lane == 0) atomicOr(err, 2);
     return;
   }
+  wave_lds_fence();
   double at = diag[i];
   for (int b = e0; b < e1; b += GL) {
     const int e = b + lane;
@@ -789,7 +798,9 @@ __global__ void __launch_bounds__(256) k_interp_fill(
         continue;
       }
       const int k0 = __shfl(f0, q, GL), k1 = __shfl(f1, q, GL), skk = __shfl(sk, q, GL);
+      wave_lds_fence();  // every lane has read the hits of the neighbour before
       for (int s = lane; s < m; s += GL) hit[s] = 0;
+      wave_lds_fence();
       for (int f = k0 + lane; f < k1; f += GL) {
         const int jj = ci[f];
         const double af = v[f];
@@ -806,6 +817,7 @@ __global__ void __launch_bounds__(256) k_interp_fill(
           hit[lo] = 1;
         }
       }
+      wave_lds_fence();
       double sg = 0.0;
       for (int s = 0; s < m; ++s)
         if (hit[s]) sg = sg + ahs[s];
@@ -1048,14 +1060,6 @@ __global__ void __launch_bounds__(kSpBinWg) k_spgemm_bin(int n, int max_cols,
       lists[(size_t)cls[t] * n + s_base[cls[t]] + pos[t]] = r0 + t * kSpBinWg + threadIdx.x;
 }
 
-// Between LDS accesses of one wave to places other lanes wrote: the hardware
-// does them in program order, this keeps the compiler to it.
-__device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 template <int H, int GL, int WG, bool FILL>
 __global__ void __launch_bounds__(WG) k_spgemm_hash(
     const int* __restrict__ list, const int* __restrict__ count, const int* __restrict__ arp,
@@ -1072,17 +1076,18 @@ __global__ void __launch_bounds__(WG) k_spgemm_hash(
   const int grp = threadIdx.x / GL, lane = threadIdx.x % GL;
   const int sh = (threadIdx.x & 63) / GL * GL;
   const uint64_t gm = (GL == 64 ? ~0ull : ((1ull << (GL & 63)) - 1)) << sh;
-  // volatile: a group's lanes are in one wave, whose LDS operations are done in
-  // program order; no barrier is needed between them
+  // a group's lanes are in one wave: a wave_lds_fence between their accesses, no
+  // barrier (volatile: a key may be taken by another lane between two looks)
   int* keys = reinterpret_cast<int*>(s_key4[grp]);
   volatile int* key = keys;
-  volatile double* val = reinterpret_cast<double*>(s_val2[FILL ? grp : 0]);
-  volatile int* col = reinterpret_cast<int*>(s_col4[FILL ? grp : 0]);
-  volatile uint16_t* slot = s_slot[FILL ? grp : 0];
+  double* val = reinterpret_cast<double*>(s_val2[FILL ? grp : 0]);
+  int* col = reinterpret_cast<int*>(s_col4[FILL ? grp : 0]);
+  uint16_t* slot = s_slot[FILL ? grp : 0];
   const int nr = *count;
   for (int r = blockIdx.x * kGroups + grp; r < nr; r += gridDim.x * kGroups) {
     const int i = list[r];
     const int e0 = arp[i], e1 = arp[i + 1];
+    wave_lds_fence();  // every lane is done with the row before
 #pragma unroll
     for (int s = 0; s < kQuads; ++s) {
       s_key4[grp][s * GL + lane] = make_int4(-1, -1, -1, -1);
@@ -1146,8 +1151,10 @@ __global__ void __launch_bounds__(WG) k_spgemm_hash(
         }
         if (FILL) {  // one entry's products after the other's
           const int last = __shfl(q, min(GL, total - p0) - 1, GL);
-          for (int t = __shfl(q, 0, GL); t <= last; ++t)
+          for (int t = __shfl(q, 0, GL); t <= last; ++t) {
             if (q == t && h >= 0) val[h] = val[h] + x;
+            wave_lds_fence();
+          }
         }
       }
     }
@@ -1193,7 +1200,6 @@ __global__ void __launch_bounds__(WG) k_spgemm_hash(
       cnt_or_cci[o + rank] = k;
       cv[o + rank] = val[slot[t]];
     }
-    wave_lds_fence();
   }
 }
 
@@ -1210,10 +1216,8 @@ __global__ void __launch_bounds__(64) k_spgemm_range(
     const int* __restrict__ brp, const int* __restrict__ bci, const double* __restrict__ bv,
     const int* __restrict__ crp, int* __restrict__ cnt_or_cci, double* __restrict__ cv,
     int* __restrict__ err) {
-  __shared__ double s_val[FILL ? kSpRange : 1];
-  __shared__ unsigned s_bits[kSpRange / 32];
-  volatile double* val = s_val;
-  volatile unsigned* bits = s_bits;
+  __shared__ double val[FILL ? kSpRange : 1];
+  __shared__ unsigned bits[kSpRange / 32];
   const int lane = threadIdx.x;
   const int nr = *count;
   for (int r = blockIdx.x; r < nr; r += gridDim.x) {
@@ -1235,9 +1239,11 @@ __global__ void __launch_bounds__(64) k_spgemm_range(
       last = max(last, __shfl_xor(last, o, 64));
     }
     for (long long lo = first; lo <= last; lo += kSpRange) {
+      wave_lds_fence();  // every lane has read the range before
       for (int s = lane; s < kSpRange / 32; s += 64) bits[s] = 0;
       if (FILL)
         for (int s = lane; s < kSpRange; s += 64) val[s] = 0.0;
+      wave_lds_fence();
       for (int b = e0; b < e1; b += 64) {
         const int e = b + lane;
         int f0 = 0, f1 = 0;
@@ -1255,9 +1261,10 @@ __global__ void __launch_bounds__(64) k_spgemm_range(
           for (int f = k0 + lane; f < k1; f += 64) {
             const long long s = (long long)bci[f] - lo;
             if (s < 0 || s >= kSpRange) continue;
-            atomicOr(&s_bits[s >> 5], 1u << (s & 31));
+            atomicOr(&bits[s >> 5], 1u << (s & 31));
             if (FILL) val[s] = val[s] + aq * bv[f];
           }
+          wave_lds_fence();  // the next B row may reach a column through another lane
         }
       }
       for (int s0 = 0; s0 < kSpRange; s0 += 64) {
