@@ -63,11 +63,13 @@ const char* kernel_class_name(int c) {
 }
 
 void* Ctx::raw_alloc(size_t bytes) {
-  if (has_alloc) return alloc.alloc(bytes, (void*)stream, alloc.user);
   void* p = nullptr;
-  if (hipMalloc(&p, bytes) == hipSuccess) return p;
-  (void)hipGetLastError();
-  return nullptr;
+  if (has_alloc)
+    p = alloc.alloc(bytes, (void*)stream, alloc.user);
+  else if (hipMalloc(&p, bytes) != hipSuccess)
+    p = nullptr;
+  if (!p) (void)hipGetLastError();  // reported here, not by the next launch's check
+  return p;
 }
 void Ctx::raw_free(void* p) {
   if (has_alloc)
@@ -81,6 +83,11 @@ void* Ctx::dmalloc(size_t bytes) {
                          " bytes was requested inside a no-allocation call");
   if (void* p = defer ? pool_take(bytes) : nullptr) return p;
   void* p = raw_alloc(bytes);
+  if (!p && defer) {  // what is held back may be what is missing
+    MGD_HIP(drain());
+    pool_trim();
+    p = raw_alloc(bytes);
+  }
   if (!p)
     fail(MGD_ENOMEM, (has_alloc ? "allocator callback returned NULL for " : "hipMalloc of ") +
                          std::to_string(bytes) + (has_alloc ? " bytes" : " bytes failed"));

@@ -170,7 +170,8 @@ struct Ctx {
 // While a scope is open, buffers released on the context stay allocated until
 // the next synchronisation (or the end of the scope, which waits if any are
 // left): a chain of launches may let its temporaries go without waiting for
-// them, whatever the allocator does with returned memory.
+// them, whatever the allocator does with returned memory.  An allocation that
+// fails meanwhile waits, releases them and tries again.
 struct DeferFrees {
   Ctx* c;
   explicit DeferFrees(Ctx* c_) : c(c_) { ++c->defer; }

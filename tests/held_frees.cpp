@@ -1,7 +1,8 @@
 // Order of waits and releases of a context (mgd::Ctx), without a GPU: this
 // program's hipStreamSynchronize takes the runtime's place, and the context's
 // allocator records every release.  Exits 0 when each held-back buffer is
-// released only after a wait that began once the buffer had been let go.
+// released only after a wait that began once the buffer had been let go, and an
+// allocation that fails first releases what is held back.
 #include <cstdio>
 #include <cstdlib>
 #include <functional>
@@ -11,6 +12,8 @@
 
 static std::map<void*, int> g_freed;     // buffer -> times released
 static std::function<void()> g_in_wait;  // what another thread does meanwhile
+static size_t g_room = size_t(1) << 40;   // bytes left to the allocator
+static std::map<void*, size_t> g_size;
 static hipError_t g_result = hipSuccess;
 
 extern "C" hipError_t hipStreamSynchronize(hipStream_t) {
@@ -29,8 +32,17 @@ static void expect(bool ok, const char* what) {
 int main() {
   mgd::Ctx c;
   c.has_alloc = true;
-  c.alloc.alloc = [](size_t n, void*, void*) { return std::malloc(n); };
-  c.alloc.free = [](void* p, void*, void*) { ++g_freed[p]; };
+  c.alloc.alloc = [](size_t n, void*, void*) -> void* {
+    if (n > g_room) return nullptr;
+    g_room -= n;
+    void* p = std::malloc(n);
+    g_size[p] = n;
+    return p;
+  };
+  c.alloc.free = [](void* p, void*, void*) {  // kept, so that no address comes twice
+    g_room += g_size[p];
+    ++g_freed[p];
+  };
   const size_t n = size_t(1) << 20;  // not from a chunk
   {
     mgd::DeferFrees frees(&c);
@@ -78,6 +90,27 @@ int main() {
     g_in_wait = nullptr;
     expect(released_in_wait == 0, "the end of a scope waits first");
     expect(g_freed[a] == 1, "the end of a scope releases what is left");
+  }
+  {
+    // memory for three buffers: what is held back makes room, small or large
+    for (size_t size : {n, size_t(4096)}) {
+      g_room = 3 * n;
+      mgd::DeferFrees frees(&c);
+      bool got = true;
+      try {
+        for (int k = 0; k < 3 * (int)(n / size) + 2; ++k) c.dfree(c.dmalloc(size));
+      } catch (const std::exception&) {
+        got = false;
+      }
+      expect(got, "an allocation that fails releases what is held back and tries again");
+      bool refused = false;
+      try {
+        (void)c.dmalloc(4 * n);
+      } catch (const std::exception&) {
+        refused = true;
+      }
+      expect(refused, "more than there is stays refused");
+    }
   }
   if (!g_bad) std::printf("ok\n");
   return g_bad ? 1 : 0;

@@ -1199,15 +1199,15 @@ def test_setup_memory_returns_in_any_order(ctx, dim, n, order):
 
 
 class _LimitedAllocator:
-    """Device memory from torch, in requests of at most `most` bytes (None: any);
-    `largest` is the largest request so far, `peak` the most bytes held at once.
+    """Device memory from torch, in requests of at most `most` bytes and at most
+    `cap` bytes at once (None: any); `largest` is the largest request so far, `peak` the most bytes held at once.
     The 4 MB chunks that small buffers come from are neither refused nor counted
     as requests."""
     CHUNK = 4 << 20
 
     def __init__(self, api):
         self.api, self.make = api, api._torch_allocator
-        self.most, self.largest, self.refused = None, 0, 0
+        self.most, self.cap, self.largest, self.refused = None, None, 0, 0
         self.held, self.size, self.peak = 0, {}, 0
 
     def __call__(self, device):
@@ -1215,6 +1215,9 @@ class _LimitedAllocator:
 
         def alloc(nbytes, stream, user):
             if self.most is not None and nbytes > self.most and nbytes != self.CHUNK:
+                self.refused += 1
+                return None
+            if self.cap is not None and self.held + nbytes > self.cap:
                 self.refused += 1
                 return None
             p = cbs[0](nbytes, stream, user)
@@ -1272,6 +1275,33 @@ def test_setup_together_shrinks_to_the_memory(monkeypatch):
     gsys.close()
     c.close()
     assert lim.held == 0
+
+
+def test_transposes_release_what_they_hold_back(monkeypatch):
+    """The copies of a transposed system's blocks stay allocated until the next
+    wait; where memory runs out they are waited for and released instead."""
+    api = gpu_modules()
+    lim = _LimitedAllocator(api)
+    monkeypatch.setattr(api, "_torch_allocator", lim)
+    c = api.Context(0)
+    inp = si.generate(6, 2, 256, 17)
+    co, gsys = gpu_system(c, inp)
+    x = to_dev(c, np.random.default_rng(2).standard_normal(gsys.n))
+    held = lim.peak = lim.held
+    t = gsys.transpose()
+    want = to_host(t.matvec(x))
+    most, kept = lim.peak - held, lim.held - held
+    t.close()
+    assert lim.held == held
+    assert 2 * most > 3 * kept
+    lim.cap, lim.refused = held + kept + (most - kept) // 3, 0
+    t = gsys.transpose()
+    assert lim.refused and lim.held == held + kept
+    lim.cap = None
+    assert np.array_equal(to_host(t.matvec(x)), want)
+    t.close()
+    gsys.close()
+    c.close()
 
 
 def test_handles_closed_by_another_thread_during_setup(ctx):
