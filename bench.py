@@ -202,12 +202,12 @@ def main():
     b = torch.as_tensor(inp.b, device=ctx.device)
     bnorm = float(torch.linalg.vector_norm(b))
 
-    def build(sysx, kind, seed, fp32, batched, graph, **kw):
+    def build(sysx, kind, seed, fp32, batched, ahead, **kw):
         torch.cuda.synchronize()
         t0 = time.perf_counter()
         M = api.BlockPreconditioner(ctx, sysx, kind, amg_seed=seed,
                                     amg_precision=1 if fp32 else 0, batched=int(batched),
-                                    use_graph=int(graph), amg_autotune=int(a.autotune), **kw)
+                                    use_graph=int(ahead), amg_autotune=int(a.autotune), **kw)
         torch.cuda.synchronize()
         return M, time.perf_counter() - t0
 
@@ -250,7 +250,7 @@ def main():
                           "calibration_bytes": {"read": 1 << 30, "written": 1 << 30}}))
         return
 
-    # headline form: FP32 hierarchies, batched V-cycles, graph replay
+    # headline form: FP32 hierarchies, batched V-cycles, steps enqueued ahead
     M32, setup32 = build(sysg, "schur2", w.seed, True, True, True)
     log(f"[bench] fp32 batched setup {setup32:.2f}s")
     for idx, label in ((0, "group 1"), (w.G, "E"), (w.G + 1, "I")):
@@ -264,10 +264,10 @@ def main():
     # the forms that split the FP32-batched / FP64-plain ratio
     forms = {}
     if not a.no_forms:
-        for key, fp32, batched, graph in (("fp64_plain", False, False, False),
-                                          ("fp64_batched_graph", False, True, True),
+        for key, fp32, batched, ahead in (("fp64_plain", False, False, False),
+                                          ("fp64_batched", False, True, True),
                                           ("fp32_sequential", True, False, False)):
-            M, su = build(sysg, "schur2", w.seed, fp32, batched, graph)
+            M, su = build(sysg, "schur2", w.seed, fp32, batched, ahead)
             ms, it, xf, rf = timed(sysg, M, b, a.form_steps)
             rr = float(torch.linalg.vector_norm(b - sysg.matvec(xf))) / bnorm
             forms[key] = {"ms": ms, "iters": it, "setup_s": su, "relres_true": rr}
@@ -275,7 +275,7 @@ def main():
                 x64h = xf.cpu().numpy()
             log(f"[bench] {key}: {ms:.1f} ms/solve, iters {it}, setup {su:.2f}s")
             del M, xf
-        forms["fp32_batched_graph"] = {"ms": ms_step, "iters": iters, "setup_s": setup32,
+        forms["fp32_batched"] = {"ms": ms_step, "iters": iters, "setup_s": setup32,
                                        "relres_true": relres}
         p = forms["fp64_plain"]["ms"]
         forms["ratios_vs_fp64_plain"] = {k: p / v["ms"] for k, v in forms.items()
@@ -286,7 +286,7 @@ def main():
     # (Sections 3.4, 3.5)
     variants = {}
     if not a.no_variants:
-        for key, kind, kw, graph in (("schur1", "schur1", {}, True),
+        for key, kind, kw, ahead in (("schur1", "schur1", {}, True),
                                      ("pctl", "pctl", {}, True),
                                      ("schur2_lower", "schur2_lower", {}, True),
                                      ("alpha_schur2", "schur2", dict(adaptive=1), True),
@@ -294,7 +294,7 @@ def main():
                                      ("aggressive_finest", "schur2", dict(amg_aggressive_levels=1),
                                       True),
                                      ("inner_tol_1e-2", "schur2", dict(inner_tol=1e-2), False)):
-            M, su = build(sysg, kind, w.seed, True, True, graph, **kw)
+            M, su = build(sysg, kind, w.seed, True, True, ahead, **kw)
             steps = 1 if key.startswith("inner") else a.form_steps
             ms, it, xv, rv = timed(sysg, M, b, steps)
             rr = float(torch.linalg.vector_norm(b - sysg.matvec(xv))) / bnorm
@@ -316,7 +316,7 @@ def main():
             del M, xv
 
     # per-kernel timing pass: HIP events on the context stream around every
-    # launch of one FP32 batched solve (direct launches, no graph)
+    # launch of one FP32 batched solve (no step enqueued ahead)
     M32d, _ = build(sysg, "schur2", w.seed, True, True, False)
     solve(sysg, M32d, b)
     ctx.reset_kernel_stats()
@@ -373,7 +373,7 @@ def main():
             f"{al_st:.0f} GB/s (stored)")
     del xa_, ya_
     # the whole solve: every launch's algorithmic bytes (the same 38-step solve,
-    # event-timed above) over the graph-replayed time of one solve
+    # event-timed above) over the time of one timed solve
     # (the class totals include the few launches profiled without a symbol:
     # vector work, whose bytes are the same under both pricings)
     solve_bytes = sum(v["bytes"] for v in stats.values())
@@ -397,19 +397,19 @@ def main():
             wb = torch.as_tensor(winp.b, device=ctx.device)
             wn = float(torch.linalg.vector_norm(wb))
             out = {}
-            for kind, batched, graph in cases:
+            for kind, batched, ahead in cases:
                 fp32 = wname == "g20_2d512"
-                M, su = build(wsys, kind, ww.seed, fp32, batched, graph)
+                M, su = build(wsys, kind, ww.seed, fp32, batched, ahead)
                 ms, it, xw, rw = timed(wsys, M, wb, a.form_steps)
                 rr = float(torch.linalg.vector_norm(wb - wsys.matvec(xw))) / wn
-                key = kind + ("_batched_graph" if batched else "_sequential") + \
+                key = kind + ("_batched" if batched else "_sequential") + \
                     ("_fp32" if fp32 else "_fp64")
                 out[key] = {"ms": ms, "iters": it, "setup_s": su, "relres_true": rr}
                 log(f"[bench] {wname} {key}: {ms:.1f} ms/solve, iters {it}, setup {su:.2f}s")
                 if wname == "g20_2d512":
                     # adjoint: A^T lambda = x - x_target with Schur2 built on A^T
                     g = xw - torch.as_tensor(winp.x_target, device=ctx.device)
-                    MT, sut = build(wsys, kind, ww.seed, fp32, batched, graph, transpose=1)
+                    MT, sut = build(wsys, kind, ww.seed, fp32, batched, ahead, transpose=1)
                     api.adjoint(ctx, wco, wsys, MT, xw, g, rtol=1e-8, flexible=1)
                     torch.cuda.synchronize()
                     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
@@ -428,7 +428,7 @@ def main():
                 del M, xw
             if wname == "g20_2d256":
                 out["batched_speedup"] = (out["bdiag_sequential_fp64"]["ms"]
-                                          / out["bdiag_batched_graph_fp64"]["ms"])
+                                          / out["bdiag_batched_fp64"]["ms"])
             workloads[wname] = out
             del wsys, wco
 

@@ -712,7 +712,7 @@ static void build_exec(block_precond* bp, std::unique_ptr<PcExec<T>>& X) {
   X = std::make_unique<PcExec<T>>();
   if (kind == MGD_PC_IDENTITY) return;
   // every single-hierarchy union the apply uses is built here, so that an
-  // apply (possibly under graph capture) never allocates
+  // apply (possibly inside a caller's graph capture) never allocates
   std::vector<int> singles;
   if (kind == MGD_PC_AMG_MONO) singles = {0};
   if (kind == MGD_PC_SCHUR2 || kind == MGD_PC_SCHUR2_LOWER) singles = {G};

@@ -91,13 +91,13 @@ struct Ctx {
   void* pinned = nullptr;
   size_t pinned_bytes = 0;
   // GMRES basis and scratch kept between calls of the same size (allocation
-  // stays out of the solve, and graph-replayed steps find the same buffers)
+  // stays out of the solve)
   std::shared_ptr<void> gmres_ws;
   // profiling
   bool profiling = false;
   // set for the duration of a no-allocation call: any device allocation is an
   // error, small readbacks stage through static host memory, and the solve
-  // runs as direct launches (no graph instantiation, no second stream)
+  // stays on the context stream, one step at a time
   bool no_alloc = false;
   struct Pending {
     int cls;

@@ -26,12 +26,6 @@ void csr_copy_from(Ctx* c, const mgd_csr* A, Csr<double>& out) {
   copy_d2d(c, out.ci.get(), A->col_idx, (size_t)A->nnz);
   copy_d2d(c, out.v.get(), A->val, (size_t)A->nnz);
 }
-void csr_copy(Ctx* c, const Csr<double>& A, Csr<double>& out) {
-  out.alloc(c, A.n_rows, A.n_cols, A.nnz);
-  copy_d2d(c, out.rp.get(), A.rp.get(), (size_t)A.n_rows + 1);
-  copy_d2d(c, out.ci.get(), A.ci.get(), (size_t)A.nnz);
-  copy_d2d(c, out.v.get(), A.v.get(), (size_t)A.nnz);
-}
 
 // ---------------------------------------------------------------------------
 // strength of connection

@@ -84,7 +84,6 @@ struct SetupHierarchy {
 
 // Copy a caller matrix into an owned one.
 void csr_copy_from(Ctx* c, const mgd_csr* A, Csr<double>& out);
-void csr_copy(Ctx* c, const Csr<double>& A, Csr<double>& out);
 // Build the hierarchies of the diagonal blocks of A0 (member q: rows and columns
 // [off[q], off[q + 1]), entries [eoff[q], eoff[q + 1])), already validated.  More
 // than one member needs setup_batches(p).
