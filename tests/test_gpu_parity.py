@@ -1296,10 +1296,11 @@ def test_transposes_release_what_they_hold_back(monkeypatch):
     assert 2 * most > 3 * kept
     lim.cap, lim.refused = held + kept + (most - kept) // 3, 0
     t = gsys.transpose()
-    assert lim.refused and lim.held == held + kept
+    assert lim.refused   # a chunk that was refused leaves its buffers on their own
     lim.cap = None
     assert np.array_equal(to_host(t.matvec(x)), want)
     t.close()
+    assert lim.held == held
     gsys.close()
     c.close()
 
