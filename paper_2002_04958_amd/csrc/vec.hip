@@ -96,10 +96,9 @@ template <bool BASES>
 __global__ void __launch_bounds__(256) k_tile_scan(const int* __restrict__ in, int n,
                                                    const long long* __restrict__ tile_sums,
                                                    int* __restrict__ out) {
-  __shared__ long long lds[256];
-  __shared__ long long s_before[4];
+  __shared__ long long s_before[4], s_wave[4];
   const long base = (long)blockIdx.x * kScanTile;
-  const int t = threadIdx.x;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   long long before = 0;
   if (BASES) {
     if (t == 0) before = tile_sums[blockIdx.x];
@@ -108,7 +107,6 @@ __global__ void __launch_bounds__(256) k_tile_scan(const int* __restrict__ in, i
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off, 64);
-  if ((t & 63) == 0) s_before[t >> 6] = before;
   int v[8];
   long long s = 0;
 #pragma unroll
@@ -117,16 +115,18 @@ __global__ void __launch_bounds__(256) k_tile_scan(const int* __restrict__ in, i
     v[k] = (i < n) ? in[i] : 0;
     s += v[k];
   }
-  lds[t] = s;
-  __syncthreads();
-  // Hillis-Steele inclusive scan over 256 thread sums
-  for (int off = 1; off < 256; off <<= 1) {
-    const long long add = (t >= off) ? lds[t - off] : 0;
-    __syncthreads();
-    lds[t] += add;
-    __syncthreads();
+  long long upto = s;  // within the wave, then the waves before it
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const long long y = __shfl_up(upto, off, 64);
+    if (lane >= off) upto += y;
   }
-  long long run = (t ? lds[t - 1] : 0) + s_before[0] + s_before[1] + s_before[2] + s_before[3];
+  if (lane == 0) s_before[w] = before;
+  if (lane == 63) s_wave[w] = upto;
+  __syncthreads();
+  long long run = upto - s;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) run += s_before[q] + (q < w ? s_wave[q] : 0);
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
     long i = base + t * 8 + k;
