@@ -36,8 +36,8 @@ __device__ __forceinline__ double block_sum256(double v, double* lds /*[4]*/) {
 // ---------------------------------------------------------------------------
 constexpr int kScanTile = 2048;  // 256 threads x 8 items
 // Tiles up to which a workgroup adds up the tile sums before its own (us, scans of
-// 2^20, 2^22, 2^24, 2^26 and 2^28 values): 11, 26, 98, 583, 5005; with the bases
-// from a launch of their own 14, 30, 108, 426, 1616.
+// 2^20, 2^22, 2^24, 2^26 and 2^28 values): 11, 25, 95, 582, 4977; with the bases
+// from a launch of their own 13, 29, 106, 411, 1565.
 constexpr int kScanOwnBase = 8192;
 
 __global__ void __launch_bounds__(256) k_tile_sums(const int* __restrict__ in, int n,
