@@ -9,6 +9,11 @@ namespace mgd {
 constexpr int kBlock = 256;     // default workgroup size (4 wavefronts of 64)
 constexpr int kRedBlocks = 1024; // fixed partial count of deterministic reductions
 
+// Lanes per row, of 64, 32, 16, 8 or 1, for a launch of a lane group per row: at most
+// `lanes`, fewer where the launch would pass the 2^32 - 1 threads a grid may have
+// (64 lanes: from 67M rows, 8 lanes: from 537M).  MGD_LANE_THREADS lowers the limit.
+int fit_lanes(long long rows, int lanes);
+
 // ---- scans (int32) -----------------------------------------------------------
 // out[0..n]: out[i] = sum_{j<i} in[j], out[n] = total, of values >= 0.  Where int32
 // cannot hold the total, out[n] = kScanTooLarge and nothing else in out may be

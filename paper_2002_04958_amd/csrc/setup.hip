@@ -98,10 +98,11 @@ static void strength(Ctx* c, const Csr<double>& A, double theta, double dom, DBu
                        diag.get(), (const int*)c->err_flag());
     MGD_CHECK_LAUNCH();
   };
-  if (A.nnz <= 10LL * A.n_rows)
-    launch(k_strength<8>, 8);
-  else
-    launch(k_strength<16>, 16);
+  switch (fit_lanes(A.n_rows, A.nnz <= 10LL * A.n_rows ? 8 : 16)) {
+    case 1: launch(k_strength<1>, 1); break;
+    case 8: launch(k_strength<8>, 8); break;
+    default: launch(k_strength<16>, 16);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -855,12 +856,12 @@ static void interpolation(Ctx* c, const Csr<double>& A, const DBuf<double>& diag
                      A.rp.get(), A.ci.get(), A.v.get(), diag.get(), S.get(), state.get(),        \
                      cidx.get(), P.rp.get(), P.ci.get(), P.v.get(), sigma.get(), c->err_flag())
   const double avg = (double)A.nnz / std::max(n, 1);
-  if (avg <= 10.0)
-    MGD_INTERP(8);
-  else if (avg <= 24.0)
-    MGD_INTERP(16);
-  else
-    MGD_INTERP(32);
+  switch (fit_lanes(n, avg <= 10.0 ? 8 : avg <= 24.0 ? 16 : 32)) {
+    case 1: MGD_INTERP(1); break;
+    case 8: MGD_INTERP(8); break;
+    case 16: MGD_INTERP(16); break;
+    default: MGD_INTERP(32);
+  }
 #undef MGD_INTERP
   MGD_CHECK_LAUNCH();
 }
@@ -934,14 +935,16 @@ void transpose(Ctx* c, const Csr<double>& A, Csr<double>& T) {
                        uv.get(), A.nnz, c->err_flag());
   MGD_CHECK_LAUNCH();
   if (T.n_rows && T.nnz) {
-    if ((double)T.nnz <= 16.0 * T.n_rows)
-      hipLaunchKernelGGL(k_sort_rows<8>, dim3(cdiv(T.n_rows, 32)), dim3(256), 0, c->stream,
+    auto sort = [&](auto kernel, int lanes) {
+      hipLaunchKernelGGL(kernel, dim3(cdiv(T.n_rows, 256 / lanes)), dim3(256), 0, c->stream,
                          T.n_rows, T.rp.get(), (const int*)uci.get(), (const double*)uv.get(),
                          T.ci.get(), T.v.get(), (const int*)c->err_flag());
-    else
-      hipLaunchKernelGGL(k_sort_rows<64>, dim3(cdiv(T.n_rows, 4)), dim3(256), 0, c->stream,
-                         T.n_rows, T.rp.get(), (const int*)uci.get(), (const double*)uv.get(),
-                         T.ci.get(), T.v.get(), (const int*)c->err_flag());
+    };
+    switch (fit_lanes(T.n_rows, (double)T.nnz <= 16.0 * T.n_rows ? 8 : 64)) {
+      case 1: sort(k_sort_rows<1>, 1); break;
+      case 64: sort(k_sort_rows<64>, 64); break;
+      default: sort(k_sort_rows<8>, 8);
+    }
     MGD_CHECK_LAUNCH();
   }
   if (c->defer) {

@@ -628,13 +628,15 @@ std::unique_ptr<Union<T>> build_union(Ctx* c, const std::vector<const SetupHiera
     b.A.ci.alloc(c, (size_t)std::max(b.A.nnz, 1));
     b.A.v.alloc(c, (size_t)std::max(b.A.nnz, 1));
     // lanes per copied row: about the mean row length
+#define MGD_ROWS_GL(K, N_, GL, ...)                                                                \
+  hipLaunchKernelGGL(K<GL>, dim3(cdiv(N_, 256 / GL)), dim3(256), 0, c->stream, __VA_ARGS__)
 #define MGD_ROWS(K, N_, AVG, ...)                                                                  \
-  if ((AVG) <= 10.0)                                                                               \
-    hipLaunchKernelGGL(K<8>, dim3(cdiv(N_, 32)), dim3(256), 0, c->stream, __VA_ARGS__);            \
-  else if ((AVG) <= 24.0)                                                                          \
-    hipLaunchKernelGGL(K<16>, dim3(cdiv(N_, 16)), dim3(256), 0, c->stream, __VA_ARGS__);           \
-  else                                                                                             \
-    hipLaunchKernelGGL(K<64>, dim3(cdiv(N_, 4)), dim3(256), 0, c->stream, __VA_ARGS__);            \
+  switch (fit_lanes(N_, (AVG) <= 10.0 ? 8 : (AVG) <= 24.0 ? 16 : 64)) {                            \
+    case 1: MGD_ROWS_GL(K, N_, 1, __VA_ARGS__); break;                                             \
+    case 8: MGD_ROWS_GL(K, N_, 8, __VA_ARGS__); break;                                             \
+    case 16: MGD_ROWS_GL(K, N_, 16, __VA_ARGS__); break;                                           \
+    default: MGD_ROWS_GL(K, N_, 64, __VA_ARGS__);                                                  \
+  }                                                                                                \
   MGD_CHECK_LAUNCH()
     if (b.nS > 0) {
       const double avg = (double)b.A.nnz / b.nS;
@@ -646,10 +648,11 @@ std::unique_ptr<Union<T>> build_union(Ctx* c, const std::vector<const SetupHiera
                            (const double*)b.A.v.get(), lv.dinv.get(), lv.dgs.get());
         MGD_CHECK_LAUNCH();
       };
-      if (avg <= 10.0)
-        dinv(k_u_dinv<8, T>, 8);
-      else
-        dinv(k_u_dinv<16, T>, 16);
+      switch (fit_lanes(b.nS, avg <= 10.0 ? 8 : 16)) {
+        case 1: dinv(k_u_dinv<1, T>, 1); break;
+        case 8: dinv(k_u_dinv<8, T>, 8); break;
+        default: dinv(k_u_dinv<16, T>, 16);
+      }
     }
     check_structure_async(c, b.nS, b.nS, b.A.nnz, b.A.rp.get(), b.A.ci.get(), false, true);
     // dense members: offsets in the extended order
@@ -684,6 +687,7 @@ std::unique_ptr<Union<T>> build_union(Ctx* c, const std::vector<const SetupHiera
                  err);
       }
 #undef MGD_ROWS
+#undef MGD_ROWS_GL
       // C-block position -> level l+1 index; level l+1 index -> C-block position
       lv.cmap.alloc(c, (size_t)std::max(b.nC, 1));
       lv.cpos.alloc(c, (size_t)std::max(nb.n, 1));

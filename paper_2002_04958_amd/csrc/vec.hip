@@ -5,6 +5,7 @@
 // and sum the per-workgroup partials in index order in a second kernel, so
 // the result depends only on n, never on scheduling.
 #include <climits>
+#include <cstdlib>
 
 #include "kernels.hpp"
 
@@ -29,6 +30,13 @@ __device__ __forceinline__ double block_sum256(double v, double* lds /*[4]*/) {
   if (threadIdx.x == 0) r = (lds[0] + lds[1]) + (lds[2] + lds[3]);
   __syncthreads();
   return r;
+}
+
+int fit_lanes(long long rows, int lanes) {
+  const char* e = std::getenv("MGD_LANE_THREADS");
+  const long long most = (e && *e ? std::atoll(e) : 0xffffffffLL) - 256;  // the last workgroup
+  while (lanes > 1 && rows * lanes > most) lanes = lanes > 16 ? 16 : lanes > 8 ? 8 : 1;
+  return lanes;
 }
 
 // ---------------------------------------------------------------------------

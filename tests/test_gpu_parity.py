@@ -1778,3 +1778,56 @@ def test_scan_of_more_tiles_than_own_bases(ctx):
     assert np.array_equal(prp, np.concatenate([[0], np.cumsum(np.where(c, 1, neighbours))]))
     assert g.info()["n"][1] == c.sum()
     assert np.array_equal(pci[prp[:-1][c]], np.arange(c.sum()))
+
+
+# ---------------------------------------------------------------------------
+# launches of a lane group per row
+# ---------------------------------------------------------------------------
+@pytest.mark.parametrize("threads", [2000, 12000, 100000])
+def test_setup_with_fewer_lanes_per_row_bit_exact(ctx, monkeypatch, threads):
+    """Where a launch of a lane group per row would have too many threads, rows
+    take fewer lanes, down to one: hierarchies of short and of long rows stay bit
+    for bit the oracle's, and V-cycles, a transposed system's matvec and a batched
+    apply what they are with the groups' full width."""
+    api = gpu_modules()
+    inp = si.generate(2, 2, 37, 31)
+    co, gsys = gpu_system(ctx, inp)
+    x = to_dev(ctx, np.random.default_rng(6).standard_normal(gsys.n))
+
+    def outputs():
+        M = api.BlockPreconditioner(ctx, gsys, "schur2", amg_seed=5, batched=1)
+        return to_host(M.apply(x)), to_host(gsys.transpose().matvec(x))
+    want = outputs()
+    monkeypatch.setenv("MGD_LANE_THREADS", str(threads))
+    for A, kw in ((oracle_system(si.generate(3, 3, 10, 22)).monolithic(), {}),
+                  (_hub_matrix(40, (10, 25, 48, 100), (9, 33, 40), 11), {"max_levels": 3})):
+        H = oamg.setup(A, oamg.AMGParams(seed=4, **kw))
+        g = api.AMG(ctx, A.indptr, A.indices, A.data, seed=4, **kw)
+        _compare_hierarchies(g, H, exact_values=True)
+        b = np.random.default_rng(2).uniform(size=A.shape[0])
+        assert_elementwise(to_host(g.apply(to_dev(ctx, b))), oamg.vcycle(H, b), 1e-12,
+                           what="V-cycle")
+    for a, b in zip(outputs(), want):
+        assert np.array_equal(a, b)
+
+
+def test_setup_of_half_a_billion_rows(ctx):
+    """2^29 rows of one entry: eight lanes each would be 2^32 threads in a launch.
+    One relaxed level, whose sweeps divide by the diagonal."""
+    import torch
+    api = gpu_modules()
+    n = 1 << 29
+    free, _ = torch.cuda.mem_get_info(ctx.device)
+    if free < 150 * 2 ** 30:
+        pytest.skip("needs about 100 GB of device memory")
+    rp = torch.arange(n + 1, dtype=torch.int32, device=ctx.device)
+    v = torch.ones(n, dtype=torch.float64, device=ctx.device)
+    v[::3] = 4.0
+    g = api.AMG(ctx, rp, rp[:n], v, seed=1)
+    assert g.info()["n"] == [n]
+    b = torch.arange(n, dtype=torch.float64, device=ctx.device)
+    z = g.apply(b)
+    assert bool(torch.equal(z * v, b))
+    g.close()
+    del rp, v, b, z
+    torch.cuda.empty_cache()
