@@ -2970,7 +2970,7 @@ static void bot_program(const BotLevel* lev, int n, int n_pre, int n_post, int t
 }
 
 // The bottom of the cycle (BotLevel, k_bottom): the levels from which on every
-// member has at most kBotRows rows, if any of them coarsens (a lone dense level
+// member has at most kBotRows rows, none of them too long, if any of them coarsens (a lone dense level
 // stays with k_dense).  MGD_BOTTOM=0 (or MGD_TAIL_ROWS, whose launch takes these
 // levels instead) keeps per-level launches, with one lane per row there: the
 // same bits.  With members of at most 0 (no bottom), 300, 600, 1200 and 2048 rows
@@ -2990,6 +2990,15 @@ static void bot_program(const BotLevel* lev, int n, int n_pre, int n_post, int t
 constexpr long long kBotWholeRows = 512 * 192;
 constexpr unsigned kBotLdsWhole = 150 * 1024, kBotLdsShared = 110 * 1024;
 constexpr long long kBotMatrix = 160 * 1024;  // bytes of a matrix and member
+// Longest row: one lane adds it entry after entry, a launch of the level shares it
+// among up to 64.  With limits of 96, 128, 192 entries and none, FP64 applies of a
+// grid of 30^2 rows with one row of 128 couplings took 45.3, 45.1, 51.3 and 51.3 us
+// (46.0 with launches alone), of 14^2 with 96 couplings 26.2, 17.5, 17.7 and 17.6
+// (26.4); FP32 applies of 44^2 with 96, 128 and 190 couplings took 58.7, 79.4 and
+// 79.4 us with 128, 68.6, 62.3 and 67.1 with 192, 68.5, 77.0 and 90.7 with none
+// (80.0, 78.2 and 75.9).
+template <typename T>
+constexpr int kBotWidth = sizeof(T) == 8 ? 128 : 192;
 constexpr int kBotDenseRows = 256;  // larger dense levels are spread over workgroups
 
 // places of the members in a level's extended stored order
@@ -3059,12 +3068,21 @@ static void build_bottom(Ctx* c, std::vector<BuildLevel<T>>& bl, const std::vect
     if (mat > 0 && m.kind != 0) return 0;
     return sum(wid(l, q, mat), mat == 0 ? sC + sF : (mat == 1 ? sF : sC));
   };
+  auto widest = [&](int l, int q, int mat) {  // its longest row there, rounded up to even
+    const UMember& m = tab[bl[l].tab + q];
+    const int sC = cdiv(m.nc, 64), sF = cdiv(f_rows(m), 64);
+    if (m.n == 0 || m.kind == 2 || (mat > 0 && m.kind != 0)) return 0;
+    const int* w = wid(l, q, mat);
+    return *std::max_element(w, w + std::max(1, mat == 0 ? sC + sF : (mat == 1 ? sF : sC)));
+  };
   int lt = nl;
   while (lt > cand) {
     bool ok = true;
     for (int q = 0; q < nm; ++q) {
       const UMember& m = tab[bl[lt - 1].tab + q];
-      for (int mat = 0; mat < 3; ++mat) ok = ok && 64LL * stored(lt - 1, q, mat) * (long long)(sizeof(T) + 2) <= kBotMatrix;
+      for (int mat = 0; mat < 3; ++mat)
+        ok = ok && 64LL * stored(lt - 1, q, mat) * (long long)(sizeof(T) + 2) <= kBotMatrix &&
+             widest(lt - 1, q, mat) <= kBotWidth<T>;
       ok = ok && (m.kind != 2 || m.n <= kBotDenseRows);
     }
     if (!ok) break;

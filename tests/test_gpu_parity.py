@@ -1613,6 +1613,22 @@ np.save(sys.argv[2], M.apply(r).cpu().numpy())
 """
 
 
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("couplings", [100, 122, 128, 180, 190])
+def test_bottom_with_long_rows(ctx, precision, couplings):
+    """Small levels whose longest row is at either side of what the bottom takes
+    (128 entries in FP64, 192 in FP32): V-cycles equal the oracle's."""
+    api = gpu_modules()
+    A = _hub_matrix(30, (couplings,), (), 11)
+    assert np.diff(A.indptr).max() in range(couplings + 1, couplings + 6)
+    H = oamg.setup(A, oamg.AMGParams(seed=5))
+    g = api.AMG(ctx, A.indptr, A.indices, A.data, seed=5, precision=precision)
+    b = np.random.default_rng(2).uniform(size=A.shape[0])
+    z = to_host(g.apply(to_dev(ctx, b), cycles=2))
+    assert_elementwise(z, oamg.apply_cycles(H, b, 2), 5e-5 if precision else 1e-12,
+                       floor=FP32_FLOOR if precision else 1e-3, what="V-cycles with a long row")
+
+
 def test_debug_union_verification_passes(ctx, monkeypatch, tmp_path):
     """MGD_DEBUG_UNION=1 (read once per process) verifies every level of every
     union on the host while it is built: the stored-row map is a permutation
